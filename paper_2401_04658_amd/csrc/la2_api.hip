@@ -109,6 +109,7 @@ struct Plan {
   int wg_pairs = 0;
   int nlong = 0;        // sequences of more than one chunk the plan has room for (the state scan's units)
   int64_t wg_slots = 0; // state slots (per head) the workspace has room for
+  int even = 0;         // ScanParams::even_chunks
   size_t map_bytes = 0;
 };
 
@@ -183,28 +184,36 @@ Plan make_plan(const la2_desc* d) {
 }
 
 // Packed batch of sequences of different lengths (batch chains per head, the longest of seqlen positions,
-// total_positions in all; 0 = not known).  With few chains the dense rule above already cuts the sequences.
-// With many chains it does not, and then a batch of very unequal lengths runs as long as its longest sequence's
-// sequential block loop: when that loop is estimated to outlast the whole batch's memory traffic, the sequences
-// are cut into chunks of a quarter of the longest one (at least four blocks).  Shorter sequences then have one
-// chunk and no pre-pass work; only the long ones pay the second read of their key-like and value-like rows.
-// The launch grid of such a plan is compact: one workgroup per (sequence, chunk) pair that exists and head (a
-// grid of batch x heads x nchunks workgroups, most of them for chunks the short sequences do not have, costs
-// about 10 ns per empty workgroup and launch: measured 1.16 ms against 0.34 ms uncut for 191 sequences x 16
-// heads x 8 chunks).  A sequence of len positions has at most len / C + 1 pairs, and only sequences longer than
-// C need state slots, at most 2 len / C each.  16-bit data at head_dim 64 / 128 (the half-block kernels) only.
-constexpr int kPackedCut = 4;   // pieces the longest sequence of such a batch is cut into
+// total_positions in all; 0 = not known), 16-bit data at head_dim 64 / 128 (the half-block kernels).
+// Such a batch takes at least its longest piece's sequential block loop, and at least the batch's positions spread
+// over the compute units: load = total_positions * heads / units positions each.  Lengths about equal: the dense
+// rule.  Otherwise (the launch grid is compact and its pairs are sorted by length, varlen_map_kernel; a grid of
+// batch x heads x nchunks workgroups, most of them for chunks the short sequences do not have, costs about 10 ns per
+// empty workgroup and launch):
+//   - chains that fill the device: longest <= 1.5 load: not cut, only sorted (65,536 positions, H 16, d 128, forward +
+//     backward: longest 4096, 5000, 6000: 0.88, 0.94, 0.97 ms; cut 0.95, 0.96, 1.00; 7000: 1.08 against 1.00 cut);
+//     above that every sequence is cut into even pieces of at most 0.65 load (longest 7000 / 8192: 1.00 / 0.99 ms;
+//     0.5 load 1.00 / 1.02, 0.8 load 1.02 / 1.00; head_dim 64 0.57, 0.57, 0.61), unless that would make more than
+//     kPackedCut pieces of the longest, whose state scans would be launches of their own: then pieces of
+//     1 / kPackedCut of the longest and a rest (longest 16384: 1.06 ms; even pieces of that size 1.10).
+//   - chains that do not: even pieces of at most 1.25 load (a plan by the longest length alone gives every sequence
+//     the same number of chunks: 65,536 positions in 20 sequences of up to 8192, H 2, d 128: 1.18 -> 0.32 ms;
+//     1.0 load 0.36, 1.5 load 0.34 ms; 40,000 positions, longest 16384, H 4, d 64: 0.31 -> 0.13 ms).
+// A sequence of len positions has at most len / C + 1 pairs, and only sequences longer than C need state slots, at
+// most 2 len / C each.
+constexpr int kPackedCut = 4;
 Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
-  Plan pl = make_plan(d);
-  if (total_positions <= 0 || d->batch <= 0) return pl;
-  if (!is16(d->dtype) || wide(d->head_dim) || g_scan_variant.load(std::memory_order_relaxed) == 1) return pl;
+  const Plan dense = make_plan(d);
+  if (total_positions <= 0 || d->batch <= 0) return dense;
+  if (!is16(d->dtype) || wide(d->head_dim) || g_scan_variant.load(std::memory_order_relaxed) == 1) return dense;
   const int B = block_size(d);
   const int nblocks = (d->seqlen + B - 1) / B;
-  auto compact = [&](Plan c) {   // the compact grid and its map for a plan that has chunks
+  // the compact grid and its map for `c` (nchunks, chunk_tokens); no pairs if the grid would not be addressable
+  auto compact = [&](Plan c) {
     const int64_t all = (int64_t)d->batch * c.nchunks;
     const int64_t pairs = std::min<int64_t>(all, total_positions / c.chunk_tokens + d->batch);
-    const int64_t slots = std::min<int64_t>(all, 2 * total_positions / c.chunk_tokens);
-    const int64_t nlong = std::min<int64_t>(d->batch, total_positions / c.chunk_tokens);
+    const int64_t slots = c.nchunks > 1 ? std::min<int64_t>(all, 2 * total_positions / c.chunk_tokens) : 0;
+    const int64_t nlong = c.nchunks > 1 ? std::min<int64_t>(d->batch, total_positions / c.chunk_tokens) : 0;
     if (pairs > ((int64_t)1 << 30)) return c;
     c.wg_pairs = (int)pairs;
     c.nlong = (int)nlong;
@@ -213,26 +222,53 @@ Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
     c.workspace = (size_t)slots * d->heads * d->head_dim * d->head_dim * sizeof(float);
     return c;
   };
-  // the dense rule (few chains) or the test knob already cut the sequences: same chunks, compact grid
-  if (pl.nchunks > 1) return compact(pl);
-  if (g_chunk_tokens_override.load(std::memory_order_relaxed) > 0) return pl;
-  if (nblocks < 8) return pl;
-  if ((int64_t)d->seqlen * d->batch <= 2 * total_positions) return pl;   // lengths about equal
-  // microseconds: the longest chain's loop (measured times per block, as in make_plan) against the batch's forward
-  // traffic at 5.5 TB/s
-  const float t_blk = is16(d->dtype) ? (d->head_dim == 256 ? 3.3f : d->head_dim == 96 ? 3.f : d->head_dim == 64 ? 1.15f : 2.1f)
-                                     : (d->head_dim == 128 ? 10.f : 3.f);
-  const float t_longest = (float)nblocks * t_blk;
-  const float t_traffic = (float)total_positions * d->heads * d->head_dim * 4.f * elem_size(d->dtype) / 5.5e6f;
-  if (t_longest <= 1.25f * t_traffic) return pl;
-  int cb = (nblocks + kPackedCut - 1) / kPackedCut;
-  if (cb < 4) cb = 4;
-  if (cb >= nblocks) return pl;
-  pl.nchunks = (nblocks + cb - 1) / cb;
-  pl.chunk_tokens = cb * B;
-  pl.workspace = (size_t)d->batch * d->heads * pl.nchunks * d->head_dim * d->head_dim * sizeof(float);
-  const Plan c = compact(pl);
-  return c.wg_pairs > 0 ? c : make_plan(d);
+  // the test knob's chunks, or (lengths about equal, few chains) the dense rule's: compact grid, pieces of one size
+  if (g_chunk_tokens_override.load(std::memory_order_relaxed) > 0) return dense.nchunks > 1 ? compact(dense) : dense;
+  const bool few = dense.nchunks > 1;
+  const int64_t as_longest = (int64_t)d->seqlen * d->batch;
+  if (few && (nblocks < 8 || as_longest * 4 <= total_positions * 5)) return compact(dense);
+  if (!few && (nblocks < 8 || as_longest <= 2 * total_positions)) return dense;
+  const int64_t load = total_positions * d->heads / device_cu_count();
+  auto blocks_of = [&](double tokens) {   // in blocks: at least four, at most the longest sequence
+    const int64_t cb = ((int64_t)tokens + B - 1) / B;
+    return (int)std::min<int64_t>(std::max<int64_t>(cb, 4), nblocks);
+  };
+  auto cut = [&](int cb, bool even) {
+    Plan p{(nblocks + cb - 1) / cb, cb * B, 0};
+    p.even = even ? 1 : 0;
+    return compact(p);
+  };
+  if (few) {
+    const Plan p = cut(blocks_of(1.25 * (double)load), true);
+    return p.wg_pairs > 0 ? p : dense;
+  }
+  if (2 * (int64_t)d->seqlen <= 3 * load) {
+    const Plan p = cut(nblocks, true);
+    return p.wg_pairs > 0 ? p : dense;
+  }
+  // (the workspace is that of the kPackedCut pieces either way: it bounds every cut into fewer)
+  Plan p = cut(blocks_of((double)((nblocks + kPackedCut - 1) / kPackedCut) * B), false);
+  if (p.wg_pairs <= 0) return dense;
+  const int fine = blocks_of(0.65 * (double)load);
+  if (fine * B >= p.chunk_tokens) {
+    const Plan e = cut(fine, true);
+    p.nchunks = e.nchunks;
+    p.chunk_tokens = e.chunk_tokens;
+    p.wg_pairs = e.wg_pairs;
+    p.nlong = e.nlong;
+    p.wg_slots = e.wg_slots;
+    p.even = 1;
+  }
+  return p;
+}
+
+// The plan a call runs by.  An uncut batch only sorts its sequences through the map: without a workspace for the map it
+// runs in the order of the sequences.
+Plan packed_call_plan(const la2_desc* d, int64_t total_positions, const void* workspace, size_t workspace_bytes) {
+  const Plan pl = make_plan_varlen(d, total_positions);
+  const bool usable = workspace != nullptr && workspace_bytes >= pl.map_bytes &&
+                      (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;
+  return pl.wg_pairs > 0 && pl.nchunks == 1 && !usable ? Plan{1, pl.chunk_tokens, 0} : pl;
 }
 
 // Grid sizes of every launch a plan leads to, checked on the host before the first one: the scan kernels take
@@ -398,6 +434,7 @@ la2::ScanParams base_params(const la2_desc* d, const Plan& pl, const float* lamb
   p.batch = d->batch; p.heads = d->heads; p.n = d->seqlen;
   p.nchunks = pl.nchunks;
   p.chunk_tokens = pl.chunk_tokens;
+  p.even_chunks = pl.even;
   p.variant = g_scan_variant.load(std::memory_order_relaxed);
   p.self_prefix = self_prefix(d, pl, cu) ? 1 : 0;
   return p;
@@ -976,7 +1013,7 @@ la2_status fwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(o, 16) || !aligned(lambda, 4) ||
       !aligned(cu_seqlens, 4))
     return LA2_ERR_STRIDE_ALIGN;
-  const Plan pl = make_plan_varlen(desc, total_positions);
+  const Plan pl = packed_call_plan(desc, total_positions, workspace, workspace_bytes);
   if (!plan_fits_a_grid(desc, pl)) return LA2_ERR_SHAPE;
   const size_t need = pl.map_bytes + pl.workspace;
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 256)))
@@ -1028,7 +1065,7 @@ la2_status bwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(d_o, 16) || !aligned(dq, 16) ||
       !aligned(dk, 16) || !aligned(dv, 16) || !aligned(lambda, 4) || !aligned(cu_seqlens, 4))
     return LA2_ERR_STRIDE_ALIGN;
-  const Plan pl = make_plan_varlen(desc, total_positions);
+  const Plan pl = packed_call_plan(desc, total_positions, workspace, workspace_bytes);
   if (!plan_fits_a_grid(desc, pl)) return LA2_ERR_SHAPE;
   // as la2_bwd: with sequence chunks the dQ scan's launch forms the local dKV states behind its own chunk states
   const bool fuse = pl.nchunks > 1 && fuses_reverse_states(desc);
@@ -1123,7 +1160,9 @@ la2_status la2_bwd_varlen_norm(const la2_desc* desc, const int32_t* cu_seqlens, 
       !aligned(d_u, 16) || !aligned(dq, 16) || !aligned(dk, 16) || !aligned(dv, 16) || !aligned(lambda, 4) ||
       !aligned(rstd, 4) || !aligned(cu_seqlens, 4))
     return LA2_ERR_STRIDE_ALIGN;
-  const size_t need = la2_varlen_workspace_bytes(desc, total_positions, LA2_OP_BWD);
+  const Plan pl = packed_call_plan(desc, total_positions, workspace, workspace_bytes);   // as la2_bwd_varlen below
+  if (!plan_fits_a_grid(desc, pl)) return LA2_ERR_SHAPE;
+  const size_t need = pl.map_bytes + pl.workspace * (pl.nchunks > 1 && fuses_reverse_states(desc) ? 2 : 1);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 256)))
     return LA2_ERR_WORKSPACE;
   // the row pass over all packed positions that belong to a sequence (one "chain" per head), then Algorithm 2 on d_u

@@ -480,6 +480,7 @@ hipError_t launch_scan_bf16(int dtype, int head_dim, bool reverse, const ScanPar
     const bool twin = p.nscan == 2 && p.y[1] == p.z[0] && p.z[1] == p.y[0];
     return launch_scan_bf16_half(dtype, head_dim, reverse, twin, p, s);
   }
+  if (p.wg_map != nullptr) return hipErrorInvalidValue;   // the full-block kernel knows no pair map
   return launch_scan_bf16_full(dtype, head_dim, reverse, p, s);
 }
 

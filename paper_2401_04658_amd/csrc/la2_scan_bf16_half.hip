@@ -97,9 +97,9 @@ void scan_bf16_half_kernel(ScanParams p) {
   // its tiles at compile-time LDS offsets.
   auto run = [&](auto wh_tag) __attribute__((always_inline)) {
   constexpr int WH = decltype(wh_tag)::value;
-  int bi, hi, chunk, slot_stride;
+  int bi, hi, chunk, slot_stride, map_nch;
   int64_t slot;
-  if (!place_workgroup(p, wg, bi, hi, chunk, slot, slot_stride)) return;
+  if (!place_workgroup(p, wg, bi, hi, chunk, slot, slot_stride, map_nch)) return;
   const int chain = bi * p.heads + hi;
   int64_t base;
   int n;
@@ -114,7 +114,8 @@ void scan_bf16_half_kernel(ScanParams p) {
       make_rsrc(NORM ? p.rstd + rstd_chain_offset(p, bi, hi) : nullptr, NORM ? (uint32_t)n * 4u : 0u);
 
   const int nblocks = (n + B - 1) / B;
-  const int cb = p.chunk_tokens / B;
+  const int chunk_tokens = chunk_length(p, n, map_nch);
+  const int cb = chunk_tokens / B;
   const int blk_lo = chunk * cb;
   const int blk_hi = min(blk_lo + cb, nblocks);
   if (RS && n == 0 && chunk == 0) {   // no positions: the state passes through
@@ -240,8 +241,8 @@ void scan_bf16_half_kernel(ScanParams p) {
   f32x16 kv[NT];
   bool have = false;   // a term is in (the next one is added to the decayed sum)
   {
-    const float lam_full = exp2f(l2 * (float)p.chunk_tokens);
-    const float lam_last = exp2f(l2 * (float)(n - (nch - 1) * p.chunk_tokens));
+    const float lam_full = exp2f(l2 * (float)chunk_tokens);
+    const float lam_last = exp2f(l2 * (float)(n - (nch - 1) * chunk_tokens));
     float* const lds = reinterpret_cast<float*>(&sT[0][0][0]) + dvt * (32 * (D + 1));
     static_assert(sizeof(sT) >= (size_t)SW * 32 * (D + 1) * sizeof(float), "room for one wave group's slices");
     // Term k: where it lives, whether it is stored transposed, the decay the sum so far takes before it is added.

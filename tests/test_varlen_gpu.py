@@ -95,6 +95,47 @@ def test_skewed_lengths_with_many_chains_are_chunked(dtype, d):
     check_packed(lengths, H, d, dtype, seed=850 + d, lam=[0.7, 0.995])
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float16, 128)])
+@pytest.mark.parametrize("kind", ["sorted", "even", "few"])
+def test_unequal_lengths_sorted_and_cut_evenly(kind, dtype, d):
+    """The three plans of a batch of unequal lengths (256 compute units): chains that fill the device, the longest
+    about the average load of a unit (uncut, the map only sorts); the longest well above it (even pieces); too few
+    chains (even pieces, one per 256 positions).  Lengths on and off the 64-position granule, empty ones included."""
+    if kind == "few":
+        lengths, H = [1500, 40, 0, 333, 64, 257, 256], 2
+    else:
+        longest, total, H = (600, 6400, 16) if kind == "sorted" else (1300, 9500, 16)
+        lengths = [longest - 23, 1, longest, 0, 449, 385, 384, 64, 65]
+        while sum(lengths) < total:
+            lengths.append(37 + 13 * (len(lengths) % 19))
+    check_packed(lengths, H, d, dtype, seed=880 + d, lam=[0.6, 0.9, 0.99, 0.997] * (H // 4) if H >= 4 else [0.8, 0.997])
+
+
+def test_an_uncut_batch_needs_no_workspace():
+    """The map that sorts an uncut batch lives in the workspace; without one the batch runs in the order of the
+    sequences, same results bit for bit."""
+    import ctypes
+    lengths, H, d = [600, 100, 577] + [70, 130] * 26, 16, 128
+    t, cu = packed_inputs(lengths, H, d, torch.bfloat16, seed=890)
+    g = {k: v.to(DEV) for k, v in t.items()}
+    cu_g = cu.to(DEV)
+    desc = binding._varlen_desc(g["q"], cu_g, max(lengths))
+    lib, stream = binding.load(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    need = int(lib.la2_varlen_workspace_bytes(ctypes.byref(desc), sum(lengths), binding.LA2_OP_FWD))
+    assert 0 < need < 4096
+    o = binding.la2_fwd_varlen(g["q"], g["k"], g["v"], g["lam"], cu_g, max(lengths))
+    o2 = torch.empty_like(o)
+    assert lib.la2_fwd_varlen(ctypes.byref(desc), cu_g.data_ptr(), sum(lengths), g["q"].data_ptr(), g["k"].data_ptr(),
+                              g["v"].data_ptr(), g["lam"].data_ptr(), o2.data_ptr(), None, 0, stream) == 0
+    grads = binding.la2_bwd_varlen(g["q"], g["k"], g["v"], g["d_o"], g["lam"], cu_g, max(lengths))
+    grads2 = [torch.empty_like(o) for _ in range(3)]
+    assert lib.la2_bwd_varlen(ctypes.byref(desc), cu_g.data_ptr(), sum(lengths), g["q"].data_ptr(), g["k"].data_ptr(),
+                              g["v"].data_ptr(), g["d_o"].data_ptr(), g["lam"].data_ptr(), grads2[0].data_ptr(),
+                              grads2[1].data_ptr(), grads2[2].data_ptr(), None, 0, stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and all(torch.equal(a, b) for a, b in zip(grads, grads2))
+
+
 def test_offset_first_sequence_and_unused_tail():
     check_packed([200, 45], 2, 128, torch.bfloat16, seed=820, lead=7, trail=9)
 
