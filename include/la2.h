@@ -30,7 +30,8 @@
  *     pointer; pointers may then be NULL.
  *   - dtype LA2_BF16 / LA2_F16: bf16 / fp16 storage and MFMA operands, fp32 accumulation and fp32 running
  *     state (fp16: the masked scores and the state, as matrix operands, must stay within the fp16 range).
- *     dtype LA2_F32: fp32 storage and fp32 arithmetic throughout.
+ *     dtype LA2_F32: fp32 storage, products exact to fp32 and fp32 sums throughout (head_dim 64 and 128: each float split
+ *     into three bf16 parts for the matrix instructions; a non-finite input makes the rows that depend on it NaN).
  *   - seqlen may be any value >= 0 (a ragged last block is masked) as long as one (batch, head) chain stays
  *     addressable with 32-bit byte offsets: (seqlen + 128) * stride_n * sizeof(element) <= 2^32, else
  *     LA2_ERR_SHAPE (dense bf16, head_dim 128: up to 16,777,088 positions).

@@ -296,7 +296,7 @@ la2_status check_desc(const la2_desc* d) {
 
 // A dense batch with a few more chains than a whole number of chains per compute unit: the units that get one
 // workgroup more set the launch's time (n 4096, head_dim 128, bf16, forward + backward: 256 chains 0.67 ms, 320
-// chains 1.14 ms; fp32: 9.5 ms for anything from 272 to 480 chains).  The dense entry points run such a batch as two
+// chains 1.14 ms).  The dense entry points run such a batch as two
 // calls: the first rows, a whole number of chains per unit (up to four), whole; the rest by the plan for that many chains, i.e. in
 // chunks (320 chains: 0.67 + 0.27 ms).  Returns the rows of the first call, 0 for one call.
 // Measured, two calls against one, forward + backward, n 2048 / 4096 / 8192 (256 units):
@@ -304,18 +304,19 @@ la2_status check_desc(const la2_desc* d) {
 //   bf16 d 64, 128   0.81-0.92    0.80-0.93    0.85-0.95    0.94-1.05    -         (n 1024: 0.95-1.12)
 //   bf16 d 96        0.76-0.88    0.82-0.91    0.91-0.98    0.98-1.11    1.04-1.07
 //   bf16 d 256       0.82-0.86    0.87-0.96    0.96-1.05    1.01-1.03    1.01
-//   fp32 d 128       0.53-0.59    0.57-0.64    0.66-0.71    0.82-0.86    0.84-0.87 (n 1024: 0.64, -, 0.74, -, 0.90)
-//   fp32 d 64        0.64-0.67    0.66-0.72    0.72-0.77    0.78-0.81    0.84-0.87 (n 1024: 0.75, -, 0.85, -, 0.94)
+//   fp32 d 128       0.84-0.90    0.90-0.94    0.96-0.97    1.09         1.08      (n 1024: 0.91, 0.94, 1.01, 1.08, 1.10)
+//   fp32 d 64        0.87-0.90    0.94         1.02-1.04    1.08-1.12    1.11-1.19 (n 1024: 0.98, 1.00, 1.09, 1.19, 1.28)
 //   chains           544          576          640
 //   bf16 d 64, 128   0.86-0.98    0.90-0.99    0.98-1.05    (n 4096 and 8192: 0.86-0.90, 0.90-0.94)
 //   bf16 d 96        0.87-0.93    0.92-0.98    1.03
 //   bf16 d 256       0.96         1.01         1.01
-//   fp32 d 128       0.73         0.79         0.91         (n 4096)
-//   fp32 d 64        1.06         1.11         1.23         (two workgroups per unit: no step at 512)
+//   fp32 d 128       0.89-0.92    0.94-0.96    -
+//   fp32 d 64        no step: four workgroups share a unit
 //   chains           800          832          864          1056         1088
 //   bf16 d 64, 128   0.90-0.93    0.93-0.95    0.97-0.99    0.94         0.96         (n 4096 and 8192)
-// The rule below takes the cells at 0.95 or under.
-int rows_of_first_call(const la2_desc* d) {
+// The rule below takes the cells at about 0.95 or under.  The workspace query answers for fp32 batches up to 1.5 chains
+// per unit (`query`), also where the call then runs as one and needs none.
+int rows_of_first_call(const la2_desc* d, bool query = false) {
   if (g_chunk_tokens_override.load(std::memory_order_relaxed) > 0) return 0;   // the caller plans
   const int cus = device_cu_count();
   const int n = d->seqlen, hd = d->head_dim;
@@ -326,7 +327,7 @@ int rows_of_first_call(const la2_desc* d) {
   int eighths = 0;
   if (d->dtype == LA2_F32) {
     if (wide(hd)) return 0;
-    if (k == 1) eighths = n >= 1024 ? 4 : 0;
+    if (k == 1) eighths = n < 1024 ? 0 : query ? 4 : hd == 128 ? (n >= 2048 ? 2 : 1) : (n >= 2048 ? 1 : 0);
     else eighths = k == 2 && hd == 128 && n >= 2048 ? 2 : 0;
   } else if (hd == 256) {
     eighths = k == 1 && n >= 2048 ? 1 : 0;
@@ -374,7 +375,7 @@ void* shifted_bytes(void* p, int64_t bytes) { return p == nullptr ? nullptr : st
 // one stream and share the workspace), or the whole batch's when it runs as one call.
 template <typename F>
 size_t over_parts(const la2_desc* d, F bytes_of) {
-  const int rows = rows_of_first_call(d);
+  const int rows = rows_of_first_call(d, true);
   if (rows == 0) return bytes_of(d);
   const RowParts p = row_parts(d, rows);
   const size_t a = bytes_of(&p.first), b = bytes_of(&p.rest);
@@ -418,7 +419,7 @@ struct ScanArgs {
 constexpr int kSelfPrefixMaxChunks = la2::kMaxPrefixTerms;   // a start state and the local states of chunks - 1 chunks
 bool self_prefix(const la2_desc* d, const Plan& pl, const int32_t* cu) {
   (void)cu;   // packed batches too: every sequence's chunks have their own slots, a sequence of one chunk has none
-  return pl.nchunks > 1 && pl.nchunks <= kSelfPrefixMaxChunks && is16(d->dtype) &&
+  return pl.nchunks > 1 && pl.nchunks <= kSelfPrefixMaxChunks &&
          !wide(d->head_dim) && pl.chunk_tokens % 32 == 0 && g_scan_variant.load(std::memory_order_relaxed) != 1;
 }
 
@@ -493,7 +494,7 @@ la2_status run_scan(const la2_desc* d, const Plan& pl, bool reverse, const ScanA
 }
 
 // Two reverse scans whose states are transposes of each other (scan 1's y, z are scan 0's z, y): one
-// state pre-pass, one launch (16-bit path).
+// state pre-pass, one launch.
 // (local_ready: the workspace already holds the chunks' local states, left there by the dQ scan's launch)
 la2_status run_dual_reverse_scan(const la2_desc* d, const Plan& pl, const ScanArgs& a0, const ScanArgs& a1,
                                  const float* lambda, void* workspace, hipStream_t s, bool local_ready = false) {
@@ -511,7 +512,8 @@ la2_status run_dual_reverse_scan(const la2_desc* d, const Plan& pl, const ScanAr
   p.x[0] = a0.x; p.y[0] = a0.y; p.z[0] = a0.z; p.w[0] = a0.w;
   p.x[1] = a1.x; p.y[1] = a1.y; p.z[1] = a1.z; p.w[1] = a1.w;
   const hipError_t e = wide(d->head_dim) ? la2::launch_scan_wide(d->dtype, d->head_dim, true, false, p, s)
-                                         : la2::launch_scan_bf16(d->dtype, d->head_dim, true, p, s);
+                       : is16(d->dtype) ? la2::launch_scan_bf16(d->dtype, d->head_dim, true, p, s)
+                                        : la2::launch_scan_f32(d->head_dim, true, p, s);
   return e == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
 }
 
@@ -867,11 +869,7 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
   for_dk.init = rev_init;
   for_dk.init_tr = true;
   for_dv.ragged_state = for_dk.ragged_state = d_kv_final != nullptr && ragged_end(desc);
-  if (is16(desc->dtype))
-    return run_dual_reverse_scan(&blocks, pl_rev, for_dv, for_dk, lambda, rev_workspace, s, /*local_ready=*/fuse);
-  st = run_scan(&blocks, pl_rev, true, for_dv, lambda, workspace, s);
-  if (st != LA2_OK) return st;
-  return run_scan(&blocks, pl_rev, true, for_dk, lambda, workspace, s);
+  return run_dual_reverse_scan(&blocks, pl_rev, for_dv, for_dk, lambda, rev_workspace, s, /*local_ready=*/fuse);
 }
 
 }  // namespace
@@ -1099,10 +1097,7 @@ la2_status bwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   }
   st = run_scan(desc, pl, false, for_dq, lambda, workspace, s);
   if (st != LA2_OK) return st;
-  if (is16(desc->dtype)) return run_dual_reverse_scan(desc, pl, for_dv, for_dk, lambda, rev_workspace, s, fuse);
-  st = run_scan(desc, pl, true, for_dv, lambda, workspace, s);
-  if (st != LA2_OK) return st;
-  return run_scan(desc, pl, true, for_dk, lambda, workspace, s);
+  return run_dual_reverse_scan(desc, pl, for_dv, for_dk, lambda, rev_workspace, s, fuse);
 }
 }  // namespace
 

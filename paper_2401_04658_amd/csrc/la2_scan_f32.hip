@@ -1,71 +1,153 @@
 // fp32 kernels for the decayed causal scan (Algorithm 1; both loops of Algorithm 2), gfx950.
 //
-// fp32 storage, fp32 products and fp32 accumulation throughout (v_mfma_f32_32x32x2_f32: no reduced
-// precision anywhere), for callers that need the 1e-5 accuracy class.  Same organisation as the bf16
-// kernels: one workgroup walks the blocks (B = 32 positions) of one sequence chunk of one (batch, head)
-// chain; wave w owns value features 32 w .. 32 w + 31 of the output and of the running state, whose
-// slice stays in MFMA accumulator registers and is used as an MFMA operand straight from there; the X,
-// Y, Z tiles of the next block stream from HBM into LDS (global_load_lds) while the current block is
-// computed.
+// fp32 storage, products exact to fp32 and fp32 accumulation, for callers that need the 1e-5 accuracy class, on the
+// bf16 matrix instructions.  A float is the exact sum of three bf16 numbers (8 significand bits each, the second and
+// the third the rounded remainders), so a product of two floats is nine bf16 products; the three smallest, below
+// 2^-25 of the product and of either sign, are left out.  Six v_mfma_f32_32x32x16_bf16 (32 cycles each) contract what
+// eight v_mfma_f32_32x32x2_f32 (64 cycles each) do, in fewer rounded additions.
 //
-// MFMA 32x32x2 fp32 lane layouts (wave64, lane l, l32 = l % 32, hh = l / 32), one float per operand:
-//   A[m][k]: m = l32, k = hh       B[k][n]: n = l32, k = hh
-//   C[m][n]: n = l32, m = 8 (v / 4) + 4 hh + v % 4 (v = 0..15)
-// so one instruction contracts TWO indices, one supplied by each half of the wave.  An accumulator
-// register v is therefore directly an operand whose two contraction indices are m(v, 0) and m(v, 1) =
-// m(v, 0) + 4; the other operand of such a product is fetched with the same pairing.
+// Organisation: one workgroup walks the blocks (B = 32 positions) of one sequence chunk of one (batch, head) chain;
+// wave w owns value features 32 w .. 32 w + 31 of the output and of the running state, whose slice stays in MFMA
+// accumulator registers and is split into operands straight from there.  X and Y tiles are split once, by the thread
+// that loads them, and sit in LDS as three bf16 planes each (the tile layout of the 16-bit kernels); a wave's own
+// columns of Z go from global memory to its registers and are split there (no other wave needs them).  The masked
+// score tile is the same for all waves: they compute it in 16 x 16 quarters (v_mfma_f32_16x16x32_bf16) and exchange it
+// through LDS.
 //
-// Tile layout in LDS: row-major fp32, unpadded, the 16-byte chunk index of a row XOR-ed with row % 16:
-// the 16-byte row reads (lanes = rows) are then bank-conflict free, the 4-byte column reads
-// (lanes = consecutive features of one row per wave half) stay contiguous per row.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include "la2_internal.h"
+// One tile buffer: the next block's values are on their way to registers while a block is computed, and are split
+// into the planes between the block's two barriers.  63 KiB (D = 128) or 32 KiB (D = 64) of LDS and 256 registers, so
+// two (four) workgroups share a compute unit and one computes while the other splits and waits.
+//
+// What bounds it: issue.  Per wave and block 3,840 cycles of matrix pipe and about 870 vector instructions (the split is
+// 5.5 per element: 64 elements of the state, 64 of the tiles; the pipes share the issue, at full load both are half
+// busy).  Against v_mfma_f32_32x32x2_f32 on tiles in fp32 (208 of 64 cycles, one workgroup per unit): forward scan of
+// 256 chains of 1024 positions, d 128, 0.28 -> 0.18 ms; forward + backward at batch 4, H 16, n 2048, d 128
+// 0.86 -> 0.44 ms, batch 16 1.20 -> 0.62 at n 1024; d 64, batch 4, n 4096 0.57 -> 0.37.  Relative error of the results
+// (2-norm, N(0, 1) data) 3.0e-7 -> 2.5e-7 at d 128, 2.7e-7 -> 2.2e-7 at d 64.
+//
+// Feature order.  In the accumulator layout a lane holds rows 8 (v / 4) + 4 hh + v % 4 of a state tile, so the eight
+// elements of a k-step would not be the eight consecutive features of an X row fragment.  The transposing reads of Y
+// take the columns with bits 2 and 3 of the index exchanged (the lanes pass the addresses of the 8-byte pieces in that
+// order); state register (t, v) then is key feature 32 t + 16 (v / 8) + 8 hh + v % 8 and a k-step's elements are
+// features 16 ks + 8 hh .. + 7.
+//
+// Values: an Inf among the inputs makes the rows that depend on it NaN (the remainder of its split is Inf - Inf).
+#include "la2_bf16_common.h"
 
 namespace la2 {
 namespace {
+using namespace bf16k;
 
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) int i32x4;
+constexpr int kBF = 32;   // block size (positions per block)
+typedef ex8<__bf16> b8;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-constexpr int kB = 32;   // block size (positions per block)
-
-__device__ __forceinline__ f32x16 mfma(float a, float b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+// the three bf16 parts of a pair of floats, packed (low half: the first)
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  auto pk = [](float x, float y) __attribute__((always_inline)) {
+    const f32x2 v = {x, y};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+  };
+  hi = pk(a, b);
+  a -= __uint_as_float(hi << 16);
+  b -= __uint_as_float(hi & 0xFFFF0000u);
+  mid = pk(a, b);
+  a -= __uint_as_float(mid << 16);
+  b -= __uint_as_float(mid & 0xFFFF0000u);
+  lo = pk(a, b);
 }
 
-__device__ __forceinline__ f32x16 zero16() {
-  f32x16 z;
+struct Parts {   // an operand of eight floats: its parts, the largest first
+  b8 p[3];
+};
+__device__ __forceinline__ Parts split8(const float (&x)[8]) {
+  union { uint32_t u[4]; b8 v; } r[3];
 #pragma unroll
-  for (int v = 0; v < 16; v++) z[v] = 0.f;
-  return z;
+  for (int i = 0; i < 4; i++) split2(x[2 * i], x[2 * i + 1], r[0].u[i], r[1].u[i], r[2].u[i]);
+  return Parts{{r[0].v, r[1].v, r[2].v}};
 }
 
-// Direct global -> LDS copy, 16 bytes per lane (as in the bf16 kernels: issued from inline assembly,
-// completion tracked by hand with s_waitcnt vmcnt).
-__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-               :
-               : "v"(voff), "s"(base), "s"(lds_base)
-               : "m0", "memory");
+// the six products of at least 2^-17 of the whole, the small ones first
+template <typename Acc, typename F>
+__device__ __forceinline__ Acc six(const Parts& a, const Parts& b, Acc c, F f) {
+  c = f(a.p[0], b.p[2], c);
+  c = f(a.p[2], b.p[0], c);
+  c = f(a.p[1], b.p[1], c);
+  c = f(a.p[0], b.p[1], c);
+  c = f(a.p[1], b.p[0], c);
+  return f(a.p[0], b.p[0], c);
+}
+__device__ __forceinline__ f32x16 mul32(const Parts& a, const Parts& b, f32x16 c) {
+  return six(a, b, c, [](b8 x, b8 y, f32x16 z) __attribute__((always_inline)) { return mfma(x, y, z); });
+}
+__device__ __forceinline__ f32x4 mul16(const Parts& a, const Parts& b, f32x4 c) {
+  return six(a, b, c, [](b8 x, b8 y, f32x4 z) __attribute__((always_inline)) { return mfma16(x, y, z); });
 }
 
-__device__ __forceinline__ uint32_t lds_offset(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+// The same split in eight steps of five or six vector instructions, each closed by pins: side work for the shadow of
+// six MFMAs (step(i) beside the i-th).
+struct Splitter {
+  float x[8];
+  union Out { uint32_t u[4]; b8 v; } out[3];
+  __device__ __forceinline__ void first(int i, int part) {   // pair i: this part, and the remainders
+    const f32x2 v = {x[2 * i], x[2 * i + 1]};
+    const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    out[part].u[i] = h;
+    x[2 * i] -= __uint_as_float(h << 16);
+    x[2 * i + 1] -= __uint_as_float(h & 0xFFFF0000u);
+    pin(x[2 * i]);
+    pin(x[2 * i + 1]);
+    pin(out[part].u[i]);
+  }
+  __device__ __forceinline__ void rest(int i) {
+    first(i, 1);
+    const f32x2 v = {x[2 * i], x[2 * i + 1]};
+    out[2].u[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    pin(out[2].u[i]);
+  }
+  __device__ __forceinline__ void step(int i) {
+    if (i == 0) first(0, 0);
+    if (i == 1) first(1, 0);
+    if (i == 2) { rest(0); first(2, 0); }
+    if (i == 3) rest(1);
+    if (i == 4) first(3, 0);
+    if (i == 5) { rest(2); rest(3); }
+  }
+  __device__ __forceinline__ Parts parts() const { return Parts{{out[0].v, out[1].v, out[2].v}}; }
+};
+// Six MFMAs of one 32 x 32 product, side(i) in the shadow of the i-th; nothing moves across their borders.
+template <typename F>
+__device__ __forceinline__ void mul32_slots(const Parts& a, const Parts& b, f32x16& c, F side) {
+  constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+  for (int i = 0; i < 6; i++) {
+    c = mfma(a.p[ia[i]], b.p[ib[i]], c);
+    side(i);
+    pin(c);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
-// element offset of feature f of tile row `row` (D floats per row, 16-byte chunks swizzled by row % 16)
+// lambda^e for e >= 0, with the logarithm to twice the working precision: l2 + l2lo = log2(lambda)
+struct Decay {
+  float l2, l2lo;
+  __device__ __forceinline__ explicit Decay(float lambda) {
+    const double d = log2((double)lambda);
+    l2 = (float)d;
+    l2lo = (float)(d - (double)l2);
+  }
+  __device__ __forceinline__ float pow(int e) const {
+    const float x = (float)e, p = l2 * x;
+    const float rest = fmaf(l2, x, -p) + l2lo * x;
+    const float y = exp2f(p);
+    return fmaf(y * 0.6931471805599453f, rest, y);
+  }
+};
+
 template <int D>
-__device__ __forceinline__ int tile_off(int row, int f) {
-  return row * D + ((((f >> 2) ^ (row & 15)) << 2) | (f & 3));
-}
-
-// key feature dk, value feature dv of state-slice element (t, v) of a lane <-> index into a d x d state
-template <int D>
-__device__ __forceinline__ int state_index(int dvt, int l32, int hh, int t, int v, bool transposed) {
-  const int dk = 32 * t + 8 * (v >> 2) + 4 * hh + (v & 3);
+__device__ __forceinline__ int state_index_f32(int dvt, int l32, int hh, int t, int v, bool transposed) {
+  const int dk = 32 * t + 16 * (v >> 3) + 8 * hh + (v & 7);
   const int dv = 32 * dvt + l32;
   return transposed ? dv * D + dk : dk * D + dv;
 }
@@ -73,28 +155,40 @@ __device__ __forceinline__ int state_index(int dvt, int l32, int hh, int t, int 
 // Scan kernel (STATE_ONLY = false) and chunk-state pre-pass (STATE_ONLY = true: only Y, Z and the state
 // update; the local state of the chunk is written to p.states).  D / 32 waves.
 template <int D, bool REV, bool STATE_ONLY>
-__global__ __launch_bounds__(2 * D, 1) void scan_f32_kernel(ScanParams p) {
+__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) void scan_f32_kernel(ScanParams p) {
+  constexpr int B = kBF;
   constexpr int NT = D / 32;          // waves; 32-wide feature tiles
-  constexpr int NJ = D / 8;           // pairs of 16-byte chunks per row (one pair per 8 features)
-  constexpr int TILE = kB * D;        // floats per tile
-  constexpr int NTL = STATE_ONLY ? 2 : 3;
-  constexpr int DMA_PER_WAVE = (TILE * 4 / 1024) / NT;   // 1 KiB instructions per tile and wave (= 4)
-  __shared__ __attribute__((aligned(1024))) float sT[2][NTL][TILE];
-  __shared__ float sRed[STATE_ONLY ? 1 : kB * NT];   // Norm epilogue: partial sums of squares, [row][wave]
+  constexpr int KS = D / 16;          // k-steps along the features
+  constexpr int CPR = D / 8;          // 8-feature pieces per row
+  constexpr int TILE = B * D;         // elements per plane
+  constexpr int PROW = 40;            // elements per row of a score plane (80 bytes: 16 rows in 16 bank groups)
+  __shared__ __attribute__((aligned(1024))) __bf16 sX[STATE_ONLY ? 1 : 3][STATE_ONLY ? 8 : TILE];
+  __shared__ __attribute__((aligned(1024))) __bf16 sY[3][TILE];
+  __shared__ __attribute__((aligned(16))) __bf16 sP[STATE_ONLY ? 1 : 3][STATE_ONLY ? 8 : B * PROW];   // [position r][c]
+  __shared__ __attribute__((aligned(16))) float sWz[B];   // weight of a row of Z in the state update
+  __shared__ float sRed[STATE_ONLY ? 1 : B * NT];   // Norm epilogue: partial sums of squares, [row][wave]
 
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l32 = l & 31, hh = l >> 5;
   const int dvt = w;
-  const int chain = blockIdx.x / p.nchunks, chunk = blockIdx.x % p.nchunks;
+  int which = 0, wg = (int)blockIdx.x;
+  if (!STATE_ONLY && p.nscan == 2) {   // two scans that read the same tiles: eight workgroups apart, on one XCD
+    if (((gridDim.x >> 1) & 7) == 0) {
+      which = (wg >> 3) & 1;
+      wg = ((wg >> 4) << 3) | (wg & 7);
+    } else {
+      which = wg & 1;
+      wg >>= 1;
+    }
+  }
+  const int chain = wg / p.nchunks, chunk = wg % p.nchunks;
   const int bi = chain / p.heads, hi = chain % p.heads;
   int64_t base;
   int n;
   chain_extent(p, bi, hi, base, n);
   const uint32_t stride_n = (uint32_t)p.stride_n;
-  const float l2 = log2f(p.lambda[hi]);
-  const float lamB = exp2f(l2 * (float)kB);
 
-  const int nblocks = (n + kB - 1) / kB;
-  const int cb = p.chunk_tokens / kB;
+  const int nblocks = (n + B - 1) / B;
+  const int cb = p.chunk_tokens / B;
   const int blk_lo = chunk * cb;
   const int blk_hi = min(blk_lo + cb, nblocks);
   if (!STATE_ONLY && blk_lo >= blk_hi) return;
@@ -102,170 +196,313 @@ __global__ __launch_bounds__(2 * D, 1) void scan_f32_kernel(ScanParams p) {
   if (STATE_ONLY && (REV ? (chunk == 0) : (blk_hi >= nblocks))) return;
   const int nblk = max(blk_hi - blk_lo, 0);
 
-  const char* g[3];
-  if (STATE_ONLY) {
-    g[0] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(p.y[0]) + base);
-    g[1] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(p.z[0]) + base);
-    g[2] = nullptr;
-  } else {
-    g[0] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(p.x[0]) + base);
-    g[1] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(p.y[0]) + base);
-    g[2] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(p.z[0]) + base);
-  }
-  constexpr int TX = 0, TY = STATE_ONLY ? 0 : 1, TZ = STATE_ONLY ? 1 : 2;
+  // Buffer descriptors over the chain's rows: rows past the end load as zeros and their stores are dropped.
+  const uint32_t chain_bytes = n > 0 ? ((uint32_t)(n - 1) * stride_n + D) * 4u : 0u;
+  auto rows_of = [&](const void* ptr) __attribute__((always_inline)) {
+    return make_rsrc(reinterpret_cast<const float*>(ptr) + base, chain_bytes);
+  };
+  const __amdgpu_buffer_rsrc_t gx = rows_of(STATE_ONLY ? p.y[0] : which ? p.x[1] : p.x[0]);
+  const __amdgpu_buffer_rsrc_t gy = rows_of(which ? p.y[1] : p.y[0]);
+  const __amdgpu_buffer_rsrc_t gz = rows_of(which ? p.z[1] : p.z[0]);
+  const __amdgpu_buffer_rsrc_t gw = rows_of(STATE_ONLY ? p.y[0] : which ? p.w[1] : p.w[0]);
 
-  // direct loads: instruction i of this wave fills LDS chunks q = 64 (DMA_PER_WAVE w + i) + l of a tile,
-  // i.e. row q / (D / 4), physical chunk q % (D / 4), which holds logical chunk (q % (D / 4)) ^ (row % 16)
-  int drow[DMA_PER_WAVE], dcol[DMA_PER_WAVE];
+  // ---- tile loads: this thread's two 8-feature pieces of X and Y (rows r0 and r0 + 16), this lane's column of Z
+  const int r0 = tid / CPR, ch = tid % CPR;
+  const int plane_at = r0 * D + 8 * (ch ^ swz<D>(r0));   // swz depends on row % 16: the second piece is 16 D further
+  float px[2][8], py[2][8], pz[16];
+  auto load8 = [&](const __amdgpu_buffer_rsrc_t& g, uint32_t off, float (&x)[8]) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < DMA_PER_WAVE; i++) {
-    const int q = 64 * (DMA_PER_WAVE * w + i) + l;
-    drow[i] = q / (D / 4);
-    dcol[i] = 4 * ((q % (D / 4)) ^ (drow[i] & 15));
-  }
-  const uint32_t wave_lds = (uint32_t)__builtin_amdgcn_readfirstlane(1024 * DMA_PER_WAVE * w);
-  auto issue = [&](int buf, int blk) __attribute__((always_inline)) {
+    for (int i = 0; i < 2; i++) {
+      const i32x4 r = __builtin_amdgcn_raw_buffer_load_b128(g, off + 16u * i, 0, 0);
 #pragma unroll
-    for (int i = 0; i < DMA_PER_WAVE; i++) {
-      const int pos = min(blk * kB + drow[i], n - 1);   // rows past the end are zeroed after landing
-      const uint32_t off = ((uint32_t)pos * stride_n + (uint32_t)dcol[i]) * 4u;
-#pragma unroll
-      for (int t = 0; t < NTL; t++) dma16(g[t], off, lds_offset(&sT[buf][t][0]) + wave_lds + 1024u * i);
+      for (int j = 0; j < 4; j++) x[4 * i + j] = __int_as_float(r[j]);
     }
   };
-  auto zero_tail = [&](int buf, int blk) __attribute__((always_inline)) {
-    if ((blk + 1) * kB > n) {
+  auto load_block = [&](int blk) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < DMA_PER_WAVE; i++)
-        if (blk * kB + drow[i] >= n) {
-          const i32x4 z = {0, 0, 0, 0};
+    for (int i = 0; i < 2; i++) {
+      const uint32_t off = ((uint32_t)(blk * B + r0 + 16 * i) * stride_n + 8u * ch) * 4u;
+      load8(gy, off, py[i]);
+      if (!STATE_ONLY) load8(gx, off, px[i]);
+    }
+    uint32_t zoff = ((uint32_t)(blk * B + 4 * hh) * stride_n + (uint32_t)(32 * dvt + l32)) * 4u;
+    pin(zoff);   // the sixteen offsets are made here: kept across blocks they would be sixteen registers
 #pragma unroll
-          for (int t = 0; t < NTL; t++)
-            *reinterpret_cast<i32x4*>(reinterpret_cast<char*>(&sT[buf][t][0]) + (wave_lds + 1024u * i + 16u * l)) = z;
-        }
+    for (int v = 0; v < 16; v++)
+      pz[v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(gz, zoff + (uint32_t)(8 * (v >> 2) + (v & 3)) * stride_n * 4u, 0, 0));
+  };
+  float zr[16];   // the Z column of the block whose planes are in LDS
+  auto write_planes = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 16; v++) zr[v] = pz[v];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      const Parts y = split8(py[i]);
+#pragma unroll
+      for (int k = 0; k < 3; k++) *reinterpret_cast<b8*>(&sY[k][plane_at + 16 * D * i]) = y.p[k];
+      if (!STATE_ONLY) {
+        const Parts x = split8(px[i]);
+#pragma unroll
+        for (int k = 0; k < 3; k++) *reinterpret_cast<b8*>(&sX[k][plane_at + 16 * D * i]) = x.p[k];
+      }
     }
   };
 
   // ---- running state slice S[:, dv tile]: NT accumulator tiles (key-feature tiles), fp32
   f32x16 kv[NT];
-  {
-    const float* gs = nullptr;
-    bool tr = false;
-    if (!STATE_ONLY && p.states != nullptr) {
-      gs = p.states + ((int64_t)chain * p.nchunks + chunk) * (D * D);
-      tr = p.state_transposed & 1;
-    } else if (!STATE_ONLY && p.init[0] != nullptr) {
-      gs = p.init[0] + (int64_t)chain * (D * D);
-      tr = p.init_transposed & 1;
+#pragma unroll
+  for (int t = 0; t < NT; t++) kv[t] = zero16();
+  const Decay lam(p.lambda[hi]);
+  if constexpr (!STATE_ONLY) {
+    // kv <- decay kv + a d x d state (row = y feature, or transposed: eight consecutive elements of a stored row)
+    auto add_state = [&](const float* gs, bool tr, float decay) __attribute__((always_inline)) {
+      uint32_t at = (uint32_t)state_index_f32<D>(dvt, l32, hh, 0, 0, tr);
+      pin(at);   // one lane offset, the rest is uniform: not sixteen addresses per tile
+#pragma unroll
+      for (int t = 0; t < NT; t++) {
+        float x[16];
+        if (tr) {
+#pragma unroll
+          for (int v = 0; v < 16; v += 4) {
+            const f32x4 r = *reinterpret_cast<const f32x4*>(gs + (32 * t + 16 * (v >> 3) + (v & 7)) + at);
+#pragma unroll
+            for (int i = 0; i < 4; i++) x[v + i] = r[i];
+          }
+        } else {
+#pragma unroll
+          for (int v = 0; v < 16; v++) x[v] = (gs + (32 * t + 16 * (v >> 3) + (v & 7)) * D)[at];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; v++) kv[t][v] = fmaf(decay, kv[t][v], x[v]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    const float* const init = which ? p.init[1] : p.init[0];
+    const bool init_tr = (p.init_transposed >> which) & 1, state_tr = (p.state_transposed >> which) & 1;
+    if (init != nullptr && (p.states == nullptr || p.self_prefix != 0)) add_state(init + (int64_t)chain * (D * D), init_tr, 0.f);
+    if (p.states != nullptr && p.self_prefix == 0) {
+      add_state(p.states + ((int64_t)chain * p.nchunks + chunk) * (D * D), state_tr, 0.f);
+    } else if (p.states != nullptr) {   // the local states of the chunks this scan passes before (ScanParams::self_prefix)
+      const int nch = min((nblocks + cb - 1) / cb, p.nchunks);   // (a longer sequence than planned for: the caller's error)
+      const float lam_full = lam.pow(p.chunk_tokens), lam_last = lam.pow(n - (nch - 1) * p.chunk_tokens);
+#pragma unroll 1
+      for (int i = 0; i < (REV ? nch - 1 - chunk : chunk); i++) {
+        const int j = REV ? nch - 1 - i : i;
+        add_state(p.states + ((int64_t)chain * p.nchunks + j) * (D * D), state_tr, j == nch - 1 ? lam_last : lam_full);
+      }
     }
-#pragma unroll
-    for (int t = 0; t < NT; t++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index<D>(dvt, l32, hh, t, v, tr)] : 0.f;
   }
 
-  // ---- per-lane constants (accumulator element v <-> tile row cc[v] = 8 (v / 4) + 4 hh + v % 4):
-  // decay mask of the score tile S^T[c][r] (lane: r = l32), update weight of row c, carried-state weight
-  float dg[16], wz[16];
+  // ---- decay weights: of the rows of Z in the state update (LDS), of the carried state at this lane's position, of the
+  // quarters of the score tile S^T[c][r] that this wave computes (lane: position
+  // r = 16 rq + l % 16, elements i: c = 16 cq + 4 (l / 16) + i).
+  if (tid < B) sWz[tid] = lam.pow(REV ? tid + 1 : B - 1 - tid);
+  const float lamB = uniform(lam.pow(B));
+  const float inter_scale = lam.pow(REV ? B - 1 - l32 : l32 + 1);
+  constexpr int NQ = 4 / NT;   // quarters per wave: w, w + NT
+  const int l16 = l & 15, g4 = l >> 4;
+  float dg[STATE_ONLY ? 1 : NQ][4];
+  if (!STATE_ONLY) {
 #pragma unroll
-  for (int v = 0; v < 16; v++) {
-    const int cc = 8 * (v >> 2) + 4 * hh + (v & 3);
-    const int e = REV ? cc - l32 : l32 - cc;
-    dg[v] = (e >= 0) ? exp2f(l2 * (float)e) : 0.f;
-    wz[v] = exp2f(l2 * (float)(REV ? cc + 1 : kB - 1 - cc));
+    for (int u = 0; u < NQ; u++) {
+      const int q = w + NT * u, cq = q & 1, rq = q >> 1;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int c = 16 * cq + 4 * g4 + i, r = 16 * rq + l16, e = REV ? c - r : r - c;
+        dg[u][i] = e >= 0 ? lam.pow(e) : 0.f;
+      }
+    }
+    for (int i = tid; i < 3 * B * PROW / 2; i += 2 * D) reinterpret_cast<uint32_t*>(&sP[0][0])[i] = 0u;   // the empty quarter stays zero
   }
-  const float inter_scale = exp2f(l2 * (float)(REV ? kB - 1 - l32 : l32 + 1));
-  float* gw = STATE_ONLY ? nullptr : reinterpret_cast<float*>(p.w[0]) + base;
 
-  if (nblk > 0) {
-    const int b0 = REV ? blk_hi - 1 : blk_lo;
-    issue(0, b0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    zero_tail(0, b0);
+  if (nblk > 0) load_block(REV ? blk_hi - 1 : blk_lo);
+
+  // ---- LDS addresses: row fragments (32 rows x 16 features; 16 rows x 32 features), transposing reads
+  const int rowk = l32 * D + 8 * (hh ^ swz<D>(l32));       // 32-row fragment of k-step ks: rowk ^ 16 ks
+  const int rowq = l16 * D + 8 * (g4 ^ swz<D>(l16));       // 16-row fragment of k-step ks: rowq ^ 32 ks (+ 16 D rows)
+  int tr0, tr1;
+  {
+    const int g2 = (l >> 4) & 1, piece = l & 3;
+    const int trc = 2 * g2 + (piece & 1), trh = 4 * (piece >> 1);   // bits 2 and 3 of the column exchanged
+    const int ra = 4 * hh + (l16 >> 2), rb = ra + 8;
+    tr0 = ra * D + 8 * (trc ^ swz<D>(ra)) + trh;
+    tr1 = rb * D + 8 * (trc ^ swz<D>(rb)) + trh;
   }
-  __syncthreads();
+  auto read_parts = [&](const __bf16 (*plane)[TILE], int at) __attribute__((always_inline)) {
+    Parts r;
+#pragma unroll
+    for (int k = 0; k < 3; k++) r.p[k] = *reinterpret_cast<const b8*>(&plane[k][at]);
+    return r;
+  };
+  auto read_ycols = [&](int q, int t) __attribute__((always_inline)) {   // rows 16 q .. + 15, key-feature tile t
+    Parts r;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      union { struct { s16x4 lo, hi; } s; b8 v; } u;
+      u.s.lo = lds_read_tr(&sY[k][16 * q * D + (tr0 ^ (32 * t))]);
+      u.s.hi = lds_read_tr(&sY[k][16 * q * D + (tr1 ^ (32 * t))]);
+      r.p[k] = u.v;
+    }
+    return r;
+  };
+
+  if (nblk > 0) write_planes();
+  lds_barrier();
 
   for (int it = 0; it < nblk; it++) {
-    const int cur = it & 1;
     const int blk = REV ? blk_hi - 1 - it : blk_lo + it;
     const bool has_next = it + 1 < nblk;
-    const int nb = REV ? blk - 1 : blk + 1;
-    if (has_next) issue(cur ^ 1, nb);
-    const float* tX = sT[cur][TX];
-    const float* tY = sT[cur][TY];
-    const float* tZ = sT[cur][TZ];
+    if (has_next) load_block(REV ? blk - 1 : blk + 1);
 
-    // Z column fragments: row cc[v] of the block, this wave's value feature l32 (used by the intra-block
-    // product and, weighted, by the state update)
-    float zc[16];
+    // The body is a sequence of slots: the MFMAs of one product, in their shadow the LDS reads and the splits of the
+    // next one (left alone the compiler puts every split in front of the product that takes it).
+    f32x16 acc = zero16();
+    Parts yt[2], zd, zf[2];
+    // Pre-pass: only the state after the last block is wanted, so every block's contribution carries its whole decay up
+    // front.
+    const float up = STATE_ONLY ? uniform(lam.pow(B * (nblk - 1 - it))) : 1.f;
+    Splitter sp;
+    auto z_into = [&](int q, bool decayed) __attribute__((always_inline)) {
 #pragma unroll
-    for (int v = 0; v < 16; v++) zc[v] = tZ[tile_off<D>(8 * (v >> 2) + 4 * hh + (v & 3), 32 * dvt + l32)];
-
-    if (!STATE_ONLY) {
-      // X row fragments: row l32, features 8 j + 4 hh .. + 3 (j = 0 .. NJ - 1): one 16-byte read each.  They
-      // serve the score product (paired with the same features of Y) and the inter-block product (state
-      // register v of tile t pairs features 32 t + 8 (v / 4) + v % 4 and + 4, i.e. j = 4 t + v / 4).
-      f32x4 xr[NJ];
+      for (int h = 0; h < 2; h++) {
+        const f32x4 wt = *reinterpret_cast<const f32x4*>(&sWz[16 * q + 8 * h + 4 * hh]);
 #pragma unroll
-      for (int j = 0; j < NJ; j++) xr[j] = *reinterpret_cast<const f32x4*>(&tX[tile_off<D>(l32, 8 * j + 4 * hh)]);
-      // inter-block part W^T[dv][r] = sum_dk State[dk][dv] X[r][dk], state straight from its registers
-      f32x16 acc = zero16();
-#pragma unroll
-      for (int t = 0; t < NT; t++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) acc = mfma(kv[t][v], xr[4 * t + (v >> 2)][v & 3], acc);
-      // score tile S^T[c][r] = sum_k Y[c][k] X[r][k]
-      f32x16 st = zero16();
-#pragma unroll
-      for (int j = 0; j < NJ; j++) {
-        const f32x4 yr = *reinterpret_cast<const f32x4*>(&tY[tile_off<D>(l32, 8 * j + 4 * hh)]);
-#pragma unroll
-        for (int i = 0; i < 4; i++) st = mfma(yr[i], xr[j][i], st);
+        for (int j = 0; j < 4; j++)
+          sp.x[4 * h + j] = decayed ? zr[8 * q + 4 * h + j] * (STATE_ONLY ? wt[j] * up : wt[j]) : zr[8 * q + 4 * h + j];
       }
-      // carried part takes its decay, scores take the mask, then the intra-block part Z^T P^T
+    };
+    if constexpr (!STATE_ONLY) {
+      auto state_into = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
-      for (int v = 0; v < 16; v++) acc[v] *= inter_scale;
+        for (int j = 0; j < 8; j++) sp.x[j] = kv[ks >> 1][8 * (ks & 1) + j];
+      };
+      // score quarters S^T[c][r] = sum_k Y[c][k] X[r][k]  (the empty quarter: computed by the wave that would idle, not used)
+      f32x4 s[NQ];
+      Parts xa[2] = {read_parts(sX, rowk), {}};
 #pragma unroll
-      for (int v = 0; v < 16; v++) acc = mfma(zc[v], st[v] * dg[v], acc);
-      const int pos = blk * kB + l32;
-      if (p.rstd != nullptr) {   // Norm epilogue (eq. (2)); the previous block's reads ended before its last barrier
+      for (int u = 0; u < NQ; u++) {
+        const int q = w + NT * u, cq = q & 1, rq = q >> 1;
+        s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ks++)
+          s[u] = mul16(read_parts(sY, 16 * cq * D + (rowq ^ (32 * ks))), read_parts(sX, 16 * rq * D + (rowq ^ (32 * ks))), s[u]);
+      }
+      state_into(0);
+#pragma unroll
+      for (int i = 0; i < 6; i++) sp.step(i);
+      Parts sa = sp.parts();
+#pragma unroll
+      for (int u = 0; u < NQ; u++) pin(s[u]);
+      __builtin_amdgcn_sched_barrier(0);
+      // inter-block part W^T[dv][r] = sum_dk State[dk][dv] X[r][dk], state straight from its registers
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        mul32_slots(sa, xa[ks & 1], acc, [&](int i) __attribute__((always_inline)) {
+          if (i == 0) {
+            if (ks + 1 < KS) {
+              xa[(ks + 1) & 1] = read_parts(sX, rowk ^ (16 * (ks + 1)));
+              state_into(ks + 1);
+            } else {
+              yt[0] = read_ycols(0, 0);
+              z_into(0, true);
+            }
+          }
+          sp.step(i);
+          if ((ks & 1) && i < 4) {   // both operands of state tile ks / 2 are made
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+              float y = kv[ks >> 1][4 * i + v] * lamB;
+              pin(y);
+              kv[ks >> 1][4 * i + v] = y;
+            }
+          }
+        });
+        if (ks < NQ) {   // the quarter's mask and decay, to LDS: row r, columns in the order of the intra-block operand
+          const int q = w + NT * ks, cq = q & 1, rq = q >> 1;
+          if (REV ? cq >= rq : cq <= rq) {
+            uint32_t part[3][2];
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+              split2(s[ks][2 * i] * dg[ks][2 * i], s[ks][2 * i + 1] * dg[ks][2 * i + 1], part[0][i], part[1][i], part[2][i]);
+            const int at = (16 * rq + l16) * PROW + 16 * cq + 8 * (g4 & 1) + 4 * (g4 >> 1);
+#pragma unroll
+            for (int k = 0; k < 3; k++) *reinterpret_cast<u32x2*>(&sP[k][at]) = u32x2{part[k][0], part[k][1]};
+          }
+        }
+        sa = sp.parts();
+      }
+    } else {
+      yt[0] = read_ycols(0, 0);
+      z_into(0, true);
+#pragma unroll
+      for (int i = 0; i < 6; i++) sp.step(i);
+    }
+    zd = sp.parts();
+    // state slice <- lambda^B state + Y^T decay(Z)
+#pragma unroll
+    for (int u = 0; u < 2 * NT; u++) {
+      const int t = u % NT;
+      mul32_slots(yt[u & 1], zd, kv[t], [&](int i) __attribute__((always_inline)) {
+        if (i == 0 && u + 1 < 2 * NT) yt[(u + 1) & 1] = read_ycols((u + 1) / NT, (u + 1) % NT);
+        if (u == NT - 1) {
+          if (i == 0) z_into(1, true);
+          sp.step(i);
+        }
+        if constexpr (!STATE_ONLY) {
+          if (u == 0 && i < 4) {   // the carried part takes the decay at this lane's position
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+              float y = acc[4 * i + v] * inter_scale;
+              pin(y);
+              acc[4 * i + v] = y;
+            }
+          }
+          if (u >= NT && u < NT + 2) {   // Z as it is, for the intra-block product
+            if (i == 0) z_into(u - NT, false);
+            sp.step(i);
+          }
+        }
+      });
+      if (u == NT - 1) zd = sp.parts();
+      if (!STATE_ONLY && u >= NT && u < NT + 2) zf[u - NT] = sp.parts();
+    }
+    lds_barrier();   // every wave has read this block's planes, the score tile is complete
+    if (has_next) write_planes();
+    if constexpr (!STATE_ONLY) {
+      // intra-block part Z^T P^T
+#pragma unroll
+      for (int q = 0; q < 2; q++) {
+        Parts pd;
+#pragma unroll
+        for (int k = 0; k < 3; k++) pd.p[k] = *reinterpret_cast<const b8*>(&sP[k][l32 * PROW + 16 * q + 8 * hh]);
+        acc = mul32(zf[q], pd, acc);
+      }
+      // output: lane = position l32, elements v = 4 g .. 4 g + 3 are value features 32 dvt + 8 g + 4 hh .. + 3
+      const int pos = blk * B + l32;
+      auto store_rows = [&]() __attribute__((always_inline)) {
+        const uint32_t off = ((uint32_t)pos * stride_n + (uint32_t)(32 * dvt + 4 * hh)) * 4u;
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          const i32x4 o4 = {__float_as_int(acc[4 * g]), __float_as_int(acc[4 * g + 1]), __float_as_int(acc[4 * g + 2]),
+                            __float_as_int(acc[4 * g + 3])};
+          __builtin_amdgcn_raw_buffer_store_b128(o4, gw, off + 32u * g, 0, 0);
+        }
+      };
+      if (p.rstd != nullptr) {   // Norm epilogue (eq. (2)); the sums meet under the block's second barrier
         norm_publish<NT>(acc, sRed, l32, hh, dvt);
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // LDS only: the next tiles stay in flight
+        lds_barrier();
         const float r = norm_collect<NT>(sRed, l32, 1.f / (float)D, p.eps);
 #pragma unroll
         for (int v = 0; v < 16; v++) acc[v] *= r;
         if (dvt == 0 && hh == 0 && pos < n) p.rstd[rstd_chain_offset(p, bi, hi) + pos] = r;
+        store_rows();
+      } else {
+        store_rows();
+        lds_barrier();
       }
-      // output: lane = position l32, elements v = 4 g .. 4 g + 3 are value features 32 dvt + 8 g + 4 hh .. + 3
-      if (pos < n) {
-        float* orow = gw + (int64_t)pos * stride_n + 32 * dvt + 4 * hh;
-#pragma unroll
-        for (int gq = 0; gq < 4; gq++) {
-          f32x4 o4 = {acc[4 * gq], acc[4 * gq + 1], acc[4 * gq + 2], acc[4 * gq + 3]};
-          *reinterpret_cast<f32x4*>(orow + 8 * gq) = o4;
-        }
-      }
+    } else {
+      lds_barrier();
     }
-
-    // state slice <- lambda^B state + Y^T decay(Z), contraction over this block's rows, paired as the
-    // Z fragments are: lanes of half hh supply row cc[v]
-#pragma unroll
-    for (int t = 0; t < NT; t++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) kv[t][v] *= lamB;
-#pragma unroll
-    for (int v = 0; v < 16; v++) {
-      const float zw = zc[v] * wz[v];
-      const int row = 8 * (v >> 2) + 4 * hh + (v & 3);
-#pragma unroll
-      for (int t = 0; t < NT; t++) kv[t] = mfma(tY[tile_off<D>(row, 32 * t + l32)], zw, kv[t]);
-    }
-
-    if (has_next) {
-      __builtin_amdgcn_s_waitcnt(0x0F70);   // this wave's part of the next tiles has landed (and its stores)
-      zero_tail(cur ^ 1, nb);
-    }
-    __syncthreads();
   }
 
   // the chunk's local state (pre-pass) or the state after the chain's last block (on request)
@@ -273,36 +510,36 @@ __global__ __launch_bounds__(2 * D, 1) void scan_f32_kernel(ScanParams p) {
   bool trf = false;
   if (STATE_ONLY) {
     gf = p.states + ((int64_t)chain * p.nchunks + chunk) * (D * D);
-  } else if (p.fin[0] != nullptr && (REV ? chunk == 0 : chunk == p.nchunks - 1)) {
-    gf = p.fin[0] + (int64_t)chain * (D * D);
-    trf = p.fin_transposed & 1;
+  } else if ((which ? p.fin[1] : p.fin[0]) != nullptr && (REV ? chunk == 0 : chunk == p.nchunks - 1)) {
+    gf = (which ? p.fin[1] : p.fin[0]) + (int64_t)chain * (D * D);
+    trf = (p.fin_transposed >> which) & 1;
   }
   if (gf != nullptr) {
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) gf[state_index<D>(dvt, l32, hh, t, v, trf)] = kv[t][v];
+      for (int v = 0; v < 16; v++) gf[state_index_f32<D>(dvt, l32, hh, t, v, trf)] = kv[t][v];
   }
 }
 
 template <bool STATE_ONLY>
 hipError_t launch(int head_dim, bool reverse, const ScanParams& p, hipStream_t s) {
-  const int64_t grid = (int64_t)p.batch * p.heads * p.nchunks;
+  const int64_t grid = (int64_t)p.batch * p.heads * p.nchunks * (STATE_ONLY ? 1 : p.nscan);
   if (grid == 0 || p.n == 0) return hipSuccess;
-  dim3 g((unsigned)grid);
+  const dim3 g((unsigned)grid), b(2 * head_dim);
   if (head_dim == 128) {
-    if (reverse) hipLaunchKernelGGL((scan_f32_kernel<128, true, STATE_ONLY>), g, dim3(256), 0, s, p);
-    else         hipLaunchKernelGGL((scan_f32_kernel<128, false, STATE_ONLY>), g, dim3(256), 0, s, p);
+    if (reverse) hipLaunchKernelGGL((scan_f32_kernel<128, true, STATE_ONLY>), g, b, 0, s, p);
+    else         hipLaunchKernelGGL((scan_f32_kernel<128, false, STATE_ONLY>), g, b, 0, s, p);
   } else {
-    if (reverse) hipLaunchKernelGGL((scan_f32_kernel<64, true, STATE_ONLY>), g, dim3(128), 0, s, p);
-    else         hipLaunchKernelGGL((scan_f32_kernel<64, false, STATE_ONLY>), g, dim3(128), 0, s, p);
+    if (reverse) hipLaunchKernelGGL((scan_f32_kernel<64, true, STATE_ONLY>), g, b, 0, s, p);
+    else         hipLaunchKernelGGL((scan_f32_kernel<64, false, STATE_ONLY>), g, b, 0, s, p);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-int block_size_f32(int) { return kB; }
+int block_size_f32(int) { return kBF; }
 
 hipError_t launch_scan_f32(int head_dim, bool reverse, const ScanParams& p, hipStream_t s) {
   return launch<false>(head_dim, reverse, p, s);

@@ -591,3 +591,50 @@ def test_left_product_backward_config2_and_extreme_decays():
     with pytest.raises(binding.LA2Error):
         f = gpu(make_inputs(1, 1, 64, 64, torch.float16, seed=1))
         binding.la2_left_product_bwd(f["q"], f["k"], f["v"], f["d_o"], f["lam"])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,chunk", [(33, 0), (95, 0), (290, 64), (290, 96)])
+def test_fp32_products_keep_fp32_accuracy_whatever_the_scale_of_a_feature(n, chunk, d):
+    """The fp32 kernels multiply on the bf16 matrix instructions, every float split into three bf16 parts.  Features
+    scaled by powers of two from 2^-20 to 2^20 (key-like and query-like inversely, so that every term counts; value-like
+    each its own): every output column stays within 1e-6 of its own size, which one part less (2^-17) would miss by a
+    factor of ten and a shared exponent by far more.  Bound: products exact to 2^-25, fp32 sums of at most 290 + 128 terms
+    and decay weights good to a few 2^-24."""
+    g = torch.Generator(device="cpu")
+    g.manual_seed(n + d)
+    b, H = 1, 3
+    draw = lambda: torch.randn((b, H, n, d), generator=g, dtype=torch.float32)
+    qk = torch.pow(2.0, torch.randint(-20, 21, (d,), generator=g).float())
+    vv = torch.pow(2.0, torch.randint(-20, 21, (d,), generator=g).float())
+    q, k, v, do = draw() * qk, draw() / qk, draw() * vv, draw() / vv
+    lam = torch.tensor([0.3, 0.95, 1.0])
+    binding.la2_set_chunk_tokens(chunk)
+    try:
+        gq, gk, gv, gdo, gl = (x.to(DEV) for x in (q, k, v, do, lam))
+        got = (binding.la2_fwd(gq, gk, gv, gl),) + tuple(binding.la2_bwd(gq, gk, gv, gdo, gl))
+        torch.cuda.synchronize()
+    finally:
+        binding.la2_set_chunk_tokens(0)
+    q, k, v, do, lam = (to64(x) for x in (q, k, v, do, lam))
+    ref = (oracle.fwd_direct(q, k, v, lam),) + tuple(oracle.bwd_direct(q, k, v, do, lam))
+    for name, x, r in zip(("o", "dq", "dk", "dv"), got, ref):
+        err = np.sqrt(((to64(x) - r) ** 2).mean(axis=2)) / np.sqrt((r ** 2).mean(axis=2))
+        assert err.max() <= 1e-6, (name, err.max())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_a_non_finite_value_reaches_later_positions_only(d):
+    n, at = 130, 70   # block 64 .. 95 holds it
+    g = torch.Generator(device="cpu")
+    g.manual_seed(d)
+    q, k, v = (torch.randn((1, 2, n, d), generator=g).to(DEV) for _ in range(3))
+    lam = torch.tensor([0.9, 0.99], device=DEV)
+    ref = binding.la2_fwd(q, k, v, lam)
+    for bad in (float("nan"), float("inf")):
+        w = v.clone()
+        w[0, 1, at, 5] = bad
+        o = binding.la2_fwd(q, k, w, lam)
+        torch.cuda.synchronize()
+        assert torch.equal(o[0, 0], ref[0, 0]) and torch.equal(o[0, 1, :64], ref[0, 1, :64])
+        assert not torch.isfinite(o[0, 1, at:, 5]).any()
