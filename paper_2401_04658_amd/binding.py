@@ -5,6 +5,7 @@ PyTorch fallback.  torch is used for device memory and streams.  If the shared
 library is missing the first call raises (build it with
 `python -m paper_2401_04658_amd.build` or `__graft_entry__.build()`).
 """
+import contextlib
 import ctypes
 import os
 
@@ -142,8 +143,20 @@ def _same_layout(ref, *others):
             raise ValueError("la2: all sequence tensors must share shape, strides, dtype and device")
 
 
+# Host time of a call is the whole cost of a small decode step (kernel 3.3 us; batch 1, H 16, d 128: 11.0 us a call
+# with torch.cuda.device and torch.cuda.current_stream around it, 7.5 with these two): the stream handle and the
+# device number are taken from where those wrappers take them, and the device is switched only if it has to be.
+_NO_SWITCH = contextlib.nullcontext()
+
+
+def _on(t):
+    """Context in which t's device is the current one."""
+    return _NO_SWITCH if t.get_device() == torch._C._cuda_getDevice() else torch.cuda.device(t.device)
+
+
 def _stream(t):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    """Handle of the current stream of t's device."""
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def la2_workspace_bytes(t, op=LA2_OP_FWD):
@@ -173,12 +186,12 @@ def la2_set_scan_variant(variant):
 
 
 def _workspace(t, op, workspace):
-    need = la2_workspace_bytes(t, op)
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=t.device)
     if workspace is None:
-        return None, 0, None
-    return ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(), workspace
+        need = la2_workspace_bytes(t, op)
+        if need == 0:
+            return None, 0, None
+        workspace = torch.empty(need, dtype=torch.uint8, device=t.device)
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
 
 
 def la2_fwd(q, k, v, lam, out=None, workspace=None):
@@ -192,7 +205,7 @@ def la2_fwd(q, k, v, lam, out=None, workspace=None):
     _same_layout(q, out)
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
                            out.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
     return out
@@ -206,7 +219,7 @@ def la2_fwd_noalloc(q, k, v, lam, out):
         raise ValueError("la2_fwd_noalloc: tensors must live on the GPU")
     _same_layout(q, k, v, out)
     desc = make_desc(q)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd_noalloc(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
                                    out.data_ptr(), _stream(q)))
     return out
@@ -224,7 +237,7 @@ def la2_bwd(q, k, v, d_o, lam, out=None, workspace=None):
     _same_layout(q, dq, dk, dv)
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_bwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(),
                            lam.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), ws_ptr, ws_bytes,
                            _stream(q)))
@@ -246,7 +259,7 @@ def la2_fwd_norm(q, k, v, lam, eps=1e-6, out=None, rstd=None, workspace=None):
         raise ValueError("la2_fwd_norm: rstd must be a contiguous fp32 [batch, heads, seqlen] tensor")
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
                                 float(eps), out.data_ptr(), rstd.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
     return out, rstd
@@ -269,7 +282,7 @@ def la2_bwd_norm(q, k, v, o, rstd, d_o, lam, out=None, d_u=None, workspace=None)
         raise ValueError("la2_bwd_norm: rstd must be a contiguous fp32 [batch, heads, seqlen] tensor")
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_bwd_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                 rstd.data_ptr(), d_o.data_ptr(), lam.data_ptr(), d_u.data_ptr(), dq.data_ptr(),
                                 dk.data_ptr(), dv.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
@@ -309,7 +322,7 @@ def la2_fwd_varlen(q, k, v, lam, cu_seqlens, max_seqlen, out=None, workspace=Non
     _same_layout(q, out)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
     ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd_varlen(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                   lam.data_ptr(), out.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
     return out
@@ -327,7 +340,7 @@ def la2_bwd_varlen(q, k, v, d_o, lam, cu_seqlens, max_seqlen, out=None, workspac
     _same_layout(q, dq, dk, dv)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
     ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_bwd_varlen(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                   d_o.data_ptr(), lam.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), ws_ptr,
                                   ws_bytes, _stream(q)))
@@ -360,7 +373,7 @@ def la2_fwd_varlen_state(q, k, v, lam, cu_seqlens, max_seqlen, kv_init=None, wan
         kv_final = torch.empty((cu_seqlens.numel() - 1, q.shape[1], q.shape[2], q.shape[2]), dtype=torch.float32,
                                device=q.device)
     ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd_varlen_state(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
                                         v.data_ptr(), lam.data_ptr(), _packed_state(kv_init, q, cu_seqlens, "kv_init"),
                                         out.data_ptr(),
@@ -385,7 +398,7 @@ def la2_bwd_varlen_state(q, k, v, d_o, lam, cu_seqlens, max_seqlen, kv_init=None
         d_kv_init = torch.empty((cu_seqlens.numel() - 1, q.shape[1], q.shape[2], q.shape[2]), dtype=torch.float32,
                                 device=q.device)
     ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_bwd_varlen_state(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
                                         v.data_ptr(), d_o.data_ptr(), lam.data_ptr(),
                                         _packed_state(kv_init, q, cu_seqlens, "kv_init"),
@@ -411,7 +424,7 @@ def la2_fwd_varlen_norm(q, k, v, lam, cu_seqlens, max_seqlen, eps=1e-6, out=None
         raise ValueError("la2_fwd_varlen_norm: rstd must be a contiguous fp32 [heads, total_positions] tensor")
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
     ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd_varlen_norm(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
                                        v.data_ptr(), lam.data_ptr(), float(eps), out.data_ptr(), rstd.data_ptr(), ws_ptr,
                                        ws_bytes, _stream(q)))
@@ -434,7 +447,7 @@ def la2_bwd_varlen_norm(q, k, v, o, rstd, d_o, lam, cu_seqlens, max_seqlen, out=
         raise ValueError("la2_bwd_varlen_norm: rstd must be a contiguous fp32 [heads, total_positions] tensor")
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
     ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_bwd_varlen_norm(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
                                        v.data_ptr(), o.data_ptr(), rstd.data_ptr(), d_o.data_ptr(), lam.data_ptr(),
                                        d_u.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), ws_ptr, ws_bytes,
@@ -457,7 +470,7 @@ def la2_decode_multi_norm(q, k, v, lam, kv_state, eps=1e-6, out=None, rstd=None)
         out = torch.empty_like(q)
     if rstd is None:
         rstd = torch.empty((b, h, t), dtype=torch.float32, device=q.device)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_decode_multi_norm(b, h, d, t, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                          lam.data_ptr(), kv_state.data_ptr(), float(eps), out.data_ptr(), rstd.data_ptr(),
                                          _stream(q)))
@@ -489,7 +502,7 @@ def la2_fwd_state(q, k, v, lam, kv_init=None, want_final=True, out=None, kv_fina
         kv_final = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD_STATE, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd_state(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
                                  _state(kv_init, q, "kv_init"), out.data_ptr(),
                                  _state(kv_final, q, "kv_final") if want_final else None,
@@ -515,7 +528,7 @@ def la2_bwd_state(q, k, v, d_o, lam, kv_init=None, d_kv_final=None, want_d_kv_in
         d_kv_init = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD_STATE, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         fwd_ws = ctypes.c_void_p(fwd_workspace.data_ptr()) if fwd_workspace is not None else None
         _check(lib.la2_bwd_saved(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(),
                                  lam.data_ptr(), _state(kv_init, q, "kv_init"),
@@ -539,7 +552,7 @@ def la2_decode_step(q, k, v, lam, kv_state, out=None):
         raise ValueError("la2_decode_step: kv_state must be dense fp32 [b, H, d, d]")
     if out is None:
         out = torch.empty_like(q)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_decode_step(b, h, d, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                    lam.data_ptr(), kv_state.data_ptr(), out.data_ptr(), _stream(q)))
     return out
@@ -559,7 +572,7 @@ def la2_decode_multi(q, k, v, lam, kv_state, out=None):
         raise ValueError("la2_decode_multi: kv_state must be dense fp32 [b, H, d, d]")
     if out is None:
         out = torch.empty_like(q)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_decode_multi(b, h, d, t, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                     lam.data_ptr(), kv_state.data_ptr(), out.data_ptr(), _stream(q)))
     return out
@@ -575,7 +588,7 @@ def la2_left_product_fwd(q, k, v, lam, out=None):
         out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
     _same_layout(q, out)
     desc = make_desc(q)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_left_product_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
                                         out.data_ptr(), _stream(q)))
     return out
@@ -592,7 +605,7 @@ def la2_left_product_bwd(q, k, v, d_o, lam, out=None):
     dq, dk, dv = out
     _same_layout(q, dq, dk, dv)
     desc = make_desc(q)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_left_product_bwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(),
                                         lam.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), _stream(q)))
     return dq, dk, dv
@@ -617,7 +630,7 @@ def la2_fwd_state_norm(q, k, v, lam, eps=1e-6, kv_init=None, want_final=True, ou
         kv_final = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD_STATE, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_fwd_state_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
                                       _state(kv_init, q, "kv_init"), float(eps), out.data_ptr(), rstd.data_ptr(),
                                       _state(kv_final, q, "kv_final") if want_final else None,
@@ -644,7 +657,7 @@ def la2_bwd_state_norm(q, k, v, o, rstd, d_o, lam, kv_init=None, d_kv_final=None
         d_kv_init = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
     desc = make_desc(q)
     ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD_STATE, workspace)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_bwd_state_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                       rstd.data_ptr(), d_o.data_ptr(), lam.data_ptr(), _state(kv_init, q, "kv_init"),
                                       _state(d_kv_final, q, "d_kv_final"), d_u.data_ptr(), out[0].data_ptr(),
@@ -668,7 +681,7 @@ def la2_decode_step_norm(q, k, v, lam, kv_state, eps=1e-6, out=None):
         raise ValueError("la2_decode_step_norm: kv_state must be dense fp32 [b, H, d, d]")
     if out is None:
         out = torch.empty_like(q)
-    with torch.cuda.device(q.device):
+    with _on(q):
         _check(lib.la2_decode_step_norm(b, h, d, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                         lam.data_ptr(), kv_state.data_ptr(), float(eps), out.data_ptr(), _stream(q)))
     return out
