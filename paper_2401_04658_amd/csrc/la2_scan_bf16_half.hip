@@ -137,9 +137,7 @@ void scan_bf16_half_kernel(ScanParams p) {
 
   // Start state: the chunk's start state or the caller's, or zero; with self_prefix (ScanParams) it is formed here.
   // Terms in scan order: the caller's start state, then the local states of the chunks passed before this one.
-  // A term stored transposed goes through LDS with workgroup barriers, so the count is the same for every wave.
   const int nch = (nblocks + cb - 1) / cb;   // chunks this chain really has
-  const bool any_tr = (p.state_transposed | p.init_transposed) != 0;
   const bool init_any = p.init[0] != nullptr || p.init[1] != nullptr;
   const bool sp = p.self_prefix != 0 && p.states != nullptr && slot >= 0;
   const int nterms = sp ? (init_any ? 1 : 0) + (REV ? nch - 1 - chunk : chunk) : 1;
@@ -164,6 +162,13 @@ void scan_bf16_half_kernel(ScanParams p) {
   constexpr int xi = TWIN ? WH : 0, yi = TWIN ? 2 + WH : 1, zi = TWIN ? 3 - WH : 2;
   const LaneAddr<D> la(l);
 
+  // The first NBUF - 1 blocks' tiles are on their way before anything else is fetched or computed: the start state (a
+  // microsecond or two of latency of its own), the decay weights.  (Waits the compiler places for its own loads cover
+  // these too: they are older.)
+#pragma unroll
+  for (int j = 0; j < NBUF - 1; j++)
+    if (j < nblk) loader.issue(sT[j], REV ? blk_hi - 1 - j : blk_lo + j);
+
   if constexpr (ACC) {
     if (group == 1) {
       // ---- the accumulating waves: same loads, same barriers as the scan waves; per block only the state
@@ -171,19 +176,10 @@ void scan_bf16_half_kernel(ScanParams p) {
       // chunk's first position: its contribution carries lambda^(B it) up front, the sum needs no running decay.
       constexpr int ACC_YOUNGER = (NBUF - 2) * NDMA;   // no stores in this wave group
       constexpr int ACC_WAIT = (ACC_YOUNGER & 15) | ((ACC_YOUNGER >> 4) << 14) | 0x0F70;
-      // the scan waves may first stage transposed start states in the tile buffers (below): join their barriers
-      // before the first tile load
-      if (any_tr) {
-#pragma unroll 1
-        for (int k = 0; k < nterms * (NW / SW); k++) __syncthreads();
-      }
       const UpdateDecay<true, B> adecay(l2, hh);
       f32x16 acc[NT];
 #pragma unroll
       for (int t = 0; t < NT; t++) acc[t] = zero16();
-#pragma unroll
-      for (int j = 0; j < NBUF - 1; j++)
-        if (j < nblk) loader.issue(sT[j], blk_lo + j);
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
 #pragma unroll
       for (int j = 0; j < NBUF - 1; j++)
@@ -243,8 +239,6 @@ void scan_bf16_half_kernel(ScanParams p) {
   {
     const float lam_full = exp2f(l2 * (float)chunk_tokens);
     const float lam_last = exp2f(l2 * (float)(n - (nch - 1) * chunk_tokens));
-    float* const lds = reinterpret_cast<float*>(&sT[0][0][0]) + dvt * (32 * (D + 1));
-    static_assert(sizeof(sT) >= (size_t)SW * 32 * (D + 1) * sizeof(float), "room for one wave group's slices");
     // Term k: where it lives, whether it is stored transposed, the decay the sum so far takes before it is added.
     auto term = [&](int k, const float*& gs, bool& tr, float& decay) __attribute__((always_inline)) {
       gs = nullptr;
@@ -273,9 +267,10 @@ void scan_bf16_half_kernel(ScanParams p) {
     };
     // The global loads of the next terms are issued before term k is consumed (a term's loads take about a microsecond
     // and the launches that form their start states here are a few microseconds long).  A wave's slice of a term is
-    // NT * 16 floats either way: its elements one by one, or (stored transposed) its 32 rows in 16-byte pieces.
+    // NT * 16 floats per lane: a column's elements one by one, or, of a state stored transposed, sixteen-byte pieces of
+    // the lane's row (four pieces that follow each other share a cache line; element by element every lane would
+    // touch a line of its own: +20 us per launch at 256 workgroups).
     constexpr int NX = NT * 16;
-    static_assert(32 * D / 256 * 4 == NX, "a wave's rows in 16-byte pieces per lane");
     constexpr int FA = D == 64 ? kMaxPrefixTerms - 1 : 1;   // terms fetched ahead (head_dim 128: 64 registers a term)
     float xb[FA + 1][NX];
     auto fetch = [&](int k, float (&x)[NX]) __attribute__((always_inline)) {
@@ -290,12 +285,13 @@ void scan_bf16_half_kernel(ScanParams p) {
 #pragma unroll
           for (int v = 0; v < 16; v++) x[16 * t + v] = gs[state_index<D>(dvt, l32, hh, t, v, false)];
       } else {
-        const float* rows = gs + (int64_t)(32 * dvt) * D;
 #pragma unroll
-        for (int i = 0; i < 32 * D / 256; i++) {
-          const f32x4 r = *reinterpret_cast<const f32x4*>(rows + 4 * (64 * i + l));
-          x[4 * i] = r[0]; x[4 * i + 1] = r[1]; x[4 * i + 2] = r[2]; x[4 * i + 3] = r[3];
-        }
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+          for (int v = 0; v < 16; v += 4) {
+            const f32x4 r = *reinterpret_cast<const f32x4*>(gs + state_index<D>(dvt, l32, hh, t, v, true));
+            x[16 * t + v] = r[0]; x[16 * t + v + 1] = r[1]; x[16 * t + v + 2] = r[2]; x[16 * t + v + 3] = r[3];
+          }
       }
     };
 #pragma unroll
@@ -303,48 +299,20 @@ void scan_bf16_half_kernel(ScanParams p) {
       if (a < nterms) fetch(a, xb[a]);
 #pragma unroll
     for (int k = 0; k < kMaxPrefixTerms; k++) {
-      if (k < nterms) {   // (the same for every wave of the workgroup)
+      if (k < nterms) {
         if (k + FA < nterms) fetch(k + FA, xb[(k + FA) % (FA + 1)]);
         const float(&x)[NX] = xb[k % (FA + 1)];
         const float* gs;
         bool tr;
         float decay;
         term(k, gs, tr, decay);
-        if (gs != nullptr && !tr) {
+        if (gs != nullptr) {
 #pragma unroll
           for (int t = 0; t < NT; t++)
 #pragma unroll
             for (int v = 0; v < 16; v++) kv[t][v] = have ? fmaf(decay, kv[t][v], x[16 * t + v]) : x[16 * t + v];
+          have = true;
         }
-        // A state stored transposed: this wave's slice is then the 32 ROWS 32 dvt .. + 31 of the stored matrix, 32 D
-        // consecutive floats.  Read element by element each lane would touch a cache line of its own (measured
-        // +20 us per launch at 256 workgroups); instead the wave copies its rows with 16-byte loads through the tile
-        // buffers, which nothing has used yet, and each lane picks its elements out of LDS (row stride D + 1 floats:
-        // no bank conflicts).  One wave group at a time, a workgroup barrier after each: the first tile loads, from
-        // any wave, overwrite that LDS.  Whether the launch has transposed states at all is uniform over the grid.
-        if (any_tr) {
-#pragma unroll 1
-          for (int gsel = 0; gsel < NW / SW; gsel++) {
-            if (gs != nullptr && tr && group == gsel) {
-#pragma unroll
-              for (int i = 0; i < 32 * D / 256; i++) {
-                const int at = 4 * (64 * i + l);
-                float* dst = lds + (at / D) * (D + 1) + at % D;
-                dst[0] = x[4 * i]; dst[1] = x[4 * i + 1]; dst[2] = x[4 * i + 2]; dst[3] = x[4 * i + 3];
-              }
-              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's own writes, before its own reads
-#pragma unroll
-              for (int t = 0; t < NT; t++)
-#pragma unroll
-                for (int v = 0; v < 16; v++) {
-                  const float y = lds[l32 * (D + 1) + 32 * t + 8 * (v >> 2) + 4 * hh + (v & 3)];
-                  kv[t][v] = have ? fmaf(decay, kv[t][v], y) : y;
-                }
-            }
-            __syncthreads();
-          }
-        }
-        if (gs != nullptr) have = true;
       }
     }
     if (!have) {
@@ -394,11 +362,7 @@ void scan_bf16_half_kernel(ScanParams p) {
     }
   }
 
-  // prologue: the first NBUF - 1 blocks' tiles
-#pragma unroll
-  for (int j = 0; j < NBUF - 1; j++)
-    if (j < nblk) loader.issue(sT[j], REV ? blk_hi - 1 - j : blk_lo + j);
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the first NBUF - 1 blocks' tiles
 #pragma unroll
   for (int j = 0; j < NBUF - 1; j++)
     if (j < nblk) loader.zero_tail(sT[j], REV ? blk_hi - 1 - j : blk_lo + j);
