@@ -441,6 +441,14 @@ la2::ScanParams base_params(const la2_desc* d, const Plan& pl, const float* lamb
   return p;
 }
 
+// Head_dim 256: a workgroup of eight waves fills a compute unit, so a launch of at most half as many workgroups as units
+// leaves half of them idle; as two workgroups per scan, half the value features each, it takes all of them (64 chains
+// of 500 positions, forward + backward: 129 -> 106 us).  With more workgroups than that some units would get two.
+int value_split(const la2_desc* d, const la2::ScanParams& p) {
+  return d->head_dim == 256 && is16(d->dtype) &&
+         2 * (int64_t)p.batch * p.heads * p.nchunks * p.nscan <= device_cu_count();
+}
+
 // chunk start states of the scan with key-like operand y and value-like operand z -> workspace
 // (local_ready: an earlier launch already left the chunks' local states there; only the scan over them runs)
 la2_status run_prepass(const la2_desc* d, const Plan& pl, bool reverse, const void* y, const void* z,
@@ -487,6 +495,7 @@ la2_status run_scan(const la2_desc* d, const Plan& pl, bool reverse, const ScanA
   p.acc_y = a.acc_y;
   p.acc_states = a.acc_states;
   p.ragged_state = a.ragged_state ? 1 : 0;
+  p.value_split = value_split(d, p);
   hipError_t e = wide(d->head_dim) ? la2::launch_scan_wide(d->dtype, d->head_dim, reverse, false, p, s)
                 : is16(d->dtype)   ? la2::launch_scan_bf16(d->dtype, d->head_dim, reverse, p, s)
                                    : la2::launch_scan_f32(d->head_dim, reverse, p, s);
@@ -511,6 +520,7 @@ la2_status run_dual_reverse_scan(const la2_desc* d, const Plan& pl, const ScanAr
   p.ragged_state = a0.ragged_state ? 1 : 0;
   p.x[0] = a0.x; p.y[0] = a0.y; p.z[0] = a0.z; p.w[0] = a0.w;
   p.x[1] = a1.x; p.y[1] = a1.y; p.z[1] = a1.z; p.w[1] = a1.w;
+  p.value_split = value_split(d, p);
   const hipError_t e = wide(d->head_dim) ? la2::launch_scan_wide(d->dtype, d->head_dim, true, false, p, s)
                        : is16(d->dtype) ? la2::launch_scan_bf16(d->dtype, d->head_dim, true, p, s)
                                         : la2::launch_scan_f32(d->head_dim, true, p, s);

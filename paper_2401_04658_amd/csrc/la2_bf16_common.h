@@ -150,6 +150,14 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
                : "m0", "memory");
 }
 
+// The same for tiles that a second workgroup on the XCD reads as well: without the hint they stay in its L2.
+__device__ __forceinline__ void dma16_shared(const void* base, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(voff), "s"(base), "s"(lds_base)
+               : "m0", "memory");
+}
+
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
@@ -264,11 +272,13 @@ struct TileLoader {
       off[i] = valid ? ((uint32_t)pos * stride_n + (uint32_t)col[i]) * 2u : 0u;
     }
   }
-  template <typename E>
+  template <bool SHARED = false, typename E>
   __device__ __forceinline__ void issue_one(E (*sT)[C::TILE], const uint32_t (&off)[DMA_PER_WAVE], int j) const {
     const int i = j / NTILES, t = j % NTILES;
     // LDS address = tile base (a constant once the buffer index is one) + scalar wave offset
-    dma16(g[t], off[i], lds_offset(&sT[t][0]) + wave_lds + 1024u * i);
+    const uint32_t at = lds_offset(&sT[t][0]) + wave_lds + 1024u * i;
+    if (SHARED) dma16_shared(g[t], off[i], at);
+    else dma16(g[t], off[i], at);
   }
   // after this wave's loads have landed: zero the rows of a ragged last block
   template <typename E>

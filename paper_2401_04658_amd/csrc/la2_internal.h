@@ -91,6 +91,8 @@ struct ScanParams {
   // passes before: G <- init (or 0); for those chunks j in scan order: G <- lambda^(length of chunk j) G + L_j.
   // For a few chunks on a small problem that is cheaper than one more dependent launch between two short kernels.
   int32_t self_prefix;
+  // Head_dim 256, scans without the Norm epilogue: non-zero = two workgroups per scan, half the value features each
+  int32_t value_split;
 };
 // self_prefix: most terms a start state is formed from (the caller's start state and the local states of three chunks)
 constexpr int kMaxPrefixTerms = 4;

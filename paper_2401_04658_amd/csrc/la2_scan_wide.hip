@@ -61,22 +61,40 @@ struct PlainAddr {
 // exchanged (requires y[1] == z[0] and z[1] == y[0]), so the workgroup streams four tiles per block (x of scan
 // 0, x of scan 1, Q, dO) and fetches each exactly once.  (Head_dim 256: sixteen waves of 128 state registers do
 // not fit a compute unit.)
-template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM = false, bool TWIN = false>
-__global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) void scan_wide_kernel(ScanParams p) {
+// SPLIT (head_dim 256 without the Norm epilogue, ScanParams::value_split): two workgroups per scan, each with half of
+// the value features, for launches that would leave half of the compute units idle.  A scan's value features are
+// independent of each other: both workgroups read all of X and Y (they sit on one XCD, the second read hits its L2)
+// and compute the score tile.  Eight waves again, two per SIMD (four waves with 32 value features each took as long per
+// block as eight): waves w and w + 4 share value features, the first with the lower half of the key features, the
+// second with the upper half; the first leaves its part of the inter-block product in LDS, under the next block's
+// barrier, for the second to finish the block.  With half the state there is room for a third tile buffer (Z: the
+// workgroup's half of the rows only).  Forward + backward, bf16: 64 chains of 500 positions 129 -> 106 us, 21 chains of
+// 777 177 -> 142, 88 chains of 1000 241 -> 213; 120 chains of 2048 508 -> 470 (only the forward and the dQ scan, the
+// reverse launch fills the units as it is).  What bounds it: vector instructions that every wave has whatever its
+// share (weights, addresses, waits): 3,900 cycles per block, half of them vector issue.
+template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT>
+__device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
+  static_assert(!SPLIT || (D == 256 && !STATE_ONLY && !NORM), "half the value features per workgroup: plain scans of head_dim 256");
   static_assert(!NORM || (!REV && !STATE_ONLY), "the Norm epilogue belongs to the forward scan");
   static_assert(!TWIN || (REV && !STATE_ONLY && !NORM), "the twin workgroup is the backward pass's reverse launch");
   constexpr int B = 32;
   using C = Cfg<D, B>;
-  constexpr int KS = C::KS, NT = C::NT, TILE = C::TILE;
-  constexpr int NTL = TWIN ? 4 : STATE_ONLY ? 2 : 3;   // tiles of a block: [X,] Y, Z; twin: X0, X1, Y0 = Z1, Z0 = Y1
+  constexpr int NT = C::NT, TILE = C::TILE;
+  constexpr int KT = SPLIT ? NT / 2 : NT;           // key-feature tiles of a wave's state slice
+  constexpr int KS = SPLIT ? C::KS / 2 : C::KS;     // k-steps of a wave's inter-block product
+  // tiles of a block: [X,] Y, Z; twin: X0, X1, Y0 = Z1, Z0 = Y1; split: X, Y (Z: the workgroup's half only, sZ)
+  constexpr int NTL = TWIN ? 4 : STATE_ONLY || SPLIT ? 2 : 3;
+  constexpr int NBUF = SPLIT ? 3 : 2;   // split: a wave has half the work per block to hide a load behind
   constexpr bool SHP = D == 256 && !STATE_ONLY;   // shared score tile (see sP below)
   // The tile loads of a block: every wave its share.  With the shared score tile, waves 4 .. 7 load (one
   // instruction per slot of the inter-block product, so that eight waves do not queue 48 of them at the tile
   // addresser right after the barrier) while waves 0 .. 3 compute the score tile.
   constexpr int NLW = SHP ? 4 : (TWIN ? 2 : 1) * NT;
   using Loader = TileLoader<D, NTL, B, NLW>;
-  constexpr int NDMA = NTL * Loader::DMA_PER_WAVE;
-  __shared__ __attribute__((aligned(1024))) E sT[2][NTL][TILE];
+  constexpr int NDMA = NTL * Loader::DMA_PER_WAVE + (SPLIT ? 2 : 0);
+  __shared__ __attribute__((aligned(1024))) E sT[NBUF][NTL][TILE];
+  constexpr int ZT = B * D / 2;
+  __shared__ __attribute__((aligned(1024))) E sZ[SPLIT ? NBUF : 1][SPLIT ? ZT : 8];   // tile layout of head_dim 128
   float* const sRed = NormExchange<NORM ? B * (D / 32) : 0>::get();   // [position][wave]
   // Head_dim 256: the masked, decayed score tile of a block is the same for the eight waves.  Waves 0 .. 3 compute a
   // 16 x 16 quarter each (16x16x32 MFMAs) and leave it in LDS in 16 bits, in the order in which a lane takes it as
@@ -90,25 +108,39 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
   // block's first LDS reads.
   constexpr bool DEFER = SHP && !NORM;
   __shared__ __attribute__((aligned(16))) E sP[DEFER ? 2 : 1][SHP ? 32 * PROW : 8];
+  __shared__ f32x4 sAcc[SPLIT ? 2 : 1][SPLIT ? 4 : 1][SPLIT ? 4 : 1][64];   // [block parity][wave][element group][lane]
   __shared__ f32x4 sDg[(STATE_ONLY || SHP) ? 1 : 4][64];               // decay mask, [element group][lane]
 
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l32 = l & 31, hh = l >> 5;
-  const int dvt = w % NT;
+  int dvt = SPLIT ? w & 3 : w % NT;
+  const int kh = SPLIT ? w >> 2 : 0;   // half of the key features
   const int group = TWIN ? __builtin_amdgcn_readfirstlane(w / NT) : 0;   // twin: which scan this wave belongs to
   // this wave's X, Y, Z among the tiles of a block
-  const int xi = TWIN ? group : 0, yi = TWIN ? 2 + group : NTL - 2, zi = TWIN ? 3 - group : NTL - 1;
+  const int xi = TWIN ? group : 0, yi = TWIN ? 2 + group : SPLIT ? 1 : NTL - 2, zi = TWIN ? 3 - group : NTL - 1;
   // A dual launch (the dK and the dV scan of Algorithm 2, which both read Q and dO) has two workgroups per (chain,
   // chunk), one per scan.  They sit eight workgroup numbers apart, i.e. on the same XCD and started at about the same
   // time, so that the second read of a shared tile can hit that XCD's L2 (workgroup numbers go round the eight XCDs);
   // when the count of pairs is no multiple of eight they are neighbours instead.
   int which = group, wg = (int)blockIdx.x;
-  if (!TWIN && !STATE_ONLY && p.nscan == 2) {
-    if (((gridDim.x >> 1) & 7) == 0) {
-      which = (int)(blockIdx.x >> 3) & 1;
-      wg = (int)((blockIdx.x >> 4) << 3) | (int)(blockIdx.x & 7);
+  const int scans = SPLIT ? (int)(gridDim.x >> 1) : (int)gridDim.x;   // workgroups, or pairs of them
+  int vh = 0;
+  if constexpr (SPLIT) {
+    if ((scans & 7) == 0) {   // the pair eight workgroup numbers apart, as below
+      vh = (wg >> 3) & 1;
+      wg = ((wg >> 4) << 3) | (wg & 7);
     } else {
-      which = (int)(blockIdx.x & 1);
-      wg = (int)(blockIdx.x >> 1);
+      vh = wg & 1;
+      wg >>= 1;
+    }
+    dvt += (NT / 2) * vh;
+  }
+  if (!TWIN && !STATE_ONLY && p.nscan == 2) {
+    if (((scans >> 1) & 7) == 0) {
+      which = (wg >> 3) & 1;
+      wg = ((wg >> 4) << 3) | (wg & 7);
+    } else {
+      which = wg & 1;
+      wg >>= 1;
     }
   }
   const int chain = wg / p.nchunks, chunk = wg % p.nchunks;
@@ -135,12 +167,25 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
     loader.g[1] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(p.x[1]) + base);
     loader.g[2] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(p.y[0]) + base);
     loader.g[NTL - 1] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(p.z[0]) + base);
+  } else if (SPLIT) {
+    loader.g[0] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(which ? p.x[1] : p.x[0]) + base);
+    loader.g[1] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(which ? p.y[1] : p.y[0]) + base);
   } else {
     if (!STATE_ONLY)
       loader.g[0] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(which ? p.x[1] : p.x[0]) + base);
     loader.g[NTL - 2] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(which ? p.y[1] : p.y[0]) + base);
     loader.g[NTL - 1] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(which ? p.z[1] : p.z[0]) + base);
   }
+  // split: the two instructions per loader wave that fetch this workgroup's half of the Z rows (eight rows per wave)
+  const char* const gz = reinterpret_cast<const char*>(reinterpret_cast<const E*>(which ? p.z[1] : p.z[0]) + base);
+  const int zrow = 8 * (w & 3) + (l >> 4);   // and row zrow + 4
+  auto z_offset = [&](int blk, int i) __attribute__((always_inline)) {
+    const int c = 128 * vh + 8 * ((l & 15) ^ swz<128>(zrow + 4 * i));
+    return ((uint32_t)min(blk * B + zrow + 4 * i, n - 1) * stride_n + (uint32_t)c) * 2u;
+  };
+  auto issue_z = [&](E* tile, int blk, int i) __attribute__((always_inline)) {
+    dma16(gz, z_offset(blk, i), lds_offset(tile) + 1024u * (2u * (uint32_t)(w & 3) + (uint32_t)i));
+  };
   E* const gw = STATE_ONLY ? nullptr : reinterpret_cast<E*>(which ? p.w[1] : p.w[0]) + base;
   // head_dim 256: LaneAddr's precomputed offsets (one XOR per read); its read_row takes a row tile, always 0 here
   struct Pow2Addr : LaneAddr<D> {
@@ -161,6 +206,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
     __device__ __forceinline__ ex8<E> read_row(const E* tile, int ks) const { return LaneAddr<D>::read_row(tile, 0, ks); }
   };
   const std::conditional_t<(D & (D - 1)) == 0, Pow2Addr, PlainAddr<D>> la(l);
+  const PlainAddr<128> lz(l);   // split: the half rows of Z
 
   // Every transposing read takes the columns of its tile in the order pi (read_cols_pi: bits 2 and 3 of the index
   // exchanged).  Element v of state tile t in a lane is therefore value feature dv = 32 dvt + pi(l32) and key feature
@@ -168,13 +214,13 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
   // k-step are key features 16 ks + 8 hh .. + 7, the order of a row fragment of X, so the state operand needs no
   // lane shuffle; and a lane's sixteen outputs are value features 32 dvt + 16 (v / 8) + 8 hh + v % 8: two 16-byte stores.
   auto state_index_pi = [&](int t, int v, bool transposed) {
-    const int dk = 32 * t + 16 * (v >> 3) + 8 * hh + 4 * ((v >> 2) & 1) + (v & 3);
+    const int dk = 32 * (KT * kh + t) + 16 * (v >> 3) + 8 * hh + 4 * ((v >> 2) & 1) + (v & 3);
     const int dv = 32 * dvt + ((l32 & 19) | ((l32 & 4) << 1) | ((l32 & 8) >> 1));
     return transposed ? dv * D + dk : dk * D + dv;
   };
   // state slice S[:, dv tile] in accumulator layout: chunk start state, the caller's start state, or zero
   // (the pre-pass forms LOCAL states, from zero)
-  f32x16 kv[NT];
+  f32x16 kv[KT];
   {
     const float* gs = nullptr;
     bool tr = false;
@@ -188,7 +234,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
       }
     }
 #pragma unroll
-    for (int t = 0; t < NT; t++)
+    for (int t = 0; t < KT; t++)
 #pragma unroll
       for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index_pi(t, v, tr)] : 0.f;
   }
@@ -231,7 +277,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
   } while (0)
   constexpr int AH1 = SHP ? 3 : 1;   // slots by which the LDS reads run ahead of their MFMAs: inter-block product,
   constexpr int AH3 = D == 256 ? 2 : 1;   // state update (a slot of one MFMA is shorter than an LDS round trip)
-  constexpr int NU = 2 * NT;                           // MFMAs of a block's state update: (k-step q, key tile t), q-major
+  constexpr int NU = 2 * KT;                           // MFMAs of a block's state update: (k-step q, key tile t), q-major
   constexpr int NS3 = (NU + 1) / 2;                    // ... in slots of two
   constexpr int PPS = NS3 >= 8 ? 2 : NS3 >= 4 ? 4 : 8; // elements of the masked score tile converted per update slot
   auto state_operand = [&](int ks) __attribute__((always_inline)) {
@@ -281,33 +327,63 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
     ex8<E> pv[2];
 #pragma unroll
     for (int q = 0; q < 2; q++) pv[q] = *reinterpret_cast<const ex8<E>*>(tile + lr * PROW + 16 * q + 8 * lh);
+    if constexpr (SPLIT) {   // the other half of the key features
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const f32x4 part = sAcc[(blkv - blk_lo) & 1][w & 3][g][lo];
+#pragma unroll
+        for (int e = 0; e < 4; e++) a[4 * g + e] += part[e];
+      }
+    }
 #pragma unroll
     for (int q = 0; q < 2; q++) a = mfma(zfv[q], pv[q], a);
     store_block(a, blkv, lr, lh);
   };
   auto block_at = [&](int it) { return REV ? blk_hi - 1 - it : blk_lo + it; };
-  if (loads) loader.issue(sT[0], block_at(0));
-  for (int it = 0; it < nblk; it++) {
+#pragma unroll
+  for (int j = 0; j < NBUF - 1; j++) {
+    if (loads && j < nblk) {
+      loader.issue(sT[j], block_at(j));
+      if constexpr (SPLIT) {
+        issue_z(sZ[j], block_at(j), 0);
+        issue_z(sZ[j], block_at(j), 1);
+      }
+    }
+  }
+  int buf = 0;   // it % NBUF
+  for (int it = 0; it < nblk; it++, buf = buf + 1 < NBUF ? buf + 1 : 0) {
     const int blk = block_at(it);
-    E (*const cur)[TILE] = sT[it & 1];
+    E (*const cur)[TILE] = sT[buf];
+    const int ahead = SPLIT ? (buf == 0 ? 2 : buf - 1) : buf ^ 1;   // the buffer of block it + NBUF - 1
     // This wave's part of the block's tiles has landed.  Vector memory operations complete in the order of their
     // issue, and the only ones younger than those loads are the two output stores per lane of the block before
     // (always issued: every block has a valid first row; a Norm scan's r store comes before them): they may stay in
     // flight, a store's acknowledgement takes as long as a load.
     // (With the deferred tail the stores are issued before the block's loads and have had a block's time.)
-    if (STATE_ONLY || DEFER || it == 0) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    // (Split: the next block's loads, the youngest operations, stay in flight where there is a next block.)
+    if (SPLIT && it + 1 < nblk) __builtin_amdgcn_s_waitcnt(0x0F70 | NDMA);
+    else if (STATE_ONLY || DEFER || it == 0) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     else __builtin_amdgcn_s_waitcnt(0x0F72);                                  // vmcnt(2)
     if (loads) loader.zero_tail(cur, blk);
+    if constexpr (SPLIT) {
+      if (loads && (blk + 1) * B > n) {
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+          if (blk * B + zrow + 4 * i >= n)
+            *reinterpret_cast<i32x4*>(reinterpret_cast<char*>(sZ[buf]) + 1024 * (2 * (w & 3) + i) + 16 * l) = i32x4{0, 0, 0, 0};
+      }
+      lds_barrier();                      // (leaves the loads in flight)
+    } else
     __syncthreads();                      // ... and everybody's; the other buffer is free (block it - 1 is done)
     if constexpr (DEFER) {
-      if (it > 0) finish_block(acc_prev, zf_prev, blk_prev, sP[(it - 1) & 1]);
+      if (it > 0 && (!SPLIT || kh == 1)) finish_block(acc_prev, zf_prev, blk_prev, sP[(it - 1) & 1]);
     }
-    const bool load_next = loads && it + 1 < nblk;
+    const bool load_next = loads && it + NBUF - 1 < nblk;
     uint32_t doff[Loader::DMA_PER_WAVE];
     if constexpr (SHP) {
-      loader.offsets(block_at(it + 1), load_next, doff);
+      loader.offsets(block_at(it + NBUF - 1), load_next, doff);
     } else {
-      if (load_next) loader.issue(sT[(it + 1) & 1], block_at(it + 1));
+      if (load_next) loader.issue(sT[ahead], block_at(it + 1));
     }
     const int nv = min(B, n - blk * B);   // valid rows of this block
     if constexpr (SHP) {
@@ -348,7 +424,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
     }
     const E* const tX = cur[xi];
     const E* const tY = cur[yi];
-    const E* const tZ = cur[zi];
+    const E* const tZ = SPLIT ? sZ[buf] : cur[zi];
 
     // (wave-uniform) the decay this block adds to the pending one, and whether the registers are brought up to date
     const float pend_new = uniform(pend + l2 * (float)nv);
@@ -357,7 +433,11 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
 
     ex8<E> zf[2], zd[2], yt[NU];
     auto read_yt = [&](int idx) __attribute__((always_inline)) {
-      if (idx < NU) yt[idx] = la.read_cols_pi(tY, 16 * (idx / NT), idx % NT);
+      if (idx < NU) yt[idx] = la.read_cols_pi(tY, 16 * (idx / KT), KT * kh + idx % KT);
+    };
+    auto read_z = [&](const E* tile, int q) __attribute__((always_inline)) {   // rows 16 q .. + 15, this wave's value features
+      if constexpr (SPLIT) return lz.read_cols_pi(tile, 16 * q, w & 3);
+      else return la.read_cols_pi(tile, 16 * q, dvt);
     };
     // update weights on the Z fragments (element j of fragment q is row c = 16 q + 8 (j / 4) + 4 hh + j % 4)
     auto weigh_z = [&]() __attribute__((always_inline)) {
@@ -386,17 +466,17 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
       ex8<E> xa[KS], ya[KS];
 #pragma unroll
       for (int a = 0; a < AH1; a++) {
-        xa[a] = la.read_row(tX, a);
+        xa[a] = la.read_row(tX, KS * kh + a);
         if constexpr (!SHP) ya[a] = la.read_row(tY, a);
       }
       ex8<E> sa = sa_first;
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) {
         if (ks + AH1 < KS) {
-          xa[ks + AH1] = la.read_row(tX, ks + AH1);
+          xa[ks + AH1] = la.read_row(tX, KS * kh + ks + AH1);
           if constexpr (!SHP) ya[ks + AH1] = la.read_row(tY, ks + AH1);
         }
-        if (ks == KS - 3 || ks == KS - 2) zf[ks - (KS - 3)] = la.read_cols_pi(tZ, 16 * (ks - (KS - 3)), dvt);
+        if (ks == KS - 3 || ks == KS - 2) zf[ks - (KS - 3)] = read_z(tZ, ks - (KS - 3));
         if (ks == KS - 1) {
 #pragma unroll
           for (int i = 0; i < 2 * AH3; i++) read_yt(i);
@@ -411,7 +491,13 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
           if constexpr (!SHP) pin(ya[ks + 1]);
         }
         if constexpr (SHP) {
-          if (ks < NDMA && load_next) loader.issue_one(sT[(it + 1) & 1], doff, ks);
+          constexpr int PER = (NDMA + KS - 1) / KS;
+#pragma unroll
+          for (int u = 0; u < PER; u++)
+            if (ks * PER + u < NDMA && load_next) {
+              if (SPLIT && ks * PER + u >= NDMA - 2) issue_z(sZ[ahead], block_at(it + NBUF - 1), ks * PER + u - (NDMA - 2));
+              else loader.template issue_one<SPLIT>(sT[ahead], doff, ks * PER + u);
+            }
         }
         pin(acc);
         if constexpr (!SHP) pin(sd);
@@ -424,7 +510,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
       pin(acc);
     } else {
 #pragma unroll
-      for (int q = 0; q < 2; q++) zf[q] = la.read_cols_pi(tZ, 16 * q, dvt);
+      for (int q = 0; q < 2; q++) zf[q] = read_z(tZ, q);
 #pragma unroll
       for (int i = 0; i < 2 * AH3; i++) read_yt(i);
     }
@@ -432,7 +518,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
     if (rescale) {
       const float scale = uniform(fast_exp2(pend_new));
 #pragma unroll
-      for (int t = 0; t < NT; t++)
+      for (int t = 0; t < KT; t++)
 #pragma unroll
         for (int v = 0; v < 16; v++) kv[t][v] *= scale;
     }
@@ -450,7 +536,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
 #pragma unroll
       for (int u = 0; u < 2; u++) {
         const int idx = 2 * s3 + u;
-        if (idx < NU) kv[idx % NT] = mfma(yt[idx], zd[idx / NT], kv[idx % NT]);
+        if (idx < NU) kv[idx % KT] = mfma(yt[idx], zd[idx / KT], kv[idx % KT]);
       }
       if constexpr (!STATE_ONLY && !SHP) {
         if (PPS * s3 < 16) {
@@ -468,7 +554,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
       }
 #pragma unroll
       for (int u = 0; u < 2; u++) {
-        if (2 * s3 + u < NU) pin(kv[(2 * s3 + u) % NT]);
+        if (2 * s3 + u < NU) pin(kv[(2 * s3 + u) % KT]);
         if (2 * s3 + 2 + u < NU) pin(yt[2 * s3 + 2 + u]);
       }
       LA2_SLOT_END();
@@ -477,6 +563,13 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
     if constexpr (DEFER) {
       sa_first = state_operand(0);   // the first state operand of the next block
       pin(sa_first);
+      if constexpr (SPLIT) {
+        if (kh == 0) {
+#pragma unroll
+          for (int g = 0; g < 4; g++)
+            sAcc[(blk - blk_lo) & 1][w & 3][g][l] = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+        }
+      }
       acc_prev = acc;
       zf_prev[0] = zf[0];
       zf_prev[1] = zf[1];
@@ -513,7 +606,7 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
   }
   if constexpr (DEFER) {
     __syncthreads();
-    finish_block(acc_prev, zf_prev, blk_prev, sP[(nblk - 1) & 1]);
+    if (!SPLIT || kh == 1) finish_block(acc_prev, zf_prev, blk_prev, sP[(nblk - 1) & 1]);
   }
 #undef LA2_SLOT_END
 
@@ -529,10 +622,19 @@ __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) v
   if (gf != nullptr) {
     const float scale = fast_exp2(pend);   // the pending decay
 #pragma unroll
-    for (int t = 0; t < NT; t++)
+    for (int t = 0; t < KT; t++)
 #pragma unroll
       for (int v = 0; v < 16; v++) gf[state_index_pi(t, v, trf)] = kv[t][v] * scale;
   }
+}
+
+template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM = false, bool TWIN = false>
+__global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) void scan_wide_kernel(ScanParams p) {
+  scan_wide_body<E, D, REV, STATE_ONLY, NORM, TWIN, false>(p);
+}
+template <typename E, int D, bool REV>
+__global__ __launch_bounds__(2 * D, 2) void scan_wide_split_kernel(ScanParams p) {
+  scan_wide_body<E, D, REV, false, false, false, true>(p);
 }
 
 template <typename E, int D>
@@ -542,6 +644,14 @@ hipError_t launch_wide(bool reverse, bool state_only, const ScanParams& p, hipSt
     if (!state_only && reverse && p.nscan == 2 && p.y[1] == p.z[0] && p.z[1] == p.y[0]) {
       hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, true>),
                          dim3((unsigned)((int64_t)p.batch * p.heads * p.nchunks)), dim3(4 * D), 0, s, p);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (D == 256) {
+    if (!state_only && p.rstd == nullptr && p.value_split != 0) {
+      const dim3 g2(2 * g.x);
+      if (reverse) hipLaunchKernelGGL((scan_wide_split_kernel<E, D, true>), g2, b, 0, s, p);
+      else         hipLaunchKernelGGL((scan_wide_split_kernel<E, D, false>), g2, b, 0, s, p);
       return hipGetLastError();
     }
   }

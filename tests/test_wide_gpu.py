@@ -80,6 +80,18 @@ def test_decay_schedule_and_small_decay(d):
     check_state(t, g, torch.bfloat16, "d%d small decay, states" % d)
 
 
+@pytest.mark.parametrize("b,H", [(13, 10), (8, 16), (9, 14), (4, 16), (3, 7)])
+@pytest.mark.parametrize("n", [33, 96, 131])
+def test_head_dim_256_one_and_two_workgroups_per_scan(n, b, H):
+    """Up to half as many scans as compute units (256) run as two workgroups each, half the value features per
+    workgroup: 130 chains not at all, 126 and 128 the forward and the dQ scan, 64 and 21 the dK / dV launch as well;
+    counts of pairs that are and are not multiples of eight.  Both ways against the oracle, with and without states."""
+    t, g = inputs(b, H, n, 256, torch.bfloat16, seed=n + b * H)
+    check_plain(t, g, torch.bfloat16, "split %d x %d n%d" % (b, H, n))
+    if n != 131:
+        check_state(t, g, torch.bfloat16, "split states %d x %d n%d" % (b, H, n))
+
+
 @pytest.mark.parametrize("chunk", [64, 192])
 @pytest.mark.parametrize("n", [700, 1024, 129])
 @pytest.mark.parametrize("d", DIMS)
