@@ -158,7 +158,6 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
   if (STATE_ONLY && (REV ? chunk == 0 : chunk == nch - 1)) return;
   const int nblk = blk_hi - blk_lo;
   const uint32_t stride_n = (uint32_t)p.stride_n;
-  const float l2 = log2f(p.lambda[hi]);
 
   const bool loads = !SHP || w >= 4;
   Loader loader(SHP ? (w & 3) : w, l, n, stride_n);
@@ -186,6 +185,19 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
   auto issue_z = [&](E* tile, int blk, int i) __attribute__((always_inline)) {
     dma16(gz, z_offset(blk, i), lds_offset(tile) + 1024u * (2u * (uint32_t)(w & 3) + (uint32_t)i));
   };
+  // the first tiles are on their way before the start state is fetched and the weights are made
+  auto block_at = [&](int it) { return REV ? blk_hi - 1 - it : blk_lo + it; };
+#pragma unroll
+  for (int j = 0; j < NBUF - 1; j++) {
+    if (loads && j < nblk) {
+      loader.issue(sT[j], block_at(j));
+      if constexpr (SPLIT) {
+        issue_z(sZ[j], block_at(j), 0);
+        issue_z(sZ[j], block_at(j), 1);
+      }
+    }
+  }
+  const float l2 = log2f(p.lambda[hi]);
   E* const gw = STATE_ONLY ? nullptr : reinterpret_cast<E*>(which ? p.w[1] : p.w[0]) + base;
   // head_dim 256: LaneAddr's precomputed offsets (one XOR per read); its read_row takes a row tile, always 0 here
   struct Pow2Addr : LaneAddr<D> {
@@ -233,10 +245,22 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
         tr = (p.init_transposed >> which) & 1;
       }
     }
+    if (!NORM && gs != nullptr && tr) {   // eight consecutive elements of a stored row: sixteen-byte loads, not a cache line
+      // per element (a Norm scan is a forward scan of (q, k, v): its states are never transposed)
 #pragma unroll
-    for (int t = 0; t < KT; t++)
+      for (int t = 0; t < KT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index_pi(t, v, tr)] : 0.f;
+        for (int v = 0; v < 16; v += 4) {
+          const f32x4 r = *reinterpret_cast<const f32x4*>(gs + state_index_pi(t, v, true));
+#pragma unroll
+          for (int e = 0; e < 4; e++) kv[t][v + e] = r[e];
+        }
+    } else {
+#pragma unroll
+      for (int t = 0; t < KT; t++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index_pi(t, v, false)] : 0.f;
+    }
   }
   // decay mask of the score tile S^T[c][r] (lane: r = l32; element v: c = 8 (v / 4) + 4 hh + v % 4): the same for
   // every wave and every block.  It lives in LDS, four elements per lane and read, not in sixteen registers: the
@@ -339,17 +363,6 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
     for (int q = 0; q < 2; q++) a = mfma(zfv[q], pv[q], a);
     store_block(a, blkv, lr, lh);
   };
-  auto block_at = [&](int it) { return REV ? blk_hi - 1 - it : blk_lo + it; };
-#pragma unroll
-  for (int j = 0; j < NBUF - 1; j++) {
-    if (loads && j < nblk) {
-      loader.issue(sT[j], block_at(j));
-      if constexpr (SPLIT) {
-        issue_z(sZ[j], block_at(j), 0);
-        issue_z(sZ[j], block_at(j), 1);
-      }
-    }
-  }
   int buf = 0;   // it % NBUF
   for (int it = 0; it < nblk; it++, buf = buf + 1 < NBUF ? buf + 1 : 0) {
     const int blk = block_at(it);
