@@ -172,7 +172,7 @@ Plan make_plan(const la2_desc* d) {
     } else {
       // the extra launches: the pre-pass and the scan over the chunk states, which plans of a few chunks do without
       Plan cut{(nblocks + cb - 1) / cb, cb * B, 0};
-      const float launches = self_prefix(d, cut, nullptr) ? 8.f : 15.f;
+      const float launches = !wide(d->head_dim) && self_prefix(d, cut, nullptr) ? 8.f : 15.f;
       if ((float)(nblocks - cb) * t_blk - 0.35f * (float)cb * t_blk - launches <= 0.f) return pl;
     }
   }
@@ -419,6 +419,8 @@ struct ScanArgs {
 constexpr int kSelfPrefixMaxChunks = la2::kMaxPrefixTerms;   // a start state and the local states of chunks - 1 chunks
 bool self_prefix(const la2_desc* d, const Plan& pl, const int32_t* cu) {
   (void)cu;   // packed batches too: every sequence's chunks have their own slots, a sequence of one chunk has none
+  // head_dim 96 (36 KiB a state): up to six chunks, no limit of registers there; at 256 a state is 256 KiB
+  if (d->head_dim == 96) return is16(d->dtype) && pl.nchunks > 1 && pl.nchunks <= 6;
   return pl.nchunks > 1 && pl.nchunks <= kSelfPrefixMaxChunks &&
          !wide(d->head_dim) && pl.chunk_tokens % 32 == 0 && g_scan_variant.load(std::memory_order_relaxed) != 1;
 }

@@ -231,36 +231,70 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
     return transposed ? dv * D + dk : dk * D + dv;
   };
   // state slice S[:, dv tile] in accumulator layout: chunk start state, the caller's start state, or zero
-  // (the pre-pass forms LOCAL states, from zero)
+  // (the pre-pass forms LOCAL states, from zero); a state stored transposed is read in sixteen-byte pieces of a stored
+  // row, not a cache line per element (a Norm scan is a forward scan of (q, k, v): its states are never transposed).
   f32x16 kv[KT];
-  {
-    const float* gs = nullptr;
-    bool tr = false;
-    if (!STATE_ONLY) {
-      if (p.states != nullptr) {
-        gs = p.states + ((int64_t)chain * p.nchunks + chunk) * (D * D);
-        tr = (p.state_transposed >> which) & 1;
-      } else if ((which ? p.init[1] : p.init[0]) != nullptr) {
-        gs = (which ? p.init[1] : p.init[0]) + (int64_t)chain * (D * D);
-        tr = (p.init_transposed >> which) & 1;
+  const float* gs = nullptr;
+  bool tr = false;
+  if (!STATE_ONLY) {
+    if (p.states != nullptr) {
+      gs = p.states + ((int64_t)chain * p.nchunks + chunk) * (D * D);
+      tr = (p.state_transposed >> which) & 1;
+    } else if ((which ? p.init[1] : p.init[0]) != nullptr) {
+      gs = (which ? p.init[1] : p.init[0]) + (int64_t)chain * (D * D);
+      tr = (p.init_transposed >> which) & 1;
+    }
+  }
+  if constexpr (D == 96 && !STATE_ONLY) {
+    // head_dim 96: or formed here from the caller's start state and the local states of the chunks the scan passes before
+    // this one (ScanParams::self_prefix)
+#pragma unroll
+    for (int t = 0; t < KT; t++) kv[t] = zero16();
+    auto add_state = [&](const float* g, bool g_tr, float decay) __attribute__((always_inline)) {
+      uint32_t at = (uint32_t)state_index_pi(0, 0, g_tr);
+      pin(at);   // one lane offset, the rest is uniform: not an address per element
+#pragma unroll
+      for (int t = 0; t < KT; t++) {
+        if (!NORM && g_tr) {
+#pragma unroll
+          for (int v = 0; v < 16; v += 4) {
+            const f32x4 r = *reinterpret_cast<const f32x4*>(g + (32 * t + 16 * (v >> 3) + (v & 7)) + at);
+#pragma unroll
+            for (int e = 0; e < 4; e++) kv[t][v + e] = fmaf(decay, kv[t][v + e], r[e]);
+          }
+        } else {
+#pragma unroll
+          for (int v = 0; v < 16; v++) kv[t][v] = fmaf(decay, kv[t][v], (g + (32 * t + 16 * (v >> 3) + (v & 7)) * D)[at]);
+        }
+      }
+    };
+    if (p.states == nullptr || p.self_prefix == 0) {
+      if (gs != nullptr) add_state(gs, tr, 0.f);
+    } else {
+      const float* const init = which ? p.init[1] : p.init[0];
+      if (init != nullptr) add_state(init + (int64_t)chain * (D * D), (p.init_transposed >> which) & 1, 0.f);
+      const int last = min(nch, p.nchunks);   // (a longer sequence than planned for: the caller's error)
+      const float lam_full = exp2f(l2 * (float)p.chunk_tokens), lam_last = exp2f(l2 * (float)(n - (last - 1) * p.chunk_tokens));
+#pragma unroll 1
+      for (int i = 0; i < (REV ? last - 1 - chunk : chunk); i++) {
+        const int j = REV ? last - 1 - i : i;
+        add_state(p.states + ((int64_t)chain * p.nchunks + j) * (D * D), tr, j == last - 1 ? lam_last : lam_full);
       }
     }
-    if (!NORM && gs != nullptr && tr) {   // eight consecutive elements of a stored row: sixteen-byte loads, not a cache line
-      // per element (a Norm scan is a forward scan of (q, k, v): its states are never transposed)
+  } else if (!NORM && gs != nullptr && tr) {
 #pragma unroll
-      for (int t = 0; t < KT; t++)
+    for (int t = 0; t < KT; t++)
 #pragma unroll
-        for (int v = 0; v < 16; v += 4) {
-          const f32x4 r = *reinterpret_cast<const f32x4*>(gs + state_index_pi(t, v, true));
+      for (int v = 0; v < 16; v += 4) {
+        const f32x4 r = *reinterpret_cast<const f32x4*>(gs + state_index_pi(t, v, true));
 #pragma unroll
-          for (int e = 0; e < 4; e++) kv[t][v + e] = r[e];
-        }
-    } else {
+        for (int e = 0; e < 4; e++) kv[t][v + e] = r[e];
+      }
+  } else {
 #pragma unroll
-      for (int t = 0; t < KT; t++)
+    for (int t = 0; t < KT; t++)
 #pragma unroll
-        for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index_pi(t, v, false)] : 0.f;
-    }
+      for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index_pi(t, v, false)] : 0.f;
   }
   // decay mask of the score tile S^T[c][r] (lane: r = l32; element v: c = 8 (v / 4) + 4 hh + v % 4): the same for
   // every wave and every block.  It lives in LDS, four elements per lane and read, not in sixteen registers: the

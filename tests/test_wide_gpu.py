@@ -102,6 +102,18 @@ def test_sequence_chunks(d, n, chunk):
     check_state(t, g, torch.bfloat16, "d%d n%d chunk %d, states" % (d, n, chunk))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("chunk", [64, 128, 256])
+def test_head_dim_96_start_states_formed_in_the_scan(chunk, dtype):
+    """Plans of up to six chunks form their start states in the scan (from the caller's start state and the local states
+    of the chunks before, stored transposed for the dQ and the dK scan); seven chunks take the state scan's launch."""
+    binding.la2_set_chunk_tokens(chunk)
+    for n in (385, 300):      # 7 / 4 / 2 and 5 / 3 / 2 chunks
+        t, g = inputs(2, 3, n, 96, dtype, seed=96 + chunk + n, lam=[0.9, 0.99, 1.0])
+        check_state(t, g, dtype, "prefix states n%d chunk%d" % (n, chunk))
+        check_plain(t, g, dtype, "prefix n%d chunk%d" % (n, chunk))
+
+
 @pytest.mark.parametrize("d", DIMS)
 def test_automatic_chunking_of_a_long_sequence(d):
     """Few chains, a long sequence: the planner cuts it into chunks on its own."""
