@@ -41,6 +41,7 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
   int64_t base;
   int n;
   chain_extent(p, bi, hi, base, n);
+  const float l2 = log2f(p.lambda[hi]);
   const int nblocks = (n + kB - 1) / kB;
   const int cb = chunk_length(p, n, map_nch) / kB;
   const int blk_lo = chunk * cb;
@@ -52,6 +53,12 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
   Loader loader(w, l, n, (uint32_t)p.stride_n);
   loader.g[0] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(p.y[0]) + base);
   loader.g[1] = reinterpret_cast<const char*>(reinterpret_cast<const E*>(p.z[0]) + base);
+  const LaneAddr<D> la(l);
+  const UpdateDecay<REV> decay(l2, hh);
+  f32x16 kv[KT];
+#pragma unroll
+  for (int t = 0; t < KT; t++) kv[t] = zero16();
+
   // loads of the chunk's block number `it` (real, or dummy when the chunk has no such block) into `buf`
   auto issue_block = [&](E (*buf)[TILE], int it) __attribute__((always_inline)) {
     uint32_t doff[Loader::DMA_PER_WAVE];
@@ -61,13 +68,7 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
   };
   if (nblk <= 0) return;
 #pragma unroll
-  for (int j = 0; j < NBUF - 1; j++) issue_block(sT[j], j);   // before the decay weights are made
-  const LaneAddr<D> la(l);
-  const float l2 = log2f(p.lambda[hi]);
-  const UpdateDecay<REV> decay(l2, hh);
-  f32x16 kv[KT];
-#pragma unroll
-  for (int t = 0; t < KT; t++) kv[t] = zero16();
+  for (int j = 0; j < NBUF - 1; j++) issue_block(sT[j], j);
   __builtin_amdgcn_s_waitcnt(WAIT_NEXT_TILES);   // the first block's tiles
   loader.zero_tail(sT[0], REV ? blk_hi - 1 : blk_lo);
   lds_barrier();
