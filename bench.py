@@ -395,7 +395,7 @@ def main():
               "bwd_ms": round(b_ms, 4), "tokens_per_s": round(sum(lengths) / ((f_ms + b_ms) * 1e-3), 1),
               "note": "the library cuts the long sequences into chunks (planned from the longest length and the total)"}
     del gp, op_, gr_, tp
-    # the same point in the library's other two data types (fp16: the same kernels as bf16; fp32: fp32 MFMA)
+    # the same point in the library's other two data types (fp16: the same kernels as bf16; fp32: three-part bf16 products)
     other_dtypes = []
     wl1 = workloads.CONFIG3[1]
     for dt, tag in ((torch.float16, "f16"), (torch.float32, "f32")):

@@ -239,9 +239,11 @@ la2_status la2_bwd_state_norm(const la2_desc* desc, const void* q, const void* k
  *                    (a value below the real sum of the lengths is safe but leaves sequences that do not fit
  *                    the workspace planned from it uncomputed); the lengths
  *                    stay on the device, and with it the host can tell a batch of about equal lengths from one
- *                    whose longest sequence would run long after all the others have finished.  Such a batch is
- *                    cut into sequence chunks (a quarter of desc->seqlen) although it has chains enough to
- *                    fill the device; the short sequences are single chunks and pay nothing for it.
+ *                    whose longest sequence would run long after all the others have finished.  The workgroups of
+ *                    such a batch start with the longest sequence (16-bit data, head_dim 64 / 128), and its long
+ *                    sequences are cut into chunks by the average load of a compute unit although it has chains
+ *                    enough to fill the device; short sequences are single chunks and pay nothing for it.  (A batch
+ *                    that is only sorted, not cut, also runs without a workspace, unsorted.)
  * Everything else as for la2_fwd / la2_bwd.  Workspace: la2_varlen_workspace_bytes(desc, total_positions, op) with
  * op = LA2_OP_FWD or LA2_OP_BWD (with total_positions = 0: la2_workspace_bytes(desc, op)).
  * A sequence of length 0 is fine.

@@ -147,9 +147,9 @@ Plan make_plan(const la2_desc* d) {
       const int want2 = (int)(2 * (int64_t)cus / chains);   // positions: 0.25 ms in 32 chunks, 0.27 ms in 64)
       if (d->seqlen / want2 >= 640) want = want2;
     }
-    // fp32 data at head_dim 64: that kernel is bound by its arithmetic and three of its workgroups share a unit
-    // (192 chains of 4096 positions, forward + backward: 2.2 ms uncut, 1.38 ms in four chunks; 64 chains: 0.79 ms in
-    // four chunks, 0.57 ms in eleven)
+    // fp32 data at head_dim 64: that kernel is bound by its issue and four of its workgroups share a unit (192 chains of
+    // 2048 positions, forward + backward: 0.61 ms uncut, 0.49 ms in four chunks; 64 chains of 4096: 0.43 ms in four
+    // chunks, 0.37 ms in eleven)
     if (!is16(d->dtype) && d->head_dim == 64) want = (int)(3 * (int64_t)cus / chains);
     if (want < 2) return pl;
     cb = (nblocks + want - 1) / want;
@@ -157,7 +157,9 @@ Plan make_plan(const la2_desc* d) {
     if (cb >= nblocks) return pl;
     // Chunking shortens the scan's sequential loop from nblocks to cb blocks but adds the pre-pass (about a
     // third of a scan block per block) and two more launches (about 15 us): not worth it for short sequences.
-    // Measured times of one block of the sequential loop, in microseconds.
+    // Measured times of one block of the sequential loop, in microseconds.  (fp32: of the kernel's predecessor on
+    // fp32 MFMA; with today's 5 and 2 the rule would leave sequences of 10 blocks whole that take 0.098 ms in three
+    // chunks and 0.128 whole, head_dim 128, 16 chains; 0.069 against 0.088 at 64.)
     const float t_blk = is16(d->dtype) ? (d->head_dim == 256 ? 3.3f : d->head_dim == 96 ? 3.f : d->head_dim == 64 ? 1.15f : 2.1f)
                                        : (d->head_dim == 128 ? 10.f : 3.f);
     if (is16(d->dtype) && d->head_dim == 256) {

@@ -15,15 +15,14 @@
 // through LDS.
 //
 // One tile buffer: the next block's values are on their way to registers while a block is computed, and are split
-// into the planes between the block's two barriers.  63 KiB (D = 128) or 32 KiB (D = 64) of LDS and 256 registers, so
+// into the planes between the block's two barriers.  56 KiB (D = 128) or 32 KiB (D = 64) of LDS and 256 registers, so
 // two (four) workgroups share a compute unit and one computes while the other splits and waits.
 //
 // What bounds it: issue.  Per wave and block 3,840 cycles of matrix pipe and about 870 vector instructions (the split is
 // 5.5 per element: 64 elements of the state, 64 of the tiles; the pipes share the issue, at full load both are half
-// busy).  Against v_mfma_f32_32x32x2_f32 on tiles in fp32 (208 of 64 cycles, one workgroup per unit): forward scan of
-// 256 chains of 1024 positions, d 128, 0.28 -> 0.18 ms; forward + backward at batch 4, H 16, n 2048, d 128
-// 0.86 -> 0.44 ms, batch 16 1.20 -> 0.62 at n 1024; d 64, batch 4, n 4096 0.57 -> 0.37.  Relative error of the results
-// (2-norm, N(0, 1) data) 3.0e-7 -> 2.5e-7 at d 128, 2.7e-7 -> 2.2e-7 at d 64.
+// busy).  Against v_mfma_f32_32x32x2_f32 on tiles in fp32 (208 of 64 cycles, one workgroup per unit), forward +
+// backward: batch 4, H 16, n 2048, d 128 0.858 -> 0.419 ms, batch 16, n 1024 1.20 -> 0.62; d 64, batch 4, n 4096
+// 0.57 -> 0.37.  Relative error of the results (2-norm, N(0, 1) data) 3.0e-7 -> 2.5e-7 at d 128, 2.7e-7 -> 2.2e-7 at d 64.
 //
 // Feature order.  In the accumulator layout a lane holds rows 8 (v / 4) + 4 hh + v % 4 of a state tile, so the eight
 // elements of a k-step would not be the eight consecutive features of an X row fragment.  The transposing reads of Y

@@ -78,3 +78,12 @@ def test_occupancy_the_kernels_are_designed_for(resources):
             assert v["Occupancy"] >= 3, (k, v["Occupancy"])
         if f in ("decode_kernel", "norm_rows_kernel"):
             assert v["Occupancy"] >= 4, (k, v["Occupancy"])
+
+
+def test_the_split_and_the_fp32_kernels_run_two_waves_per_simd_without_spills(resources):
+    seen = set()
+    for k, v in resources.items():
+        if family(k) in ("scan_wide_split_kernel", "scan_f32_kernel"):
+            seen.add(family(k))
+            assert v["Occupancy"] >= 2 and v["ScratchSize"] == 0, (k, v["Occupancy"], v["ScratchSize"])
+    assert seen == {"scan_wide_split_kernel", "scan_f32_kernel"}
