@@ -455,6 +455,32 @@ def test_packed_batches_of_unequal_lengths_are_cut_into_chunks(lib):
     assert lib.la2_varlen_workspace_bytes(ctypes.byref(short), 4000 * 40, 0) == 0
 
 
+def test_packed_plans_by_the_average_load_of_a_compute_unit(lib):
+    """Unequal lengths, 256 compute units.  Longest at most 1.5 times the load (total x heads / units): not cut, the
+    workspace holds the sorted map only, and a call without one is not refused for it.  Few chains: pieces of at most
+    1.25 load (at least 256 positions), whatever the longest length alone would ask for."""
+    lib.la2_varlen_workspace_bytes.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32]
+    lib.la2_varlen_workspace_bytes.restype = ctypes.c_size_t
+    round256 = lambda x: (x + 255) // 256 * 256
+
+    def desc(batch, heads, longest, d):
+        x = dense(lib, batch, heads, longest, d, binding.LA2_BF16)
+        x.stride_b, x.stride_h, x.stride_n = 0, d, heads * d
+        return x
+    ws = lambda x, total, op: lib.la2_varlen_workspace_bytes(ctypes.byref(x), total, op)
+    x = desc(55, 16, 4096, 128)                                       # load 4096
+    assert ws(x, 65536, 0) == ws(x, 65536, 1) == round256(55 * 16)
+    assert lib.la2_fwd_varlen(ctypes.byref(x), None, 65536, P, P, P, P, P, None, 0, None) == E_NULL   # not E_WS
+    assert ws(x, 0, 0) == 0 and ws(x, 55 * 4096, 0) == 0
+    x = desc(20, 2, 8192, 128)                                        # load 512: pieces of at most 640
+    pairs, slots = 65536 // 640 + 20, 2 * 65536 // 640
+    for op, sets in ((0, 1), (1, 2)):
+        assert ws(x, 65536, op) == round256(pairs * 16 + 20 * 4) + sets * slots * 2 * 128 * 128 * 4
+    assert lib.la2_fwd_varlen(ctypes.byref(x), P, 65536, P, P, P, P, P, None, 0, None) == E_WS
+    x = desc(20, 2, 8192, 64)
+    assert ws(x, 3000, 0) == round256((3000 // 256 + 20) * 16 + 11 * 4) + (2 * 3000 // 256) * 2 * 64 * 64 * 4
+
+
 def test_packed_norm_and_multi_token_norm_validate_before_any_launch(lib):
     vp, i64, f32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_float
     lib.la2_fwd_varlen_norm.argtypes = [vp, vp, i64, vp, vp, vp, vp, f32, vp, vp, vp, ctypes.c_size_t, vp]

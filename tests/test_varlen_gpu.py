@@ -208,6 +208,36 @@ def test_a_total_below_the_real_one_drops_sequences_and_stays_inside_the_workspa
             assert_close("seq %d %s" % (b, name), got[lo:hi].permute(1, 0, 2)[None], ref, dtype)
 
 
+def test_a_total_below_the_real_one_with_even_pieces():
+    """The same with the automatic even cut: what fits the map and the slots planned from the told total is computed, the
+    other sequences stay untouched, nothing is written past the workspace."""
+    import ctypes
+    lengths, H, d, dtype, told, guard = [900, 64, 1500, 33, 700, 300], 2, 128, torch.bfloat16, 1500, 4096
+    t, cu = packed_inputs(lengths, H, d, dtype, seed=895)
+    g = {k: v.to(DEV) for k, v in t.items()}
+    cu_g = cu.to(DEV)
+    lib = binding.load()
+    desc = binding._varlen_desc(g["q"], cu_g, max(lengths))
+    need = int(lib.la2_varlen_workspace_bytes(ctypes.byref(desc), told, binding.LA2_OP_FWD))
+    ws = torch.full((need + guard,), 0xAB, dtype=torch.uint8, device=DEV)
+    o = torch.full_like(g["q"], float("nan"))
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert lib.la2_fwd_varlen(ctypes.byref(desc), cu_g.data_ptr(), told, g["q"].data_ptr(), g["k"].data_ptr(),
+                              g["v"].data_ptr(), g["lam"].data_ptr(), o.data_ptr(), ws.data_ptr(), need, stream) == 0
+    torch.cuda.synchronize()
+    assert bool((ws[need:] == 0xAB).all())
+    # pieces of at most 256: 1500 / 256 + 6 = 11 pairs and 2 * 1500 / 256 = 11 slots; 900 takes 4 of each, 64 a pair,
+    # 1500 would take 6 pairs and slots (11 and 10 in all: fits), everything behind it finds the map full
+    lam64 = to64(t["lam"])
+    for b, n in enumerate(lengths):
+        lo, hi = int(cu[b]), int(cu[b + 1])
+        if b > 2:
+            assert torch.isnan(o[lo:hi].float()).all(), b
+            continue
+        seq = {name: to64(t[name][lo:hi]).transpose(1, 0, 2)[None] for name in ("q", "k", "v")}
+        assert_close("seq %d o" % b, o[lo:hi].permute(1, 0, 2)[None], oracle.fwd_direct(seq["q"], seq["k"], seq["v"], lam64), dtype)
+
+
 def test_empty_cases_and_validation():
     lam = torch.ones(2, device=DEV)
     x = torch.zeros((0, 2, 64), dtype=torch.bfloat16, device=DEV)
