@@ -316,9 +316,8 @@ la2_status check_desc(const la2_desc* d) {
 //   fp32 d 64        no step: four workgroups share a unit
 //   chains           800          832          864          1056         1088
 //   bf16 d 64, 128   0.90-0.93    0.93-0.95    0.97-0.99    0.94         0.96         (n 4096 and 8192)
-// The rule below takes the cells at about 0.95 or under.  The workspace query answers for fp32 batches up to 1.5 chains
-// per unit (`query`), also where the call then runs as one and needs none.
-int rows_of_first_call(const la2_desc* d, bool query = false) {
+// The rule below takes the cells at about 0.95 or under.  The workspace query and every call ask this one function.
+int rows_of_first_call(const la2_desc* d) {
   if (g_chunk_tokens_override.load(std::memory_order_relaxed) > 0) return 0;   // the caller plans
   const int cus = device_cu_count();
   const int n = d->seqlen, hd = d->head_dim;
@@ -329,7 +328,7 @@ int rows_of_first_call(const la2_desc* d, bool query = false) {
   int eighths = 0;
   if (d->dtype == LA2_F32) {
     if (wide(hd)) return 0;
-    if (k == 1) eighths = n < 1024 ? 0 : query ? 4 : hd == 128 ? (n >= 2048 ? 2 : 1) : (n >= 2048 ? 1 : 0);
+    if (k == 1) eighths = hd == 128 ? (n >= 2048 ? 2 : n >= 1024 ? 1 : 0) : (n >= 2048 ? 1 : 0);
     else eighths = k == 2 && hd == 128 && n >= 2048 ? 2 : 0;
   } else if (hd == 256) {
     eighths = k == 1 && n >= 2048 ? 1 : 0;
@@ -377,7 +376,7 @@ void* shifted_bytes(void* p, int64_t bytes) { return p == nullptr ? nullptr : st
 // one stream and share the workspace), or the whole batch's when it runs as one call.
 template <typename F>
 size_t over_parts(const la2_desc* d, F bytes_of) {
-  const int rows = rows_of_first_call(d, true);
+  const int rows = rows_of_first_call(d);
   if (rows == 0) return bytes_of(d);
   const RowParts p = row_parts(d, rows);
   const size_t a = bytes_of(&p.first), b = bytes_of(&p.rest);

@@ -635,7 +635,8 @@ def test_batches_a_little_above_the_unit_count_take_the_workspace_of_their_remai
              (52, 16, 4096, 128, BF), (50, 16, 8192, 64, F16), (66, 16, 4096, 64, BF),     # ... three and four
              (34, 8, 2048, 256, BF), (36, 8, 4096, 256, F16),                              # head_dim 256: up to 1.125
              (18, 16, 2048, 96, BF), (20, 16, 4096, 96, BF), (34, 16, 4096, 96, F16),      # head_dim 96
-             (20, 16, 4096, 128, F32), (24, 16, 1024, 64, F32), (34, 16, 4096, 128, F32)]  # fp32: up to 1.5
+             (20, 16, 4096, 128, F32), (18, 16, 1024, 128, F32), (18, 16, 2048, 64, F32),  # fp32: up to 1.25 (1.125 at
+             (34, 16, 4096, 128, F32)]                                                     # n 1024 and at head_dim 64)
     for b, h, n, d, dt in split:
         first = (b * h // 256) * 256 // h
         whole, rest = dense(lib, b, h, n, d, dt), dense(lib, b - first, h, n, d, dt)
@@ -646,10 +647,10 @@ def test_batches_a_little_above_the_unit_count_take_the_workspace_of_their_remai
             assert ws(whole, op) == ws(rest, op) > 0, (b, h, n, d, dt, op)
     # heads that do not divide the unit count: the first part has 21 x 12 = 252 chains, which the fp32 head_dim 64 plan
     # cuts in three; both parts then use the workspace, one after the other, and the query answers for the larger
-    parts = [dense(lib, 21, 12, 1024, 64, F32), dense(lib, 1, 12, 1024, 64, F32)]
-    assert plan(lib, 21, 12, 1024, 64, F32)[0] == 3 and plan(lib, 1, 12, 1024, 64, F32)[0] > 1
+    parts = [dense(lib, 21, 12, 2048, 64, F32), dense(lib, 1, 12, 2048, 64, F32)]
+    assert plan(lib, 21, 12, 2048, 64, F32)[0] == 3 and plan(lib, 1, 12, 2048, 64, F32)[0] > 1
     for op in (0, 1, 2, 3):
-        assert ws(dense(lib, 22, 12, 1024, 64, F32), op) == max(ws(p_, op) for p_ in parts) > 0
+        assert ws(dense(lib, 22, 12, 2048, 64, F32), op) == max(ws(p_, op) for p_ in parts) > 0
     # not split: too many chains for the shape, a whole number of rounds, sequences too short, five rounds, three
     # rounds of the kernels whose rule stops at two
     for b, h, n, d, dt in ((23, 16, 4096, 128, BF), (21, 16, 2048, 128, BF), (16, 16, 4096, 128, BF),
@@ -657,6 +658,8 @@ def test_batches_a_little_above_the_unit_count_take_the_workspace_of_their_remai
                            (38, 8, 2048, 256, BF), (34, 8, 1024, 256, BF), (68, 8, 4096, 256, BF),
                            (20, 16, 2048, 96, BF), (36, 16, 4096, 96, BF), (25, 16, 4096, 64, F32),
                            (24, 16, 512, 64, F32), (34, 16, 4096, 64, F32), (48, 16, 4096, 128, BF),
+                           (24, 16, 1024, 64, F32), (17, 16, 1024, 64, F32), (20, 16, 2048, 64, F32),
+                           (19, 16, 1025, 128, F32), (21, 16, 4096, 128, F32), (24, 16, 4096, 128, F32),
                            (32, 16, 4096, 128, BF), (54, 16, 4096, 128, BF), (68, 16, 4096, 128, BF),
                            (82, 16, 4096, 128, BF), (50, 16, 2048, 128, BF), (50, 16, 4096, 96, BF),
                            (50, 16, 4096, 128, F32)):
@@ -667,6 +670,28 @@ def test_batches_a_little_above_the_unit_count_take_the_workspace_of_their_remai
         assert ws(d, 0) == 20 * 16 * 4 * 128 * 128 * 4
     finally:
         lib.la2_set_chunk_tokens(0)
+
+
+def test_the_workspace_query_is_what_the_call_asks_for(lib):
+    """fp32 batches around the limits of the two-call rule, whole and ragged lengths, a gradient of the final state coming
+    in (at a ragged end it is handed over through the workspace, one state per chain of a call): every backward entry
+    point takes exactly the bytes that the query answers, and refuses one byte less before it launches anything.  Without
+    a device an accepted call ends in its first launch's error."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("fake pointers: an accepted call would run on them")
+    lib.la2_set_chunk_tokens(0)
+    for d in (64, 128):
+        for b, h in ((257, 1), (17, 16), (22, 12), (18, 16), (19, 16), (20, 16), (21, 16), (22, 16), (24, 16)):
+            for n in (1024, 1025, 2048, 2049, 3001):
+                desc = dense(lib, b, h, n, d, binding.LA2_F32)
+                ref = ctypes.byref(desc)
+                need = lib.la2_workspace_bytes(ref, 3)
+                saved = lambda size: lib.la2_bwd_saved(ref, P, P, P, P, P, P, P, P, P, P, P, None, 0, 0, P, size, None)
+                norm = lambda size: lib.la2_bwd_state_norm(ref, P, P, P, P, P, P, P, P, P, P, P, P, P, P, P, size, None)
+                for call in (saved, norm):
+                    assert call(need) == E_LAUNCH, (b, h, n, d, need)
+                    assert need == 0 or call(need - 1) == E_WS, (b, h, n, d, need)
 
 
 def test_two_call_batches_are_validated_before_the_first_launch(lib):

@@ -268,3 +268,36 @@ def test_random_batch_above_whole_rounds_two_calls_against_one(i):
     for name in got:
         assert torch.isfinite(got[name].float()).all(), name
         assert rel_diff(got[name], ref[name]) <= tol, (name, rel_diff(got[name], ref[name]))
+
+
+@pytest.mark.parametrize("n", [1025, 2049])
+@pytest.mark.parametrize("b", [17, 19])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_states_just_above_one_chain_per_unit(d, b, n):
+    """272 and 304 fp32 chains (256 compute units) of ragged lengths, on both sides of the two-call rule's limits for each
+    head_dim and length, states and their gradients handed over, with the workspaces that the query answers for:
+    against the oracle, and the normalised backward against the plain one on the same gradient."""
+    H = 16
+    two = {(64, 17, 2049), (128, 17, 1025), (128, 17, 2049), (128, 19, 2049)}
+    t = workloads.Workload("case", b, H, n, d, torch.float32, seed=b * n + d, backward=True).tensors()
+    g = {name: t[name].to(DEV) for name in ("q", "k", "v", "d_o", "lam")}
+    gen = torch.Generator(device="cpu")
+    gen.manual_seed(n)
+    kv0, dkvf = (torch.randn((b, H, d, d), generator=gen) * 0.3 for _ in range(2))
+    assert (binding.la2_workspace_bytes(g["q"], binding.LA2_OP_FWD) > 0) == ((d, b, n) in two)
+    o, kvf = binding.la2_fwd_state(g["q"], g["k"], g["v"], g["lam"], kv_init=kv0.to(DEV))
+    grads = binding.la2_bwd_state(g["q"], g["k"], g["v"], g["d_o"], g["lam"], kv_init=kv0.to(DEV), d_kv_final=dkvf.to(DEV))
+    on, rstd, _ = binding.la2_fwd_state_norm(g["q"], g["k"], g["v"], g["lam"], 1e-6, kv_init=kv0.to(DEV))
+    d_u = torch.empty_like(g["d_o"])
+    gn = binding.la2_bwd_state_norm(g["q"], g["k"], g["v"], on, rstd, g["d_o"], g["lam"], kv_init=kv0.to(DEV),
+                                    d_kv_final=dkvf.to(DEV), d_u=d_u)
+    gp = binding.la2_bwd_state(g["q"], g["k"], g["v"], d_u, g["lam"], kv_init=kv0.to(DEV), d_kv_final=dkvf.to(DEV))
+    torch.cuda.synchronize()
+    q, k, v, do, lam = (to64(t[x]) for x in ("q", "k", "v", "d_o", "lam"))
+    ro, rkvf = oracle.fwd_recurrent(q, k, v, lam, kv_init=to64(kv0), return_state=True)
+    refs = oracle.bwd_recurrent_state(q, k, v, do, lam, kv_init=to64(kv0), d_kv_final=to64(dkvf))
+    assert_close("o", o, ro, torch.float32)
+    assert_close("kv_final", kvf, rkvf, torch.float32)
+    for name, got, ref in zip(("dq", "dk", "dv", "d_kv_init"), grads, refs):
+        assert_close(name, got, ref, torch.float32)
+    assert all(torch.equal(x, y) for x, y in zip(gn[:4], gp[:4]))
