@@ -245,7 +245,7 @@ SPLIT_CASES += [(36, 16, 4096, 128, False, torch.float16), (34, 16, 4100, 64, Tr
                 (50, 16, 4096, 64, False, torch.bfloat16),                                           # three
                 (34, 8, 2048, 256, False, torch.bfloat16), (36, 8, 2100, 256, True, torch.float16),
                 (18, 16, 2048, 96, False, torch.float16), (34, 16, 4096, 96, False, torch.bfloat16),
-                (24, 16, 1024, 64, False, torch.float32), (20, 16, 1100, 128, True, torch.float32),
+                (18, 16, 2048, 64, False, torch.float32), (18, 16, 1100, 128, True, torch.float32),
                 (34, 16, 2048, 128, False, torch.float32)]
 
 
