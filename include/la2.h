@@ -336,7 +336,8 @@ la2_status la2_decode_step_norm(int32_t batch, int32_t heads, int32_t head_dim, 
  *                            a call plans its chunks for the whole blocks of a ragged seqlen only (see
  *                            la2_fwd_state); if that plan differs from this call's, the saved states are not used
  *                            and the result is that of la2_bwd_state.
- * The chunk plan also depends on la2_set_chunk_tokens() and the device: both calls must see the same.
+ * The chunk plan also depends on la2_set_chunk_tokens() and the device, and what the workspace holds of 16-bit data on
+ * la2_set_scan_variant(): both calls must see the same.
  * A batch that runs as two calls (see la2_chunk_plan) left only its second part's chunk states in fwd_workspace; the
  * second part of this call reads them, the first part, should its own plan cut, recomputes.
  */

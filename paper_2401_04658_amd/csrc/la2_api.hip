@@ -422,8 +422,9 @@ bool self_prefix(const la2_desc* d, const Plan& pl, const int32_t* cu) {
   (void)cu;   // packed batches too: every sequence's chunks have their own slots, a sequence of one chunk has none
   // head_dim 96 (36 KiB a state): up to six chunks, no limit of registers there; at 256 a state is 256 KiB
   if (d->head_dim == 96) return is16(d->dtype) && pl.nchunks > 1 && pl.nchunks <= 6;
-  return pl.nchunks > 1 && pl.nchunks <= kSelfPrefixMaxChunks &&
-         !wide(d->head_dim) && pl.chunk_tokens % 32 == 0 && g_scan_variant.load(std::memory_order_relaxed) != 1;
+  if (wide(d->head_dim) || pl.nchunks <= 1 || pl.nchunks > kSelfPrefixMaxChunks || pl.chunk_tokens % 32 != 0) return false;
+  // (the scan variant is a knob of the 16-bit kernels: what an fp32 workspace holds does not depend on it)
+  return !is16(d->dtype) || g_scan_variant.load(std::memory_order_relaxed) != 1;
 }
 
 la2::ScanParams base_params(const la2_desc* d, const Plan& pl, const float* lambda, void* workspace,

@@ -285,6 +285,32 @@ def test_backward_reuses_the_forward_chunk_states(dtype, d, n, chunk):
         assert_close(tag + " d_kv_init", g0, rg0, dtype)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nchunks", [3, 4, 5])
+def test_fp32_ignores_the_scan_variant_between_forward_and_backward(nchunks, d):
+    """The scan variant is a knob of the 16-bit kernels: an fp32 forward call and a backward call that reads its chunk
+    states agree on what the workspace holds whatever the knob says in between."""
+    b, H, chunk = 2, 3, 64
+    n = chunk * nchunks - 7
+    t = inputs(b, H, n, d, torch.float32, seed=31 * nchunks + d, lam=0.99)
+    g = {k: v.to(DEV) for k, v in t.items()}
+    binding.la2_set_chunk_tokens(chunk)
+    results = []
+    for first, second in ((0, 0), (0, 1), (1, 0)):
+        binding.la2_set_scan_variant(first)
+        ws_f = torch.empty(binding.la2_workspace_bytes(g["q"], binding.LA2_OP_FWD), dtype=torch.uint8, device=DEV)
+        o = binding.la2_fwd(g["q"], g["k"], g["v"], g["lam"], workspace=ws_f)
+        binding.la2_set_scan_variant(second)
+        grads = binding.la2_bwd_state(g["q"], g["k"], g["v"], g["d_o"], g["lam"], fwd_workspace=ws_f)
+        torch.cuda.synchronize()
+        results.append((o,) + grads)
+    q, k, v, do, lam = (to64(t[x]) for x in ("q", "k", "v", "d_o", "lam"))
+    for name, got, ref in zip(("dq", "dk", "dv"), results[0][1:], oracle.bwd_direct(q, k, v, do, lam)):
+        assert_close(name, got, ref, torch.float32)
+    for other in results[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(results[0], other))
+
+
 @pytest.mark.parametrize("d,n,chunk", [(64, 1000, 128), (128, 1025, 256), (128, 1000, 256)])
 def test_backward_after_a_forward_that_wrote_kv_final_at_a_ragged_length(d, n, chunk):
     """The forward call that hands out kv_final for a ragged length plans its chunks for the whole blocks only.
