@@ -30,8 +30,11 @@
  *     pointer; pointers may then be NULL.
  *   - dtype LA2_BF16 / LA2_F16: bf16 / fp16 storage and MFMA operands, fp32 accumulation and fp32 running
  *     state (fp16: the masked scores and the state, as matrix operands, must stay within the fp16 range).
- *     dtype LA2_F32: fp32 storage, products exact to fp32 and fp32 sums throughout (head_dim 64 and 128: each float split
- *     into three bf16 parts for the matrix instructions; a non-finite input makes the rows that depend on it NaN).
+ *     dtype LA2_F32: fp32 storage, products to 2^-24 and fp32 sums throughout, over the whole range of the type (head_dim
+ *     64 and 128: each float split into three bf16 parts for the matrix instructions; values that these cannot take, Inf
+ *     and NaN among them, go through the fp32 matrix instructions).
+ *   - An Inf or NaN reaches the positions that depend on it, and those of its own block of la2_block_size() positions that
+ *     do not (the masked products there are 0 times it).
  *   - seqlen may be any value >= 0 (a ragged last block is masked) as long as one (batch, head) chain stays
  *     addressable with 32-bit byte offsets: (seqlen + 128) * stride_n * sizeof(element) <= 2^32, else
  *     LA2_ERR_SHAPE (dense bf16, head_dim 128: up to 16,777,088 positions).

@@ -1,10 +1,19 @@
 // fp32 kernels for the decayed causal scan (Algorithm 1; both loops of Algorithm 2), gfx950.
 //
-// fp32 storage, products exact to fp32 and fp32 accumulation, for callers that need the 1e-5 accuracy class, on the
-// bf16 matrix instructions.  A float is the exact sum of three bf16 numbers (8 significand bits each, the second and
-// the third the rounded remainders), so a product of two floats is nine bf16 products; the three smallest, below
-// 2^-25 of the product and of either sign, are left out.  Six v_mfma_f32_32x32x16_bf16 (32 cycles each) contract what
-// eight v_mfma_f32_32x32x2_f32 (64 cycles each) do, in fewer rounded additions.
+// fp32 storage and fp32 sums, for callers that need the 1e-5 accuracy class, on the bf16 matrix instructions.  A float is
+// the exact sum of three bf16 numbers hi, mid, lo (8 significand bits each, the second and the third the rounded
+// remainders: at most 2^-8 and 2^-17 of it), so a product of two floats is nine bf16 products; mid lo, lo mid and lo lo,
+// together at most 2^-24 of the product and of either sign (rms 2^-27.5), are left out.  Six v_mfma_f32_32x32x16_bf16 (32
+// cycles each) contract what eight v_mfma_f32_32x32x2_f32 (64 cycles each) do, in fewer rounded additions.
+//
+// Range.  lo of a value below 2^-110 would fall out of bf16's range, so every operand is scaled by 2^16 before it is split:
+// X, Y, and Z with its weights; the state then carries 2^32, the scores 2^32, an output 2^48, taken off before it is
+// stored.  Subnormals are operands like any other (bf16 parts reach down to 2^-133, 2^-149 after scaling: exact).  What
+// leaves the range at the other end (an operand of 2^111 or more, a state or score of 2^95, an output of 2^79; Inf and
+// NaN) turns some output or state element infinite or NaN, whatever else it meets.  A workgroup looks for that (one
+// v_maximum3 per two outputs) and, if it finds it, walks its chunk again on v_mfma_f32_32x32x2_f32: that walk's state, and
+// its outputs from the first such block on, are what is kept.  Its tiles are fp32 in the place of the planes; it is written
+// for registers, not for speed.
 //
 // Organisation: one workgroup walks the blocks (B = 32 positions) of one sequence chunk of one (batch, head) chain;
 // wave w owns value features 32 w .. 32 w + 31 of the output and of the running state, whose slice stays in MFMA
@@ -18,19 +27,18 @@
 // into the planes between the block's two barriers.  56 KiB (D = 128) or 32 KiB (D = 64) of LDS and 256 registers, so
 // two (four) workgroups share a compute unit and one computes while the other splits and waits.
 //
-// What bounds it: issue.  Per wave and block 3,840 cycles of matrix pipe and about 870 vector instructions (the split is
-// 5.5 per element: 64 elements of the state, 64 of the tiles; the pipes share the issue, at full load both are half
-// busy).  Against v_mfma_f32_32x32x2_f32 on tiles in fp32 (208 of 64 cycles, one workgroup per unit), forward +
-// backward: batch 4, H 16, n 2048, d 128 0.858 -> 0.419 ms, batch 16, n 1024 1.20 -> 0.62; d 64, batch 4, n 4096
-// 0.57 -> 0.37.  Relative error of the results (2-norm, N(0, 1) data) 3.0e-7 -> 2.5e-7 at d 128, 2.7e-7 -> 2.2e-7 at d 64.
+// What bounds it: issue.  Per wave and block 3,840 cycles of matrix pipe and about 930 vector instructions (the split is
+// 5.5 per element: 64 elements of the state, 64 of the tiles; 58 for the scaling and the look at the outputs; the pipes
+// share the issue, at full load both are half busy).  Against v_mfma_f32_32x32x2_f32 on tiles in fp32 (208 of 64 cycles, one
+// workgroup per unit), forward + backward: batch 4, H 16, n 2048, d 128 0.856 -> 0.417 ms, batch 16, n 1024 1.20 -> 0.63;
+// d 64, batch 4, n 2048 0.330 -> 0.200, batch 16, n 1024 0.57 -> 0.33 (without the scaling and the look 0.405, 0.60, 0.194,
+// 0.31).  Relative error of the results (2-norm, N(0, 1) data, n 200) 2.5e-7 -> 2.0e-7 at d 128, 2.1e-7 -> 1.7e-7 at d 64.
 //
 // Feature order.  In the accumulator layout a lane holds rows 8 (v / 4) + 4 hh + v % 4 of a state tile, so the eight
 // elements of a k-step would not be the eight consecutive features of an X row fragment.  The transposing reads of Y
 // take the columns with bits 2 and 3 of the index exchanged (the lanes pass the addresses of the 8-byte pieces in that
 // order); state register (t, v) then is key feature 32 t + 16 (v / 8) + 8 hh + v % 8 and a k-step's elements are
 // features 16 ks + 8 hh .. + 7.
-//
-// Values: an Inf among the inputs makes the rows that depend on it NaN (the remainder of its split is Inf - Inf).
 #include "la2_bf16_common.h"
 
 namespace la2 {
@@ -38,9 +46,14 @@ namespace {
 using namespace bf16k;
 
 constexpr int kBF = 32;   // block size (positions per block)
+constexpr float kUp = 65536.f;   // 2^16: what an operand is scaled by before it is split
 typedef ex8<__bf16> b8;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {   // contracts two indices, one per wave half
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
 
 // the three bf16 parts of a pair of floats, packed (low half: the first)
 __device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
@@ -67,7 +80,7 @@ __device__ __forceinline__ Parts split8(const float (&x)[8]) {
   return Parts{{r[0].v, r[1].v, r[2].v}};
 }
 
-// the six products of at least 2^-17 of the whole, the small ones first
+// hi lo, lo hi, mid mid (at most 2^-16 of the whole), hi mid, mid hi, hi hi, in this order
 template <typename Acc, typename F>
 __device__ __forceinline__ Acc six(const Parts& a, const Parts& b, Acc c, F f) {
   c = f(a.p[0], b.p[2], c);
@@ -151,48 +164,55 @@ __device__ __forceinline__ int state_index_f32(int dvt, int l32, int hh, int t, 
   return transposed ? dv * D + dk : dk * D + dv;
 }
 
-// Scan kernel (STATE_ONLY = false) and chunk-state pre-pass (STATE_ONLY = true: only Y, Z and the state
-// update; the local state of the chunk is written to p.states).  D / 32 waves.
-template <int D, bool REV, bool STATE_ONLY>
-__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) void scan_f32_kernel(ScanParams p) {
+template <int D, bool STATE_ONLY>
+struct Lds {
+  static constexpr int PROW = 40;   // elements per row of a score plane (80 bytes: 16 rows in 16 bank groups)
+  __attribute__((aligned(1024))) __bf16 x[STATE_ONLY ? 1 : 3][STATE_ONLY ? 512 : kBF * D];
+  __attribute__((aligned(1024))) __bf16 y[3][kBF * D];
+  __attribute__((aligned(16))) __bf16 p[STATE_ONLY ? 1 : 3][STATE_ONLY ? 8 : kBF * PROW];   // [position r][c]
+  __attribute__((aligned(16))) float wz[kBF];          // weight of a row of Z in the state update
+  float red[STATE_ONLY ? 1 : kBF * (D / 32)];          // Norm epilogue: partial sums of squares, [row][wave]
+  int good;                                            // blocks before a value that is not finite
+};
+
+struct Place {   // what a workgroup works on; the same for all its lanes
+  int which, chain, chunk, bi, hi, n;
+  int64_t base;
+};
+
+// One walk over the workgroup's chunk: the scan, or (STATE_ONLY) the chunk-state pre-pass (only Y, Z and the state update).
+// D / 32 waves.  Leaves the state after the chunk, times 2^32 if not FP32, in kv.
+// FP32 = false: on split operands; returns -1, or (to all waves) the number of blocks, in the order of the walk, whose
+// outputs are in order when the chunk has to be walked again for the others and the state.  FP32 = true: on the fp32 matrix
+// instructions; outputs of the blocks from number `from` on are stored.
+template <int D, bool REV, bool STATE_ONLY, bool FP32>
+__device__ __forceinline__ int walk(const ScanParams& p, Lds<D, STATE_ONLY>& lds, const Place& place, f32x16 (&kv)[D / 32],
+                                    int from = 0) {
   constexpr int B = kBF;
   constexpr int NT = D / 32;          // waves; 32-wide feature tiles
   constexpr int KS = D / 16;          // k-steps along the features
   constexpr int CPR = D / 8;          // 8-feature pieces per row
   constexpr int TILE = B * D;         // elements per plane
-  constexpr int PROW = 40;            // elements per row of a score plane (80 bytes: 16 rows in 16 bank groups)
-  __shared__ __attribute__((aligned(1024))) __bf16 sX[STATE_ONLY ? 1 : 3][STATE_ONLY ? 8 : TILE];
-  __shared__ __attribute__((aligned(1024))) __bf16 sY[3][TILE];
-  __shared__ __attribute__((aligned(16))) __bf16 sP[STATE_ONLY ? 1 : 3][STATE_ONLY ? 8 : B * PROW];   // [position r][c]
-  __shared__ __attribute__((aligned(16))) float sWz[B];   // weight of a row of Z in the state update
-  __shared__ float sRed[STATE_ONLY ? 1 : B * NT];   // Norm epilogue: partial sums of squares, [row][wave]
+  constexpr int PROW = Lds<D, STATE_ONLY>::PROW;
+  constexpr float UP = FP32 ? 1.f : kUp;
+  auto& sX = lds.x;
+  auto& sY = lds.y;
+  auto& sP = lds.p;
+  auto& sWz = lds.wz;
+  auto& sRed = lds.red;
 
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l32 = l & 31, hh = l >> 5;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // (nothing of one walk is kept in registers for the other)
+  const int w = tid >> 6, l = tid & 63, l32 = l & 31, hh = l >> 5;
   const int dvt = w;
-  int which = 0, wg = (int)blockIdx.x;
-  if (!STATE_ONLY && p.nscan == 2) {   // two scans that read the same tiles: eight workgroups apart, on one XCD
-    if (((gridDim.x >> 1) & 7) == 0) {
-      which = (wg >> 3) & 1;
-      wg = ((wg >> 4) << 3) | (wg & 7);
-    } else {
-      which = wg & 1;
-      wg >>= 1;
-    }
-  }
-  const int chain = wg / p.nchunks, chunk = wg % p.nchunks;
-  const int bi = chain / p.heads, hi = chain % p.heads;
-  int64_t base;
-  int n;
-  chain_extent(p, bi, hi, base, n);
+  const int which = place.which, chain = place.chain, chunk = place.chunk, bi = place.bi, hi = place.hi, n = place.n;
+  const int64_t base = place.base;
   const uint32_t stride_n = (uint32_t)p.stride_n;
 
   const int nblocks = (n + B - 1) / B;
   const int cb = p.chunk_tokens / B;
   const int blk_lo = chunk * cb;
   const int blk_hi = min(blk_lo + cb, nblocks);
-  if (!STATE_ONLY && blk_lo >= blk_hi) return;
-  // pre-pass: the chunk a scan of THIS chain passes last has no successor (packed batch: chains of different lengths)
-  if (STATE_ONLY && (REV ? (chunk == 0) : (blk_hi >= nblocks))) return;
   const int nblk = max(blk_hi - blk_lo, 0);
 
   // Buffer descriptors over the chain's rows: rows past the end load as zeros and their stores are dropped.
@@ -236,6 +256,11 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) v
     for (int v = 0; v < 16; v++) zr[v] = pz[v];
 #pragma unroll
     for (int i = 0; i < 2; i++) {
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        py[i][j] *= kUp;
+        if (!STATE_ONLY) px[i][j] *= kUp;
+      }
       const Parts y = split8(py[i]);
 #pragma unroll
       for (int k = 0; k < 3; k++) *reinterpret_cast<b8*>(&sY[k][plane_at + 16 * D * i]) = y.p[k];
@@ -248,12 +273,11 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) v
   };
 
   // ---- running state slice S[:, dv tile]: NT accumulator tiles (key-feature tiles), fp32
-  f32x16 kv[NT];
+  const Decay lam(p.lambda[hi]);
 #pragma unroll
   for (int t = 0; t < NT; t++) kv[t] = zero16();
-  const Decay lam(p.lambda[hi]);
   if constexpr (!STATE_ONLY) {
-    // kv <- decay kv + a d x d state (row = y feature, or transposed: eight consecutive elements of a stored row)
+    // kv <- decay kv + UP^2 * a d x d state (row = y feature, or transposed: eight consecutive elements of a stored row)
     auto add_state = [&](const float* gs, bool tr, float decay) __attribute__((always_inline)) {
       uint32_t at = (uint32_t)state_index_f32<D>(dvt, l32, hh, 0, 0, tr);
       pin(at);   // one lane offset, the rest is uniform: not sixteen addresses per tile
@@ -272,7 +296,7 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) v
           for (int v = 0; v < 16; v++) x[v] = (gs + (32 * t + 16 * (v >> 3) + (v & 7)) * D)[at];
         }
 #pragma unroll
-        for (int v = 0; v < 16; v++) kv[t][v] = fmaf(decay, kv[t][v], x[v]);
+        for (int v = 0; v < 16; v++) kv[t][v] = fmaf(decay, kv[t][v], x[v] * (UP * UP));
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -295,13 +319,14 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) v
   // ---- decay weights: of the rows of Z in the state update (LDS), of the carried state at this lane's position, of the
   // quarters of the score tile S^T[c][r] that this wave computes (lane: position
   // r = 16 rq + l % 16, elements i: c = 16 cq + 4 (l / 16) + i).
-  if (tid < B) sWz[tid] = lam.pow(REV ? tid + 1 : B - 1 - tid);
+  if (tid < B) sWz[tid] = UP * lam.pow(REV ? tid + 1 : B - 1 - tid);
+  if (!FP32 && tid == 0) lds.good = nblk + 1;
   const float lamB = uniform(lam.pow(B));
   const float inter_scale = lam.pow(REV ? B - 1 - l32 : l32 + 1);
   constexpr int NQ = 4 / NT;   // quarters per wave: w, w + NT
   const int l16 = l & 15, g4 = l >> 4;
   float dg[STATE_ONLY ? 1 : NQ][4];
-  if (!STATE_ONLY) {
+  if (!STATE_ONLY && !FP32) {
 #pragma unroll
     for (int u = 0; u < NQ; u++) {
       const int q = w + NT * u, cq = q & 1, rq = q >> 1;
@@ -314,7 +339,7 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) v
     for (int i = tid; i < 3 * B * PROW / 2; i += 2 * D) reinterpret_cast<uint32_t*>(&sP[0][0])[i] = 0u;   // the empty quarter stays zero
   }
 
-  if (nblk > 0) load_block(REV ? blk_hi - 1 : blk_lo);
+  if (!FP32 && nblk > 0) load_block(REV ? blk_hi - 1 : blk_lo);
 
   // ---- LDS addresses: row fragments (32 rows x 16 features; 16 rows x 32 features), transposing reads
   const int rowk = l32 * D + 8 * (hh ^ swz<D>(l32));       // 32-row fragment of k-step ks: rowk ^ 16 ks
@@ -345,179 +370,317 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) v
     return r;
   };
 
-  if (nblk > 0) write_planes();
-  lds_barrier();
+  auto block_at = [&](int it) { return REV ? blk_hi - 1 - it : blk_lo + it; };
 
-  for (int it = 0; it < nblk; it++) {
-    const int blk = REV ? blk_hi - 1 - it : blk_lo + it;
-    const bool has_next = it + 1 < nblk;
-    if (has_next) load_block(REV ? blk - 1 : blk + 1);
-
-    // The body is a sequence of slots: the MFMAs of one product, in their shadow the LDS reads and the splits of the
-    // next one (left alone the compiler puts every split in front of the product that takes it).
-    f32x16 acc = zero16();
-    Parts yt[2], zd, zf[2];
-    // Pre-pass: only the state after the last block is wanted, so every block's contribution carries its whole decay up
-    // front.
-    const float up = STATE_ONLY ? uniform(lam.pow(B * (nblk - 1 - it))) : 1.f;
-    Splitter sp;
-    auto z_into = [&](int q, bool decayed) __attribute__((always_inline)) {
+  // Output of a block: lane = position l32, elements v = 4 g .. 4 g + 3 are value features 32 dvt + 8 g + 4 hh .. + 3.
+  // One workgroup barrier, before which the caller is done with the block's LDS.
+  auto emit = [&](f32x16& w, int blk, bool keep) __attribute__((always_inline)) {
+    const int pos = keep ? blk * B + l32 : n;
+    auto store_rows = [&]() __attribute__((always_inline)) {
+      const uint32_t off = ((uint32_t)pos * stride_n + (uint32_t)(32 * dvt + 4 * hh)) * 4u;
 #pragma unroll
-      for (int h = 0; h < 2; h++) {
-        const f32x4 wt = *reinterpret_cast<const f32x4*>(&sWz[16 * q + 8 * h + 4 * hh]);
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-          sp.x[4 * h + j] = decayed ? zr[8 * q + 4 * h + j] * (STATE_ONLY ? wt[j] * up : wt[j]) : zr[8 * q + 4 * h + j];
+      for (int g = 0; g < 4; g++) {
+        const i32x4 o4 = {__float_as_int(w[4 * g]), __float_as_int(w[4 * g + 1]), __float_as_int(w[4 * g + 2]),
+                          __float_as_int(w[4 * g + 3])};
+        __builtin_amdgcn_raw_buffer_store_b128(o4, gw, off + 32u * g, 0, 0);
       }
     };
-    if constexpr (!STATE_ONLY) {
-      auto state_into = [&](int ks) __attribute__((always_inline)) {
+    if (p.rstd != nullptr) {   // Norm epilogue (eq. (2)); the sums meet under the barrier
+      norm_publish<NT>(w, sRed, l32, hh, dvt);
+      lds_barrier();
+      const float r = norm_collect<NT>(sRed, l32, 1.f / (float)D, p.eps);
 #pragma unroll
-        for (int j = 0; j < 8; j++) sp.x[j] = kv[ks >> 1][8 * (ks & 1) + j];
+      for (int v = 0; v < 16; v++) w[v] *= r;
+      if (dvt == 0 && hh == 0 && pos < n) p.rstd[rstd_chain_offset(p, bi, hi) + pos] = r;
+      store_rows();
+    } else {
+      store_rows();
+      lds_barrier();
+    }
+  };
+
+  if constexpr (!FP32) {
+    if (nblk > 0) write_planes();
+    lds_barrier();
+
+    float worst = 0.f;   // largest magnitude among this lane's outputs so far; NaN if one is NaN
+    int good = 0;        // blocks up to which that is finite
+
+    for (int it = 0; it < nblk; it++) {
+      const int blk = block_at(it);
+      const bool has_next = it + 1 < nblk;
+      if (has_next) load_block(REV ? blk - 1 : blk + 1);
+
+      // The body is a sequence of slots: the MFMAs of one product, in their shadow the LDS reads and the splits of the
+      // next one (left alone the compiler puts every split in front of the product that takes it).
+      f32x16 acc = zero16();
+      Parts yt[2], zd, zf[2];
+      // Pre-pass: only the state after the last block is wanted, so every block's contribution carries its whole decay up
+      // front.
+      const float up = STATE_ONLY ? uniform(lam.pow(B * (nblk - 1 - it))) : 1.f;
+      Splitter sp;
+      auto z_into = [&](int q, bool decayed) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+          const f32x4 wt = *reinterpret_cast<const f32x4*>(&sWz[16 * q + 8 * h + 4 * hh]);
+#pragma unroll
+          for (int j = 0; j < 4; j++)
+            sp.x[4 * h + j] = zr[8 * q + 4 * h + j] * (!decayed ? kUp : STATE_ONLY ? wt[j] * up : wt[j]);
+        }
       };
-      // score quarters S^T[c][r] = sum_k Y[c][k] X[r][k]  (the empty quarter: computed by the wave that would idle, not used)
-      f32x4 s[NQ];
-      Parts xa[2] = {read_parts(sX, rowk), {}};
+      if constexpr (!STATE_ONLY) {
+        auto state_into = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < NQ; u++) {
-        const int q = w + NT * u, cq = q & 1, rq = q >> 1;
-        s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int j = 0; j < 8; j++) sp.x[j] = kv[ks >> 1][8 * (ks & 1) + j];
+        };
+        // score quarters S^T[c][r] = sum_k Y[c][k] X[r][k]  (the empty quarter: computed by the wave that would idle, not used)
+        f32x4 s[NQ];
+        Parts xa[2] = {read_parts(sX, rowk), {}};
 #pragma unroll
-        for (int ks = 0; ks < D / 32; ks++)
-          s[u] = mul16(read_parts(sY, 16 * cq * D + (rowq ^ (32 * ks))), read_parts(sX, 16 * rq * D + (rowq ^ (32 * ks))), s[u]);
-      }
-      state_into(0);
+        for (int u = 0; u < NQ; u++) {
+          const int q = w + NT * u, cq = q & 1, rq = q >> 1;
+          s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < 6; i++) sp.step(i);
-      Parts sa = sp.parts();
+          for (int ks = 0; ks < D / 32; ks++)
+            s[u] = mul16(read_parts(sY, 16 * cq * D + (rowq ^ (32 * ks))), read_parts(sX, 16 * rq * D + (rowq ^ (32 * ks))), s[u]);
+        }
+        state_into(0);
 #pragma unroll
-      for (int u = 0; u < NQ; u++) pin(s[u]);
-      __builtin_amdgcn_sched_barrier(0);
-      // inter-block part W^T[dv][r] = sum_dk State[dk][dv] X[r][dk], state straight from its registers
+        for (int i = 0; i < 6; i++) sp.step(i);
+        Parts sa = sp.parts();
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        mul32_slots(sa, xa[ks & 1], acc, [&](int i) __attribute__((always_inline)) {
-          if (i == 0) {
-            if (ks + 1 < KS) {
-              xa[(ks + 1) & 1] = read_parts(sX, rowk ^ (16 * (ks + 1)));
-              state_into(ks + 1);
-            } else {
-              yt[0] = read_ycols(0, 0);
-              z_into(0, true);
+        for (int u = 0; u < NQ; u++) pin(s[u]);
+        __builtin_amdgcn_sched_barrier(0);
+        // inter-block part W^T[dv][r] = sum_dk State[dk][dv] X[r][dk], state straight from its registers
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) {
+          mul32_slots(sa, xa[ks & 1], acc, [&](int i) __attribute__((always_inline)) {
+            if (i == 0) {
+              if (ks + 1 < KS) {
+                xa[(ks + 1) & 1] = read_parts(sX, rowk ^ (16 * (ks + 1)));
+                state_into(ks + 1);
+              } else {
+                yt[0] = read_ycols(0, 0);
+                z_into(0, true);
+              }
+            }
+            sp.step(i);
+            if ((ks & 1) && i < 4) {   // both operands of state tile ks / 2 are made
+#pragma unroll
+              for (int v = 0; v < 4; v++) {
+                float y = kv[ks >> 1][4 * i + v] * lamB;
+                pin(y);
+                kv[ks >> 1][4 * i + v] = y;
+              }
+            }
+          });
+          if (ks < NQ) {   // the quarter's mask and decay, to LDS: row r, columns in the order of the intra-block operand
+            const int q = w + NT * ks, cq = q & 1, rq = q >> 1;
+            if (REV ? cq >= rq : cq <= rq) {
+              uint32_t part[3][2];
+#pragma unroll
+              for (int i = 0; i < 2; i++)
+                split2(s[ks][2 * i] * dg[ks][2 * i], s[ks][2 * i + 1] * dg[ks][2 * i + 1], part[0][i], part[1][i], part[2][i]);
+              const int at = (16 * rq + l16) * PROW + 16 * cq + 8 * (g4 & 1) + 4 * (g4 >> 1);
+#pragma unroll
+              for (int k = 0; k < 3; k++) *reinterpret_cast<u32x2*>(&sP[k][at]) = u32x2{part[k][0], part[k][1]};
             }
           }
-          sp.step(i);
-          if ((ks & 1) && i < 4) {   // both operands of state tile ks / 2 are made
+          sa = sp.parts();
+        }
+      } else {
+        yt[0] = read_ycols(0, 0);
+        z_into(0, true);
 #pragma unroll
-            for (int v = 0; v < 4; v++) {
-              float y = kv[ks >> 1][4 * i + v] * lamB;
-              pin(y);
-              kv[ks >> 1][4 * i + v] = y;
+        for (int i = 0; i < 6; i++) sp.step(i);
+      }
+      zd = sp.parts();
+      // state slice <- lambda^B state + Y^T decay(Z)
+#pragma unroll
+      for (int u = 0; u < 2 * NT; u++) {
+        const int t = u % NT;
+        mul32_slots(yt[u & 1], zd, kv[t], [&](int i) __attribute__((always_inline)) {
+          if (i == 0 && u + 1 < 2 * NT) yt[(u + 1) & 1] = read_ycols((u + 1) / NT, (u + 1) % NT);
+          if (u == NT - 1) {
+            if (i == 0) z_into(1, true);
+            sp.step(i);
+          }
+          if constexpr (!STATE_ONLY) {
+            if (u == 0 && i < 4) {   // the carried part takes the decay at this lane's position
+#pragma unroll
+              for (int v = 0; v < 4; v++) {
+                float y = acc[4 * i + v] * inter_scale;
+                pin(y);
+                acc[4 * i + v] = y;
+              }
+            }
+            if (u >= NT && u < NT + 2) {   // Z as it is, for the intra-block product
+              if (i == 0) z_into(u - NT, false);
+              sp.step(i);
             }
           }
         });
-        if (ks < NQ) {   // the quarter's mask and decay, to LDS: row r, columns in the order of the intra-block operand
-          const int q = w + NT * ks, cq = q & 1, rq = q >> 1;
-          if (REV ? cq >= rq : cq <= rq) {
-            uint32_t part[3][2];
-#pragma unroll
-            for (int i = 0; i < 2; i++)
-              split2(s[ks][2 * i] * dg[ks][2 * i], s[ks][2 * i + 1] * dg[ks][2 * i + 1], part[0][i], part[1][i], part[2][i]);
-            const int at = (16 * rq + l16) * PROW + 16 * cq + 8 * (g4 & 1) + 4 * (g4 >> 1);
-#pragma unroll
-            for (int k = 0; k < 3; k++) *reinterpret_cast<u32x2*>(&sP[k][at]) = u32x2{part[k][0], part[k][1]};
-          }
-        }
-        sa = sp.parts();
+        if (u == NT - 1) zd = sp.parts();
+        if (!STATE_ONLY && u >= NT && u < NT + 2) zf[u - NT] = sp.parts();
       }
-    } else {
-      yt[0] = read_ycols(0, 0);
-      z_into(0, true);
+      lds_barrier();   // every wave has read this block's planes, the score tile is complete
+      if (has_next) write_planes();
+      if constexpr (!STATE_ONLY) {
+        // intra-block part Z^T P^T
 #pragma unroll
-      for (int i = 0; i < 6; i++) sp.step(i);
-    }
-    zd = sp.parts();
-    // state slice <- lambda^B state + Y^T decay(Z)
+        for (int q = 0; q < 2; q++) {
+          Parts pd;
 #pragma unroll
-    for (int u = 0; u < 2 * NT; u++) {
-      const int t = u % NT;
-      mul32_slots(yt[u & 1], zd, kv[t], [&](int i) __attribute__((always_inline)) {
-        if (i == 0 && u + 1 < 2 * NT) yt[(u + 1) & 1] = read_ycols((u + 1) / NT, (u + 1) % NT);
-        if (u == NT - 1) {
-          if (i == 0) z_into(1, true);
-          sp.step(i);
+          for (int k = 0; k < 3; k++) pd.p[k] = *reinterpret_cast<const b8*>(&sP[k][l32 * PROW + 16 * q + 8 * hh]);
+          acc = mul32(zf[q], pd, acc);
         }
-        if constexpr (!STATE_ONLY) {
-          if (u == 0 && i < 4) {   // the carried part takes the decay at this lane's position
 #pragma unroll
-            for (int v = 0; v < 4; v++) {
-              float y = acc[4 * i + v] * inter_scale;
-              pin(y);
-              acc[4 * i + v] = y;
-            }
-          }
-          if (u >= NT && u < NT + 2) {   // Z as it is, for the intra-block product
-            if (i == 0) z_into(u - NT, false);
-            sp.step(i);
-          }
+        for (int v = 0; v < 16; v++) {
+          worst = __builtin_elementwise_maximum(worst, __builtin_fabsf(acc[v]));
+          acc[v] *= 1.f / (kUp * kUp * kUp);
         }
-      });
-      if (u == NT - 1) zd = sp.parts();
-      if (!STATE_ONLY && u >= NT && u < NT + 2) zf[u - NT] = sp.parts();
-    }
-    lds_barrier();   // every wave has read this block's planes, the score tile is complete
-    if (has_next) write_planes();
-    if constexpr (!STATE_ONLY) {
-      // intra-block part Z^T P^T
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        Parts pd;
-#pragma unroll
-        for (int k = 0; k < 3; k++) pd.p[k] = *reinterpret_cast<const b8*>(&sP[k][l32 * PROW + 16 * q + 8 * hh]);
-        acc = mul32(zf[q], pd, acc);
-      }
-      // output: lane = position l32, elements v = 4 g .. 4 g + 3 are value features 32 dvt + 8 g + 4 hh .. + 3
-      const int pos = blk * B + l32;
-      auto store_rows = [&]() __attribute__((always_inline)) {
-        const uint32_t off = ((uint32_t)pos * stride_n + (uint32_t)(32 * dvt + 4 * hh)) * 4u;
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-          const i32x4 o4 = {__float_as_int(acc[4 * g]), __float_as_int(acc[4 * g + 1]), __float_as_int(acc[4 * g + 2]),
-                            __float_as_int(acc[4 * g + 3])};
-          __builtin_amdgcn_raw_buffer_store_b128(o4, gw, off + 32u * g, 0, 0);
-        }
-      };
-      if (p.rstd != nullptr) {   // Norm epilogue (eq. (2)); the sums meet under the block's second barrier
-        norm_publish<NT>(acc, sRed, l32, hh, dvt);
-        lds_barrier();
-        const float r = norm_collect<NT>(sRed, l32, 1.f / (float)D, p.eps);
-#pragma unroll
-        for (int v = 0; v < 16; v++) acc[v] *= r;
-        if (dvt == 0 && hh == 0 && pos < n) p.rstd[rstd_chain_offset(p, bi, hi) + pos] = r;
-        store_rows();
+        good += worst < __builtin_inff() ? 1 : 0;
+        emit(acc, blk, true);
       } else {
-        store_rows();
         lds_barrier();
       }
-    } else {
-      lds_barrier();
     }
+
+    // Everything that left the range of the scaled parts, Inf and NaN among the inputs included, has made an output or an
+    // element of the state infinite or NaN by now.  Such a chunk is walked again from its start, in fp32 throughout.
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) worst = __builtin_elementwise_maximum(worst, __builtin_fabsf(kv[t][v]));
+    if (!(worst < __builtin_inff())) atomicMin(&lds.good, good);
+    lds_barrier();
+    const int first = __builtin_amdgcn_readfirstlane(lds.good);
+    if (first <= nblk) return first;
+  } else {
+    float* const fY = reinterpret_cast<float*>(&sY[0][0]);
+    float* const fX = STATE_ONLY ? fY : reinterpret_cast<float*>(&sX[0][0]);
+    static_assert(sizeof(lds.y) >= sizeof(float) * TILE && (STATE_ONLY || sizeof(lds.x) >= sizeof(float) * TILE),
+                  "fp32 tiles in the planes' place");
+    // feature f of tile row r: 16-byte pieces swizzled by r % 16
+    auto at = [](int r, int f) { return r * D + ((((f >> 2) ^ (r & 15)) << 2) | (f & 3)); };
+    lds_barrier();   // the weights are written
+#pragma unroll 1
+    for (int it = 0; it < nblk; it++) {
+      const int blk = block_at(it);
+      // made from the lane number in every block: kept over the loop the addresses and weights would not fit the registers
+      int lo = l;
+      asm volatile("" : "+v"(lo));
+      const int row = lo & 31, half = lo >> 5;
+      const int col = (row & 19) | ((row & 4) << 1) | ((row & 8) >> 1);   // feature of state row `row`: bits 2 and 3 exchanged
+      load_block(blk);   // (the block before ended with a barrier: its tiles are free)
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 8; j += 4) {
+          *reinterpret_cast<f32x4*>(&fY[at(r0 + 16 * i, 8 * ch + j)]) = f32x4{py[i][j], py[i][j + 1], py[i][j + 2], py[i][j + 3]};
+          if (!STATE_ONLY)
+            *reinterpret_cast<f32x4*>(&fX[at(r0 + 16 * i, 8 * ch + j)]) = f32x4{px[i][j], px[i][j + 1], px[i][j + 2], px[i][j + 3]};
+        }
+      lds_barrier();
+      f32x16 acc = zero16();
+      if constexpr (!STATE_ONLY) {
+        f32x16 st = zero16();
+#pragma unroll
+        for (int t = 0; t < NT; t++)   // inter-block part, two key features per instruction: state register v's
+#pragma unroll
+          for (int v = 0; v < 16; v += 4) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(&fX[at(row, 32 * t + 16 * (v >> 3) + 8 * half + (v & 7))]);
+#pragma unroll
+            for (int i = 0; i < 4; i++) acc = mfma_f32(kv[t][v + i], x[i], acc);
+            __builtin_amdgcn_sched_barrier(0);   // (few operands in flight: there are no registers for more)
+          }
+#pragma unroll
+        for (int j = 0; j < D / 8; j++) {   // scores S^T[c][r]
+          const f32x4 x = *reinterpret_cast<const f32x4*>(&fX[at(row, 8 * j + 4 * half)]);
+          const f32x4 y = *reinterpret_cast<const f32x4*>(&fY[at(row, 8 * j + 4 * half)]);
+#pragma unroll
+          for (int i = 0; i < 4; i++) st = mfma_f32(y[i], x[i], st);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[v] *= inter_scale;
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const int c = 8 * (v >> 2) + 4 * half + (v & 3), e = REV ? c - row : row - c;
+          acc = mfma_f32(pz[v], st[v] * (e >= 0 ? lam.pow(e) : 0.f), acc);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; t++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) kv[t][v] *= lamB;
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        const int c = 8 * (v >> 2) + 4 * half + (v & 3);
+        const float zw = pz[v] * sWz[c];
+#pragma unroll
+        for (int t = 0; t < NT; t++) kv[t] = mfma_f32(fY[at(c, 32 * t + col)], zw, kv[t]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (STATE_ONLY) lds_barrier();
+      else emit(acc, blk, it >= from);
+    }
+  }
+
+  return -1;
+}
+
+// Scan kernel (STATE_ONLY = false) and chunk-state pre-pass (STATE_ONLY = true: the local state of the chunk is written to
+// p.states).  D / 32 waves.
+template <int D, bool REV, bool STATE_ONLY>
+__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) void scan_f32_kernel(ScanParams p) {
+  constexpr int NT = D / 32;
+  __shared__ Lds<D, STATE_ONLY> lds;
+  Place at;
+  at.which = 0;
+  int wg = (int)blockIdx.x;
+  if (!STATE_ONLY && p.nscan == 2) {   // two scans that read the same tiles: eight workgroups apart, on one XCD
+    if (((gridDim.x >> 1) & 7) == 0) {
+      at.which = (wg >> 3) & 1;
+      wg = ((wg >> 4) << 3) | (wg & 7);
+    } else {
+      at.which = wg & 1;
+      wg >>= 1;
+    }
+  }
+  at.chain = wg / p.nchunks;
+  at.chunk = wg % p.nchunks;
+  at.bi = at.chain / p.heads;
+  at.hi = at.chain % p.heads;
+  chain_extent(p, at.bi, at.hi, at.base, at.n);
+  const int first = at.chunk * p.chunk_tokens;
+  if (!STATE_ONLY && first >= at.n) return;
+  // pre-pass: the chunk a scan of THIS chain passes last has no successor (packed batch: chains of different lengths)
+  if (STATE_ONLY && (REV ? (at.chunk == 0) : (first + p.chunk_tokens >= at.n))) return;
+
+  f32x16 kv[NT];
+  float down = 1.f / (kUp * kUp);
+  const int from = walk<D, REV, STATE_ONLY, false>(p, lds, at, kv);
+  if (from >= 0) {
+    walk<D, REV, STATE_ONLY, true>(p, lds, at, kv, from);
+    down = 1.f;
   }
 
   // the chunk's local state (pre-pass) or the state after the chain's last block (on request)
   float* gf = nullptr;
   bool trf = false;
   if (STATE_ONLY) {
-    gf = p.states + ((int64_t)chain * p.nchunks + chunk) * (D * D);
-  } else if ((which ? p.fin[1] : p.fin[0]) != nullptr && (REV ? chunk == 0 : chunk == p.nchunks - 1)) {
-    gf = (which ? p.fin[1] : p.fin[0]) + (int64_t)chain * (D * D);
-    trf = (p.fin_transposed >> which) & 1;
+    gf = p.states + ((int64_t)at.chain * p.nchunks + at.chunk) * (D * D);
+  } else if ((at.which ? p.fin[1] : p.fin[0]) != nullptr && (REV ? at.chunk == 0 : at.chunk == p.nchunks - 1)) {
+    gf = (at.which ? p.fin[1] : p.fin[0]) + (int64_t)at.chain * (D * D);
+    trf = (p.fin_transposed >> at.which) & 1;
   }
   if (gf != nullptr) {
+    const int l = (int)threadIdx.x & 63, dvt = (int)threadIdx.x >> 6;
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) gf[state_index_f32<D>(dvt, l32, hh, t, v, trf)] = kv[t][v];
+      for (int v = 0; v < 16; v++) gf[state_index_f32<D>(dvt, l & 31, l >> 5, t, v, trf)] = kv[t][v] * down;
   }
 }
 

@@ -599,8 +599,8 @@ def test_fp32_products_keep_fp32_accuracy_whatever_the_scale_of_a_feature(n, chu
     """The fp32 kernels multiply on the bf16 matrix instructions, every float split into three bf16 parts.  Features
     scaled by powers of two from 2^-20 to 2^20 (key-like and query-like inversely, so that every term counts; value-like
     each its own): every output column stays within 1e-6 of its own size, which one part less (2^-17) would miss by a
-    factor of ten and a shared exponent by far more.  Bound: products exact to 2^-25, fp32 sums of at most 290 + 128 terms
-    and decay weights good to a few 2^-24."""
+    factor of ten and a shared exponent by far more.  Bound: products within 2^-24 (rms 2^-27), fp32 sums of at most
+    290 + 128 terms and decay weights good to a few 2^-24."""
     g = torch.Generator(device="cpu")
     g.manual_seed(n + d)
     b, H = 1, 3
@@ -623,8 +623,117 @@ def test_fp32_products_keep_fp32_accuracy_whatever_the_scale_of_a_feature(n, chu
         assert err.max() <= 1e-6, (name, err.max())
 
 
+def fp32_case(n, d, exps=(0, 0, 0, 0), seed=11):
+    """q, k, v, d_o of N(0, 1) times 2^e each, three heads."""
+    g = torch.Generator(device="cpu")
+    g.manual_seed(seed + n + d)
+    return [torch.randn((1, 3, n, d), generator=g) * 2.0 ** e for e in exps] + [torch.tensor([0.3, 0.95, 1.0])]
+
+
+def fp32_run(x):
+    q, k, v, do, lam = (t.to(DEV) for t in x)
+    out = (binding.la2_fwd(q, k, v, lam),) + tuple(binding.la2_bwd(q, k, v, do, lam))
+    torch.cuda.synchronize()
+    return out
+
+
+def fp32_refs(x):
+    q, k, v, do, lam = (to64(t) for t in x)
+    return (oracle.fwd_direct(q, k, v, lam),) + tuple(oracle.bwd_direct(q, k, v, do, lam))
+
+
+@pytest.mark.parametrize("exps", [(0, -116, 0, 0), (116, -116, 0, 0), (0, 0, -116, 100), (-130, 20, 0, 116), (0, -58, -58, 0),
+                                  (-60, -60, 90, 0), (60, 60, -60, 0), (116, 0, -50, -50), (0, 115, 4, -115), (118, -120, 0, 0),
+                                  (40, 40, 40, 0)])
+@pytest.mark.parametrize("d,chunk", [(64, 0), (128, 0), (64, 64), (128, 96)])
+def test_fp32_accuracy_over_the_range_of_the_type(d, chunk, exps):
+    """Inputs, scores and states from 2^-130 to 2^122: every output is as accurate as on ordinary data.  (The bf16 parts of
+    a value below 2^-110 would leave bf16's range, those of one above 3.39e38 as well.  No combination has scores or states
+    that fp32 itself rounds to its subnormals.)"""
+    n = 200
+    x = fp32_case(n, d, exps)
+    binding.la2_set_chunk_tokens(chunk)
+    got, refs = fp32_run(x), fp32_refs(x)
+    for name, y, r in zip(("o", "dq", "dk", "dv"), got, refs):
+        big = np.abs(r).max()
+        if big > 3e38 or big < 1e-36:     # beyond the type, or rounded to its subnormals
+            continue
+        assert np.isfinite(to64(y)).all(), (name, big)
+        err = np.sqrt(((to64(y) - r) ** 2).sum() / (r ** 2).sum())
+        assert err <= 1e-6, (name, err, big)
+
+
+@pytest.mark.parametrize("d,chunk", [(64, 0), (128, 0), (64, 64), (128, 96)])
+@pytest.mark.parametrize("which", [0, 1, 2, 3])
+def test_fp32_one_largest_value_is_a_finite_number(which, d, chunk):
+    """A value next to fp32's largest (rounded to bf16 it is Inf) among ordinary ones: every result is finite and within
+    264 roundings (d + n products and sums) of the sum of the magnitudes it is made of."""
+    n, at, bound = 200, 70, 264 * 2.0 ** -24
+    x = fp32_case(n, d, (-6, -6, -6, -6), seed=which)
+    for value in (3.4028234e38, -3.4e38):
+        x[which][0, 1, at, 5] = value
+        binding.la2_set_chunk_tokens(chunk)
+        got, refs, sizes = fp32_run(x), fp32_refs(x), fp32_refs([t.abs() for t in x])
+        for name, y, r, size in zip(("o", "dq", "dk", "dv"), got, refs, sizes):
+            assert size.max() < 3e38
+            assert np.isfinite(to64(y)).all(), name
+            assert (np.abs(to64(y) - r) <= bound * size).all(), (name, (np.abs(to64(y) - r) / size).max())
+
+
+@pytest.mark.parametrize("d,n", [(64, 200), (128, 200), (64, 192), (128, 193)])
+def test_fp32_chunks_that_are_walked_again_keep_states_and_norm(d, n):
+    """A query value that overflows the split operands sends its chunk through the fp32 matrix instructions: start and
+    final states (in place too), their gradients, the Norm epilogue and every other row as without it."""
+    x = fp32_case(n, d, seed=5)
+    gen = torch.Generator(device="cpu")
+    gen.manual_seed(d + n)
+    kv0, dkv = (torch.randn((1, 3, d, d), generator=gen) for _ in range(2))
+    q, k, v, do, lam = (t.to(DEV) for t in x)
+    odd = q.clone()
+    odd[0, 1, 70, 5] = 1e36
+    for chunk in (0, 64):
+        binding.la2_set_chunk_tokens(chunk)
+        outs = []
+        for y in (q, odd):
+            o, kvf = binding.la2_fwd_state(y, k, v, lam, kv_init=kv0.to(DEV))
+            grads = binding.la2_bwd_state(q, k, v, torch.where(y == 1e36, y, do), lam, kv_init=kv0.to(DEV), d_kv_final=dkv.to(DEV))
+            on, rstd = binding.la2_fwd_norm(y, k, v, lam, 1e-6)
+            kept = kv0.to(DEV)
+            om = binding.la2_decode_multi(y, k, v, lam, kept)
+            torch.cuda.synchronize()
+            outs.append([to64(z) for z in (o, grads[0], on, rstd, om, kvf, kept)])
+        for i, (a, b) in enumerate(zip(*outs)):
+            assert np.abs(a).max() < 1e6
+            if i < 5:      # all rows but the one that the value belongs to
+                rows = np.delete(np.arange(n), 70)
+                assert np.abs(b[0, 1, 70]).max() > 1e30 or i == 3 or i == 2
+                a, b = a[:, :, rows], b[:, :, rows]
+            # (Norm: a row's r takes the relative error of its norm, up to 264 roundings where its terms cancel)
+            assert np.abs(a - b).max() <= (264 * 2.0 ** -24 if i in (2, 3) else 2e-6) * np.abs(a).max(), (chunk, i)
+
+
 @pytest.mark.parametrize("d", [64, 128])
-def test_fp32_a_non_finite_value_reaches_later_positions_only(d):
+@pytest.mark.parametrize("chunk", [0, 64])
+def test_fp32_infinite_values_stay_infinite(chunk, d):
+    """One infinite key feature: the state row it enters is infinite, and every later block's output is the infinity of
+    the sign of q_t[i] v_s[j], not NaN; dv's infinities towards earlier positions come from an infinite query."""
+    n, at = 200, 70
+    x = fp32_case(n, d, (-3, -3, -3, -3))
+    binding.la2_set_chunk_tokens(chunk)
+    q, k, v, do, lam = x
+    bad = [q, k.clone(), v, do, lam]
+    bad[1][0, 1, at, 5] = float("inf")
+    o = fp32_run(bad)[0].cpu()
+    assert torch.equal(o[0, 1, 96:], torch.sign(q[0, 1, 96:, 5, None] * v[0, 1, at]) * float("inf"))
+    bad = [q.clone(), k, v, do, lam]
+    bad[0][0, 1, at, 5] = float("-inf")
+    dv = fp32_run(bad)[3].cpu()
+    assert torch.equal(dv[0, 1, :64], torch.sign(k[0, 1, :64, 5, None] * do[0, 1, at]) * float("-inf"))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_a_non_finite_value_reaches_its_block_and_later_positions_only(d):
+    """(Positions 64 .. 69 share the block of 32 with it: their masked products are 0 times it, which is NaN.)"""
     n, at = 130, 70   # block 64 .. 95 holds it
     g = torch.Generator(device="cpu")
     g.manual_seed(d)
