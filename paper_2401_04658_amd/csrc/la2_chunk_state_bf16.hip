@@ -128,13 +128,15 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
 // The chunk processed first starts from init (element e read at its transposed place if init_tr) or 0.
 // The carried state decays by lambda^(chunk length): all chunks are chunk_tokens long except the last
 // one of the sequence, which a reverse scan passes first.
-// A thread owns four consecutive elements of the d x d state.  With up to MAXC chunks it fetches all local
-// states first (independent loads, all in flight together) and then runs the recurrence on registers; the
-// launch sits between two kernels that wait for it, so its latency is what counts, not its bytes.
+// A thread owns four consecutive elements of the d x d state.  It fetches the local states of kScanMaxChunks chunks
+// (independent loads, all in flight together), runs the recurrence on registers and goes on to the next ones; the
+// launch sits between two kernels that wait for it, so its latency is what counts, not its bytes.  (One chunk at a time
+// beyond the first 32 it paid a round trip to memory per chunk: 1 chain of 65,536 positions, d 128, 256 chunks, forward +
+// backward 0.313 -> 0.173 ms.)
 constexpr int kScanMaxChunks = 32;
 // wg_map != nullptr (packed batch with a compact grid, see ScanParams): a "unit" is a sequence of long_list and a
 // head; the chain's states are `heads` slots apart.
-__global__ void state_scan_kernel(float* states, const float* lambda, int heads, int nchunks, int chunk_tokens,
+__global__ __launch_bounds__(256) void state_scan_kernel(float* states, const float* lambda, int heads, int nchunks, int chunk_tokens,
                                   int dd, int reverse, const float* init, int init_tr, int d, int n,
                                   const int32_t* cu_seqlens, const int4* wg_map, const int32_t* long_list,
                                   int even_chunks) {
@@ -185,31 +187,23 @@ __global__ void state_scan_kernel(float* states, const float* lambda, int heads,
       g = *reinterpret_cast<const f32x4*>(gi + e);
     }
   }
-  if (nch <= kScanMaxChunks) {
+#pragma unroll 1
+  for (int i0 = 0; i0 < nch; i0 += kScanMaxChunks) {
     f32x4 loc[kScanMaxChunks];
 #pragma unroll
     for (int i = 0; i < kScanMaxChunks; i++) {
-      const int j = reverse ? nch - 1 - i : i;
-      if (i < nch - 1) loc[i] = s[(int64_t)j * step];   // the chunk processed last has no successor: not read
+      const int j = reverse ? nch - 1 - (i0 + i) : i0 + i;
+      if (i0 + i < nch - 1) loc[i] = s[(int64_t)j * step];   // the chunk processed last has no successor: not read
     }
 #pragma unroll
     for (int i = 0; i < kScanMaxChunks; i++) {
-      if (i < nch) {
-        const int j = reverse ? nch - 1 - i : i;
+      if (i0 + i < nch) {
+        const int j = reverse ? nch - 1 - (i0 + i) : i0 + i;
         s[(int64_t)j * step] = g;
         const float decay = (j == nch - 1) ? lamLast : lamFull;
-        if (i < nch - 1) g = decay * g + loc[i];
+        if (i0 + i < nch - 1) g = decay * g + loc[i];
       }
     }
-    return;
-  }
-  for (int i = 0; i < nch; i++) {
-    const int j = reverse ? nch - 1 - i : i;
-    const bool last = (i == nch - 1);
-    f32x4 loc = {0.f, 0.f, 0.f, 0.f};
-    if (!last) loc = s[(int64_t)j * step];
-    s[(int64_t)j * step] = g;
-    g = (j == nch - 1 ? lamLast : lamFull) * g + loc;
   }
 }
 

@@ -113,6 +113,21 @@ def test_plans_of_few_chunks_form_their_start_states_in_the_scan(nchunks, d, dty
         check_segment(t, dtype, tag + " start state only", use_final=False)
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.float16, 128), (torch.float32, 64), (torch.bfloat16, 96),
+                                     (torch.bfloat16, 256)])
+@pytest.mark.parametrize("nchunks", [32, 33, 64, 65, 71])
+def test_scan_over_more_chunks_than_it_holds_at_once(nchunks, dtype, d):
+    """The scan over the chunk states takes 32 of them at a time: counts on both sides of one and two such runs, a last
+    chunk that is whole and one that ends inside a block, with all states and with none."""
+    chunk = 64
+    for n in (nchunks * chunk, nchunks * chunk - 45):
+        binding.la2_set_chunk_tokens(chunk)
+        t = inputs(1, 2, n, d, dtype, seed=700 + nchunks + d + n, lam=[0.99, 0.9995])
+        assert binding.la2_chunk_plan(t["q"]) == (nchunks, chunk)
+        check_segment(t, dtype, "%d chunks n%d d%d %s" % (nchunks, n, d, dtype))
+        check_segment(t, dtype, "%d chunks n%d d%d %s, no states" % (nchunks, n, d, dtype), use_init=False, use_final=False)
+
+
 def test_fp32_chunked_segment():
     binding.la2_set_chunk_tokens(128)
     t = inputs(1, 2, 384, 128, torch.float32, seed=777)

@@ -111,6 +111,12 @@ def test_unequal_lengths_sorted_and_cut_evenly(kind, dtype, d):
     check_packed(lengths, H, d, dtype, seed=880 + d, lam=[0.6, 0.9, 0.99, 0.997] * (H // 4) if H >= 4 else [0.8, 0.997])
 
 
+def test_a_sequence_of_more_chunks_than_the_state_scan_holds_at_once():
+    """Few chains, pieces of 256 positions: 36, 33 and 32 chunks in one batch, the scan over their states takes 32 at a
+    time."""
+    check_packed([9000, 300, 0, 8200, 8192], 1, 64, torch.bfloat16, seed=897, lam=[0.9995])
+
+
 def test_an_uncut_batch_needs_no_workspace():
     """The map that sorts an uncut batch lives in the workspace; without one the batch runs in the order of the
     sequences, same results bit for bit."""
