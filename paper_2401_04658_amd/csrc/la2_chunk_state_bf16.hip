@@ -35,15 +35,15 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
 
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l32 = l & 31, hh = l >> 5;
   const int dvt = w % NT, kt0 = (w / NT) * KT;
-  int bi, hi, chunk, slot_stride, map_nch;
+  int bi, hi, chunk, slot_stride, chunk_tokens;
   int64_t slot;
-  if (!place_workgroup(p, (int)blockIdx.x, bi, hi, chunk, slot, slot_stride, map_nch)) return;
+  if (!place_workgroup(p, (int)blockIdx.x, bi, hi, chunk, slot, slot_stride, chunk_tokens)) return;
   int64_t base;
   int n;
   chain_extent(p, bi, hi, base, n);
   const float l2 = log2f(p.lambda[hi]);
   const int nblocks = (n + kB - 1) / kB;
-  const int cb = chunk_length(p, n, map_nch) / kB;
+  const int cb = chunk_tokens / kB;
   const int blk_lo = chunk * cb;
   const int blk_hi = min(blk_lo + cb, nblocks);
   const int nblk = blk_hi - blk_lo;
@@ -138,8 +138,7 @@ constexpr int kScanMaxChunks = 32;
 // head; the chain's states are `heads` slots apart.
 __global__ __launch_bounds__(256) void state_scan_kernel(float* states, const float* lambda, int heads, int nchunks, int chunk_tokens,
                                   int dd, int reverse, const float* init, int init_tr, int d, int n,
-                                  const int32_t* cu_seqlens, const int4* wg_map, const int32_t* long_list,
-                                  int even_chunks) {
+                                  const int32_t* cu_seqlens, const int4* wg_map, const int32_t* long_list) {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   const int dd4 = dd >> 2;
   const int per_chain = (dd4 + (int)blockDim.x - 1) / (int)blockDim.x;   // workgroups per chain
@@ -148,13 +147,12 @@ __global__ __launch_bounds__(256) void state_scan_kernel(float* states, const fl
   if (e4 >= dd4) return;
   int bi, hi;
   int64_t first_slot, stride;   // the chain's chunk-0 state slot, slots between its consecutive chunks
-  int map_nch = 1;
   if (wg_map != nullptr) {
     const int pair = long_list[unit / heads];
     if (pair < 0) return;
     const int4 m = wg_map[pair];
     bi = m.x;
-    map_nch = m.w;
+    chunk_tokens = m.w;
     hi = unit % heads;
     first_slot = (int64_t)m.z * heads + hi;
     stride = heads;
@@ -166,7 +164,6 @@ __global__ __launch_bounds__(256) void state_scan_kernel(float* states, const fl
   }
   const int chain = bi * heads + hi;
   if (cu_seqlens != nullptr) n = cu_seqlens[bi + 1] - cu_seqlens[bi];   // this sequence's length
-  if (even_chunks) chunk_tokens = even_chunk_length(n, map_nch);
   int nch = (n + chunk_tokens - 1) / chunk_tokens;   // chunks this chain really has (<= nchunks)
   // (a packed sequence longer than the launch was planned for is the caller's error; it must not reach past the
   // chain's slots.  With a pair map the sequence's slots were counted from this same length.)
@@ -209,7 +206,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(float* states, const fl
 
 // Packed batch in sequence chunks: the (sequence, chunk) pairs for the compact launch grid, the longest pairs first.
 // One workgroup walks the sequences 256 at a time with a running count of pairs and of state slots.
-//   map[pair] = {sequence, chunk, first state slot of the sequence (-1: single chunk, no slots), its chunk count}
+//   map[pair] = {sequence, chunk, first state slot of the sequence (-1: single chunk, no slots), positions per chunk}
 // Entries past the last pair, up to npairs, get sequence -1.  A batch whose lengths sum to more than the host was
 // told would need more entries than the map has, or more state slots than the workspace (nslots per head): such
 // sequences are dropped (nothing is written past the end of either; they are not computed).
@@ -220,82 +217,96 @@ __global__ __launch_bounds__(256) void state_scan_kernel(float* states, const fl
 // by length, in kLengthClasses classes, the short pairs fill the gaps that the long ones leave.  Forward + backward,
 // bf16, 65,536 positions, H 16, d 128, the same cut in the order of the sequences and sorted: 42 sequences of 65 to
 // 8192 positions 1.14 -> 1.06 ms; 55 of up to 4096, uncut, 0.99 -> 0.88 ms.
+//
+// Cost: one workgroup between the call and its first scan, so latency: one sequence per thread and round, no division for a
+// sequence that is not cut, and a batch of one round is counted once and placed from registers.  2, 42, 923 and 3000
+// sequences: 3.7, 5.1, 6.4, 17 us (256 at a time, counted twice, 4.7, 6.2, 11.7, 31).
 constexpr int kLengthClasses = 64;
-// class of a pair of `len` positions, at most c: 0 the longest
-__device__ __forceinline__ int length_class(int len, int c) {
-  return (kLengthClasses - 1) - (int)(((int64_t)min(len, c) * (kLengthClasses - 1)) / c);
-}
-__global__ __launch_bounds__(256) void varlen_map_kernel(const int32_t* cu_seqlens, int batch, int chunk_tokens, int npairs,
-                                                         int4* map, int nlong, int32_t* long_list, int nslots,
-                                                         int even_chunks) {
-  __shared__ int wave_sum[4][3];
+__global__ __launch_bounds__(1024) void varlen_map_kernel(const int32_t* cu_seqlens, int batch, int chunk_tokens, int npairs,
+                                                          int4* map, int nlong, int32_t* long_list, int nslots,
+                                                          int even_chunks) {
+  __shared__ int wave_sum[16][3];
   __shared__ int at[kLengthClasses];   // first pass: pairs of every class; second: where the class's next pair goes
-  const int t = (int)threadIdx.x, l = t & 63, w = t >> 6;
+  const int t = (int)threadIdx.x, l = t & 63, w = t >> 6, round = (int)blockDim.x, nw = round >> 6;
   if (t < kLengthClasses) at[t] = 0;
-  int used = 0;   // pairs of the sequences that are computed
-  for (int pass = 0; pass < 2; pass++) {
-    int base_pairs = 0, base_slots = 0, base_long = 0;
+  // class of a pair of `len` positions, at most chunk_tokens: 0 the longest
+  const float per_class = (float)(kLengthClasses - 1) / (float)chunk_tokens;
+  auto class_of = [&](int len) {
+    return kLengthClasses - 1 - min((int)((float)min(len, chunk_tokens) * per_class), kLengthClasses - 1);
+  };
+  int len = 0, nch = 0, piece = chunk_tokens;       // this thread's sequence: positions, chunks, positions of all but the last
+  int first_slot = 0, place = 0;                    // ... its first state slot, its place in long_list
+  bool fits = false;
+  int base_pairs = 0, base_slots = 0, base_long = 0;   // of the rounds before
+  auto count_round = [&](int b) __attribute__((always_inline)) {
+    len = nch = 0;
+    // (a sequence without positions keeps one pair: its workgroups pass a start state on where one is handed over)
+    if (b < batch) {
+      len = max(cu_seqlens[b + 1] - cu_seqlens[b], 0);
+      nch = len <= chunk_tokens ? 1
+            : even_chunks       ? even_chunk_count(len, chunk_tokens)
+                                : (int)(((uint32_t)len + (uint32_t)chunk_tokens - 1u) / (uint32_t)chunk_tokens);
+    }
+    const int slots = nch > 1 ? nch : 0;
+    int ip = nch, is = slots, il = slots ? 1 : 0;   // inclusive scan of the three counts
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int yp = __shfl_up(ip, off), ys = __shfl_up(is, off), yl = __shfl_up(il, off);
+      if (l >= off) { ip += yp; is += ys; il += yl; }
+    }
+    if (l == 63) { wave_sum[w][0] = ip; wave_sum[w][1] = is; wave_sum[w][2] = il; }
     __syncthreads();
-    if (pass == 1) {
-      if (w == 0) {   // counts -> first places, one class per lane
-        const int own = at[l];
-        int sum = own;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const int y = __shfl_up(sum, off);
-          if (l >= off) sum += y;
-        }
-        at[l] = sum - own;
-        if (l == 63) wave_sum[0][0] = sum;
-      }
-      __syncthreads();
-      used = wave_sum[0][0];
-      __syncthreads();
+    ip += base_pairs;
+    is += base_slots;
+    il += base_long;
+    for (int i = 0; i < nw; i++) {
+      const int sp = wave_sum[i][0], ss = wave_sum[i][1], sl = wave_sum[i][2];
+      if (i < w) { ip += sp; is += ss; il += sl; }
+      base_pairs += sp; base_slots += ss; base_long += sl;
     }
-    for (int b0 = 0; b0 < batch; b0 += 256) {
-      const int b = b0 + t;
-      int len = 0, nch = 0;
-      // (a sequence without positions keeps one pair: its workgroups pass a start state on where one is handed over)
-      if (b < batch) {
-        len = cu_seqlens[b + 1] - cu_seqlens[b];
-        nch = even_chunks ? even_chunk_count(max(len, 0), chunk_tokens) : max(1, (len + chunk_tokens - 1) / chunk_tokens);
-      }
-      const int slots = nch > 1 ? nch : 0;
-      int ip = nch, is = slots, il = slots ? 1 : 0;   // inclusive scan of the three counts
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int yp = __shfl_up(ip, off), ys = __shfl_up(is, off), yl = __shfl_up(il, off);
-        if (l >= off) { ip += yp; is += ys; il += yl; }
-      }
-      if (l == 63) { wave_sum[w][0] = ip; wave_sum[w][1] = is; wave_sum[w][2] = il; }
-      __syncthreads();
-      for (int i = 0; i < w; i++) { ip += wave_sum[i][0]; is += wave_sum[i][1]; il += wave_sum[i][2]; }
-      const int first_slot = base_slots + is - slots, place = base_long + il - 1;
-      const bool fits = base_pairs + ip <= npairs && (!slots || first_slot + slots <= nslots);
-      for (int i = 0; i < 4; i++) { base_pairs += wave_sum[i][0]; base_slots += wave_sum[i][1]; base_long += wave_sum[i][2]; }
-      if (b < batch && fits) {
-        // all chunks of a sequence but its last have one length
-        const int piece = even_chunks ? even_chunk_length(max(len, 0), nch) : chunk_tokens;
-        const int whole = length_class(piece, chunk_tokens);
-        const int last = length_class(max(0, len - (nch - 1) * piece), chunk_tokens);
-        if (pass == 0) {
-          if (nch > 1) atomicAdd(&at[whole], nch - 1);
-          atomicAdd(&at[last], 1);
-        } else {
-          const int first = nch > 1 ? atomicAdd(&at[whole], nch - 1) : 0;
-          for (int j = 0; j < nch - 1; j++) map[first + j] = make_int4(b, j, first_slot, nch);
-          map[atomicAdd(&at[last], 1)] = make_int4(b, nch - 1, slots ? first_slot : -1, nch);
-          if (slots && place < nlong) long_list[place] = first;
-        }
-      } else if (pass == 1 && b < batch && slots && place < nlong) {
-        long_list[place] = -1;
-      }
-      __syncthreads();
+    __syncthreads();
+    first_slot = is - slots;
+    place = il - 1;
+    fits = b < batch && ip <= npairs && (nch <= 1 || is <= nslots);
+    if (even_chunks && nch > 1) piece = even_chunk_length(len, nch);
+  };
+  __syncthreads();
+  for (int b0 = 0; b0 < batch; b0 += round) {
+    count_round(b0 + t);
+    if (fits) {
+      if (nch > 1) atomicAdd(&at[class_of(piece)], nch - 1);
+      atomicAdd(&at[class_of(len - (nch - 1) * piece)], 1);
     }
-    if (pass == 1)
-      for (int i = base_long + t; i < nlong; i += 256) long_list[i] = -1;
   }
-  for (int i = used + t; i < npairs; i += 256) map[i] = make_int4(-1, 0, -1, 0);
+  __syncthreads();
+  if (w == 0) {   // counts -> first places, one class per lane
+    const int own = at[l];
+    int sum = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(sum, off);
+      if (l >= off) sum += y;
+    }
+    at[l] = sum - own;
+    if (l == 63) wave_sum[0][0] = sum;
+  }
+  __syncthreads();
+  const int used = wave_sum[0][0], all_long = base_long;   // pairs of the sequences that are computed; sequences with slots
+  __syncthreads();
+  base_pairs = base_slots = base_long = 0;
+  for (int b0 = 0; b0 < batch; b0 += round) {
+    if (batch > round) count_round(b0 + t);
+    if (fits) {
+      const int first = nch > 1 ? atomicAdd(&at[class_of(piece)], nch - 1) : 0;
+      for (int j = 0; j < nch - 1; j++) map[first + j] = make_int4(b0 + t, j, first_slot, piece);
+      map[atomicAdd(&at[class_of(len - (nch - 1) * piece)], 1)] = make_int4(b0 + t, nch - 1, nch > 1 ? first_slot : -1, nch > 1 ? piece : chunk_tokens);
+      if (nch > 1 && place < nlong) long_list[place] = first;
+    } else if (nch > 1 && place < nlong) {
+      long_list[place] = -1;
+    }
+  }
+  for (int i = all_long + t; i < nlong; i += round) long_list[i] = -1;
+  for (int i = used + t; i < npairs; i += round) map[i] = make_int4(-1, 0, -1, 0);
 }
 
 }  // namespace
@@ -329,14 +340,13 @@ hipError_t launch_state_scan(int head_dim, bool reverse, const ScanParams& p, hi
   const int dd = head_dim * head_dim;
   dim3 g((unsigned)(units * ((dd / 4 + 255) / 256))), b(256);   // the host checked that this fits a grid
   hipLaunchKernelGGL(state_scan_kernel, g, b, 0, s, p.states, p.lambda, p.heads, p.nchunks, p.chunk_tokens, dd,
-                     reverse ? 1 : 0, p.init[0], p.init_transposed & 1, head_dim, p.n, p.cu_seqlens, p.wg_map, p.long_list,
-                     p.even_chunks);
+                     reverse ? 1 : 0, p.init[0], p.init_transposed & 1, head_dim, p.n, p.cu_seqlens, p.wg_map, p.long_list);
   return hipGetLastError();
 }
 
 hipError_t launch_varlen_map(const ScanParams& p, int4* map, int32_t* long_list, int64_t nslots, hipStream_t s) {
   if (p.wg_pairs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(varlen_map_kernel, dim3(1), dim3(256), 0, s, p.cu_seqlens, p.batch, p.chunk_tokens, p.wg_pairs, map,
+  hipLaunchKernelGGL(varlen_map_kernel, dim3(1), dim3(p.batch <= 256 ? 256 : 1024), 0, s, p.cu_seqlens, p.batch, p.chunk_tokens, p.wg_pairs, map,
                      p.nlong, long_list, (int)std::min<int64_t>(nslots, 0x7FFFFFFF), p.even_chunks);
   return hipGetLastError();
 }

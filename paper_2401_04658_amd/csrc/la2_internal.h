@@ -67,7 +67,7 @@ struct ScanParams {
   // Packed batch cut into sequence chunks (16-bit half-block path only; nullptr otherwise): a compact launch
   // grid.  Instead of batch * heads * nchunks workgroups, most of them for chunks that short sequences do not
   // have, the launch has wg_pairs * heads workgroups and workgroup i serves head i % heads of the (sequence,
-  // chunk) pair wg_map[i / heads] = {sequence, chunk, state slot or -1, chunks of the sequence}; entries past
+  // chunk) pair wg_map[i / heads] = {sequence, chunk, state slot or -1, positions per chunk}; entries past
   // the last pair carry sequence -1.  Only sequences of more than one chunk have state slots: chunk j of
   // such a sequence keeps its state at states[(slot + j') * heads + head], consecutive chunks heads states apart.
   // The map is written by varlen_map_kernel from cu_seqlens (launch_varlen_map).
@@ -77,8 +77,8 @@ struct ScanParams {
   // the units of the state scan's launch, which would otherwise be mostly workgroups with nothing to do
   const int32_t* long_list;
   int32_t nlong;
-  // ... non-zero: a sequence is cut into pieces of about equal length, at most chunk_tokens (see even_chunk_length);
-  // 0: into pieces of chunk_tokens and a rest
+  // ... for launch_varlen_map, non-zero: a sequence is cut into pieces of about equal length, at most chunk_tokens (see
+  // even_chunk_length); 0: into pieces of chunk_tokens and a rest
   int32_t even_chunks;
   // 16-bit half-block kernels only: states at sequence ends that are no block boundaries.  Non-zero: a forward
   // scan hands out in fin the state right after a chain's last position even if that position is not a block's
@@ -99,11 +99,11 @@ constexpr int kMaxPrefixTerms = 4;
 
 // Which (batch row or sequence, head, chunk) a workgroup of a scan-type launch serves, and where that chunk's
 // state lives ([D][D] floats at states + slot * D * D; slot < 0: the chain has a single chunk and no state slot).
-// slot_stride: slots between consecutive chunks of the chain.  nch: the chain's chunks as the pair map has them (0
-// without a map).  false: no work for this workgroup.
+// slot_stride: slots between consecutive chunks of the chain.  chunk_tokens: positions per chunk of this chain (its last
+// chunk may be shorter).  false: no work for this workgroup.
 __device__ __forceinline__ bool place_workgroup(const ScanParams& p, int wg, int& bi, int& hi, int& chunk,
-                                                int64_t& slot, int& slot_stride, int& nch) {
-  nch = 0;
+                                                int64_t& slot, int& slot_stride, int& chunk_tokens) {
+  chunk_tokens = p.chunk_tokens;
   if (p.wg_map == nullptr) {
     const int chain = wg / p.nchunks;
     chunk = wg % p.nchunks;
@@ -119,7 +119,7 @@ __device__ __forceinline__ bool place_workgroup(const ScanParams& p, int wg, int
   hi = wg % p.heads;
   bi = seq;
   chunk = __builtin_amdgcn_readfirstlane(m.y);
-  nch = __builtin_amdgcn_readfirstlane(m.w);
+  chunk_tokens = __builtin_amdgcn_readfirstlane(m.w);
   slot = first_slot < 0 ? -1 : ((int64_t)first_slot + chunk) * p.heads + hi;
   slot_stride = p.heads;
   return seq >= 0;
@@ -146,20 +146,17 @@ __device__ __forceinline__ void chain_extent(const ScanParams& p, int bi, int hi
 // Even cuts of a packed batch (ScanParams::even_chunks).  A sequence of n positions is cut into ceil(n / chunk_tokens)
 // pieces of about equal length: even_chunk_length is that length (a multiple of kChunkGranule, at most chunk_tokens),
 // even_chunk_count how many pieces the granule's rounding leaves; cutting at the length of that many pieces gives that
-// many again.  chunk_length: positions per chunk of a chain (its last chunk may be shorter), nch from the pair map.
+// many again.
 constexpr int kChunkGranule = 64;
 __host__ __device__ __forceinline__ int even_chunk_length(int n, int nch) {
   const int blocks = (n + kChunkGranule - 1) / kChunkGranule;
   return ((blocks + nch - 1) / nch) * kChunkGranule;
 }
 __host__ __device__ __forceinline__ int even_chunk_count(int n, int chunk_tokens) {
-  const int pieces = (int)(((int64_t)n + chunk_tokens - 1) / chunk_tokens);
+  const int pieces = (int)(((uint32_t)n + (uint32_t)chunk_tokens - 1u) / (uint32_t)chunk_tokens);
   if (pieces <= 1) return 1;
   const int len = even_chunk_length(n, pieces);
   return (n + len - 1) / len;
-}
-__device__ __forceinline__ int chunk_length(const ScanParams& p, int n, int nch) {
-  return p.even_chunks != 0 ? max(even_chunk_length(n, max(nch, 1)), kChunkGranule) : p.chunk_tokens;
 }
 
 // Where a chain's r values start in p.rstd: dense batches [batch * heads][rstd_stride positions]; packed batches

@@ -97,9 +97,9 @@ void scan_bf16_half_kernel(ScanParams p) {
   // its tiles at compile-time LDS offsets.
   auto run = [&](auto wh_tag) __attribute__((always_inline)) {
   constexpr int WH = decltype(wh_tag)::value;
-  int bi, hi, chunk, slot_stride, map_nch;
+  int bi, hi, chunk, slot_stride, chunk_tokens;
   int64_t slot;
-  if (!place_workgroup(p, wg, bi, hi, chunk, slot, slot_stride, map_nch)) return;
+  if (!place_workgroup(p, wg, bi, hi, chunk, slot, slot_stride, chunk_tokens)) return;
   const int chain = bi * p.heads + hi;
   int64_t base;
   int n;
@@ -114,7 +114,6 @@ void scan_bf16_half_kernel(ScanParams p) {
       make_rsrc(NORM ? p.rstd + rstd_chain_offset(p, bi, hi) : nullptr, NORM ? (uint32_t)n * 4u : 0u);
 
   const int nblocks = (n + B - 1) / B;
-  const int chunk_tokens = chunk_length(p, n, map_nch);
   const int cb = chunk_tokens / B;
   const int blk_lo = chunk * cb;
   const int blk_hi = min(blk_lo + cb, nblocks);

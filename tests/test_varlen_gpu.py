@@ -111,6 +111,20 @@ def test_unequal_lengths_sorted_and_cut_evenly(kind, dtype, d):
     check_packed(lengths, H, d, dtype, seed=880 + d, lam=[0.6, 0.9, 0.99, 0.997] * (H // 4) if H >= 4 else [0.8, 0.997])
 
 
+@pytest.mark.parametrize("batch", [255, 256, 257, 1023, 1024, 1025, 2070])
+@pytest.mark.parametrize("even", [False, True])
+def test_pair_map_over_its_rounds_of_sequences(even, batch):
+    """The pair map takes 256 sequences at once, or 1024 at a time: long ones at the ends of such a round, empty ones,
+    pieces of one size (the test knob) and even pieces (the automatic cut)."""
+    lengths = [(7 * i) % 61 for i in range(batch)]
+    for i in (0, 200, 255, 256, 1000, 1023, 1024, 2047, batch - 1):
+        if i < batch:
+            lengths[i] = 700 + i % 90
+    if not even:
+        binding.la2_set_chunk_tokens(128)
+    check_packed(lengths, 1, 64, torch.bfloat16, seed=898 + batch, lam=[0.99])
+
+
 def test_a_sequence_of_more_chunks_than_the_state_scan_holds_at_once():
     """Few chains, pieces of 256 positions: 36, 33 and 32 chunks in one batch, the scan over their states takes 32 at a
     time."""
