@@ -192,9 +192,16 @@ Plan make_plan(const la2_desc* d) {
 // rule.  Otherwise (the launch grid is compact and its pairs are sorted by length, varlen_map_kernel; a grid of
 // batch x heads x nchunks workgroups, most of them for chunks the short sequences do not have, costs about 10 ns per
 // empty workgroup and launch):
-//   - chains that fill the device: longest <= 1.5 load: not cut, only sorted (65,536 positions, H 16, d 128, forward +
-//     backward: longest 4096, 5000, 6000: 0.88, 0.94, 0.97 ms; cut 0.95, 0.96, 1.00; 7000: 1.08 against 1.00 cut);
-//     above that every sequence is cut into even pieces of at most 0.65 load (longest 7000 / 8192: 1.00 / 0.99 ms;
+//   - chains that fill the device: longest <= 1.5 load, every sequence counted kSequenceCost positions longer: not cut, only sorted
+//     (65,536 positions, H 16, d 128, forward + backward: longest 4096, 5000, 6000: 0.88, 0.94, 0.97 ms; cut 0.95, 0.96,
+//     1.00; 7000: 1.08 against 1.00 cut.  The start of a workgroup takes about as long as 34 positions, and in a batch of
+//     many short sequences a long one hides behind them: 922 sequences of 64 and one of 6553, longest = 1.6 load,
+//     1.08 ms; cut, with its pre-pass and the dQ launch that forms states, 1.21; 10,000 positions, longest 1000, 0.185
+//     against 0.219.  At head_dim 64 that cut costs less and pays from a load of about 1000 and 512 positions x heads per
+//     sequence on, for which the count is an eighth: sequences of 64 and one of 1.6 load, uncut against cut, H 16, load 626,
+//     1253, 1875, 4097: 0.109, 0.203, 0.293, 0.625 against 0.113, 0.198, 0.278, 0.567 ms; H 2, load 512, 1024: 0.082, 0.149
+//     against 0.098, 0.176).
+//     Above that every sequence is cut into even pieces of at most 0.65 load (longest 7000 / 8192: 1.00 / 0.99 ms;
 //     0.5 load 1.00 / 1.02, 0.8 load 1.02 / 1.00; head_dim 64 0.57, 0.57, 0.61), unless that would make more than
 //     kPackedCut pieces of the longest, whose state scans would be launches of their own: then pieces of
 //     1 / kPackedCut of the longest and a rest (longest 16384: 1.06 ms; even pieces of that size 1.10).
@@ -204,6 +211,7 @@ Plan make_plan(const la2_desc* d) {
 // A sequence of len positions has at most len / C + 1 pairs, and only sequences longer than C need state slots, at
 // most 2 len / C each.
 constexpr int kPackedCut = 4;
+constexpr int64_t kSequenceCost = 32;      // positions
 Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
   const Plan dense = make_plan(d);
   if (total_positions <= 0 || d->batch <= 0) return dense;
@@ -230,7 +238,8 @@ Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
   const int64_t as_longest = (int64_t)d->seqlen * d->batch;
   if (few && (nblocks < 8 || as_longest * 4 <= total_positions * 5)) return compact(dense);
   if (!few && (nblocks < 8 || as_longest <= 2 * total_positions)) return dense;
-  const int64_t load = total_positions * d->heads / device_cu_count();
+  const int64_t units = device_cu_count();
+  const int64_t load = total_positions * d->heads / units;
   auto blocks_of = [&](double tokens) {   // in blocks: at least four, at most the longest sequence
     const int64_t cb = ((int64_t)tokens + B - 1) / B;
     return (int)std::min<int64_t>(std::max<int64_t>(cb, 4), nblocks);
@@ -244,7 +253,9 @@ Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
     const Plan p = cut(blocks_of(1.25 * (double)load), true);
     return p.wg_pairs > 0 ? p : dense;
   }
-  if (2 * (int64_t)d->seqlen <= 3 * load) {
+  const bool cheap_cut = d->head_dim == 64 && load >= 1024 && total_positions * d->heads >= 512 * (int64_t)d->batch;
+  const int64_t start_cost = (cheap_cut ? kSequenceCost / 8 : kSequenceCost) * d->batch * d->heads / units;
+  if (2 * (int64_t)d->seqlen <= 3 * (load + start_cost)) {
     const Plan p = cut(nblocks, true);
     return p.wg_pairs > 0 ? p : dense;
   }
