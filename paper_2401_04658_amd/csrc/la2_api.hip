@@ -116,6 +116,9 @@ struct Plan {
 bool self_prefix(const la2_desc* d, const Plan& pl, const int32_t* cu);
 bool fuses_reverse_states(const la2_desc* d);
 
+// Measured time of one block (64 positions) of a 16-bit scan's sequential loop, in microseconds.
+float block_time_16(int head_dim) { return head_dim == 256 ? 3.3f : head_dim == 96 ? 3.f : head_dim == 64 ? 1.15f : 2.1f; }
+
 // Sequence chunks: the block loop of one chain is sequential, so when batch*heads cannot fill the
 // compute units the sequence is cut into chunks that run in parallel from pre-computed start states.
 Plan make_plan(const la2_desc* d) {
@@ -160,8 +163,7 @@ Plan make_plan(const la2_desc* d) {
     // Measured times of one block of the sequential loop, in microseconds.  (fp32: of the kernel's predecessor on
     // fp32 MFMA; with today's 5 and 2 the rule would leave sequences of 10 blocks whole that take 0.098 ms in three
     // chunks and 0.128 whole, head_dim 128, 16 chains; 0.069 against 0.088 at 64.)
-    const float t_blk = is16(d->dtype) ? (d->head_dim == 256 ? 3.3f : d->head_dim == 96 ? 3.f : d->head_dim == 64 ? 1.15f : 2.1f)
-                                       : (d->head_dim == 128 ? 10.f : 3.f);
+    const float t_blk = is16(d->dtype) ? block_time_16(d->head_dim) : d->head_dim == 128 ? 10.f : 3.f;
     if (is16(d->dtype) && d->head_dim == 256) {
       // One workgroup of this kernel fills a compute unit, and a block takes it 3.3 us with every unit busy but
       // 2.3 us with half of them idle; the pre-pass costs 0.6 of a scan block per block.  Measured at 128 chains of
@@ -192,7 +194,7 @@ Plan make_plan(const la2_desc* d) {
 // rule.  Otherwise (the launch grid is compact and its pairs are sorted by length, varlen_map_kernel; a grid of
 // batch x heads x nchunks workgroups, most of them for chunks the short sequences do not have, costs about 10 ns per
 // empty workgroup and launch):
-//   - chains that fill the device: longest <= 1.5 load, every sequence counted kSequenceCost positions longer: not cut, only sorted
+//   - chains that fill the device: longest <= 1.5 load, every sequence counted kSequenceCost positions longer: not cut
 //     (65,536 positions, H 16, d 128, forward + backward: longest 4096, 5000, 6000: 0.88, 0.94, 0.97 ms; cut 0.95, 0.96,
 //     1.00; 7000: 1.08 against 1.00 cut.  The start of a workgroup takes about as long as 34 positions, and in a batch of
 //     many short sequences a long one hides behind them: 922 sequences of 64 and one of 6553, longest = 1.6 load,
@@ -205,6 +207,12 @@ Plan make_plan(const la2_desc* d) {
 //     0.5 load 1.00 / 1.02, 0.8 load 1.02 / 1.00; head_dim 64 0.57, 0.57, 0.61), unless that would make more than
 //     kPackedCut pieces of the longest, whose state scans would be launches of their own: then pieces of
 //     1 / kPackedCut of the longest and a rest (longest 16384: 1.06 ms; even pieces of that size 1.10).
+//   - ... and sorted, for a map launch of 4 us or more in front of the forward and of the backward, if the sequences have
+//     kSortAverage positions on average and one scan takes kSortScan or more (lengths spread evenly over their logarithm,
+//     in random order, sorted against not: load 600, d 128 0.95, 0.80 (H 16, 4), load 1200 0.92, 0.85-0.91, load 2400
+//     0.91-0.95, 0.81-0.95; d 64, load 1200 0.87-0.99, load 2400 0.81-0.95, load 4800 0.77-0.95; already in descending order
+//     1.01-1.06.  Below: d 64, load 600 0.89-1.13, in descending order 1.08-1.12.  Average 57 positions and one long sequence:
+//     0.81-1.10 at H 16 and 32, 1.05-1.45 at H 1 and 2, whose maps are long).
 //   - chains that do not: even pieces of at most 1.25 load (a plan by the longest length alone gives every sequence
 //     the same number of chunks: 65,536 positions in 20 sequences of up to 8192, H 2, d 128: 1.18 -> 0.32 ms;
 //     1.0 load 0.36, 1.5 load 0.34 ms; 40,000 positions, longest 16384, H 4, d 64: 0.31 -> 0.13 ms).
@@ -212,6 +220,8 @@ Plan make_plan(const la2_desc* d) {
 // most 2 len / C each.
 constexpr int kPackedCut = 4;
 constexpr int64_t kSequenceCost = 32;      // positions
+constexpr int64_t kSortAverage = 128;      // positions per sequence
+constexpr float kSortScan = 17.f;          // microseconds
 Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
   const Plan dense = make_plan(d);
   if (total_positions <= 0 || d->batch <= 0) return dense;
@@ -240,6 +250,7 @@ Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
   if (!few && (nblocks < 8 || as_longest <= 2 * total_positions)) return dense;
   const int64_t units = device_cu_count();
   const int64_t load = total_positions * d->heads / units;
+  const float t_block = block_time_16(d->head_dim);
   auto blocks_of = [&](double tokens) {   // in blocks: at least four, at most the longest sequence
     const int64_t cb = ((int64_t)tokens + B - 1) / B;
     return (int)std::min<int64_t>(std::max<int64_t>(cb, 4), nblocks);
@@ -256,6 +267,7 @@ Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
   const bool cheap_cut = d->head_dim == 64 && load >= 1024 && total_positions * d->heads >= 512 * (int64_t)d->batch;
   const int64_t start_cost = (cheap_cut ? kSequenceCost / 8 : kSequenceCost) * d->batch * d->heads / units;
   if (2 * (int64_t)d->seqlen <= 3 * (load + start_cost)) {
+    if (total_positions < kSortAverage * d->batch || (float)load * t_block < kSortScan * (float)B) return dense;
     const Plan p = cut(nblocks, true);
     return p.wg_pairs > 0 ? p : dense;
   }

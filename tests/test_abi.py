@@ -472,8 +472,13 @@ def test_packed_plans_by_the_average_load_of_a_compute_unit(lib):
     assert ws(x, 65536, 0) == ws(x, 65536, 1) == round256(55 * 16)
     assert lib.la2_fwd_varlen(ctypes.byref(x), None, 65536, P, P, P, P, P, None, 0, None) == E_NULL   # not E_WS
     assert ws(x, 0, 0) == 0 and ws(x, 55 * 4096, 0) == 0
+    # sorted only where that pays for the map's launch: a scan of 17 us (load 518 at d 128, 946 at d 64), 128 positions on average
+    for d, total, batch, longest in ((128, 8400, 40, 600), (64, 15800, 60, 700)):
+        assert ws(desc(batch, 16, longest, d), total, 0) == round256(batch * 16)
+        assert ws(desc(batch, 16, longest, d), total - 900, 0) == 0
+        assert ws(desc(total // 128 + 1, 16, longest, d), total, 1) == 0
     # every sequence counts 32 positions more against the longest: 923 sequences, load 4096, longest 6553 stay whole
-    assert ws(desc(923, 16, 6553, 128), 65536, 0) == round256(923 * 16) and ws(desc(100, 16, 6553, 128), 65536, 0) > round256(100 * 16)
+    assert ws(desc(923, 16, 6553, 128), 65536, 0) == 0 and ws(desc(100, 16, 6553, 128), 65536, 0) > round256(100 * 16)
     x = desc(20, 2, 8192, 128)                                        # load 512: pieces of at most 640
     pairs, slots = 65536 // 640 + 20, 2 * 65536 // 640
     for op, sets in ((0, 1), (1, 2)):

@@ -104,7 +104,7 @@ def test_unequal_lengths_sorted_and_cut_evenly(kind, dtype, d):
     if kind == "few":
         lengths, H = [1500, 40, 0, 333, 64, 257, 256], 2
     else:
-        longest, total, H = (600, 6400, 16) if kind == "sorted" else (1300, 9500, 16)
+        longest, total, H = (600, 16500, 16) if kind == "sorted" else (1300, 9500, 16)
         lengths = [longest - 23, 1, longest, 0, 449, 385, 384, 64, 65]
         while sum(lengths) < total:
             lengths.append(37 + 13 * (len(lengths) % 19))
@@ -135,7 +135,7 @@ def test_an_uncut_batch_needs_no_workspace():
     """The map that sorts an uncut batch lives in the workspace; without one the batch runs in the order of the
     sequences, same results bit for bit."""
     import ctypes
-    lengths, H, d = [600, 100, 577] + [70, 130] * 26, 16, 128
+    lengths, H, d = [600, 100, 577] + [170, 230] * 26, 16, 128
     t, cu = packed_inputs(lengths, H, d, torch.bfloat16, seed=890)
     g = {k: v.to(DEV) for k, v in t.items()}
     cu_g = cu.to(DEV)
