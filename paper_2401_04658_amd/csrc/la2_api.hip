@@ -215,13 +215,18 @@ Plan make_plan(const la2_desc* d) {
 //     0.81-1.10 at H 16 and 32, 1.05-1.45 at H 1 and 2, whose maps are long).
 //   - chains that do not: even pieces of at most 1.25 load (a plan by the longest length alone gives every sequence
 //     the same number of chunks: 65,536 positions in 20 sequences of up to 8192, H 2, d 128: 1.18 -> 0.32 ms;
-//     1.0 load 0.36, 1.5 load 0.34 ms; 40,000 positions, longest 16384, H 4, d 64: 0.31 -> 0.13 ms).
+//     1.0 load 0.36, 1.5 load 0.34 ms; 40,000 positions, longest 16384, H 4, d 64: 0.31 -> 0.13 ms), but kPackedCut of
+//     them, where the dense rule has no more, if the loop that is longer for it takes kLongerLoop at most: the state
+//     scan's three launches fall away (two sequences, H 32, d 64, longest 1100, 1350, 1800: 56, 63, 79 us against 67, 68, 84;
+//     33 sequences, longest 2000, H 2, d 64, at 4.6 us longer: 67 against 56; with the dense rule at six chunks or more,
+//     longest 1333 of 8, H 1, d 128: 87 against 76).
 // A sequence of len positions has at most len / C + 1 pairs, and only sequences longer than C need state slots, at
 // most 2 len / C each.
 constexpr int kPackedCut = 4;
 constexpr int64_t kSequenceCost = 32;      // positions
 constexpr int64_t kSortAverage = 128;      // positions per sequence
 constexpr float kSortScan = 17.f;          // microseconds
+constexpr float kLongerLoop = 3.f;         // microseconds
 Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
   const Plan dense = make_plan(d);
   if (total_positions <= 0 || d->batch <= 0) return dense;
@@ -261,7 +266,10 @@ Plan make_plan_varlen(const la2_desc* d, int64_t total_positions) {
     return compact(p);
   };
   if (few) {
-    const Plan p = cut(blocks_of(1.25 * (double)load), true);
+    int cb = blocks_of(1.25 * (double)load);
+    const int four = (nblocks + kPackedCut - 1) / kPackedCut;
+    if (dense.nchunks <= kPackedCut && four > cb && (float)(four - cb) * t_block <= kLongerLoop) cb = four;
+    const Plan p = cut(cb, true);
     return p.wg_pairs > 0 ? p : dense;
   }
   const bool cheap_cut = d->head_dim == 64 && load >= 1024 && total_positions * d->heads >= 512 * (int64_t)d->batch;

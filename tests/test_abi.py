@@ -479,6 +479,12 @@ def test_packed_plans_by_the_average_load_of_a_compute_unit(lib):
         assert ws(desc(total // 128 + 1, 16, longest, d), total, 1) == 0
     # every sequence counts 32 positions more against the longest: 923 sequences, load 4096, longest 6553 stay whole
     assert ws(desc(923, 16, 6553, 128), 65536, 0) == 0 and ws(desc(100, 16, 6553, 128), 65536, 0) > round256(100 * 16)
+    # few chains, a dense plan of four chunks: four pieces rather than six; a dense plan of more: by the load
+    x = desc(2, 32, 1350, 64)
+    assert plan(lib, 2, 32, 1350, 64, binding.LA2_BF16)[0] == 4
+    assert ws(x, 1500, 0) == round256((1500 // 384 + 2) * 16 + 2 * 4) + (2 * 1500 // 384) * 32 * 64 * 64 * 4
+    x = desc(2, 4, 1350, 64)
+    assert ws(x, 1500, 0) == round256((1500 // 256 + 2) * 16 + 2 * 4) + (2 * 1500 // 256) * 4 * 64 * 64 * 4
     x = desc(20, 2, 8192, 128)                                        # load 512: pieces of at most 640
     pairs, slots = 65536 // 640 + 20, 2 * 65536 // 640
     for op, sets in ((0, 1), (1, 2)):
