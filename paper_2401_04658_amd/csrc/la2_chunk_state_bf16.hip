@@ -168,6 +168,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(float* states, const fl
   // (a packed sequence longer than the launch was planned for is the caller's error; it must not reach past the
   // chain's slots.  With a pair map the sequence's slots were counted from this same length.)
   if (wg_map == nullptr) nch = min(nch, nchunks);
+  nch = __builtin_amdgcn_readfirstlane(nch);   // one chain per workgroup: scalar comparisons below
   const float l2 = log2f(lambda[hi]);
   const float lamFull = exp2f(l2 * (float)chunk_tokens);
   const float lamLast = exp2f(l2 * (float)(n - (nch - 1) * chunk_tokens));
@@ -192,13 +193,18 @@ __global__ __launch_bounds__(256) void state_scan_kernel(float* states, const fl
       const int j = reverse ? nch - 1 - (i0 + i) : i0 + i;
       if (i0 + i < nch - 1) loc[i] = s[(int64_t)j * step];   // the chunk processed last has no successor: not read
     }
+    // All of them have arrived: a wait between the stores below would be one for the stores before it.  (left: opaque, so
+    // that the comparisons are made again and not kept from above in scalar registers.)
+#pragma unroll
+    for (int i = 0; i < kScanMaxChunks; i++) asm volatile("" : "+v"(loc[i]));
+    int left = nch - i0;
+    asm("" : "+s"(left));
 #pragma unroll
     for (int i = 0; i < kScanMaxChunks; i++) {
-      if (i0 + i < nch) {
+      if (i < left) {
         const int j = reverse ? nch - 1 - (i0 + i) : i0 + i;
         s[(int64_t)j * step] = g;
-        const float decay = (j == nch - 1) ? lamLast : lamFull;
-        if (i0 + i < nch - 1) g = decay * g + loc[i];
+        g = (j == nch - 1 ? lamLast : lamFull) * g + loc[i];   // (behind the last chunk: not used)
       }
     }
   }
