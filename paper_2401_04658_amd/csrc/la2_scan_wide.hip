@@ -185,18 +185,26 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
   auto issue_z = [&](E* tile, int blk, int i) __attribute__((always_inline)) {
     dma16(gz, z_offset(blk, i), lds_offset(tile) + 1024u * (2u * (uint32_t)(w & 3) + (uint32_t)i));
   };
-  // the first tiles are on their way before the start state is fetched and the weights are made
   auto block_at = [&](int it) { return REV ? blk_hi - 1 - it : blk_lo + it; };
+  auto issue_first = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int j = 0; j < NBUF - 1; j++) {
-    if (loads && j < nblk) {
-      loader.issue(sT[j], block_at(j));
-      if constexpr (SPLIT) {
-        issue_z(sZ[j], block_at(j), 0);
-        issue_z(sZ[j], block_at(j), 1);
+    for (int j = 0; j < NBUF - 1; j++) {
+      if (loads && j < nblk) {
+        loader.issue(sT[j], block_at(j));
+        if constexpr (SPLIT) {
+          issue_z(sZ[j], block_at(j), 0);
+          issue_z(sZ[j], block_at(j), 1);
+        }
       }
     }
-  }
+  };
+  // The first tiles are on their way before the start state is fetched and the weights are made, where that does not put
+  // registers of the loads into the block loop: at head_dim 96 with the Norm epilogue it did (a spilled one is reloaded
+  // behind the tile loads in flight: 256 chains of 1024 positions, forward + backward, 0.194 against 0.180 ms, 4096
+  // positions 0.755 against 0.687), and at head_dim 256 eight waves that fetch 256 KiB of state wait for it either way (40
+  // positions on 256 chains: 30.0 us tiles first, 29.0 state first).
+  constexpr bool TILES_FIRST = SPLIT || (D == 96 && !NORM);
+  if (TILES_FIRST) issue_first();
   const float l2 = log2f(p.lambda[hi]);
   E* const gw = STATE_ONLY ? nullptr : reinterpret_cast<E*>(which ? p.w[1] : p.w[0]) + base;
   // head_dim 256: LaneAddr's precomputed offsets (one XOR per read); its read_row takes a row tile, always 0 here
@@ -281,20 +289,32 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
         add_state(p.states + ((int64_t)chain * p.nchunks + j) * (D * D), tr, j == last - 1 ? lam_last : lam_full);
       }
     }
-  } else if (!NORM && gs != nullptr && tr) {
+  } else if (NORM) {   // (an offset per element: as below it took registers that the block loop has not got)
 #pragma unroll
     for (int t = 0; t < KT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v += 4) {
-        const f32x4 r = *reinterpret_cast<const f32x4*>(gs + state_index_pi(t, v, true));
+      for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index_pi(t, v, tr)] : 0.f;
+  } else if (gs != nullptr) {
+    uint32_t at = (uint32_t)state_index_pi(0, 0, !NORM && tr);
+    pin(at);   // as above; and one branch around all of it, not one per element
+    if (!NORM && tr) {
 #pragma unroll
-        for (int e = 0; e < 4; e++) kv[t][v + e] = r[e];
-      }
+      for (int t = 0; t < KT; t++)
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+          const f32x4 r = *reinterpret_cast<const f32x4*>(gs + (32 * t + 16 * (v >> 3) + (v & 7)) + at);
+#pragma unroll
+          for (int e = 0; e < 4; e++) kv[t][v + e] = r[e];
+        }
+    } else {
+#pragma unroll
+      for (int t = 0; t < KT; t++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) kv[t][v] = (gs + (32 * t + 16 * (v >> 3) + (v & 7)) * D)[at];
+    }
   } else {
 #pragma unroll
-    for (int t = 0; t < KT; t++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index_pi(t, v, false)] : 0.f;
+    for (int t = 0; t < KT; t++) kv[t] = zero16();
   }
   // decay mask of the score tile S^T[c][r] (lane: r = l32; element v: c = 8 (v / 4) + 4 hh + v % 4): the same for
   // every wave and every block.  It lives in LDS, four elements per lane and read, not in sixteen registers: the
@@ -397,6 +417,7 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
     for (int q = 0; q < 2; q++) a = mfma(zfv[q], pv[q], a);
     store_block(a, blkv, lr, lh);
   };
+  if (!TILES_FIRST) issue_first();
   int buf = 0;   // it % NBUF
   for (int it = 0; it < nblk; it++, buf = buf + 1 < NBUF ? buf + 1 : 0) {
     const int blk = block_at(it);
