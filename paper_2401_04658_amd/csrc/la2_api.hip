@@ -451,8 +451,15 @@ struct ScanArgs {
 constexpr int kSelfPrefixMaxChunks = la2::kMaxPrefixTerms;   // a start state and the local states of chunks - 1 chunks
 bool self_prefix(const la2_desc* d, const Plan& pl, const int32_t* cu) {
   (void)cu;   // packed batches too: every sequence's chunks have their own slots, a sequence of one chunk has none
-  // head_dim 96 (36 KiB a state): up to six chunks, no limit of registers there; at 256 a state is 256 KiB
-  if (d->head_dim == 96) return is16(d->dtype) && pl.nchunks > 1 && pl.nchunks <= 6;
+  // Head_dim 96 (36 KiB a state, a loop: no limit of registers).  Every chunk before adds about 5 us to the last chunk's
+  // prologues in a step's three scans, whatever else runs; three launches fall away, the dearer the more states they scan.
+  // Forward + backward with against without, two to six chunks: 4 chains of 256 positions a chunk 0.89, 0.96, 1.02, 1.09,
+  // 1.16, of 640 0.94, 0.97, 1.01, 1.04, 1.09; 24 chains 0.87, 0.93, 1.00, 1.03, 1.08; 48 chains 0.83, 0.91, 0.97, 1.00,
+  // 1.04; 96 chains 0.82, 0.84, 0.96, 0.94, 0.96.  (At 256 a state is 256 KiB.)
+  if (d->head_dim == 96) {
+    const int64_t most = std::min<int64_t>(6, std::max<int64_t>(3, (int64_t)d->batch * d->heads / 16));
+    return is16(d->dtype) && pl.nchunks > 1 && pl.nchunks <= most;
+  }
   if (wide(d->head_dim) || pl.nchunks <= 1 || pl.nchunks > kSelfPrefixMaxChunks || pl.chunk_tokens % 32 != 0) return false;
   // (the scan variant is a knob of the 16-bit kernels: what an fp32 workspace holds does not depend on it)
   return !is16(d->dtype) || g_scan_variant.load(std::memory_order_relaxed) != 1;

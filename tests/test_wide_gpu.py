@@ -105,13 +105,15 @@ def test_sequence_chunks(d, n, chunk):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("chunk", [64, 128, 256])
 def test_head_dim_96_start_states_formed_in_the_scan(chunk, dtype):
-    """Plans of up to six chunks form their start states in the scan (from the caller's start state and the local states
-    of the chunks before, stored transposed for the dQ and the dK scan); seven chunks take the state scan's launch."""
+    """Plans of up to three chunks, with 96 chains up to six, form their start states in the scan (from the caller's start
+    state and the local states of the chunks before, stored transposed for the dQ and the dK scan); more chunks take the
+    state scan's launch."""
     binding.la2_set_chunk_tokens(chunk)
-    for n in (385, 300):      # 7 / 4 / 2 and 5 / 3 / 2 chunks
-        t, g = inputs(2, 3, n, 96, dtype, seed=96 + chunk + n, lam=[0.9, 0.99, 1.0])
-        check_state(t, g, dtype, "prefix states n%d chunk%d" % (n, chunk))
-        check_plain(t, g, dtype, "prefix n%d chunk%d" % (n, chunk))
+    for b, H in ((2, 3), (32, 3)):
+        for n in (385, 300):      # 7 / 4 / 2 and 5 / 3 / 2 chunks
+            t, g = inputs(b, H, n, 96, dtype, seed=96 + chunk + n, lam=[0.9, 0.99, 1.0])
+            check_state(t, g, dtype, "prefix states %d chains n%d chunk%d" % (b * H, n, chunk))
+            check_plain(t, g, dtype, "prefix %d chains n%d chunk%d" % (b * H, n, chunk))
 
 
 @pytest.mark.parametrize("d", DIMS)
