@@ -145,18 +145,22 @@ def _same_layout(ref, *others):
 
 # Host time of a call is the whole cost of a small decode step (kernel 3.3 us; batch 1, H 16, d 128: 11.0 us a call
 # with torch.cuda.device and torch.cuda.current_stream around it, 7.5 with these two): the stream handle and the
-# device number are taken from where those wrappers take them, and the device is switched only if it has to be.
+# device number are taken from where those wrappers take them (a torch without these two: from the wrappers), and the
+# device is switched only if it has to be.
 _NO_SWITCH = contextlib.nullcontext()
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_current_stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None)
+                   or (lambda device: torch.cuda.current_stream(device).cuda_stream))
 
 
 def _on(t):
     """Context in which t's device is the current one."""
-    return _NO_SWITCH if t.get_device() == torch._C._cuda_getDevice() else torch.cuda.device(t.device)
+    return _NO_SWITCH if t.get_device() == _current_device() else torch.cuda.device(t.device)
 
 
 def _stream(t):
     """Handle of the current stream of t's device."""
-    return torch._C._cuda_getCurrentRawStream(t.get_device())
+    return _current_stream(t.get_device())
 
 
 def la2_workspace_bytes(t, op=LA2_OP_FWD):
