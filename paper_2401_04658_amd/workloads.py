@@ -108,3 +108,20 @@ class DecodeWorkload:
 
 
 CONFIG5 = DecodeWorkload()
+
+
+def packed_plan_lengths(kind):
+    """(sequence lengths, heads) of small packed batches, one for each way the library plans a 16-bit packed batch on its
+    own at head_dim 64 / 128 (256 compute units): "sorted" uncut, the longest sequence first in the grid; "even" pieces
+    of a batch whose longest outlasts the average unit; "quarters" of a longest that far outlasts it; "few" chains, pieces
+    by the load; "four" of them where that saves the scan over the chunk states.  On and off the 64-position granule,
+    empty sequences among them."""
+    if kind == "few":
+        return [1500, 40, 0, 333, 64, 257, 256], 2
+    if kind == "four":
+        return [1100, 0, 150], 32
+    longest, total, heads = {"sorted": (600, 16500, 16), "even": (1300, 9500, 16), "quarters": (3000, 9500, 16)}[kind]
+    lengths = [longest - 23, 1, longest, 0, 449, 385, 384, 64, 65]
+    while sum(lengths) < total:
+        lengths.append(37 + 13 * (len(lengths) % 19))
+    return lengths, heads

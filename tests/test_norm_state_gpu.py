@@ -145,16 +145,29 @@ def _packed(lengths, H, d, dtype, seed, lead=0, trail=0):
                                      (torch.bfloat16, 96)])
 @pytest.mark.parametrize("chunk", [0, 128])
 def test_norm_over_packed_sequences(dtype, d, chunk):
+    check_norm_packed([70, 0, 1, 31, 300, 517, 64], 2, d, dtype, chunk, seed=900 + d)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.float16, 64)])
+@pytest.mark.parametrize("kind", ["sorted", "even", "quarters", "few", "four"])
+def test_norm_over_packed_sequences_by_every_plan(kind, dtype, d):
+    """The automatic plans of a packed batch (workloads.packed_plan_lengths), normalised."""
+    lengths, H = workloads.packed_plan_lengths(kind)
+    check_norm_packed(lengths, H, d, dtype, 0, seed=940 + d, lam=[0.7, 0.97, 0.995, 1.0][:H] * max(1, H // 4))
+
+
+def check_norm_packed(lengths, H, d, dtype, chunk, seed, lam=None):
     import numpy as np
-    lengths = [70, 0, 1, 31, 300, 517, 64]
-    t, cu = _packed(lengths, 2, d, dtype, seed=900 + d, lead=3, trail=5)
+    t, cu = _packed(lengths, H, d, dtype, seed=seed, lead=3, trail=5)
+    if lam is not None:
+        t["lam"] = torch.as_tensor(lam, dtype=torch.float32)
     g = {k_: v_.to(DEV) for k_, v_ in t.items()}
     cu_g = torch.from_numpy(cu).to(DEV)
     eps = 1e-5
     binding.la2_set_chunk_tokens(chunk)
     try:
         o = torch.full_like(g["q"], float("nan"))
-        rstd = torch.full((2, g["q"].shape[0]), float("nan"), dtype=torch.float32, device=DEV)
+        rstd = torch.full((H, g["q"].shape[0]), float("nan"), dtype=torch.float32, device=DEV)
         binding.la2_fwd_varlen_norm(g["q"], g["k"], g["v"], g["lam"], cu_g, max(lengths), eps, out=o, rstd=rstd)
         grads = tuple(torch.full_like(g["q"], float("nan")) for _ in range(3))
         d_u = torch.full_like(g["q"], float("nan"))

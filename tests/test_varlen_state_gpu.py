@@ -277,3 +277,32 @@ def test_padded_rows_and_head_major_storage():
         assert torch.equal(o, ref_o) and torch.equal(kvf, ref_kvf), place.__name__
         for a, b in zip(got, ref_g):
             assert torch.equal(a, b), place.__name__
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.float16, 128)])
+@pytest.mark.parametrize("kind", ["sorted", "even", "quarters", "few", "four"])
+def test_states_by_every_plan(kind, dtype, d):
+    """The automatic plans of a packed batch (workloads.packed_plan_lengths) with start and final states and their
+    gradients: uncut and sorted, even pieces, quarters of the longest, few chains by the load, four pieces."""
+    lengths, H = workloads.packed_plan_lengths(kind)
+    check_packed_state(lengths, H, d, dtype, seed=960 + d, lam=([0.7, 0.97, 0.995, 1.0] * 8)[:H])
+
+
+def test_the_lengths_reach_the_plans_they_are_named_for():
+    """What la2_varlen_workspace_bytes says of each (256 compute units)."""
+    import ctypes
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("written for 256 compute units")
+    for d in (64, 128):
+        for kind, slots_of in (("sorted", lambda total, n: 0), ("even", None), ("quarters", lambda total, n: 2 * total // (-(-n // 256) * 64)),
+                               ("few", lambda total, n: 2 * total // 256), ("four", lambda total, n: 2 * total // (-(-n // 256) * 64))):
+            lengths, H = workloads.packed_plan_lengths(kind)
+            total, longest = sum(lengths), max(lengths)
+            desc = binding.la2_desc(len(lengths), H, longest, d, binding.LA2_BF16, 0, 0, d, H * d)
+            need = int(binding.load().la2_varlen_workspace_bytes(ctypes.byref(desc), total, binding.LA2_OP_FWD))
+            states = need // (H * d * d * 4)
+            assert need > 0, (kind, d)
+            if slots_of is not None:
+                assert states == slots_of(total, longest), (kind, d, states, slots_of(total, longest))
+            else:
+                assert states > 0
