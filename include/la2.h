@@ -90,7 +90,7 @@ void la2_desc_dense(la2_desc* desc, int32_t batch, int32_t heads, int32_t seqlen
 /*
  * Bytes of device workspace la2_fwd / la2_bwd need for this problem (op is a la2_op).  The
  * workspace holds the d x d states of the sequence chunks that are processed in parallel when
- * batch*heads alone cannot fill the GPU (their start states; for a plan of at most four chunks their local
+ * batch*heads alone cannot fill the GPU (their start states; for a plan of a few chunks their local
  * states, from which every workgroup forms its own start state); it may be 0.  Returns 0 for an invalid descriptor.
  * The value depends on the device's compute-unit count and on la2_set_chunk_tokens().
  */
@@ -103,15 +103,15 @@ size_t la2_workspace_bytes(const la2_desc* desc, int32_t op);
  * holds one d x d fp32 start state per (batch, head, chunk) when nchunks > 1.  Depends on the device's
  * compute-unit count and on la2_set_chunk_tokens(), like la2_workspace_bytes().
  * One case it does not describe: a batch with a few more chains than a whole number (one to four) per compute unit,
- * which as one launch gives some units a workgroup more than the others and takes nearly as long as the next whole round (fp32:
- * twice the time of one chain per unit for anything between one and two).  Every entry point that takes a dense
+ * which as one launch gives some units a workgroup more than the others and takes up to twice as long as whole
+ * rounds.  Every entry point that takes a dense
  * batch (la2_fwd, la2_bwd, their _state, _saved, _norm and _noalloc forms) runs it as two calls on the given
  * stream: the first floor(rounds * units / heads) batch rows by the plan of that many rows (one chunk), the
  * remaining rows, with their rows of the states and of rstd, by the plan of a descriptor with that many rows
  * (several chunks); la2_workspace_bytes() answers for both, and what either part would refuse is refused before the
  * first launch.  A forward call's workspace then holds the chunk states of its second part, which is what
  * la2_bwd_saved reads.  Which shapes: seqlen >= 2048 (fp32: 1024), no la2_set_chunk_tokens(), and a partial round
- * of at most 1/8 to 4/8 of the unit count, by dtype and head_dim, as measured.  Results are those of the same block
+ * of at most 1/8 to 3/8 of the unit count, by dtype and head_dim, as measured.  Results are those of the same block
  * loop either way, up to the rounding of the chunk states.
  */
 la2_status la2_chunk_plan(const la2_desc* desc, int32_t* nchunks, int32_t* chunk_tokens);
@@ -243,10 +243,11 @@ la2_status la2_bwd_state_norm(const la2_desc* desc, const void* q, const void* k
  *                    the workspace planned from it uncomputed); the lengths
  *                    stay on the device, and with it the host can tell a batch of about equal lengths from one
  *                    whose longest sequence would run long after all the others have finished.  The workgroups of
- *                    such a batch start with the longest sequence (16-bit data, head_dim 64 / 128), and its long
- *                    sequences are cut into chunks by the average load of a compute unit although it has chains
- *                    enough to fill the device; short sequences are single chunks and pay nothing for it.  (A batch
- *                    that is only sorted, not cut, also runs without a workspace, unsorted.)
+ *                    such a batch start with the longest sequence (16-bit data, head_dim 64 / 128; not where the
+ *                    launch that sorts them would cost more), and its long sequences are cut into chunks by the
+ *                    average load of a compute unit although it has chains enough to fill the device; short
+ *                    sequences are single chunks and pay nothing for it.  (A batch that is only sorted, not cut, also
+ *                    runs without a workspace, unsorted.)
  * Everything else as for la2_fwd / la2_bwd.  Workspace: la2_varlen_workspace_bytes(desc, total_positions, op) with
  * op = LA2_OP_FWD or LA2_OP_BWD (with total_positions = 0: la2_workspace_bytes(desc, op)).
  * A sequence of length 0 is fine.

@@ -150,9 +150,8 @@ Plan make_plan(const la2_desc* d) {
       const int want2 = (int)(2 * (int64_t)cus / chains);   // positions: 0.25 ms in 32 chunks, 0.27 ms in 64)
       if (d->seqlen / want2 >= 640) want = want2;
     }
-    // fp32 data at head_dim 64: that kernel is bound by its issue and four of its workgroups share a unit (192 chains of
-    // 2048 positions, forward + backward: 0.61 ms uncut, 0.49 ms in four chunks; 64 chains of 4096: 0.43 ms in four
-    // chunks, 0.37 ms in eleven)
+    // fp32 data at head_dim 64: three, of the four that share a unit (192 chains of 2048 positions, forward + backward:
+    // 0.61 ms uncut, 0.49 ms in four chunks; 64 chains of 4096: 0.43 ms in four chunks, 0.37 ms in eleven)
     if (!is16(d->dtype) && d->head_dim == 64) want = (int)(3 * (int64_t)cus / chains);
     if (want < 2) return pl;
     cb = (nblocks + want - 1) / want;
@@ -160,10 +159,11 @@ Plan make_plan(const la2_desc* d) {
     if (cb >= nblocks) return pl;
     // Chunking shortens the scan's sequential loop from nblocks to cb blocks but adds the pre-pass (about a
     // third of a scan block per block) and two more launches (about 15 us): not worth it for short sequences.
-    // Measured times of one block of the sequential loop, in microseconds.  (fp32: of the kernel's predecessor on
-    // fp32 MFMA; with today's 5 and 2 the rule would leave sequences of 10 blocks whole that take 0.098 ms in three
-    // chunks and 0.128 whole, head_dim 128, 16 chains; 0.069 against 0.088 at 64.)
-    const float t_blk = is16(d->dtype) ? block_time_16(d->head_dim) : d->head_dim == 128 ? 10.f : 3.f;
+    // 16-bit data: measured times of one block of the sequential loop, in microseconds.  fp32: not times (a block takes 5
+    // and 2 us) but thresholds that stand for the whole comparison, whose other terms are 16-bit data's: from 10 blocks on
+    // a cut pays there (16 chains of 10 blocks, head_dim 128: 0.098 ms in three chunks, 0.128 whole; 64: 0.069, 0.088).
+    constexpr float kCutF32_128 = 10.f, kCutF32_64 = 3.f;
+    const float t_blk = is16(d->dtype) ? block_time_16(d->head_dim) : d->head_dim == 128 ? kCutF32_128 : kCutF32_64;
     if (is16(d->dtype) && d->head_dim == 256) {
       // One workgroup of this kernel fills a compute unit, and a block takes it 3.3 us with every unit busy but
       // 2.3 us with half of them idle; the pre-pass costs 0.6 of a scan block per block.  Measured at 128 chains of
@@ -175,6 +175,8 @@ Plan make_plan(const la2_desc* d) {
       if (t_cut >= t_uncut) return pl;
     } else {
       // the extra launches: the pre-pass and the scan over the chunk states, which plans of a few chunks do without
+      // (head_dim 96 is charged for it all the same: with 8 it would cut from 513 positions on, where 4 chains take 59.5 us
+      // in chunks of 256 against 61.5 whole, but 48 chains 75 against 66 and 96 chains 90 against 70)
       Plan cut{(nblocks + cb - 1) / cb, cb * B, 0};
       const float launches = !wide(d->head_dim) && self_prefix(d, cut, nullptr) ? 8.f : 15.f;
       if ((float)(nblocks - cb) * t_blk - 0.35f * (float)cb * t_blk - launches <= 0.f) return pl;
@@ -329,8 +331,7 @@ la2_status check_desc(const la2_desc* d) {
 
 // A dense batch with a few more chains than a whole number of chains per compute unit: the units that get one
 // workgroup more set the launch's time (n 4096, head_dim 128, bf16, forward + backward: 256 chains 0.67 ms, 320
-// chains 1.14 ms).  The dense entry points run such a batch as two
-// calls: the first rows, a whole number of chains per unit (up to four), whole; the rest by the plan for that many chains, i.e. in
+// chains 1.14 ms).  The dense entry points run such a batch as two calls: the first rows, a whole number of chains per unit (up to four), whole; the rest by the plan for that many chains, i.e. in
 // chunks (320 chains: 0.67 + 0.27 ms).  Returns the rows of the first call, 0 for one call.
 // Measured, two calls against one, forward + backward, n 2048 / 4096 / 8192 (256 units):
 //   chains           272          288          320          352          384
@@ -442,7 +443,8 @@ struct ScanArgs {
   bool ragged_state = false;
 };
 
-// A problem cut into a few chunks (16-bit half-block kernels; dense or packed batch): no launch for the scan over the chunks'
+// A problem cut into a few chunks (16-bit half-block and fp32 kernels up to four, head_dim 96 as below; dense or packed
+// batch): no launch for the scan over the chunks'
 // local states; every scan workgroup forms its own start state from them (ScanParams::self_prefix).  At that size
 // the launches are a few microseconds each and run one after the other, so a dependent launch less is worth more
 // than the few extra state reads (batch 4, H 16, n 2048, d 64, four chunks: each fold takes a 4.3 us launch away and
@@ -485,7 +487,7 @@ la2::ScanParams base_params(const la2_desc* d, const Plan& pl, const float* lamb
 
 // Head_dim 256: a workgroup of eight waves fills a compute unit, so a launch of at most half as many workgroups as units
 // leaves half of them idle; as two workgroups per scan, half the value features each, it takes all of them (64 chains
-// of 500 positions, forward + backward: 129 -> 106 us).  With more workgroups than that some units would get two.
+// of 500 positions, forward + backward: 129 -> 96 us).  With more workgroups than that some units would get two.
 int value_split(const la2_desc* d, const la2::ScanParams& p) {
   return d->head_dim == 256 && is16(d->dtype) &&
          2 * (int64_t)p.batch * p.heads * p.nchunks * p.nscan <= device_cu_count();

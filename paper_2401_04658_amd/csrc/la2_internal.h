@@ -86,7 +86,7 @@ struct ScanParams {
   // lambda^rem, rem = rows of that block), a reverse scan's start state enters right behind the chain's last
   // position likewise, and a chain of no positions passes its start state (or zero) on to fin.
   int32_t ragged_state;
-  // 16-bit half-block kernels only: non-zero = `states` holds the chunks' LOCAL states (no scan over
+  // 16-bit half-block, fp32 and head_dim 96 kernels: non-zero = `states` holds the chunks' LOCAL states (no scan over
   // them has run) and every workgroup forms its own start state from the local states of the chunks its scan
   // passes before: G <- init (or 0); for those chunks j in scan order: G <- lambda^(length of chunk j) G + L_j.
   // For a few chunks on a small problem that is cheaper than one more dependent launch between two short kernels.
@@ -94,7 +94,8 @@ struct ScanParams {
   // Head_dim 256, scans without the Norm epilogue: non-zero = two workgroups per scan, half the value features each
   int32_t value_split;
 };
-// self_prefix: most terms a start state is formed from (the caller's start state and the local states of three chunks)
+// self_prefix: most terms a start state is formed from in the 16-bit half-block kernels, which keep them in registers (the
+// caller's start state and the local states of three chunks); the fp32 and the head_dim 96 kernels loop over them
 constexpr int kMaxPrefixTerms = 4;
 
 // Which (batch row or sequence, head, chunk) a workgroup of a scan-type launch serves, and where that chunk's

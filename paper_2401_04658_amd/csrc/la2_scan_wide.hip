@@ -68,8 +68,8 @@ struct PlainAddr {
 // block as eight): waves w and w + 4 share value features, the first with the lower half of the key features, the
 // second with the upper half; the first leaves its part of the inter-block product in LDS, under the next block's
 // barrier, for the second to finish the block.  With half the state there is room for a third tile buffer (Z: the
-// workgroup's half of the rows only).  Forward + backward, bf16: 64 chains of 500 positions 129 -> 106 us, 21 chains of
-// 777 177 -> 142, 88 chains of 1000 241 -> 213; 120 chains of 2048 508 -> 470 (only the forward and the dQ scan, the
+// workgroup's half of the rows only).  Forward + backward, bf16: 64 chains of 500 positions 129 -> 96 us, 21 chains of
+// 777 177 -> 140, 88 chains of 1000 241 -> 213; 128 chains of 2048 502 -> 478 (only the forward and the dQ scan, the
 // reverse launch fills the units as it is).  What bounds it: vector instructions that every wave has whatever its
 // share (weights, addresses, waits): 3,900 cycles per block, half of them vector issue.
 template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT>
