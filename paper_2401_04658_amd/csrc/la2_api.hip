@@ -613,6 +613,94 @@ size_t bwd_workspace_need(const la2_desc* d, bool has_d_kv_final) {
   return split ? state_workspace(d, true).total : make_plan(d).workspace * (fuses_reverse_states(d) ? 2 : 1);
 }
 
+// Short sequences on few chains, 16-bit data, head_dim 64 / 128: the whole pass in one launch that looks back over all
+// positions (la2_short_bf16.hip) instead of the block recurrence.  Its work is the 64 x 64 position blocks on one side of the
+// diagonal, chains k (k + 1) / 2 for k = n / 64; the recurrence's is three (forward: two) dependent launches where it cuts the
+// sequences, one loop over them where it does not.  Short against recurrence, forward + backward in us (256 units; n, time):
+//   chains      d 64                                                 d 128
+//   4           1024 40 22, 2048 46 36, 3000 47 50                   1024 65 32, 2048 70 55, 3000 77 80
+//   16          777 40 22, 1500 48 38, 2048 50 54                    777 72 32, 1500 83 65, 2048 88 95
+//   32          777 43 27, 1024 44 34, 1500 59 56                    777 83 48, 1024 85 60, 1500 97 107
+//   64          512 43 25, 777 53 41, 1024 55 58                     512 69 44, 777 100 81, 1024 100 112
+//   128         256 27 20, 400 41 34, 512 48 41                      128 27 20, 256 45 38, 400 64 70
+//   256         64 15 12, 128 20 18, 256 33 34                       32 16 16, 64 21 18, 128 32 34
+//   512         64 20 17, 128 31 29                                  64 34 29, 128 57 67
+// A forward pass of one block of 32 is no faster (4.1 against 4.2 us), and few chains longer than 1536 lose in the forward
+// what they gain in the backward (4 chains of 2048, d 64: 16 against 17.5).  What the forward takes the backward takes too: the
+// chunk states that la2_bwd_saved reads have then not been written.
+bool short_sequences(const la2_desc* d, bool backward) {
+  if (!is16(d->dtype) || wide(d->head_dim)) return false;
+  if (g_chunk_tokens_override.load(std::memory_order_relaxed) > 0 || g_scan_variant.load(std::memory_order_relaxed) != 0)
+    return false;   // the caller plans, or asks for a kernel
+  const int n = d->seqlen;
+  const int64_t cus = device_cu_count(), chains = (int64_t)d->batch * d->heads;
+  const int64_t k = (n + 63) / 64, blocks = chains * (k * (k + 1) / 2);
+  if (n < 1 || n > (backward ? 3072 : 1536) || (!backward && n <= 32)) return false;
+  if (4 * chains <= cus || (2 * chains <= cus && d->head_dim == 64)) return blocks <= 20 * cus;
+  if (2 * chains <= cus) return blocks <= 5 * cus;
+  return chains <= 2 * cus && n <= (d->head_dim == 64 ? 128 : 64);
+}
+
+// Packed batches: where the recurrence would cut unequal lengths it has a map that takes only what the told total has room for;
+// that stays so.
+bool short_packed(const la2_desc* d, const Plan& pl, int64_t total_positions, bool backward) {
+  return short_sequences(d, backward) && (pl.wg_pairs == 0 || 4 * (int64_t)d->seqlen * d->batch <= 5 * total_positions);
+}
+
+// A start state and the state that is handed out in the same place: the one launch has workgroups that read the first while
+// others write the second.
+bool same_state(const la2_desc* d, const float* fin, const float* init) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(fin), b = reinterpret_cast<uintptr_t>(init);
+  const uintptr_t bytes = (uintptr_t)d->batch * d->heads * d->head_dim * d->head_dim * sizeof(float);
+  return fin != nullptr && init != nullptr && a < b + bytes && b < a + bytes;
+}
+
+la2::ShortParams short_params(const la2_desc* d, const float* lambda, const int32_t* cu) {
+  la2::ShortParams p{};
+  p.lambda = lambda;
+  p.stride_b = d->stride_b; p.stride_h = d->stride_h; p.stride_n = d->stride_n;
+  p.batch = d->batch; p.heads = d->heads; p.n = d->seqlen;
+  p.cu_seqlens = cu;
+  return p;
+}
+
+la2_status run_short_fwd(const la2_desc* d, const void* q, const void* k, const void* v, const float* lambda,
+                         const float* kv_init, void* o, float* kv_final, float* rstd, float eps, int rstd_stride,
+                         const int32_t* cu, hipStream_t s) {
+  la2::ShortParams p = short_params(d, lambda, cu);
+  p.nscan = 1;
+  p.x[0] = q; p.y[0] = k; p.z[0] = v; p.w[0] = o;
+  p.init[0] = kv_init;
+  p.state_y = k; p.state_z = v;
+  p.state_init = kv_init;
+  p.fin = kv_final;
+  p.rstd = rstd; p.eps = eps; p.rstd_stride = rstd_stride;
+  return la2::launch_short_scans(d->dtype, d->head_dim, p, s) == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
+}
+
+// dQ, dV, dK and the start state's gradient: the three scans of la2_bwd (bwd_saved_one_call)
+la2_status run_short_bwd(const la2_desc* d, const void* q, const void* k, const void* v, const void* d_o,
+                         const float* lambda, const float* kv_init, const float* d_kv_final, void* dq, void* dk, void* dv,
+                         float* d_kv_init, const int32_t* cu, hipStream_t s) {
+  la2::ShortParams p = short_params(d, lambda, cu);
+  p.nscan = 3;
+  p.rev = 6;
+  p.x[0] = d_o; p.y[0] = v; p.z[0] = k; p.w[0] = dq;
+  p.x[1] = k; p.y[1] = q; p.z[1] = d_o; p.w[1] = dv;
+  p.x[2] = v; p.y[2] = d_o; p.z[2] = q; p.w[2] = dk;
+  p.init[0] = kv_init; p.init[1] = d_kv_final; p.init[2] = d_kv_final;
+  p.init_transposed = 5;   // dQ reads KV^T, dK dKV^T
+  p.state_y = q; p.state_z = d_o;
+  p.state_init = d_kv_final;
+  p.state_rev = 1;
+  if (same_state(d, d_kv_init, kv_init) || same_state(d, d_kv_init, d_kv_final)) {   // ... the state in a launch behind them
+    if (la2::launch_short_scans(d->dtype, d->head_dim, p, s) != hipSuccess) return LA2_ERR_LAUNCH;
+    p.nscan = 0;
+  }
+  p.fin = d_kv_init;
+  return la2::launch_short_scans(d->dtype, d->head_dim, p, s) == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
+}
+
 la2::RecurParams recur_params(const la2_desc* d, const float* lambda, int t0, int t1, bool reverse) {
   la2::RecurParams p{};
   p.lambda = lambda;
@@ -728,6 +816,8 @@ la2_status fwd_state_one_call(const la2_desc* desc, const void* q, const void* k
   if (pl.workspace > 0 && (workspace == nullptr || workspace_bytes < pl.workspace)) return LA2_ERR_WORKSPACE;
   if (pl.workspace > 0 && !aligned(workspace, 256)) return LA2_ERR_WORKSPACE;
   if (check_only) return LA2_OK;
+  if (short_sequences(desc, false) && !same_state(desc, kv_final, kv_init))
+    return run_short_fwd(desc, q, k, v, lambda, kv_init, o, kv_final, rstd, eps, desc->seqlen, nullptr, s);
   if (blocks.seqlen > 0) {
     ScanArgs a{q, k, v, o};
     a.init = kv_init;
@@ -891,6 +981,8 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return LA2_ERR_WORKSPACE;
   if (need > 0 && !aligned(workspace, 256)) return LA2_ERR_WORKSPACE;
   if (check_only) return LA2_OK;
+  if (short_sequences(desc, true))
+    return run_short_bwd(desc, q, k, v, d_o, lambda, kv_init, d_kv_final, dq, dk, dv, d_kv_init, nullptr, s);
   float* handoff = split ? reinterpret_cast<float*>(static_cast<char*>(workspace) + sw.chunk_states) : nullptr;
   void* rev_workspace = workspace;
   if (fuse) {
@@ -1071,6 +1163,8 @@ la2_status fwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 256)))
     return LA2_ERR_WORKSPACE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+  if (short_packed(desc, pl, total_positions, false) && !same_state(desc, kv_final, kv_init))
+    return run_short_fwd(desc, q, k, v, lambda, kv_init, o, kv_final, rstd, eps, (int)total_positions, cu_seqlens, s);
   ScanArgs a{q, k, v, o};
   a.cu = cu_seqlens;
   a.rstd = rstd;   // packed layout [heads][total_positions]
@@ -1124,6 +1218,8 @@ la2_status bwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   const size_t need = pl.map_bytes + pl.workspace * (fuse ? 2 : 1);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 256)))
     return LA2_ERR_WORKSPACE;
+  if (short_packed(desc, pl, total_positions, true))
+    return run_short_bwd(desc, q, k, v, d_o, lambda, kv_init, d_kv_final, dq, dk, dv, d_kv_init, cu_seqlens, s);
   // the three scans of la2_bwd, each chain a sequence of its own length; states as in la2_bwd_state
   ScanArgs for_dq{d_o, v, k, dq}, for_dv{k, q, d_o, dv}, for_dk{v, d_o, q, dk};
   for_dq.cu = for_dv.cu = for_dk.cu = cu_seqlens;

@@ -250,6 +250,33 @@ hipError_t launch_recur(int head_dim, int dtype, int batch, int ninst, const Rec
 // blocks of 32 positions, the state after position t1 - 1 exact for any t1 - t0.  Needs t0 < t1.
 hipError_t launch_tail_bf16(int dtype, int head_dim, int batch, const RecurParams& p, hipStream_t s);
 
+// Short sequences on few chains, 16-bit data, head_dim 64 / 128: up to three scans and the state of one of them in one launch,
+// every row block from all the positions it depends on (no chunk states, no workspace).  Scan i is as ScanParams describes;
+// bit i of rev: reverse; its start state init[i] (bit i of init_transposed: stored transposed) must not share memory with
+// fin, which is written by workgroups of their own.
+struct ShortParams {
+  const void* x[3];
+  const void* y[3];
+  const void* z[3];
+  void* w[3];
+  const float* init[3];
+  int32_t nscan, rev, init_transposed;
+  // the state that is handed out (fin, nullptr: none): of the scan with these y, z and start state
+  const void* state_y;
+  const void* state_z;
+  const float* state_init;
+  float* fin;
+  int32_t state_rev;
+  const float* lambda;
+  int64_t stride_b, stride_h, stride_n;  // elements
+  int32_t batch, heads, n;
+  const int32_t* cu_seqlens;   // packed sequences, n the longest; or nullptr
+  float* rstd;                 // Norm epilogue of scan 0 (nscan 1): as ScanParams
+  float eps;
+  int32_t rstd_stride;
+};
+hipError_t launch_short_scans(int dtype, int head_dim, const ShortParams& p, hipStream_t s);
+
 // Backward of the Norm epilogue, row by row: du = rstd * (g - o * mean_j(g_j o_j)) with o the normalised
 // output and g its gradient; o, g, du share the layout given by the strides (elements), rstd is
 // [batch * heads][n] fp32.
