@@ -110,6 +110,7 @@ struct Plan {
   int nlong = 0;        // sequences of more than one chunk the plan has room for (the state scan's units)
   int64_t wg_slots = 0; // state slots (per head) the workspace has room for
   int even = 0;         // ScanParams::even_chunks
+  int64_t total = 0;    // positions of a packed batch, all sequences together; 0: not known, or a dense batch
   size_t map_bytes = 0;
 };
 
@@ -303,7 +304,19 @@ Plan packed_call_plan(const la2_desc* d, int64_t total_positions, const void* wo
   const Plan pl = make_plan_varlen(d, total_positions);
   const bool usable = workspace != nullptr && workspace_bytes >= pl.map_bytes &&
                       (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;
-  return pl.wg_pairs > 0 && pl.nchunks == 1 && !usable ? Plan{1, pl.chunk_tokens, 0} : pl;
+  Plan run = pl.wg_pairs > 0 && pl.nchunks == 1 && !usable ? Plan{1, pl.chunk_tokens, 0} : pl;
+  run.total = total_positions;
+  return run;
+}
+
+// ScanParams::keep, by the bytes of one tensor (q, k, v, o, ...).  Forward + backward with the tiles kept against non-temporal
+// loads (both with streaming stores at head_dim 64 / 128), bf16, inputs changing from pass to pass: head_dim 64 / 128, 16 MiB
+// 0.97-1.01, 32 MiB 0.95-0.97, 64 MiB 0.94-0.97, 128 MiB 1.00-1.04, 256 MiB 1.03-1.07; head_dim 96, 18 and 72 MiB 0.91, 144
+// 0.97-0.99, 288 MiB 1.00; head_dim 256, 32 MiB 0.96, 128 MiB 0.99, 256 MiB 1.00-1.03.
+int keep_tiles(const la2_desc* d, const Plan& pl) {
+  const int64_t rows = (pl.total > 0 ? pl.total : (int64_t)d->batch * d->seqlen) * d->heads;
+  const int64_t most = (int64_t)(wide(d->head_dim) ? 160 : 96) << 20;
+  return rows * d->head_dim * elem_size(d->dtype) <= most;
 }
 
 // Grid sizes of every launch a plan leads to, checked on the host before the first one: the scan kernels take
@@ -482,6 +495,7 @@ la2::ScanParams base_params(const la2_desc* d, const Plan& pl, const float* lamb
   p.even_chunks = pl.even;
   p.variant = g_scan_variant.load(std::memory_order_relaxed);
   p.self_prefix = self_prefix(d, pl, cu) ? 1 : 0;
+  p.keep = keep_tiles(d, pl);
   return p;
 }
 

@@ -137,8 +137,9 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // Direct global -> LDS copy, 16 bytes per lane: lane i reads base + voff (its own byte offset) and
-// writes LDS byte address lds_base + 16 i (lds_base is wave-uniform and travels in M0).  The tiles are
-// read exactly once, so the load carries the non-temporal hint (measured 5-10 % faster).
+// writes LDS byte address lds_base + 16 i (lds_base is wave-uniform and travels in M0).  The load carries the
+// non-temporal hint: for tensors that are too large to be found in a cache when the next launch reads them (a stream
+// keeps out of the way of what can be: see ScanParams::keep).
 // Written as inline assembly on purpose: the compiler then keeps no record of an asynchronous LDS
 // write and inserts no vmcnt(0) wait in front of later LDS reads (it cannot always prove that they
 // touch a different tile buffer).  Completion is tracked by hand: see the s_waitcnt at the end of
@@ -150,7 +151,8 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
                : "m0", "memory");
 }
 
-// The same for tiles that a second workgroup on the XCD reads as well: without the hint they stay in its L2.
+// The same without the hint, for tiles that another workgroup or the next launch reads as well: they stay in the XCD's L2 and
+// in the memory-side cache.
 __device__ __forceinline__ void dma16_shared(const void* base, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
@@ -249,7 +251,7 @@ struct TileLoader {
       col[i] = 8 * ((q % C::CPR) ^ swz<D>(q / C::CPR));
     }
   }
-  template <typename E>
+  template <bool SHARED = false, typename E>
   __device__ __forceinline__ void issue(E (*sT)[C::TILE], int blk) const {
 #pragma unroll
     for (int i = 0; i < DMA_PER_WAVE; i++) {
@@ -257,7 +259,11 @@ struct TileLoader {
       // 32-bit byte offset from the (wave-uniform) chain base; the host checked that a chain spans < 4 GiB
       const uint32_t off = ((uint32_t)pos * stride_n + (uint32_t)col[i]) * 2u;
 #pragma unroll
-      for (int t = 0; t < NTILES; t++) dma16(g[t], off, lds_offset(&sT[t][0]) + wave_lds + 1024u * i);
+      for (int t = 0; t < NTILES; t++) {
+        const uint32_t at = lds_offset(&sT[t][0]) + wave_lds + 1024u * i;
+        if (SHARED) dma16_shared(g[t], off, at);
+        else dma16(g[t], off, at);
+      }
     }
   }
   // The same loads one at a time (j = 0 .. NTILES DMA_PER_WAVE - 1), so that they can be spread over

@@ -17,6 +17,9 @@ using namespace bf16k;
 // buffers, the tiles of block it + NBUF - 1 stream in while block it is used.  Every block's loads are
 // issued unconditionally (past the chunk's end as dummy loads of one cache line), so the count of
 // outstanding loads is the same in every iteration and one s_waitcnt immediate serves.
+// The loads carry no non-temporal hint at any size: the scan behind this launch reads the same tiles again.  (Forward +
+// backward of the packed 65,536 positions, sequences of up to 8192, H 16, d 128, with the streaming stores of the scans: 968 us
+// with the hint, 914 without; one chain of 65,536, H 16: 874 and 868.  Without those stores it lost at the latter: 867, 897.)
 // Two waves per SIMD: 2 NT waves (8 at d = 128, 4 at d = 64); wave w owns value features 32 (w % NT) .. + 31 and
 // the key-feature tiles of half w / NT of the state slice, so that one wave's LDS and MFMA latencies hide behind
 // the other's instructions (a wave issues one instruction at a time).
@@ -64,7 +67,7 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
     uint32_t doff[Loader::DMA_PER_WAVE];
     loader.offsets(REV ? blk_hi - 1 - it : blk_lo + it, it < nblk, doff);
 #pragma unroll
-    for (int j = 0; j < NDMA; j++) loader.issue_one(buf, doff, j);
+    for (int j = 0; j < NDMA; j++) loader.template issue_one<true>(buf, doff, j);   // the scan reads these tiles again
   };
   if (nblk <= 0) return;
 #pragma unroll

@@ -93,6 +93,10 @@ struct ScanParams {
   int32_t self_prefix;
   // Head_dim 256, scans without the Norm epilogue: non-zero = two workgroups per scan, half the value features each
   int32_t value_split;
+  // 16-bit scans and the pre-pass of head_dim 96 / 256, non-zero: the tiles stay in the caches.  Launches of one pass read the same
+  // tensors two or three times; where those are small enough to be found in the 256 MiB memory-side cache (keep_tiles in
+  // la2_api.hip) their loads carry no non-temporal hint.
+  int32_t keep;
 };
 // self_prefix: most terms a start state is formed from in the 16-bit half-block kernels, which keep them in registers (the
 // caller's start state and the local states of three chunks); the fp32 and the head_dim 96 kernels loop over them

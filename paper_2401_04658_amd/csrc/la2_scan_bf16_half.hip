@@ -43,10 +43,13 @@ constexpr int kBH = 32;
 // by lambda^rem, which gives the state right after the last position.  Reverse: a start state that enters behind
 // such a block reaches row r with lambda^(rem-1-r) and is carried on with lambda^rem.  A chain without positions
 // hands its start state (or zero) to fin.  All of it is off the per-block path of a chain's other blocks.
-template <typename E, int D, bool REV, bool TWIN, int NBUF, bool NORM = false, bool ACC = false, bool RS = false>
+//
+// KEEP: the tile loads without the non-temporal hint (ScanParams::keep).
+template <typename E, int D, bool KEEP, bool REV, bool TWIN, int NBUF, bool NORM = false, bool ACC = false, bool RS = false>
 __global__ __launch_bounds__(((TWIN || ACC) ? 4 : 2) * D, ((TWIN || ACC) ? 1 : 2) * (128 / D))
 void scan_bf16_half_kernel(ScanParams p) {
   static_assert(D == 128 || D == 64, "head_dim");
+  static_assert(REV == TWIN, "forward: one scan; reverse: both scans of Algorithm 2's second loop");
   static_assert(!NORM || (!REV && !TWIN), "the Norm epilogue belongs to the forward pass");
   static_assert(!ACC || (!REV && !TWIN && !NORM), "the accumulating wave group rides on a plain forward scan");
   static_assert(!RS || !ACC, "ragged-end states: forward scans (with or without the Norm epilogue) and reverse scans");
@@ -63,10 +66,12 @@ void scan_bf16_half_kernel(ScanParams p) {
   // which is dead by then: see the epilogue.
   __shared__ __attribute__((aligned(16))) E sW[ACC ? SW : NW][NORM ? LW : 32 * LW];
   float* const sRed = NormExchange<NORM ? 2 * 32 * SW : 0>::get();   // [block parity][position][wave]
-  // Cache policy of the output stores (buffer instruction bits: 2 = nt, 16 = sc1).  Measured: the twin
-  // workgroup, a third of whose traffic is stores, runs 9-13 % faster with streaming write-through stores;
-  // the plain kernel is 8 % slower with any non-temporal store policy and keeps the default.
-  constexpr int kStorePolicy = TWIN ? 18 : 0;
+  // Cache policy of the output stores (buffer instruction bits: 2 = nt, 16 = sc1): streaming, write-through.  Nobody here reads
+  // an output again, and one that stays out of the caches leaves them to the inputs, which the next launch reads again.
+  // Forward + backward against the default policy in the plain scans (which only the twin streamed past before, 9-13 %):
+  // tensors of 16 MiB 0.92-0.94, 64 MiB 0.91-0.96, 128 MiB 0.92-0.97, 256 MiB in chunks 0.95-0.96, uncut 0.98 (a forward
+  // pass alone, repeated on the same 1 GiB of tensors, 1.06-1.08; nt without sc1 1.01-1.02).
+  constexpr int kStorePolicy = 18;
   constexpr int NDMA = NTL * Loader::DMA_PER_WAVE;   // direct loads per wave and block
   constexpr int NST = 32 * 4 / 64 + (NORM ? 1 : 0);   // stores per lane and block: 16-byte output stores, r
   constexpr int DMA_PER_SLOT = (NDMA + KS - 1) / KS;   // direct loads issued in each slot of phase 1
@@ -78,21 +83,10 @@ void scan_bf16_half_kernel(ScanParams p) {
 
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l32 = l & 31, hh = l >> 5;
   const int dvt = w % SW;
-  int which = 0, wg = (int)blockIdx.x;
+  int which = 0;
+  const int wg = (int)blockIdx.x;
   const int group = __builtin_amdgcn_readfirstlane(w / SW);   // TWIN: which scan; ACC: scan waves or accumulating waves
-  if (TWIN) {
-    which = group;
-  } else if (ACC) {
-    // one scan only
-  } else if (p.nscan == 2) {   // same pairing as scan_bf16_kernel
-    if (((gridDim.x >> 1) & 7) == 0) {
-      which = (int)(blockIdx.x >> 3) & 1;
-      wg = (int)((blockIdx.x >> 4) << 3) | (int)(blockIdx.x & 7);
-    } else {
-      which = (int)(blockIdx.x & 1);
-      wg = (int)(blockIdx.x >> 1);
-    }
-  }
+  if (TWIN) which = group;
   // In a twin workgroup the two wave groups run two instantiations of the body, so that each sees
   // its tiles at compile-time LDS offsets.
   auto run = [&](auto wh_tag) __attribute__((always_inline)) {
@@ -166,7 +160,7 @@ void scan_bf16_half_kernel(ScanParams p) {
   // these too: they are older.)
 #pragma unroll
   for (int j = 0; j < NBUF - 1; j++)
-    if (j < nblk) loader.issue(sT[j], REV ? blk_hi - 1 - j : blk_lo + j);
+    if (j < nblk) loader.template issue<KEEP>(sT[j], REV ? blk_hi - 1 - j : blk_lo + j);
 
   if constexpr (ACC) {
     if (group == 1) {
@@ -190,7 +184,7 @@ void scan_bf16_half_kernel(ScanParams p) {
         uint32_t doff[Loader::DMA_PER_WAVE];
         loader.offsets(blk_lo + it + (NBUF - 1), has_ahead, doff);
 #pragma unroll
-        for (int j = 0; j < NDMA; j++) loader.issue_one(sT[(cur + NBUF - 1) % NBUF], doff, j);
+        for (int j = 0; j < NDMA; j++) loader.template issue_one<KEEP>(sT[(cur + NBUF - 1) % NBUF], doff, j);
         const E* tY = sT[cur][NTL - 1];
         const E* tZ = sT[cur][0];
         ex8<E> zf[2], yt[2][NT];
@@ -443,7 +437,7 @@ void scan_bf16_half_kernel(ScanParams p) {
       if (ks + 1 < KS) { sa = state_operand(ks + 1); pin(sa); }
 #pragma unroll
       for (int u = 0; u < DMA_PER_SLOT; u++)
-        if (ks * DMA_PER_SLOT + u < NDMA) loader.issue_one(sAhead, doff, ks * DMA_PER_SLOT + u);
+        if (ks * DMA_PER_SLOT + u < NDMA) loader.template issue_one<KEEP>(sAhead, doff, ks * DMA_PER_SLOT + u);
       if (ks < 2) zf[ks] = la.read_cols(tZ, 16 * ks, dvt);
       if (ks >= 2 && (ks & 1) == 0) {   // state tile ks / 2 - 1: both operands made in slots <= ks - 1
         const int t = (ks >> 1) - 1;
@@ -590,45 +584,42 @@ void scan_bf16_half_kernel(ScanParams p) {
 }  // namespace
 
 namespace {
-template <typename E, int D>
+template <typename E, int D, bool KEEP>
 hipError_t launch_half(bool reverse, bool twin, const ScanParams& p, hipStream_t s) {
-  const int64_t grid = (p.wg_map != nullptr ? (int64_t)p.wg_pairs * p.heads : (int64_t)p.batch * p.heads * p.nchunks) * p.nscan;
+  if (reverse != twin) return hipErrorInvalidValue;   // a reverse launch is the twin, a forward launch one scan
+  const int64_t grid = p.wg_map != nullptr ? (int64_t)p.wg_pairs * p.heads : (int64_t)p.batch * p.heads * p.nchunks;
   // Three tile buffers in every case.  More buffers (5 for a plain, 4 for a twin workgroup that has the
   // compute unit to itself) measured no faster: such launches are bound by the memory system, not by the
   // bytes a workgroup keeps in flight.
-  constexpr int kPlain = 2 * D, kDouble = 4 * D;   // threads: one wave per 32 value features, or two such groups
+  const dim3 g((unsigned)grid), plain(2 * D), twice(4 * D);   // threads: one wave per 32 value features, or two such groups
   if (p.ragged_state != 0) {   // the host pairs this only with a reverse twin launch or a forward scan without ACC
-    if (twin && reverse)
-      hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, true, true, 3, false, false, true>), dim3((unsigned)(grid / 2)),
-                         dim3(kDouble), 0, s, p);
-    else if (!twin && !reverse && p.acc_states == nullptr && p.rstd == nullptr)
-      hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, false, false, 3, false, false, true>), dim3((unsigned)grid),
-                         dim3(kPlain), 0, s, p);
-    else if (!twin && !reverse && p.acc_states == nullptr)
-      hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, false, false, 3, true, false, true>), dim3((unsigned)grid),
-                         dim3(kPlain), 0, s, p);
-    else
-      return hipErrorInvalidValue;
-  } else if (twin) {
-    dim3 gt((unsigned)(grid / 2)), bt(kDouble);
-    if (reverse) hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, true, true, 3>), gt, bt, 0, s, p);
-    else         hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, false, true, 3>), gt, bt, 0, s, p);
+    if (p.acc_states != nullptr) return hipErrorInvalidValue;
+    if (reverse) hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, true, true, 3, false, false, true>), g, twice, 0, s, p);
+    else if (p.rstd == nullptr)
+      hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, false, false, true>), g, plain, 0, s, p);
+    else hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, true, false, true>), g, plain, 0, s, p);
+  } else if (reverse) {
+    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, true, true, 3>), g, twice, 0, s, p);
+  } else if (p.acc_states != nullptr) {
+    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, false, true>), g, twice, 0, s, p);
+  } else if (p.rstd != nullptr) {
+    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, true>), g, plain, 0, s, p);
   } else {
-    dim3 g((unsigned)grid), b(kPlain);
-    if (reverse) hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, true, false, 3>), g, b, 0, s, p);
-    else if (p.acc_states != nullptr)
-      hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, false, false, 3, false, true>), g, dim3(kDouble), 0, s, p);
-    else if (p.rstd != nullptr) hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, false, false, 3, true>), g, b, 0, s, p);
-    else         hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, false, false, 3>), g, b, 0, s, p);
+    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3>), g, plain, 0, s, p);
   }
   return hipGetLastError();
+}
+template <typename E>
+hipError_t launch_half_of(int head_dim, bool reverse, bool twin, const ScanParams& p, hipStream_t s) {
+  if (head_dim == 64)
+    return p.keep != 0 ? launch_half<E, 64, true>(reverse, twin, p, s) : launch_half<E, 64, false>(reverse, twin, p, s);
+  return p.keep != 0 ? launch_half<E, 128, true>(reverse, twin, p, s) : launch_half<E, 128, false>(reverse, twin, p, s);
 }
 }  // namespace
 
 hipError_t launch_scan_bf16_half(int dtype, int head_dim, bool reverse, bool twin, const ScanParams& p, hipStream_t s) {
-  if (head_dim == 64)
-    return dtype == kF16 ? launch_half<_Float16, 64>(reverse, twin, p, s) : launch_half<__bf16, 64>(reverse, twin, p, s);
-  return dtype == kF16 ? launch_half<_Float16, 128>(reverse, twin, p, s) : launch_half<__bf16, 128>(reverse, twin, p, s);
+  return dtype == kF16 ? launch_half_of<_Float16>(head_dim, reverse, twin, p, s)
+                       : launch_half_of<__bf16>(head_dim, reverse, twin, p, s);
 }
 
 }  // namespace la2

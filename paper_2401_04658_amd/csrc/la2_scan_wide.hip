@@ -72,7 +72,8 @@ struct PlainAddr {
 // 777 177 -> 140, 88 chains of 1000 241 -> 213; 128 chains of 2048 502 -> 478 (only the forward and the dQ scan, the
 // reverse launch fills the units as it is).  What bounds it: vector instructions that every wave has whatever its
 // share (weights, addresses, waits): 3,900 cycles per block, half of them vector issue.
-template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT>
+// KEEP: the tile loads without the non-temporal hint (ScanParams::keep).
+template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT, bool KEEP>
 __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
   static_assert(!SPLIT || (D == 256 && !STATE_ONLY && !NORM), "half the value features per workgroup: plain scans of head_dim 256");
   static_assert(!NORM || (!REV && !STATE_ONLY), "the Norm epilogue belongs to the forward scan");
@@ -183,14 +184,16 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
     return ((uint32_t)min(blk * B + zrow + 4 * i, n - 1) * stride_n + (uint32_t)c) * 2u;
   };
   auto issue_z = [&](E* tile, int blk, int i) __attribute__((always_inline)) {
-    dma16(gz, z_offset(blk, i), lds_offset(tile) + 1024u * (2u * (uint32_t)(w & 3) + (uint32_t)i));
+    const uint32_t at = lds_offset(tile) + 1024u * (2u * (uint32_t)(w & 3) + (uint32_t)i);
+    if (KEEP) dma16_shared(gz, z_offset(blk, i), at);
+    else dma16(gz, z_offset(blk, i), at);
   };
   auto block_at = [&](int it) { return REV ? blk_hi - 1 - it : blk_lo + it; };
   auto issue_first = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < NBUF - 1; j++) {
       if (loads && j < nblk) {
-        loader.issue(sT[j], block_at(j));
+        loader.template issue<KEEP>(sT[j], block_at(j));
         if constexpr (SPLIT) {
           issue_z(sZ[j], block_at(j), 0);
           issue_z(sZ[j], block_at(j), 1);
@@ -451,7 +454,7 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
     if constexpr (SHP) {
       loader.offsets(block_at(it + NBUF - 1), load_next, doff);
     } else {
-      if (load_next) loader.issue(sT[ahead], block_at(it + 1));
+      if (load_next) loader.template issue<KEEP>(sT[ahead], block_at(it + 1));
     }
     const int nv = min(B, n - blk * B);   // valid rows of this block
     if constexpr (SHP) {
@@ -564,7 +567,7 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
           for (int u = 0; u < PER; u++)
             if (ks * PER + u < NDMA && load_next) {
               if (SPLIT && ks * PER + u >= NDMA - 2) issue_z(sZ[ahead], block_at(it + NBUF - 1), ks * PER + u - (NDMA - 2));
-              else loader.template issue_one<SPLIT>(sT[ahead], doff, ks * PER + u);
+              else loader.template issue_one<SPLIT || KEEP>(sT[ahead], doff, ks * PER + u);
             }
         }
         pin(acc);
@@ -696,21 +699,21 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
   }
 }
 
-template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM = false, bool TWIN = false>
+template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool KEEP>
 __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) void scan_wide_kernel(ScanParams p) {
-  scan_wide_body<E, D, REV, STATE_ONLY, NORM, TWIN, false>(p);
+  scan_wide_body<E, D, REV, STATE_ONLY, NORM, TWIN, false, KEEP>(p);
 }
-template <typename E, int D, bool REV>
+template <typename E, int D, bool REV, bool KEEP>
 __global__ __launch_bounds__(2 * D, 2) void scan_wide_split_kernel(ScanParams p) {
-  scan_wide_body<E, D, REV, false, false, false, true>(p);
+  scan_wide_body<E, D, REV, false, false, false, true, KEEP>(p);
 }
 
-template <typename E, int D>
+template <typename E, int D, bool KEEP>
 hipError_t launch_wide(bool reverse, bool state_only, const ScanParams& p, hipStream_t s) {
   const dim3 g((unsigned)((int64_t)p.batch * p.heads * p.nchunks * (state_only ? 1 : p.nscan))), b(2 * D);
   if constexpr (D == 96) {
     if (!state_only && reverse && p.nscan == 2 && p.y[1] == p.z[0] && p.z[1] == p.y[0]) {
-      hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, true>),
+      hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, true, KEEP>),
                          dim3((unsigned)((int64_t)p.batch * p.heads * p.nchunks)), dim3(4 * D), 0, s, p);
       return hipGetLastError();
     }
@@ -718,21 +721,25 @@ hipError_t launch_wide(bool reverse, bool state_only, const ScanParams& p, hipSt
   if constexpr (D == 256) {
     if (!state_only && p.rstd == nullptr && p.value_split != 0) {
       const dim3 g2(2 * g.x);
-      if (reverse) hipLaunchKernelGGL((scan_wide_split_kernel<E, D, true>), g2, b, 0, s, p);
-      else         hipLaunchKernelGGL((scan_wide_split_kernel<E, D, false>), g2, b, 0, s, p);
+      if (reverse) hipLaunchKernelGGL((scan_wide_split_kernel<E, D, true, KEEP>), g2, b, 0, s, p);
+      else         hipLaunchKernelGGL((scan_wide_split_kernel<E, D, false, KEEP>), g2, b, 0, s, p);
       return hipGetLastError();
     }
   }
   if (!state_only && !reverse && p.rstd != nullptr) {
-    hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, true>), g, b, 0, s, p);
+    hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, true, false, KEEP>), g, b, 0, s, p);
   } else if (state_only) {
-    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, true>), g, b, 0, s, p);
-    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, true>), g, b, 0, s, p);
+    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, true, false, false, KEEP>), g, b, 0, s, p);
+    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, true, false, false, KEEP>), g, b, 0, s, p);
   } else {
-    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false>), g, b, 0, s, p);
-    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false>), g, b, 0, s, p);
+    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, false, KEEP>), g, b, 0, s, p);
+    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, false, false, KEEP>), g, b, 0, s, p);
   }
   return hipGetLastError();
+}
+template <typename E, int D>
+hipError_t launch_wide_of(bool reverse, bool state_only, const ScanParams& p, hipStream_t s) {
+  return p.keep != 0 ? launch_wide<E, D, true>(reverse, state_only, p, s) : launch_wide<E, D, false>(reverse, state_only, p, s);
 }
 
 }  // namespace
@@ -741,10 +748,10 @@ hipError_t launch_scan_wide(int dtype, int head_dim, bool reverse, bool state_on
                             hipStream_t s) {
   if ((int64_t)p.batch * p.heads * p.nchunks == 0 || p.n == 0) return hipSuccess;
   if (head_dim == 256)
-    return dtype == kF16 ? launch_wide<_Float16, 256>(reverse, state_only, p, s)
-                         : launch_wide<__bf16, 256>(reverse, state_only, p, s);
-  return dtype == kF16 ? launch_wide<_Float16, 96>(reverse, state_only, p, s)
-                       : launch_wide<__bf16, 96>(reverse, state_only, p, s);
+    return dtype == kF16 ? launch_wide_of<_Float16, 256>(reverse, state_only, p, s)
+                         : launch_wide_of<__bf16, 256>(reverse, state_only, p, s);
+  return dtype == kF16 ? launch_wide_of<_Float16, 96>(reverse, state_only, p, s)
+                       : launch_wide_of<__bf16, 96>(reverse, state_only, p, s);
 }
 
 }  // namespace la2
