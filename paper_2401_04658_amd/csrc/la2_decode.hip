@@ -30,9 +30,10 @@ __device__ __forceinline__ void store_elem(void* p, int64_t i, float x) {
   else reinterpret_cast<float*>(p)[i] = x;
 }
 
+// STREAM: the state passes by the caches (loads non-temporal, stores non-temporal and written through): see stream_state.
 // NORM: the output row is normalised (eq. (2) read as root-mean-square normalisation over the head's features:
 // o <- o / sqrt(mean_j o_j^2 + eps)) before it is stored.
-template <int D, int DT, bool NORM = false>
+template <int D, int DT, bool NORM, bool STREAM>
 __global__ __launch_bounds__(threads_for(D)) void decode_kernel(const void* q, const void* k, const void* v,
                                                           const float* lambda, float* kv, void* o, int heads,
                                                           float eps) {
@@ -52,10 +53,16 @@ __global__ __launch_bounds__(threads_for(D)) void decode_kernel(const void* q, c
     sv[tid] = load_elem<DT>(v, chain * D + tid);
   }
   const int cg = tid % TPR, rg = tid / TPR;
-  float4* state = reinterpret_cast<float4*>(kv + chain * (int64_t)(D * D));
-  float4 s[ITER];
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  typedef __attribute__((ext_vector_type(4))) int i32x4;
+  f32x4* state = reinterpret_cast<f32x4*>(kv + chain * (int64_t)(D * D));
+  const __amdgpu_buffer_rsrc_t streamed = __builtin_amdgcn_make_buffer_rsrc(state, 0, D * D * 4, 0x00027000);
+  f32x4 s[ITER];
 #pragma unroll
-  for (int it = 0; it < ITER; it++) s[it] = state[(int64_t)(rg + RG * it) * TPR + cg];
+  for (int it = 0; it < ITER; it++) {
+    const f32x4* const at = &state[(int64_t)(rg + RG * it) * TPR + cg];
+    s[it] = STREAM ? __builtin_nontemporal_load(at) : *at;
+  }
   __syncthreads();
   const float4 v4 = *reinterpret_cast<const float4*>(&sv[4 * cg]);
   float4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -68,11 +75,9 @@ __global__ __launch_bounds__(threads_for(D)) void decode_kernel(const void* q, c
     t.y = fmaf(lam, s[it].y, ki * v4.y);
     t.z = fmaf(lam, s[it].z, ki * v4.z);
     t.w = fmaf(lam, s[it].w, ki * v4.w);
-    {  // streaming (non-temporal) store of the new state row piece: measured 4-7 % faster than the default policy
-      typedef __attribute__((ext_vector_type(4))) float f32x4;
-      const f32x4 tv = {t.x, t.y, t.z, t.w};
-      __builtin_nontemporal_store(tv, reinterpret_cast<f32x4*>(&state[(int64_t)i * TPR + cg]));
-    }
+    const f32x4 tv = {t.x, t.y, t.z, t.w};
+    if (STREAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, tv), streamed, (i * TPR + cg) * 16, 0, 18);   // nt, sc1
+    else        __builtin_nontemporal_store(tv, &state[(int64_t)i * TPR + cg]);   // (4-7 % faster than the default policy)
     acc.x = fmaf(qi, t.x, acc.x);
     acc.y = fmaf(qi, t.y, acc.y);
     acc.z = fmaf(qi, t.z, acc.z);
@@ -115,18 +120,35 @@ hipError_t launch_state_copy(float* dst, const float* src, int64_t count, hipStr
   return hipGetLastError();
 }
 
+// Whether a decode step's states pass by the caches.  A state that the 256 MiB memory-side cache still holds when the next step
+// comes is better left there; a model of several layers goes through all their states before it returns to the first one,
+// and what does not fit costs more than a stream.  Decode step, head_dim 128, through the caches (stores nt) against streaming,
+// us: states of 64, 128, 256 MiB, one state used again at once 22.5 23.4, 43 47, 82 91; three in turn 22.5 23.4, 44 47, 106 92;
+// twelve in turn 29.7 23.4, 55 47, 106 91.  Eight tokens a launch: 256 MiB 93 103, 114 104, 114 103.  The line: from where two
+// states never fit together, so that a state is found again only if nothing else runs in between.  Head_dim 256, whose
+// workgroup has a compute unit to itself and loads and stores by turns, gains nothing (three of 256 MiB in turn 105, 106).
+bool stream_state(int64_t chains, int head_dim) {
+  return head_dim != 256 && chains * head_dim * head_dim * (int64_t)sizeof(float) >= (int64_t)160 << 20;
+}
+
 hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const void* q, const void* k,
                          const void* v, const float* lambda, float* kv, void* o, bool norm, float eps,
                          hipStream_t s) {
   const int64_t chains = (int64_t)batch * heads;
   if (chains == 0) return hipSuccess;
   dim3 g((unsigned)chains);
-#define LA2_LAUNCH_DECODE(D, DT)                                                                                    \
-  do {                                                                                                              \
-    if (norm) hipLaunchKernelGGL((decode_kernel<D, DT, true>), g, dim3(threads_for(D)), 0, s, q, k, v, lambda, kv, \
-                                 o, heads, eps);                                                                    \
-    else      hipLaunchKernelGGL((decode_kernel<D, DT, false>), g, dim3(threads_for(D)), 0, s, q, k, v, lambda, kv, \
-                                 o, heads, eps);                                                                    \
+  const bool stream = stream_state(chains, head_dim);
+#define LA2_LAUNCH_DECODE_S(D, DT, STREAM)                                                                              \
+  do {                                                                                                                  \
+    if (norm) hipLaunchKernelGGL((decode_kernel<D, DT, true, STREAM>), g, dim3(threads_for(D)), 0, s, q, k, v, lambda, \
+                                 kv, o, heads, eps);                                                                    \
+    else      hipLaunchKernelGGL((decode_kernel<D, DT, false, STREAM>), g, dim3(threads_for(D)), 0, s, q, k, v, lambda, \
+                                 kv, o, heads, eps);                                                                    \
+  } while (0)
+#define LA2_LAUNCH_DECODE(D, DT)                     \
+  do {                                               \
+    if (stream) LA2_LAUNCH_DECODE_S(D, DT, true);    \
+    else        LA2_LAUNCH_DECODE_S(D, DT, false);   \
   } while (0)
 #define LA2_LAUNCH_DECODE_D(D)                         \
   do {                                                 \
@@ -140,6 +162,7 @@ hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const vo
   else LA2_LAUNCH_DECODE_D(64);
 #undef LA2_LAUNCH_DECODE_D
 #undef LA2_LAUNCH_DECODE
+#undef LA2_LAUNCH_DECODE_S
   return hipGetLastError();
 }
 

@@ -307,6 +307,8 @@ hipError_t launch_norm_fwd_rows(int head_dim, int dtype, const NormBwdParams& p,
 // dst[i] = src ? src[i] : 0 for count floats (a state that passes through an empty sequence)
 hipError_t launch_state_copy(float* dst, const float* src, int64_t count, hipStream_t s);
 
+// Decoding kernels: whether states of this size are updated past the caches
+bool stream_state(int64_t chains, int head_dim);
 // norm: the output row is divided by sqrt(mean of its squares + eps) before it is stored
 hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const void* q, const void* k,
                          const void* v, const float* lambda, float* kv, void* o, bool norm, float eps,

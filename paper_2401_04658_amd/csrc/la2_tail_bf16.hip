@@ -21,7 +21,8 @@ using namespace bf16k;
 // spill and take 0.148 ms).
 // NORM: the Norm epilogue of eq. (2) (the waves exchange the sums of squares of their 32 features of every row
 // through LDS, one more barrier per block; wave 0 stores r).
-template <typename E, int D, bool NORM = false>
+// STREAM: the state passes by the caches (stream_state).
+template <typename E, int D, bool NORM, bool STREAM>
 __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(D == 128 ? 3 : 1))) void tail_bf16_kernel(RecurParams p) {
   constexpr int B = 32;
   using C = Cfg<D, B>;
@@ -54,7 +55,10 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(D == 128 
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) kv[t][v] = gs ? gs[state_index<D>(dvt, l32, hh, t, v, tr)] : 0.f;
+      for (int v = 0; v < 16; v++) {
+        const float* const at = gs + state_index<D>(dvt, l32, hh, t, v, tr);
+        kv[t][v] = gs == nullptr ? 0.f : STREAM ? __builtin_nontemporal_load(at) : *at;
+      }
   }
   // decay mask of the score tile S^T[c][r] (lane: r = l32; element v: c = 8 (v / 4) + 4 hh + v % 4) and the
   // weight lambda^(r+1) of the carried state at this lane's position
@@ -141,10 +145,15 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(D == 128 
   if (p.fin[0] != nullptr) {
     float* gf = p.fin[0] + chain * (int64_t)(D * D);
     const bool trf = p.fin_transposed & 1;
+    const __amdgpu_buffer_rsrc_t streamed = make_rsrc(gf, D * D * 4);
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) gf[state_index<D>(dvt, l32, hh, t, v, trf)] = kv[t][v];
+      for (int v = 0; v < 16; v++) {
+        const int at = state_index<D>(dvt, l32, hh, t, v, trf);
+        if (STREAM) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(kv[t][v]), streamed, 4 * at, 0, 18);   // nt, sc1: two whole 128-byte pieces
+        else        gf[at] = kv[t][v];
+      }
   }
 }
 
@@ -154,10 +163,16 @@ hipError_t launch_tail_bf16(int dtype, int head_dim, int batch, const RecurParam
   const int64_t chains = (int64_t)batch * p.heads;
   if (chains == 0 || p.t1 <= p.t0) return hipSuccess;
   dim3 g((unsigned)chains);
-#define LA2_LAUNCH_TAIL(E, D)                                                                        \
-  do {                                                                                               \
-    if (p.rstd != nullptr) hipLaunchKernelGGL((tail_bf16_kernel<E, D, true>), g, dim3(2 * D), 0, s, p); \
-    else                   hipLaunchKernelGGL((tail_bf16_kernel<E, D, false>), g, dim3(2 * D), 0, s, p); \
+  const bool stream = stream_state(chains, head_dim);
+#define LA2_LAUNCH_TAIL_S(E, D, STREAM)                                                                       \
+  do {                                                                                                        \
+    if (p.rstd != nullptr) hipLaunchKernelGGL((tail_bf16_kernel<E, D, true, STREAM>), g, dim3(2 * D), 0, s, p); \
+    else                   hipLaunchKernelGGL((tail_bf16_kernel<E, D, false, STREAM>), g, dim3(2 * D), 0, s, p); \
+  } while (0)
+#define LA2_LAUNCH_TAIL(E, D)                    \
+  do {                                           \
+    if (stream) LA2_LAUNCH_TAIL_S(E, D, true);   \
+    else        LA2_LAUNCH_TAIL_S(E, D, false);  \
   } while (0)
   if (dtype == kF16) {
     if (head_dim == 128) LA2_LAUNCH_TAIL(_Float16, 128);
@@ -167,6 +182,7 @@ hipError_t launch_tail_bf16(int dtype, int head_dim, int batch, const RecurParam
     else                 LA2_LAUNCH_TAIL(__bf16, 64);
   }
 #undef LA2_LAUNCH_TAIL
+#undef LA2_LAUNCH_TAIL_S
   return hipGetLastError();
 }
 
