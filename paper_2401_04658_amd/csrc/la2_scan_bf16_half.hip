@@ -28,7 +28,7 @@ constexpr int kBH = 32;
 // NORM: the Norm epilogue of eq. (2) on a forward scan: the four waves exchange the sums of squares of
 // their quarter rows through LDS (under the block's one barrier, which moves behind the intra-block
 // product for this), scale the finished tile and wave 0 stores r.  The LDS is full, so this variant has no
-// staging buffer of its own: it stages each wave's output in the block's X tile, which is dead by then.
+// output tile of its own: it stages each wave's output in the block's X tile, which is dead by then.
 //
 // ACC: a forward scan whose workgroup has a second group of waves (as many again; FOUR tiles per block: X, Y,
 // Z and p.acc_y).  The first group runs the scan as usual; the second accumulates
@@ -61,16 +61,18 @@ void scan_bf16_half_kernel(ScanParams p) {
   constexpr int NTL = (TWIN || ACC) ? 4 : 3;          // tiles per block
   using Loader = TileLoader<D, NTL, B, NW>;
   __shared__ __attribute__((aligned(1024))) E sT[NBUF][NTL][TILE];
-  // Output staging, 32 positions x 32 features per wave.  The NORM variant has no LDS left for it beside its
-  // exchange buffer (two workgroups of 80 KiB per compute unit) and stages in the block's own X tile instead,
-  // which is dead by then: see the epilogue.
-  __shared__ __attribute__((aligned(16))) E sW[ACC ? SW : NW][NORM ? LW : 32 * LW];
+  // Output tile of a scan.  The NORM variant has no LDS left for it beside its exchange buffer (two workgroups of 80 KiB
+  // per compute unit) and uses the block's own X tile instead, which is dead by then: see the output.
+  __shared__ __attribute__((aligned(1024))) E sW[TWIN ? 2 : 1][NORM ? 8 : TILE];
   float* const sRed = NormExchange<NORM ? 2 * 32 * SW : 0>::get();   // [block parity][position][wave]
   // Cache policy of the output stores (buffer instruction bits: 2 = nt, 16 = sc1): streaming, write-through.  Nobody here reads
   // an output again, and one that stays out of the caches leaves them to the inputs, which the next launch reads again.
   // Forward + backward against the default policy in the plain scans (which only the twin streamed past before, 9-13 %):
   // tensors of 16 MiB 0.92-0.94, 64 MiB 0.91-0.96, 128 MiB 0.92-0.97, 256 MiB in chunks 0.95-0.96, uncut 0.98 (a forward
   // pass alone, repeated on the same 1 GiB of tensors, 1.06-1.08; nt without sc1 1.01-1.02).
+  // Whole rows against 64-byte pieces of them (both streaming): packed 65,536 positions, d 128, H 16 914 -> 877 us, d 64, H 32
+  // 940 -> 852; one chain batch of 65,536, d 128, from saved states 870 -> 858; batch 16, n 4096, d 64 342 -> 336; batch 4, n 2048,
+  // d 64 68.7 -> 70.1 (the second barrier of a block).
   constexpr int kStorePolicy = 18;
   constexpr int NDMA = NTL * Loader::DMA_PER_WAVE;   // direct loads per wave and block
   constexpr int NST = 32 * 4 / 64 + (NORM ? 1 : 0);   // stores per lane and block: 16-byte output stores, r
@@ -206,6 +208,7 @@ void scan_bf16_half_kernel(ScanParams p) {
           loader.zero_tail(sT[(cur + 1) % NBUF], blk_lo + it + 1);
           lds_barrier();
         }
+        lds_barrier();   // the scan waves' staging
         return has_next;
       };
       for (int it = 0;; it += NBUF) {
@@ -375,7 +378,7 @@ void scan_bf16_half_kernel(ScanParams p) {
     return to_perm_order(f);
   };
   ex8<E> sa_first = state_operand(0);
-  E* const stage = sW[w];
+  E* const stage = sW[TWIN ? WH : 0];
 
 #define LA2_SLOT_END()                 \
   do {                                 \
@@ -535,23 +538,29 @@ void scan_bf16_half_kernel(ScanParams p) {
       const uint32_t roff = (dvt == 0 && hh == 0) ? (uint32_t)(blk * B + l32) * 4u : 0xFFFFFFF0u;
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(r), brs, roff, 0, 0);
     }
-    // Staging area of this wave.  NORM: the quarter of this block's X tile that this wave's own direct loads
-    // fill.  Every wave is past the block's last tile read (the barrier above), and the next writer of that
-    // quarter is this wave's own direct load two blocks on, issued after the reads below have returned.
-    E* const st = NORM ? const_cast<E*>(tX) + w * (TILE / SW) : stage;
+    // Output: the scan's waves stage their feature tiles in the output tile and, behind a barrier, store whole rows, 1 KiB an
+    // instruction (a wave storing its own tile writes 64 bytes of sixteen rows, the rest of each row following from
+    // other waves at other times).
+    // NORM: the output tile is the block's X tile, every wave being past the block's last tile read (the barrier above), and a
+    // wave keeps to the quarter of it that its own direct loads fill: the next writer of that quarter is this wave's own
+    // load two blocks on, issued after the reads below have returned.  (Whole rows here cost a third barrier: batch 8, n 3001,
+    // d 64 192 -> 194 us, n 4096, d 128 501 -> 505; packed 40,000 positions, d 128 681 -> 675.)
+    E* const st = NORM ? const_cast<E*>(tX) + dvt * (TILE / SW) : stage;
 #pragma unroll
     for (int g = 0; g < 4; g++) {
       ex4<E> pk;
 #pragma unroll
       for (int e = 0; e < 4; e++) pk[e] = (E)inter[4 * g + e];
-      *reinterpret_cast<ex4<E>*>(st + l32 * LW + 8 * (g ^ ((l32 >> 2) & 3)) + 4 * hh) = pk;
+      const int at = NORM ? l32 * LW + 8 * (g ^ ((l32 >> 2) & 3)) : l32 * D + 8 * ((4 * dvt + g) ^ swz<D>(l32));
+      *reinterpret_cast<ex4<E>*>(st + at + 4 * hh) = pk;
     }
+    if (!NORM) lds_barrier();   // (the tile is written again behind the next block's first barrier)
 #pragma unroll
-    for (int i = 0; i < 32 * 4 / 64; i++) {
-      const int id = l + 64 * i;
-      const int row = id >> 2, cc = id & 3;
-      const i32x4 v = *reinterpret_cast<const i32x4*>(st + row * LW + 8 * (cc ^ ((row >> 2) & 3)));
-      const uint32_t off = ((uint32_t)(blk * B + row) * stride_n + (uint32_t)(32 * dvt + cc * 8)) * 2u;
+    for (int i = 0; i < 2; i++) {
+      const int piece = l + 64 * i;
+      const int row = NORM ? piece / 4 : (B / SW) * dvt + piece / C::CPR, cc = NORM ? piece % 4 : piece % C::CPR;
+      const i32x4 v = *reinterpret_cast<const i32x4*>(st + (NORM ? row * LW + 8 * (cc ^ ((row >> 2) & 3)) : row * D + 8 * (cc ^ swz<D>(row))));
+      const uint32_t off = ((uint32_t)(blk * B + row) * stride_n + (uint32_t)((NORM ? 32 * dvt : 0) + 8 * cc)) * 2u;
       __builtin_amdgcn_raw_buffer_store_b128(v, bw, off, 0, kStorePolicy);
     }
     LA2_SLOT_END();
