@@ -1,7 +1,7 @@
 // Recurrent decode step (Sec. 3.2.1, recursive form): kv <- lambda kv + k^T v, o = q kv, gfx950.
 //
 // Memory bound: the fp32 state (d x d per (batch, head)) is read and written once; everything
-// else is negligible.  One workgroup per (batch, head); each thread streams float4 pieces of the
+// else is negligible.  One workgroup (or a few) per (batch, head); each thread streams float4 pieces of the
 // state rows with all of its loads issued up front, then the partial q.kv sums of the row groups
 // are reduced through LDS.
 #include <hip/hip_runtime.h>
@@ -30,37 +30,41 @@ __device__ __forceinline__ void store_elem(void* p, int64_t i, float x) {
   else reinterpret_cast<float*>(p)[i] = x;
 }
 
+// CS: workgroups of 256 threads that share a chain, each with D / CS of the state's columns (column_split).
 // STREAM: the state passes by the caches (loads non-temporal, stores non-temporal and written through): see stream_state.
 // NORM: the output row is normalised (eq. (2) read as root-mean-square normalisation over the head's features:
 // o <- o / sqrt(mean_j o_j^2 + eps)) before it is stored.
-template <int D, int DT, bool NORM, bool STREAM>
-__global__ __launch_bounds__(threads_for(D)) void decode_kernel(const void* q, const void* k, const void* v,
+template <int D, int DT, bool NORM, bool STREAM, int CS = 1>
+__global__ __launch_bounds__(CS == 1 ? threads_for(D) : 256) void decode_kernel(const void* q, const void* k, const void* v,
                                                           const float* lambda, float* kv, void* o, int heads,
                                                           float eps) {
-  constexpr int kThreads = threads_for(D);
-  constexpr int TPR = D / 4;            // threads per state row (float4 each)
+  static_assert(CS == 1 || !NORM, "the norm of a row needs all of its columns");
+  constexpr int kThreads = CS == 1 ? threads_for(D) : 256;
+  constexpr int DC = D / CS;            // state columns of this workgroup
+  constexpr int TPR = DC / 4;           // threads per state row (float4 each)
   constexpr int RG = kThreads / TPR;    // rows in flight per sweep
   constexpr int ITER = D / RG;
-  __shared__ float sq[D], sk[D], sv[D];
+  __shared__ float sq[D], sk[D], sv[DC];
   __shared__ float4 sacc[RG][TPR];
 
   const int tid = threadIdx.x;
-  const int64_t chain = blockIdx.x;
+  const int64_t chain = blockIdx.x / CS;
+  const int c0 = DC * (int)(blockIdx.x % CS);   // first column
   const float lam = lambda[chain % heads];
   if (tid < D) {
     sq[tid] = load_elem<DT>(q, chain * D + tid);
     sk[tid] = load_elem<DT>(k, chain * D + tid);
-    sv[tid] = load_elem<DT>(v, chain * D + tid);
+    if (tid < DC) sv[tid] = load_elem<DT>(v, chain * D + c0 + tid);
   }
   const int cg = tid % TPR, rg = tid / TPR;
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   typedef __attribute__((ext_vector_type(4))) int i32x4;
-  f32x4* state = reinterpret_cast<f32x4*>(kv + chain * (int64_t)(D * D));
-  const __amdgpu_buffer_rsrc_t streamed = __builtin_amdgcn_make_buffer_rsrc(state, 0, D * D * 4, 0x00027000);
+  f32x4* state = reinterpret_cast<f32x4*>(kv + chain * (int64_t)(D * D) + c0);
+  const __amdgpu_buffer_rsrc_t streamed = __builtin_amdgcn_make_buffer_rsrc(state, 0, (D * D - c0) * 4, 0x00027000);
   f32x4 s[ITER];
 #pragma unroll
   for (int it = 0; it < ITER; it++) {
-    const f32x4* const at = &state[(int64_t)(rg + RG * it) * TPR + cg];
+    const f32x4* const at = &state[(int64_t)(rg + RG * it) * (D / 4) + cg];
     s[it] = STREAM ? __builtin_nontemporal_load(at) : *at;
   }
   __syncthreads();
@@ -76,8 +80,8 @@ __global__ __launch_bounds__(threads_for(D)) void decode_kernel(const void* q, c
     t.z = fmaf(lam, s[it].z, ki * v4.z);
     t.w = fmaf(lam, s[it].w, ki * v4.w);
     const f32x4 tv = {t.x, t.y, t.z, t.w};
-    if (STREAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, tv), streamed, (i * TPR + cg) * 16, 0, 18);   // nt, sc1
-    else        __builtin_nontemporal_store(tv, &state[(int64_t)i * TPR + cg]);   // (4-7 % faster than the default policy)
+    if (STREAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, tv), streamed, (i * (D / 4) + cg) * 16, 0, 18);   // nt, sc1
+    else        __builtin_nontemporal_store(tv, &state[(int64_t)i * (D / 4) + cg]);   // (4-7 % faster than the default policy)
     acc.x = fmaf(qi, t.x, acc.x);
     acc.y = fmaf(qi, t.y, acc.y);
     acc.z = fmaf(qi, t.z, acc.z);
@@ -86,10 +90,10 @@ __global__ __launch_bounds__(threads_for(D)) void decode_kernel(const void* q, c
   sacc[rg][cg] = acc;
   __syncthreads();
   float sum = 0.f;
-  if (tid < D) {
+  if (tid < DC) {
     const float* flat = reinterpret_cast<const float*>(sacc);
 #pragma unroll
-    for (int g = 0; g < RG; g++) sum += flat[g * D + tid];
+    for (int g = 0; g < RG; g++) sum += flat[g * DC + tid];
   }
   if (NORM) {   // sum of squares over the row: inside each wave by lane exchanges, across the waves through LDS
     constexpr int NWAVE = (D + 63) / 64;   // waves that hold row elements
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(threads_for(D)) void decode_kernel(const void* q, c
     for (int i = 0; i < NWAVE; i++) tot += ssq[i];
     sum *= 1.f / sqrtf(tot * (1.f / (float)D) + eps);
   }
-  if (tid < D) store_elem<DT>(o, chain * D + tid, sum);
+  if (tid < DC) store_elem<DT>(o, chain * D + c0 + tid, sum);
 }
 
 __global__ void state_copy_kernel(float* dst, const float* src, int64_t count) {
@@ -131,6 +135,18 @@ bool stream_state(int64_t chains, int head_dim) {
   return head_dim != 256 && chains * head_dim * head_dim * (int64_t)sizeof(float) >= (int64_t)160 << 20;
 }
 
+namespace {
+// Workgroups that share a chain's state, a part of its columns each (the columns are independent of each other; not with the
+// norm).  On few chains the launch is one workgroup's latency, and at head_dim 256 the undivided workgroup of 1024 threads has
+// a compute unit to itself.  Undivided, halves, quarters, us (states changing from launch to launch): head_dim 256, 16 chains
+// 6.5 5.1 3.9, 64 9.0 7.9 7.2, 128 13.6 11.2 11.3, 256 24.8 22.9 22.7, 512 48.5 45.5 53, 1024 105 107 112; head_dim 128, 16 chains
+// 2.8 2.5 2.5, 64 3.6 3.4 3.4, 128 4.6 3.6 3.6, 256 6.7 6.8 6.9, 4096 91 93 100.
+int column_split(int64_t chains, int head_dim) {
+  if (head_dim == 256) return chains <= 64 ? 4 : chains <= 512 ? 2 : 1;
+  return head_dim == 128 && chains <= 128 ? 2 : 1;
+}
+}  // namespace
+
 hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const void* q, const void* k,
                          const void* v, const float* lambda, float* kv, void* o, bool norm, float eps,
                          hipStream_t s) {
@@ -138,6 +154,7 @@ hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const vo
   if (chains == 0) return hipSuccess;
   dim3 g((unsigned)chains);
   const bool stream = stream_state(chains, head_dim);
+  const int cs = norm ? 1 : column_split(chains, head_dim);
 #define LA2_LAUNCH_DECODE_S(D, DT, STREAM)                                                                              \
   do {                                                                                                                  \
     if (norm) hipLaunchKernelGGL((decode_kernel<D, DT, true, STREAM>), g, dim3(threads_for(D)), 0, s, q, k, v, lambda, \
@@ -145,10 +162,16 @@ hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const vo
     else      hipLaunchKernelGGL((decode_kernel<D, DT, false, STREAM>), g, dim3(threads_for(D)), 0, s, q, k, v, lambda, \
                                  kv, o, heads, eps);                                                                    \
   } while (0)
-#define LA2_LAUNCH_DECODE(D, DT)                     \
-  do {                                               \
-    if (stream) LA2_LAUNCH_DECODE_S(D, DT, true);    \
-    else        LA2_LAUNCH_DECODE_S(D, DT, false);   \
+#define LA2_LAUNCH_DECODE_C(D, DT, CS)                                                                                  \
+  hipLaunchKernelGGL((decode_kernel<D, DT, false, false, CS>), dim3(CS * g.x), dim3(256), 0, s, q, k, v, lambda, kv, o, \
+                     heads, eps)
+#define LA2_LAUNCH_DECODE(D, DT)                                               \
+  do {                                                                         \
+    if (D == 256 && cs == 4)      LA2_LAUNCH_DECODE_C(256, DT, 4);             \
+    else if (D == 256 && cs == 2) LA2_LAUNCH_DECODE_C(256, DT, 2);             \
+    else if (D == 128 && cs == 2) LA2_LAUNCH_DECODE_C(128, DT, 2);             \
+    else if (D != 256 && stream)  LA2_LAUNCH_DECODE_S(D, DT, D != 256);        \
+    else                          LA2_LAUNCH_DECODE_S(D, DT, false);           \
   } while (0)
 #define LA2_LAUNCH_DECODE_D(D)                         \
   do {                                                 \
@@ -163,6 +186,7 @@ hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const vo
 #undef LA2_LAUNCH_DECODE_D
 #undef LA2_LAUNCH_DECODE
 #undef LA2_LAUNCH_DECODE_S
+#undef LA2_LAUNCH_DECODE_C
   return hipGetLastError();
 }
 
