@@ -15,6 +15,7 @@ namespace {
 // threads of a workgroup: a multiple of the D / 4 threads that share a state row, 16 or 12 float4 pieces
 // of state rows per thread
 constexpr int threads_for(int d) { return d == 256 ? 1024 : d == 96 ? 192 : 256; }
+constexpr int split_threads(int d, int cs) { return d == 256 && cs == 2 ? 512 : 256; }
 
 // element i of a tensor of type DT (kF32, kBF16 or kF16) as fp32, and the store that goes with it
 template <int DT>
@@ -30,16 +31,17 @@ __device__ __forceinline__ void store_elem(void* p, int64_t i, float x) {
   else reinterpret_cast<float*>(p)[i] = x;
 }
 
-// CS: workgroups of 256 threads that share a chain, each with D / CS of the state's columns (column_split).
+// CS: workgroups that share a chain, each with D / CS of the state's columns (column_split).  A thread holds at most 16
+// pieces of 16 bytes in flight: 32 of them (256 threads at halves of head_dim 256) take 158 registers and leave three waves per SIMD.
 // STREAM: the state passes by the caches (loads non-temporal, stores non-temporal and written through): see stream_state.
 // NORM: the output row is normalised (eq. (2) read as root-mean-square normalisation over the head's features:
 // o <- o / sqrt(mean_j o_j^2 + eps)) before it is stored.
 template <int D, int DT, bool NORM, bool STREAM, int CS = 1>
-__global__ __launch_bounds__(CS == 1 ? threads_for(D) : 256) void decode_kernel(const void* q, const void* k, const void* v,
+__global__ __launch_bounds__(CS == 1 ? threads_for(D) : split_threads(D, CS)) void decode_kernel(const void* q, const void* k, const void* v,
                                                           const float* lambda, float* kv, void* o, int heads,
                                                           float eps) {
   static_assert(CS == 1 || !NORM, "the norm of a row needs all of its columns");
-  constexpr int kThreads = CS == 1 ? threads_for(D) : 256;
+  constexpr int kThreads = CS == 1 ? threads_for(D) : split_threads(D, CS);
   constexpr int DC = D / CS;            // state columns of this workgroup
   constexpr int TPR = DC / 4;           // threads per state row (float4 each)
   constexpr int RG = kThreads / TPR;    // rows in flight per sweep
@@ -138,11 +140,12 @@ bool stream_state(int64_t chains, int head_dim) {
 namespace {
 // Workgroups that share a chain's state, a part of its columns each (the columns are independent of each other; not with the
 // norm).  On few chains the launch is one workgroup's latency, and at head_dim 256 the undivided workgroup of 1024 threads has
-// a compute unit to itself.  Undivided, halves, quarters, us (states changing from launch to launch): head_dim 256, 16 chains
-// 6.5 5.1 3.9, 64 9.0 7.9 7.2, 128 13.6 11.2 11.3, 256 24.8 22.9 22.7, 512 48.5 45.5 53, 1024 105 107 112; head_dim 128, 16 chains
-// 2.8 2.5 2.5, 64 3.6 3.4 3.4, 128 4.6 3.6 3.6, 256 6.7 6.8 6.9, 4096 91 93 100.
+// a compute unit to itself.  Undivided against divided, us, three states in turn / 768 MiB of states, which no cache holds:
+// head_dim 256, quarters, 16 chains 5.8 3.4 / 8.9 4.7, 64 9.0 7.2 / 11.9 9.4; halves, 128 13.5 11.1 / 17.0 16.4, 256 24.8 23.2 /
+// 27.1 29.4, 512 48.5 48.7 / 54.6 54.9, so the line is at 128.  Head_dim 128, halves, 16 chains 2.8 2.5 / 3.9 3.3, 64 3.2 2.9 /
+// 4.5 4.1, 128 3.9 3.6 / 5.8 5.4, 256 6.7 6.8; quarters are no faster there (16 chains 2.5, 128 3.6).
 int column_split(int64_t chains, int head_dim) {
-  if (head_dim == 256) return chains <= 64 ? 4 : chains <= 512 ? 2 : 1;
+  if (head_dim == 256) return chains <= 64 ? 4 : chains <= 128 ? 2 : 1;
   return head_dim == 128 && chains <= 128 ? 2 : 1;
 }
 }  // namespace
@@ -163,8 +166,8 @@ hipError_t launch_decode(int batch, int heads, int head_dim, int dtype, const vo
                                  kv, o, heads, eps);                                                                    \
   } while (0)
 #define LA2_LAUNCH_DECODE_C(D, DT, CS)                                                                                  \
-  hipLaunchKernelGGL((decode_kernel<D, DT, false, false, CS>), dim3(CS * g.x), dim3(256), 0, s, q, k, v, lambda, kv, o, \
-                     heads, eps)
+  hipLaunchKernelGGL((decode_kernel<D, DT, false, false, CS>), dim3(CS * g.x), dim3(split_threads(D, CS)), 0, s, q, k, v, \
+                     lambda, kv, o, heads, eps)
 #define LA2_LAUNCH_DECODE(D, DT)                                               \
   do {                                                                         \
     if (D == 256 && cs == 4)      LA2_LAUNCH_DECODE_C(256, DT, 4);             \

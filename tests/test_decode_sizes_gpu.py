@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 SIZES = [(64, 10239), (64, 10240), (96, 4551), (96, 4552), (128, 128), (128, 129), (128, 2559), (128, 2560),
-         (256, 64), (256, 65), (256, 512), (256, 513), (256, 640)]
+         (256, 64), (256, 65), (256, 128), (256, 129), (256, 512), (256, 513), (256, 640)]
 
 
 @pytest.mark.parametrize("d,chains", SIZES)
