@@ -207,9 +207,9 @@ void scan_bf16_half_kernel(ScanParams p) {
         if (has_next) {
           __builtin_amdgcn_s_waitcnt(ACC_WAIT);
           loader.zero_tail(sT[(cur + 1) % NBUF], blk_lo + it + 1);
-          lds_barrier();
         }
-        lds_barrier();   // the scan waves' staging
+        lds_barrier();   // the two barriers that the scan waves pass in every block
+        lds_barrier();
         return has_next;
       };
       for (int it = 0;; it += NBUF) {
@@ -496,12 +496,16 @@ void scan_bf16_half_kernel(ScanParams p) {
       for (int t = 2 * h; t < 2 * h + 2; t++) pin(kv[t]);
       LA2_SLOT_END();
     }
+    // First barrier, also of the last block: behind it the next block's tiles are there for every wave, and the output tile
+    // is free, which every wave has then read the rows of the block before from.
     // NORM: the block's one barrier comes after phase 4 instead, where it also publishes the rows' sums of squares
     if (has_next) {
       __builtin_amdgcn_s_waitcnt(WAIT_NEXT_TILES);
       loader.zero_tail(sNext, nb);
-      if (!NORM) {
-        lds_barrier();
+    }
+    if (!NORM) {
+      lds_barrier();
+      if (has_next) {
 #pragma unroll
         for (int ks = 0; ks < AHEAD; ks++) {
           xa[ks] = la.read_row(sNext[xi], 0, ks);
@@ -555,7 +559,7 @@ void scan_bf16_half_kernel(ScanParams p) {
       const int at = NORM ? l32 * LW + 8 * (g ^ ((l32 >> 2) & 3)) : l32 * D + 8 * ((4 * dvt + g) ^ swz<D>(l32));
       *reinterpret_cast<ex4<E>*>(st + at + 4 * hh) = pk;
     }
-    if (!NORM) lds_barrier();   // (the tile is written again behind the next block's first barrier)
+    if (!NORM) lds_barrier();   // second barrier (the tile is written again behind the next block's first one)
 #pragma unroll
     for (int i = 0; i < 2; i++) {
       const int piece = l + 64 * i;
