@@ -42,6 +42,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
   using C = Cfg<D, kStep>;
   constexpr int KS = C::KS, NT = C::NT, TILE = C::TILE;
   constexpr int DPW = C::DMA_PER_TILE / kWaves;   // direct loads per wave and tile
+  constexpr bool F16 = std::is_same<E, _Float16>::value;
   __shared__ __attribute__((aligned(1024))) E sT[2][2][TILE];   // [buffer][Y, Z]
   static_assert(sizeof(sT) >= sizeof(float) * kGroups * kRows * D, "the key groups' sums take the tiles' place");
   float* const part = reinterpret_cast<float*>(&sT[0][0][0]);
@@ -93,6 +94,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
   const int end_tile = is_state || rev ? last_tile : min((row0 + kRows - 1) >> 5, last_tile);
   const int ntiles = end_tile - first_tile + 1;
   const int nsteps = (ntiles + kGroups - 1) / kGroups;
+  // Steps run from the far end towards the rows (a state: towards the end that it is the state at)
+  auto step_first = [&](int s) __attribute__((always_inline)) { return 32 * first_tile + kStep * (rev ? nsteps - 1 - s : s); };
 
   // Direct loads: wave w issues loads DPW w .. of a tile; lane l of load j fills 16-byte piece q = 64 j + l, row q / CPR,
   // which holds the row's piece (q % CPR) ^ swz(row).  Rows past the end: the last row's, zeroed after they have landed.
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
     lcol[i] = 8u * (uint32_t)((q % C::CPR) ^ swz<D>(q / C::CPR));
   }
   auto issue = [&](int s) __attribute__((always_inline)) {
-    const int first = 32 * first_tile + kStep * s;
+    const int first = step_first(s);
     E (*const buf)[TILE] = sT[s & 1];
 #pragma unroll
     for (int i = 0; i < DPW; i++) {
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
   };
   // step s's tiles are there for all waves (and everybody is done with the step before)
   auto arrive = [&](int s) __attribute__((always_inline)) {
-    const int first = 32 * first_tile + kStep * s;
+    const int first = step_first(s);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     if (first + kStep > n) {
 #pragma unroll
@@ -137,34 +140,46 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
 
   if (is_state) {
     // State right behind the chain's last position (rev: entering its first): sum_c weight(c) y_c^T z_c + lambda^n init,
-    // weight lambda^(n - 1 - c) (rev: lambda^(c + 1)).
+    // weight lambda^(n - 1 - c) (rev: lambda^(c + 1)).  As in the scans, z carries the decay inside its tile of 32 positions when
+    // it is rounded to 16 bits and the sums carry the rest in fp32: in fp16 the whole decay would make it subnormal, or zero.
     const int dvt = (kWaves * state_part + w) / NT, dkt = w % NT;
     f32x16 acc = zero16();
-    float gj[8];
+    // element j's factor and, for rows 16 k .. 16 k + 15 of a tile, a lane's, no exponent negative; row of element j: 16 k + 4 hh +
+    // 8 (j / 4) + j % 4
+    float gj[8], gk[2];
 #pragma unroll
     for (int j = 0; j < 8; j++) gj[j] = uniform(exp2f(l2 * (float)(rev ? 8 * (j >> 2) + (j & 3) : 11 - 8 * (j >> 2) - (j & 3))));
+#pragma unroll
+    for (int k = 0; k < 2; k++) gk[k] = exp2f(l2 * (float)(rev ? 16 * k + 4 * hh + 1 : 16 * (1 - k) + 4 * (1 - hh)));
+    const float lam32 = uniform(exp2f(l2 * 32.f));
     for (int s = 0; s < nsteps; s++) {
       arrive(s);
       if (s + 1 < nsteps) issue(s + 1);
       const E* const tY = sT[s & 1][0];
       const E* const tZ = sT[s & 1][1];
-      const int first = kStep * s;
 #pragma unroll
-      for (int k = 0; k < kStep / 16; k++) {
-        const int c0 = 16 * k;   // rows c0 .. c0 + 15, element j: c0 + 4 hh + 8 (j / 4) + j % 4
-        const ex8<E> z = la.read_cols(tZ, c0, dvt);
-        const int c = first + c0 + 4 * hh;
-        ex8<E> zd;
-        if (rev || first + kStep <= n) {   // weight = a lane's factor times an element's, no exponent negative
-          const float step = fast_exp2(l2 * (float)(rev ? c + 1 : n - 12 - c));
+      for (int g = 0; g < kGroups; g++) {
+        const int tile = rev ? kGroups - 1 - g : g;
+        const int valid = min(max(n - step_first(s) - 32 * tile, 0), 32);   // rows; those past them are zero
+        const bool whole = rev || valid == 32;
+        const float carry = whole ? lam32 : uniform(exp2f(l2 * (float)valid));
 #pragma unroll
-          for (int j = 0; j < 8; j++) zd[j] = (E)((float)z[j] * (step * gj[j]));
-        } else {                           // the ragged end: rows past it are zero
+        for (int v = 0; v < 16; v++) acc[v] *= carry;
 #pragma unroll
-          for (int j = 0; j < 8; j++)
-            zd[j] = (E)((float)z[j] * fast_exp2(l2 * (float)max(n - 1 - c - 8 * (j >> 2) - (j & 3), 0)));
+        for (int k = 0; k < 2; k++) {
+          const int c0 = 32 * tile + 16 * k;
+          const ex8<E> z = la.read_cols(tZ, c0, dvt);
+          ex8<E> zd;
+          if (whole) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) zd[j] = (E)((float)z[j] * (gk[k] * gj[j]));
+          } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+              zd[j] = (E)((float)z[j] * fast_exp2(l2 * (float)max(valid - 1 - 16 * k - 4 * hh - 8 * (j >> 2) - (j & 3), 0)));
+          }
+          acc = mfma(la.read_cols(tY, c0, dkt), zd, acc);
         }
-        acc = mfma(la.read_cols(tY, c0, dkt), zd, acc);
       }
     }
     const float lam_n = exp2f(l2 * (float)n);
@@ -218,23 +233,41 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
         acc[t] = mfma(a, xf[kk], acc[t]);
       }
     }
-    const float scale = exp2f(l2 * (float)max(rev ? n - 1 - r : r + 1, 0));
+    if (!F16) {
+      const float scale = exp2f(l2 * (float)max(rev ? n - 1 - r : r + 1, 0));
+#pragma unroll
+      for (int t = 0; t < NT; t++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[t][v] *= scale;
+    }
+  }
+  // Decay of a score tile S^T[c][r] off the diagonal: a lane's factor times an element's, no exponent negative.
+  // bf16: lambda^(|r - c|) of this lane's row and element v's key row, 32 positions apart, and one factor for the whole tiles in between.
+  // fp16: what the scores carry when they are rounded may not take them below the type's range, which starts at 2^-14.  So
+  // that is the decay to the tile's near edge only, and the sums, which then stand at that edge (`at`), take the rest in fp32.
+  // And every row of a tile is scaled by a power of two (exponent `scaled` - 127, undone in the sums) that takes its largest
+  // score to 2^14 or more (one of 2^-26 or more): the scores of small gradients one by one would be subnormal where their sum in
+  // a state is not.  (Error against 64 bits, n 777, lambda 0.99, d 64, gradients of 1.2e-5: 1.9e-3 in the recurrence, 4.5e-3 with the
+  // whole decay on the scores, 2.4e-3 without the scale, 1.7e-3 so.  Time, forward / backward, 16 chains of 777, d 128 14.2 -> 15.7,
+  // 19.0 -> 20.2 us; d 64 9.8 -> 11.4, 11.5 -> 12.8.)
+  const float lane_decay = exp2f(l2 * (float)(F16 ? (rev ? 4 * hh : 4 - 4 * hh) : rev ? 4 * hh - l32 + 32 : l32 - 4 * hh + 5));
+  float od[16];
+#pragma unroll
+  for (int v = 0; v < 16; v++) od[v] = scalar_reg(exp2f(l2 * (float)(rev ? 8 * (v >> 2) + (v & 3) : 27 - 8 * (v >> 2) - (v & 3))));
+  int at = rev ? n - 1 : -1, scaled = 127;
+  auto rescale = [&](int gap, int now) __attribute__((always_inline)) {   // the sums, `gap` positions on
+    const float f = fast_exp2(l2 * (float)max(gap, 0)) * __uint_as_float((uint32_t)(127 + now - scaled) << 23);
+    scaled = now;
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) acc[t][v] *= scale;
-  }
-  // decay of a score tile S^T[c][r] off the diagonal, without the whole tiles in between: lambda^(|r - c| of this lane's row
-  // and element v's key row, 32 positions apart) = a lane's factor times an element's, no exponent negative
-  const float row_decay = exp2f(l2 * (float)(rev ? 4 * hh - l32 + 31 : l32 - 4 * hh + 4));
-  float od[16];
-#pragma unroll
-  for (int v = 0; v < 16; v++) od[v] = scalar_reg(exp2f(l2 * (float)(rev ? 8 * (v >> 2) + (v & 3) + 1 : 28 - 8 * (v >> 2) - (v & 3))));
+      for (int v = 0; v < 16; v++) acc[t][v] *= f;
+  };
 
   for (int s = 0; s < nsteps; s++) {
     arrive(s);
     if (s + 1 < nsteps) issue(s + 1);
-    const int tile = first_tile + kGroups * s + kg;
+    const int tile = (step_first(s) >> 5) + kg;
     const int ahead = row0 + 32 * rh - 32 * tile;
     const int dist = rev ? -ahead : ahead;
     if (dist >= 0 && tile <= end_tile) {   // (wave-uniform: not a tile on the masked side)
@@ -243,25 +276,42 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
       f32x16 st = zero16();
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) st = mfma(la.read_row(tY, kg, ks), xf[ks], st);
-      ex8<E> pf[2];
       if (dist == 0) {
 #pragma unroll
         for (int v = 0; v < 16; v++) {
           const int cc = 8 * (v >> 2) + 4 * hh + (v & 3);
           const int e = rev ? cc - l32 : l32 - cc;
-          pf[v >> 3][v & 7] = (E)(st[v] * (e >= 0 ? fast_exp2(l2 * (float)e) : 0.f));
+          st[v] *= e >= 0 ? fast_exp2(l2 * (float)e) : 0.f;
         }
       } else {
-        const float far = row_decay * fast_exp2(l2 * (float)(dist - 32));
+        const float far = F16 ? lane_decay : lane_decay * fast_exp2(l2 * (float)(dist - 32));
 #pragma unroll
-        for (int v = 0; v < 16; v++) pf[v >> 3][v & 7] = (E)(st[v] * (far * od[v]));
+        for (int v = 0; v < 16; v++) st[v] *= far * od[v];
       }
+      if constexpr (F16) {
+        float most = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; v++) most = fmaxf(most, fabsf(st[v]));
+        const u32x2 halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
+        most = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));   // (the row's other keys)
+        const int near = 32 * tile + (rev ? 0 : 31), to = dist == 0 ? r : near;
+        rescale(rev ? at - to : to - at, min(max(127 + 14 - ((int)(__float_as_uint(most) >> 23) - 127), 127), 167));
+        at = near;
+        const float up = __uint_as_float((uint32_t)scaled << 23);
+#pragma unroll
+        for (int v = 0; v < 16; v++) st[v] *= up;
+      }
+      ex8<E> pf[2];
+#pragma unroll
+      for (int v = 0; v < 16; v++) pf[v >> 3][v & 7] = (E)st[v];
 #pragma unroll
       for (int t = 0; t < NT; t++)
 #pragma unroll
         for (int q = 0; q < 2; q++) acc[t] = mfma(la.read_cols(tZ, 32 * kg + 16 * q, t), pf[q], acc[t]);
     }
   }
+
+  if constexpr (F16) rescale(kg == rh ? 0 : rev ? at - r : r - at, 127);   // (a group on the diagonal stands at its rows)
 
   // The key groups' sums: [group][row][feature], 16-byte pieces swizzled by the row.  Lane: position, elements 4 g .. + 3 of
   // tile t are value features 32 t + 8 g + 4 hh .. + 3.

@@ -184,3 +184,39 @@ def test_short_backward_of_the_norm_and_graph_replay(d):
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(outs, ref)), replay
+
+
+@pytest.mark.parametrize("padding", ["none", "last", "first"])
+@pytest.mark.parametrize("grad", [1.0, 1e-3, 1e-4])
+@pytest.mark.parametrize("d,n", [(64, 777), (128, 1500)])
+def test_fp16_short_passes_lose_no_range(d, n, grad, padding):
+    """fp16 starts at 2^-14 and ends, subnormal, at 2^-24.  The recurrence rounds operands that carry the decay of one block at most
+    and sums the rest in fp32; the short path may not round anything smaller: not a state's operands by the decay of the whole
+    sequence (padding: a third of the positions is zero, what is left has decayed when the state is handed out), not the scores
+    of small gradients (gradients without loss scaling) one by one.  Every head's error against 64 bits, on the short path and
+    on the recurrence's kernels; they round different operands, so the bound has a quarter of slack (the fp16 arithmetic of both,
+    followed on the CPU over 60 shapes, decays and scales: at most 1.02 times)."""
+    lams = [0.9, 0.98, 0.99, 0.9999]
+    gen = torch.Generator(device="cpu")
+    gen.manual_seed(n + d)
+    q, k, v, do = (torch.randn((1, 4, n, d), generator=gen) * d ** -0.5 for _ in range(4))
+    do = do * grad
+    cut = n // 3
+    for x in (k, v, do):
+        if padding != "none":
+            x[:, :, slice(n - cut, n) if padding == "last" else slice(0, cut)] = 0
+    q, k, v, do = (x.to(torch.float16) for x in (q, k, v, do))
+    lam = torch.tensor(lams)
+    g = [x.to(DEV) for x in (q, k, v, do, lam)]
+    outs = []
+    for variant in (0, 2):
+        binding.la2_set_scan_variant(variant)
+        outs.append(tuple(binding.la2_fwd_state(*g[:3], g[4])) + tuple(binding.la2_bwd_state(*g)))
+    torch.cuda.synchronize()
+    q64, k64, v64, do64, lam64 = (to64(x) for x in (q, k, v, do, lam))
+    refs = tuple(oracle.fwd_recurrent(q64, k64, v64, lam64, return_state=True)) + tuple(oracle.bwd_recurrent_state(q64, k64, v64, do64, lam64))
+    assert all(np.all(np.isfinite(to64(x))) for x in outs[0])
+    for name, short, blocks, ref in zip(("o", "kv_final", "dq", "dk", "dv", "d_kv_init"), *outs, refs):
+        for h in range(4):
+            a, b = (rms_rel(to64(x[0, h]), ref[0, h]) for x in (short, blocks))
+            assert a <= 1.25 * b, "%s lambda %g: %.2e on the short path, %.2e in blocks" % (name, lams[h], a, b)
