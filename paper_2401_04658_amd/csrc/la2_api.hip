@@ -629,36 +629,83 @@ size_t bwd_workspace_need(const la2_desc* d, bool has_d_kv_final) {
 
 // Short sequences on few chains, 16-bit data, head_dim 64 / 128: the whole pass in one launch that looks back over all
 // positions (la2_short_bf16.hip) instead of the block recurrence.  Its work is the 64 x 64 position blocks on one side of the
-// diagonal, chains k (k + 1) / 2 for k = n / 64; the recurrence's is three (forward: two) dependent launches where it cuts the
-// sequences, one loop over them where it does not.  Short against recurrence, forward + backward in us (256 units; n, time):
-//   chains      d 64                                                 d 128
-//   4           1024 40 22, 2048 46 36, 3000 47 50                   1024 65 32, 2048 70 55, 3000 77 80
-//   16          777 40 22, 1500 48 38, 2048 50 54                    777 72 32, 1500 83 65, 2048 88 95
-//   32          777 43 27, 1024 44 34, 1500 59 56                    777 83 48, 1024 85 60, 1500 97 107
-//   64          512 43 25, 777 53 41, 1024 55 58                     512 69 44, 777 100 81, 1024 100 112
-//   128         256 27 20, 400 41 34, 512 48 41                      128 27 20, 256 45 38, 400 64 70
-//   256         64 15 12, 128 20 18, 256 33 34                       32 16 16, 64 21 18, 128 32 34
-//   512         64 20 17, 128 31 29                                  64 34 29, 128 57 67
-// A forward pass of one block of 32 is no faster (4.1 against 4.2 us), and few chains longer than 1536 lose in the forward
-// what they gain in the backward (4 chains of 2048, d 64: 16 against 17.5).  What the forward takes the backward takes too: the
-// chunk states that la2_bwd_saved reads have then not been written.
-bool short_sequences(const la2_desc* d, bool backward) {
-  if (!is16(d->dtype) || wide(d->head_dim)) return false;
-  if (g_chunk_tokens_override.load(std::memory_order_relaxed) > 0 || g_scan_variant.load(std::memory_order_relaxed) != 0)
-    return false;   // the caller plans, or asks for a kernel
+// diagonal, chains k (k + 1) / 2 for k = n / 64, for each of its scans; every block of 64 rows also reads a start state that is
+// given, and a state that is handed out takes workgroups of its own.  The recurrence's is two (backward: three) dependent launches
+// where it cuts the sequences, one loop over them where it does not, and states cost it next to nothing.
+// Short against recurrence, bf16, us from a replayed graph (256 units):
+//   chains, n          forward      ... state out  ... in        ... in and out  backward     ... d_kv_init    ... all three states
+//   d 128  4, 1536     21.4  22.2   22.2  23.4     24.7  22.3    24.8  23.5      24.0  45.5   23.9  46.3     32.1  46.5
+//          16, 64      5.8   6.1    5.9   7.3      9.1   6.6     9.2   7.9       5.9   13.5   6.0   14.6     10.3  17.8
+//          16, 777     14.7  22.0   15.6  21.8     17.2  23.1    17.6  23.2      18.9  47.7   21.8  49.6     34.8  55.1
+//          32, 1024    18.9  25.3   21.3  27.3     22.6  26.9    27.8  28.9      41.4  51.6   48.5  53.5     69.6  56.7
+//          64, 512     13.8  20.4   20.4  21.9     19.0  21.0    27.7  22.5      31.2  48.9   36.3  51.7     58.1  54.1
+//          128, 256    11.5  12.6   17.2  14.7     16.7  13.3    24.6  15.7      25.5  29.6   31.6  31.8     56.0  35.9
+//          256, 64     6.9   6.4    12.7  9.7      12.8  9.3     27.1  13.1      12.3  14.6   18.4  17.9     41.8  25.0
+//   d 64   4, 1536     14.4  16.3   20.2  17.0     15.8  16.4    21.9  17.1      15.7  30.1   20.8  30.6     22.6  30.8
+//          16, 777     10.4  14.4   13.7  14.8     11.2  14.6    15.5  15.2      11.9  26.7   14.2  27.7     15.9  28.4
+//          64, 512     8.5   14.4   9.8   15.2     10.2  14.6    11.8  15.3      15.9  29.7   16.9  30.6     23.9  31.1
+//          128, 256    7.0   9.1    8.0   10.0     8.9   9.2     9.6   10.2      12.9  18.6   13.8  19.5     22.2  20.1
+//          512, 128    8.9   8.4    11.3  10.7     12.5  9.2     17.6  11.5      19.1  18.3   22.7  20.5     40.6  22.3
+// The lines below are where the ratio reaches 1, from 15 numbers of chains, 1 to 512, times 17 lengths, 33 to 3072, times the ten forms
+// (forward with a start state or not, with the state out or not; backward with each of its states or not), times both types: of
+// the 4700 measured cells that they take four are slower than the recurrence, by 3 to 6 %.  (fp16 has more to do in the short
+// path: the scores' scales.)  A forward pass of one block of 32 is no faster.
+bool short_kernel_takes(const la2_desc* d) {
+  return is16(d->dtype) && !wide(d->head_dim) && d->seqlen > 0 && g_chunk_tokens_override.load(std::memory_order_relaxed) <= 0 &&
+         g_scan_variant.load(std::memory_order_relaxed) == 0;   // (the caller plans, or asks for a kernel)
+}
+
+// position blocks of one scan on a compute unit; per_row: more work of every row block, in position blocks
+double short_blocks(const la2_desc* d, double per_row) {
+  const double chains = (double)d->batch * d->heads, k = (d->seqlen + 63) / 64;
+  return chains * (k * (k + 1) / 2 + per_row * (k + 1)) / device_cu_count();
+}
+
+// in, out: with a start state, with the state handed out.  What is taken with states is also taken without (la2_bwd_saved relies
+// on it).
+bool short_forward(const la2_desc* d, bool in, bool out) {
+  if (!short_kernel_takes(d)) return false;
+  const bool f16 = d->dtype == LA2_F16;
   const int n = d->seqlen;
   const int64_t cus = device_cu_count(), chains = (int64_t)d->batch * d->heads;
-  const int64_t k = (n + 63) / 64, blocks = chains * (k * (k + 1) / 2);
-  if (n < 1 || n > (backward ? 3072 : 1536) || (!backward && n <= 32)) return false;
-  if (4 * chains <= cus || (2 * chains <= cus && d->head_dim == 64)) return blocks <= 20 * cus;
-  if (2 * chains <= cus) return blocks <= 5 * cus;
-  return chains <= 2 * cus && n <= (d->head_dim == 64 ? 128 : 64);
+  const double blocks = short_blocks(d, 0);
+  if (d->head_dim == 128) {
+    if (n <= (f16 ? 64 : 32) || n > (f16 ? 1280 : 1536)) return false;
+    if (in) {
+      if (n <= (out && !f16 ? 64 : 128) || n > (f16 ? 1024 : 1280)) return false;
+      if (8 * chains <= cus) return blocks <= (out && f16 ? 15 : 20);
+      return !out && 4 * chains <= cus && blocks <= 11;
+    }
+    return 4 * chains <= cus ? blocks <= 20 : !out && 2 * chains <= cus && blocks <= 5;
+  }
+  if (n <= (in && !out ? 64 : 32)) return false;
+  if (in || out) return n <= (in && out ? 640 : 1024) && 2 * chains <= cus && blocks <= (!in ? 20 : out ? 15 : 17.25);
+  if (2 * chains <= cus) return n <= (f16 ? 1280 : 1536) && blocks <= 20;
+  return chains <= 2 * cus && n <= (f16 ? 64 : 128) && blocks <= 5;
+}
+
+// in: scans that begin with a given state (kv_init: one, d_kv_final: two); out: d_kv_init is wanted
+bool short_backward(const la2_desc* d, int in, bool out) {
+  if (!short_kernel_takes(d)) return false;
+  const bool f16 = d->dtype == LA2_F16;
+  const int n = d->seqlen;
+  const int64_t cus = device_cu_count(), chains = (int64_t)d->batch * d->heads;
+  const bool few = 4 * chains <= cus, some = 2 * chains <= cus;
+  if (d->head_dim == 128) {
+    if (n > 3072 - (f16 ? 512 : 0) - (in > 0 ? 512 : 0)) return false;
+    if (!some) return in == 0 && !out && chains <= 2 * cus && n <= 64;
+    return short_blocks(d, 1.5 * in + (out ? 0.5 : 0)) <= (!few ? 5 : 8 * chains <= cus ? 20 : f16 ? 15 : 17.25);
+  }
+  if (n > (out ? 2048 : f16 ? 2560 : 3072)) return false;
+  if (few) return short_blocks(d, 0) <= (in == 0 && !out ? 20 : f16 ? 16.5 : 19);
+  if (some) return short_blocks(d, 2.0 * in + (out ? 0.5 : 0)) <= (f16 ? 17 : 19);
+  return chains <= 2 * cus && n <= 128 && short_blocks(d, (f16 ? 1.0 : 0.5) * in + (out ? 0.25 : 0)) <= 5;
 }
 
 // Packed batches: where the recurrence would cut unequal lengths it has a map that takes only what the told total has room for;
 // that stays so.
-bool short_packed(const la2_desc* d, const Plan& pl, int64_t total_positions, bool backward) {
-  return short_sequences(d, backward) && (pl.wg_pairs == 0 || 4 * (int64_t)d->seqlen * d->batch <= 5 * total_positions);
+bool packed_without_map(const la2_desc* d, const Plan& pl, int64_t total_positions) {
+  return pl.wg_pairs == 0 || 4 * (int64_t)d->seqlen * d->batch <= 5 * total_positions;
 }
 
 // A start state and the state that is handed out in the same place: the one launch has workgroups that read the first while
@@ -830,7 +877,7 @@ la2_status fwd_state_one_call(const la2_desc* desc, const void* q, const void* k
   if (pl.workspace > 0 && (workspace == nullptr || workspace_bytes < pl.workspace)) return LA2_ERR_WORKSPACE;
   if (pl.workspace > 0 && !aligned(workspace, 256)) return LA2_ERR_WORKSPACE;
   if (check_only) return LA2_OK;
-  if (short_sequences(desc, false) && !same_state(desc, kv_final, kv_init))
+  if (short_forward(desc, kv_init != nullptr, kv_final != nullptr) && !same_state(desc, kv_final, kv_init))
     return run_short_fwd(desc, q, k, v, lambda, kv_init, o, kv_final, rstd, eps, desc->seqlen, nullptr, s);
   if (blocks.seqlen > 0) {
     ScanArgs a{q, k, v, o};
@@ -995,8 +1042,16 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return LA2_ERR_WORKSPACE;
   if (need > 0 && !aligned(workspace, 256)) return LA2_ERR_WORKSPACE;
   if (check_only) return LA2_OK;
-  if (short_sequences(desc, true))
+  // A forward call on the short path leaves its workspace as it was (whether that call handed out kv_final is not relied on):
+  // where this call is not short itself the states are recomputed, or, without the room for that, it is short all the same.
+  const bool unwritten = for_dq.saved_states != nullptr && short_forward(desc, kv_init != nullptr, false);
+  if (short_backward(desc, (kv_init != nullptr ? 1 : 0) + (d_kv_final != nullptr ? 2 : 0), d_kv_init != nullptr) ||
+      (unwritten && workspace_bytes < pl.workspace * (fuse ? 2 : 1)))
     return run_short_bwd(desc, q, k, v, d_o, lambda, kv_init, d_kv_final, dq, dk, dv, d_kv_init, nullptr, s);
+  if (unwritten) {
+    for_dq.saved_states = nullptr;
+    for_dq.saved_tr = false;
+  }
   float* handoff = split ? reinterpret_cast<float*>(static_cast<char*>(workspace) + sw.chunk_states) : nullptr;
   void* rev_workspace = workspace;
   if (fuse) {
@@ -1177,7 +1232,8 @@ la2_status fwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 256)))
     return LA2_ERR_WORKSPACE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  if (short_packed(desc, pl, total_positions, false) && !same_state(desc, kv_final, kv_init))
+  if (packed_without_map(desc, pl, total_positions) && short_forward(desc, kv_init != nullptr, kv_final != nullptr) &&
+      !same_state(desc, kv_final, kv_init))
     return run_short_fwd(desc, q, k, v, lambda, kv_init, o, kv_final, rstd, eps, (int)total_positions, cu_seqlens, s);
   ScanArgs a{q, k, v, o};
   a.cu = cu_seqlens;
@@ -1232,7 +1288,8 @@ la2_status bwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   const size_t need = pl.map_bytes + pl.workspace * (fuse ? 2 : 1);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 256)))
     return LA2_ERR_WORKSPACE;
-  if (short_packed(desc, pl, total_positions, true))
+  if (packed_without_map(desc, pl, total_positions) &&
+      short_backward(desc, (kv_init != nullptr ? 1 : 0) + (d_kv_final != nullptr ? 2 : 0), d_kv_init != nullptr))
     return run_short_bwd(desc, q, k, v, d_o, lambda, kv_init, d_kv_final, dq, dk, dv, d_kv_init, cu_seqlens, s);
   // the three scans of la2_bwd, each chain a sequence of its own length; states as in la2_bwd_state
   ScanArgs for_dq{d_o, v, k, dq}, for_dv{k, q, d_o, dv}, for_dk{v, d_o, q, dk};

@@ -70,7 +70,10 @@ def test_short_passes_with_and_without_states(dtype, d, n):
 
 # (chains, n) on both sides of every border of the rule: blocks of work, lengths, chains
 BORDERS = [(4, 1536), (4, 1537), (4, 3072), (4, 3073), (64, 768), (64, 769), (65, 200), (96, 256), (128, 256), (128, 257),
-           (128, 512), (129, 64), (129, 65), (256, 128), (256, 129), (512, 64), (513, 64), (16, 32), (16, 33)]
+           (128, 512), (129, 64), (129, 65), (256, 128), (256, 129), (512, 64), (513, 64), (16, 32), (16, 33),
+           # ... and of what states change: lengths, blocks of work with the states' share
+           (4, 640), (4, 641), (4, 1024), (4, 1025), (4, 1280), (4, 1281), (4, 2048), (4, 2049), (4, 2560), (4, 2561),
+           (32, 1024), (33, 640), (48, 512), (64, 384), (64, 640), (96, 128), (128, 128), (128, 200), (129, 33), (192, 128)]
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -78,7 +81,8 @@ BORDERS = [(4, 1536), (4, 1537), (4, 3072), (4, 3073), (64, 768), (64, 769), (65
 def test_short_against_the_block_recurrence(chains, n, d):
     """Both paths round the same operands to 16 bits in different places: their errors against fp64 are of one size (bound on
     the rms difference: both paths' rms bounds together).  The backward that is handed the forward call's workspace gives the
-    same bits as the one that is not, whatever was in that workspace."""
+    same bits as the one that is not, whatever was in that workspace, unless it read chunk states there: on a cut sequence,
+    where the forward call has written its workspace and the backward call uses its own."""
     H = next(h for h in (16, 8, 4, 3, 1) if chains % h == 0)
     dtype = torch.bfloat16
     gen = torch.Generator(device=DEV)
@@ -89,14 +93,19 @@ def test_short_against_the_block_recurrence(chains, n, d):
     runs = []
     for variant in (0, 2):
         binding.la2_set_scan_variant(variant)
-        ws = torch.full((max(1, binding.la2_workspace_bytes(q, binding.LA2_OP_FWD_STATE)),), 0xFF, dtype=torch.uint8, device=DEV)
+        ws, ws_b = (torch.full((max(1, binding.la2_workspace_bytes(q, op)),), 0xFF, dtype=torch.uint8, device=DEV)
+                    for op in (binding.LA2_OP_FWD_STATE, binding.LA2_OP_BWD_STATE))
         o, kvf = binding.la2_fwd_state(q, k, v, lam, kv_init=kv0, workspace=ws)
         grads = binding.la2_bwd_state(q, k, v, do, lam, kv_init=kv0, d_kv_final=dkvf)
-        saved = binding.la2_bwd_state(q, k, v, do, lam, kv_init=kv0, d_kv_final=dkvf, fwd_workspace=ws, fwd_wrote_kv_final=True)
+        saved = binding.la2_bwd_state(q, k, v, do, lam, kv_init=kv0, d_kv_final=dkvf, workspace=ws_b, fwd_workspace=ws,
+                                      fwd_wrote_kv_final=True)
         torch.cuda.synchronize()
+        read_states = not (ws == 0xFF).all() and not (ws_b == 0xFF).all()
+        if variant == 2:
+            assert read_states == (binding.la2_chunk_plan(q)[0] > 1)
         for x, y in zip(grads, saved):
-            # (chunked recurrence: the saved states are the forward's, the recomputed ones the dQ scan's own transposes)
-            assert torch.equal(x, y) or rms_rel(to64(x), to64(y)) <= RMS_TOL[dtype]
+            # (the saved states are the forward's, the recomputed ones the dQ scan's own transposes)
+            assert torch.equal(x, y) or (read_states and rms_rel(to64(x), to64(y)) <= RMS_TOL[dtype])
         runs.append((o, kvf) + tuple(grads))
     for name, a, b in zip(("o", "kv_final", "dq", "dk", "dv", "d_kv_init"), *runs):
         assert torch.isfinite(a).all(), name
@@ -220,3 +229,31 @@ def test_fp16_short_passes_lose_no_range(d, n, grad, padding):
         for h in range(4):
             a, b = (rms_rel(to64(x[0, h]), ref[0, h]) for x in (short, blocks))
             assert a <= 1.25 * b, "%s lambda %g: %.2e on the short path, %.2e in blocks" % (name, lams[h], a, b)
+
+
+@pytest.mark.parametrize("dtype,d,chains,n", [(torch.bfloat16, 128, 64, 640), (torch.bfloat16, 128, 16, 1536), (torch.float16, 64, 32, 1024)])
+def test_backward_in_blocks_after_a_short_forward(dtype, d, chains, n):
+    """A forward pass without states on the short path (its workspace stays as it was) and a backward with all of them that the
+    recurrence is faster at: it forms its own chunk states, or, given only the room for the other half of them, takes the short
+    path as well.  Either way nothing is read from the forward call's workspace."""
+    H = 16
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(chains + n + d)
+    q, k, v, do = ((torch.randn((chains // H, H, n, d), generator=gen, device=DEV) * d ** -0.5).to(dtype) for _ in range(4))
+    dkvf = torch.randn((chains // H, H, d, d), generator=gen, device=DEV) * 0.1
+    lam = torch.exp(-torch.pow(2.0, -8.0 * torch.arange(1, H + 1) / H)).to(DEV)
+    nchunks, _ = binding.la2_chunk_plan(q)
+    states = chains * nchunks * d * d * 4
+    assert nchunks > 1
+    ws = torch.full((states,), 0xFF, dtype=torch.uint8, device=DEV)   # (as fp32: NaN)
+    binding.la2_fwd(q, k, v, lam, workspace=ws)
+    fresh = binding.la2_bwd_state(q, k, v, do, lam, d_kv_final=dkvf)
+    outs = []
+    for size in (2 * states, states):
+        ws_b = torch.full((size,), 0xFF, dtype=torch.uint8, device=DEV)
+        outs.append(binding.la2_bwd_state(q, k, v, do, lam, d_kv_final=dkvf, workspace=ws_b, fwd_workspace=ws))
+        torch.cuda.synchronize()
+        assert bool((ws_b == 0xFF).all()) == (size == states)
+    assert bool((ws == 0xFF).all())
+    for x, y, z in zip(fresh, *outs):
+        assert torch.isfinite(x).all() and torch.equal(x, y) and rms_rel(to64(z), to64(x)) <= 2 * RMS_TOL[dtype]
