@@ -215,6 +215,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
   if (init != nullptr) {
     init += (int64_t)chain * (D * D);
     const bool tr = (p.init_transposed >> which) & 1;
+    const uint32_t lane = tr ? (uint32_t)(l32 * D + 8 * hh) : (uint32_t)(8 * hh * D + l32);   // (32-bit: no address pairs to spill)
 #pragma unroll
     for (int kk = 0; kk < KS; kk++) {
       if (kk / (KS / kGroups) != kg) continue;   // (unrolled with a uniform condition: xf[] is indexed by constants)
@@ -222,13 +223,13 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void short_scan_kerne
       for (int t = 0; t < NT; t++) {
         ex8<E> a;
         if (tr) {
-          const float* const g = init + (32 * t + l32) * D + 16 * kk + 8 * hh;
-          const f32x4 lo = *reinterpret_cast<const f32x4*>(g), up = *reinterpret_cast<const f32x4*>(g + 4);
+          const uint32_t at = lane + (uint32_t)(32 * t * D + 16 * kk);
+          const f32x4 lo = *reinterpret_cast<const f32x4*>(init + at), up = *reinterpret_cast<const f32x4*>(init + at + 4);
 #pragma unroll
           for (int j = 0; j < 4; j++) { a[j] = (E)lo[j]; a[4 + j] = (E)up[j]; }
         } else {
 #pragma unroll
-          for (int j = 0; j < 8; j++) a[j] = (E)init[(16 * kk + 8 * hh + j) * D + 32 * t + l32];
+          for (int j = 0; j < 8; j++) a[j] = (E)init[lane + (uint32_t)((16 * kk + j) * D + 32 * t)];
         }
         acc[t] = mfma(a, xf[kk], acc[t]);
       }

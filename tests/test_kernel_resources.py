@@ -33,7 +33,7 @@ def test_every_kernel_is_reported(resources):
     fams = {family(k) for k in resources}
     for f in ("scan_bf16_half_kernel", "scan_wide_kernel", "chunk_state_bf16_kernel", "scan_bf16_kernel", "scan_f32_kernel",
               "decode_kernel", "tail_bf16_kernel", "left_product_bf16_kernel", "norm_rows_kernel", "state_scan_kernel",
-              "recur_kernel", "varlen_map_kernel"):
+              "recur_kernel", "varlen_map_kernel", "short_scan_kernel"):
         assert f in fams, f
     for k, v in resources.items():
         for key in ("VGPRs", "ScratchSize", "Occupancy", "LDS"):
@@ -53,7 +53,7 @@ def test_no_kernel_has_a_dynamic_stack_or_more_lds_than_a_compute_unit(resources
 SCRATCH_LIMIT = {
     "scan_bf16_half_kernel": 32, "scan_wide_kernel": 32, "chunk_state_bf16_kernel": 0, "scan_bf16_kernel": 0,
     "scan_f32_kernel": 0, "decode_kernel": 0, "tail_bf16_kernel": 0, "left_product_bf16_kernel": 0,
-    "norm_rows_kernel": 0,
+    "norm_rows_kernel": 0, "short_scan_kernel": 0,
 }
 
 
@@ -76,6 +76,9 @@ def test_occupancy_the_kernels_are_designed_for(resources):
             assert v["Occupancy"] >= 2, (k, v["Occupancy"])
         if f == "scan_wide_kernel" and "Li96E" in k and not k.split("Li96E")[1].startswith("Lb1ELb0ELb0ELb1E"):
             assert v["Occupancy"] >= 3, (k, v["Occupancy"])
+        if f == "short_scan_kernel":   # workgroups of four waves: four share a unit at head_dim 64, two at 128 (by LDS too)
+            assert v["Occupancy"] >= (4 if "Li64E" in k else 2), (k, v["Occupancy"])
+            assert v["LDS"] * (4 if "Li64E" in k else 2) <= LDS_PER_CU, (k, v["LDS"])
         if f in ("decode_kernel", "norm_rows_kernel"):
             assert v["Occupancy"] >= 4, (k, v["Occupancy"])
 
