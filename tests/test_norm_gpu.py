@@ -58,6 +58,7 @@ def check_norm(t, dtype, eps, tag, g=None):
     return o, rstd, d_u, (dq, dk, dv)
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [1, 31, 64, 129, 200, 517])
@@ -85,6 +86,7 @@ def test_norm_eps_values(eps):
         assert torch.max(torch.abs(ms - 1.0)).item() <= {torch.bfloat16: 2e-2, torch.float16: 2.5e-3, torch.float32: 1e-5}[dtype]
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_norm_strided_layout():
     """[b, n, H, d] storage viewed as [b, H, n, d]; rstd stays dense [b, H, n]."""
     b, H, n, d = 2, 4, 260, 128
@@ -99,6 +101,7 @@ def test_norm_strided_layout():
             assert x.stride() == g["q"].stride()
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_norm_backward_is_algorithm2_on_d_u():
     """la2_bwd_norm = the row pass followed by la2_bwd on d_u: bitwise the same gradients."""
     t = make_inputs(2, 2, 300, 128, torch.bfloat16, seed=741)

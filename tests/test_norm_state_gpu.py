@@ -75,6 +75,7 @@ def test_segment_chunked(dtype, d, chunk):
     check(t, g, dtype, "d%d %s chunk %d, zero start" % (d, dtype, chunk), init=False)
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("d", [64, 128, 256])
 def test_two_segments_against_the_whole_sequence(d):
     t, g = inputs(1, 2, 150, d, torch.bfloat16, seed=3200 + d, lam=[0.9, 0.97])
@@ -93,6 +94,7 @@ def test_two_segments_against_the_whole_sequence(d):
     assert_close("whole o", ow, ro, torch.bfloat16)
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_strided_layout_and_given_buffers():
     t, g = inputs(2, 3, 90, 128, torch.bfloat16, seed=3300)
     for name in ("q", "k", "v", "d_o"):

@@ -65,6 +65,7 @@ def test_config2_fwd_bwd_bf16_full():
 
 
 # ---- small shapes spanning several tiles and ragged tails, both dtypes, both head dims ------------------------------
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [1, 31, 128, 129, 200, 384, 517])
@@ -212,6 +213,7 @@ def test_unscaled_values_and_slow_decay(dtype):
     check_fwd_bwd(t, dtype, "unscaled %s" % dtype)
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_extreme_decays():
     """lambda = 1 (pure causal prefix sum) and a very small lambda (only the diagonal survives)."""
     for dtype in (torch.bfloat16, torch.float16, torch.float32):
@@ -219,6 +221,7 @@ def test_extreme_decays():
         check_fwd_bwd(t, dtype, "extreme decays %s" % dtype)
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_strided_layout():
     """[b, n, H, d] storage viewed as [b, H, n, d]: strides go through the descriptor."""
     b, H, n, d = 2, 4, 260, 128
@@ -296,8 +299,10 @@ def test_batches_a_little_above_the_compute_unit_count(b, H, n, d, strided, dtyp
         assert torch.isfinite(x.float()).all()
 
 
-def test_deterministic_and_causal():
-    t = gpu(make_inputs(2, 2, 700, 128, torch.bfloat16, seed=41))
+@pytest.mark.parametrize("d,n", [(128, 700), (64, 1300)])
+def test_deterministic_and_causal(both_paths, d, n):
+    t = gpu(make_inputs(2, 2, n, d, torch.bfloat16, seed=41))
+    assert binding.la2_chunk_plan(t["q"])[0] > 1   # (blocks: pre-pass, accumulating dQ launch and twin launch)
     o1 = binding.la2_fwd(t["q"], t["k"], t["v"], t["lam"])
     o2 = binding.la2_fwd(t["q"], t["k"], t["v"], t["lam"])
     g1 = binding.la2_bwd(t["q"], t["k"], t["v"], t["d_o"], t["lam"])
@@ -420,6 +425,7 @@ def test_decode_matches_forward(d, dtype):
     assert max_rel(to64(kv), kvf) <= 1e-5
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_hip_graph_capture_and_replay():
     """The library allocates nothing and never synchronises, so a forward + backward (incl. the chunked
     path with its workspace) can be captured into a HIP graph.  Replays, with eager work and
@@ -461,6 +467,7 @@ def test_hip_graph_capture_and_replay():
             torch.cuda.synchronize()
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_hip_graph_capture_of_the_other_entry_points():
     """Segments with state hand-over (ragged: block kernels + short-run kernels), the normalised operator,
     multi-token decode and a decode step in one captured graph; replays reproduce the eager results bit for bit."""

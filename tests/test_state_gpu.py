@@ -60,6 +60,7 @@ def check_segment(t, dtype, tag, use_init=True, use_final=True):
     assert_close(tag + " d_kv_init", dkv0, rdkv0, dtype)
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [64, 128, 320])
@@ -68,6 +69,7 @@ def test_segment_with_all_states(dtype, d, n):
     check_segment(t, dtype, "n%d d%d %s" % (n, d, dtype))
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [1, 31, 64, 100, 129, 300])
@@ -134,6 +136,7 @@ def test_fp32_chunked_segment():
     check_segment(t, torch.float32, "fp32 chunked")
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 def test_two_segments_equal_the_whole_sequence(dtype):
     """Forward left to right, backward right to left through the hand-over states, against the oracle's
@@ -159,6 +162,7 @@ def test_two_segments_equal_the_whole_sequence(dtype):
     assert_close("two segments dv", torch.cat([dv1, dv2], 2), rv, dtype)
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_prefill_then_decode():
     """The final state of a prefill continues with la2_decode_step (same state layout)."""
     b, H, n, d = 2, 4, 256, 128

@@ -63,6 +63,7 @@ def check_packed(lengths, H, d, dtype, seed, lead=0, trail=0, lam=None):
         assert torch.isfinite(x[int(cu[0]): int(cu[-1])].float()).all()
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
 @pytest.mark.parametrize("d", [64, 128])
 def test_mixed_lengths(dtype, d):
@@ -156,6 +157,7 @@ def test_an_uncut_batch_needs_no_workspace():
     assert torch.equal(o, o2) and all(torch.equal(a, b) for a, b in zip(grads, grads2))
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_offset_first_sequence_and_unused_tail():
     check_packed([200, 45], 2, 128, torch.bfloat16, seed=820, lead=7, trail=9)
 
@@ -166,6 +168,7 @@ def test_scan_variants(variant):
     check_packed([129, 64, 300], 2, 128, torch.bfloat16, seed=830 + variant)
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_equal_lengths_reproduce_the_dense_batch_bit_for_bit():
     b, H, n, d = 3, 4, 260, 128
     t = workloads.Workload("dense", b, H, n, d, torch.bfloat16, seed=840).tensors()

@@ -78,6 +78,7 @@ def check_packed_state(lengths, H, d, dtype, seed, lam=None, use_init=True, use_
         assert torch.isnan(kvf).all()   # not asked for: not written
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("d", [64, 128])
 def test_mixed_lengths_with_all_states(dtype, d):
@@ -85,6 +86,7 @@ def test_mixed_lengths_with_all_states(dtype, d):
     check_packed_state([70, 0, 1, 31, 32, 33, 100, 517, 64, 3, 96], 3, d, dtype, seed=900 + d, lam=[0.5, 0.93, 1.0])
 
 
+@pytest.mark.usefixtures("both_paths")
 @pytest.mark.parametrize("d", [64, 128])
 def test_either_end_only(d):
     lengths = [45, 64, 0, 130, 7]
@@ -101,6 +103,7 @@ def test_mixed_lengths_chunked(dtype, d, chunk):
     check_packed_state([700, 130, 64, 1000, 5, 0, 383, 192], 2, d, dtype, seed=920 + d + chunk, lam=[0.8, 0.99])
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_small_lambda_keeps_the_ragged_end_state_exact():
     """A decay so strong that lambda^31 underflows in fp32: the ragged block's weights are formed from
     non-negative exponents only, never as a correction by a negative power."""
@@ -115,6 +118,7 @@ def test_skewed_lengths_with_many_chains(d):
     check_packed_state(lengths, 2, d, torch.bfloat16, seed=940 + d, lam=[0.7, 0.995])
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_packed_prefill_then_decode_continues_the_sequences():
     """What the final states are for: a packed prefill, then decode steps from its states, equal the oracle's
     forward pass over each sequence with the decoded positions appended."""
@@ -144,6 +148,7 @@ def test_packed_prefill_then_decode_continues_the_sequences():
         assert_close("decode step %d after the packed prefill" % s, o1, want, dtype)
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_two_packed_calls_equal_one():
     """Every sequence fed in two pieces (the second call starts from the first call's states) against the oracle's
     direct form of the whole sequences; gradients flow back through the hand-over states."""
@@ -244,6 +249,7 @@ def test_hip_graph_capture_of_the_packed_entry_points():
         torch.cuda.synchronize()
 
 
+@pytest.mark.usefixtures("both_paths")
 def test_padded_rows_and_head_major_storage():
     """Packed tensors need not be dense: rows padded to d + 8 elements, and heads stored outermost ([H, total, d]
     viewed as [total, H, d]); states stay dense."""

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2401_04658_amd import binding, workloads
-from parity import assert_close, to64
+from parity import TOL, assert_close, to64
 
 pytestmark = pytest.mark.gpu
 
@@ -341,3 +341,38 @@ def test_hip_graph_capture_and_replay(d):
             assert torch.equal(got, ref), (replay, i)
         run(buffers())                 # eager work between the replays
         torch.cuda.synchronize()
+
+
+# tensors of more than 160 MiB, whose tiles are loaded past the caches; chunks (pre-pass) at both head dimensions, and head_dim 256
+# un-chunked, where the forward and the dQ scan run as two workgroups each and the dK / dV launch as one
+@pytest.mark.parametrize("d,chains,n,cut", [(96, 24, 40003, True), (256, 16, 24579, True), (256, 128, 3071, False)])
+def test_large_tensors_on_sampled_rows(d, chains, n, cut):
+    H = 8
+    dtype = torch.bfloat16
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + n)
+    q, k, v, do = ((torch.randn((chains // H, H, n, d), generator=gen, device=DEV) * d ** -0.5).to(dtype) for _ in range(4))
+    assert q.numel() * 2 > 160 << 20
+    lam = torch.exp(-torch.pow(2.0, -8.0 * torch.arange(1, H + 1) / H)).to(DEV)
+    nchunks, chunk = binding.la2_chunk_plan(q)
+    assert (nchunks > 1) == cut
+    o = binding.la2_fwd(q, k, v, lam)
+    grads = binding.la2_bwd(q, k, v, do, lam)
+    on, rstd = binding.la2_fwd_norm(q, k, v, lam, 1e-4)
+    torch.cuda.synchronize()
+    for x in (o, on, rstd) + tuple(grads):
+        assert torch.isfinite(x.float()).all()
+    rows = np.array(sorted({0, 1, 31, 32, n // 2, n - 33, n - 2, n - 1} | {c * chunk + e for c in (1, nchunks - 1) for e in (-1, 0)
+                                                                     if 0 < c * chunk < n}), dtype=np.int64)
+    for b, h in ((0, 0), (chains // H - 1, H // 2), (0, H - 1)):
+        x = [to64(t[b, h]) for t in (q, k, v, do)]
+        lam_h = float(lam[h].double())
+        ref = oracle.fwd_rows(*x[:3], lam_h, rows)
+        refs = (ref,) + tuple(oracle.bwd_rows(*x, lam_h, rows))
+        for name, got, want in zip(("o", "dq", "dk", "dv"), (o,) + tuple(grads), refs):
+            err = np.max(np.abs(to64(got[b, h])[rows] - want)) / np.max(np.abs(want))
+            assert err <= TOL[dtype], "%s b%d h%d: %.2e" % (name, b, h, err)
+        r = 1.0 / np.sqrt(np.mean(ref * ref, axis=-1) + 1e-4)
+        assert np.max(np.abs(to64(rstd[b, h])[rows] / r - 1)) <= TOL[dtype]
+        want = ref * r[:, None]
+        assert np.max(np.abs(to64(on[b, h])[rows] - want)) <= TOL[dtype] * np.max(np.abs(want))
