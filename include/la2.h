@@ -102,7 +102,12 @@ size_t la2_workspace_bytes(const la2_desc* desc, int32_t op);
  * loop of Algorithm 1 / 2 runs over the whole sequence in one workgroup per (batch, head).  The workspace
  * holds one d x d fp32 start state per (batch, head, chunk) when nchunks > 1.  Depends on the device's
  * compute-unit count and on la2_set_chunk_tokens(), like la2_workspace_bytes().
- * One case it does not describe: a batch with a few more chains than a whole number (one to four) per compute unit,
+ * Two cases it does not describe.  Short sequences on few chains (16-bit data, head_dim 64 and 128, no
+ * la2_set_chunk_tokens(), la2_set_scan_variant() 0; up to 1536 positions forward and 3072 backward, fewer the more
+ * chains there are and the more states a call carries) run as one launch that forms every output row from all the
+ * positions it depends on, without chunks and in time quadratic in seqlen, where that was measured to be faster.
+ * What a call asks for stays the same: the workspace of the plan is required as always and left as it is.
+ * And a batch with a few more chains than a whole number (one to four) per compute unit,
  * which as one launch gives some units a workgroup more than the others and takes up to twice as long as whole
  * rounds.  Every entry point that takes a dense
  * batch (la2_fwd, la2_bwd, their _state, _saved, _norm and _noalloc forms) runs it as two calls on the given
@@ -341,7 +346,8 @@ la2_status la2_decode_step_norm(int32_t batch, int32_t heads, int32_t head_dim, 
  *                            la2_fwd_state); if that plan differs from this call's, the saved states are not used
  *                            and the result is that of la2_bwd_state.
  * The chunk plan also depends on la2_set_chunk_tokens() and the device, and what the workspace holds of 16-bit data on
- * la2_set_scan_variant(): both calls must see the same.
+ * la2_set_scan_variant(): both calls must see the same.  A forward call that ran as one launch (see la2_chunk_plan) left no
+ * states there; this call knows by the same rule and does not read the buffer then.
  * A batch that runs as two calls (see la2_chunk_plan) left only its second part's chunk states in fwd_workspace; the
  * second part of this call reads them, the first part, should its own plan cut, recomputes.
  */
@@ -401,9 +407,10 @@ la2_status la2_decode_multi_norm(int32_t batch, int32_t heads, int32_t head_dim,
                                  void* hip_stream);
 
 /*
- * Block size B (rows of the intra-block tile, Algorithm 1) of the scan kernel the library launches
- * for this descriptor under the current la2_set_scan_variant(); results do not depend on it beyond
- * rounding.  Returns 0 for an invalid descriptor.  Used to report FLOPs with the formula of
+ * Block size B (rows of the intra-block tile, Algorithm 1) of the scan kernel of the block recurrence
+ * for this descriptor under the current la2_set_scan_variant() (a call that runs as one launch, see
+ * la2_chunk_plan, has no such blocks; an Inf or NaN spreads over as many positions there); results do not depend
+ * on it beyond rounding.  Returns 0 for an invalid descriptor.  Used to report FLOPs with the formula of
  * Algorithms 1 and 2.
  */
 int32_t la2_block_size(const la2_desc* desc);
@@ -419,13 +426,14 @@ void la2_set_chunk_tokens(int32_t tokens);
 /*
  * Test / tuning knob: which 16-bit scan kernel la2_fwd / la2_bwd launch at head_dim 64 and 128.
  *   0  automatic (currently the half-block kernel: blocks of 32 positions, up to two workgroups per
- *      compute unit; it measured faster than the full-block kernel at every launch size)
+ *      compute unit; it measured faster than the full-block kernel at every launch size; short sequences on few
+ *      chains run as one launch of masked products instead, see la2_chunk_plan)
  *   1  the full-block kernel (blocks of 64 positions, one workgroup per compute unit)
  *   2  the half-block kernel
  * Other values are taken as 0.  Both kernels implement Algorithm 1's block recurrence (the block
- * size is the algorithm's free parameter B); results differ by rounding only.  Process-global, as
- * la2_set_chunk_tokens.  Ignored for fp32, for head_dim 96 / 256, and by calls that carry states or the Norm
- * epilogue (only the half-block kernel has those).  With 1 the backward pass of a sequence-chunked problem forms
+ * size is the algorithm's free parameter B); results differ by rounding only, from the one launch's too.
+ * Process-global, as la2_set_chunk_tokens.  Ignored for fp32 and for head_dim 96 / 256.  Calls that carry states or
+ * the Norm epilogue run the half-block kernel with 1 as with 2 (only it has those).  With 1 the backward pass of a sequence-chunked problem forms
  * the chunk states of its second loop in a pass of its own instead of inside the first loop's launch.
  */
 void la2_set_scan_variant(int32_t variant);

@@ -11,7 +11,8 @@
 // straight from those registers, so the state needs no LDS copy and no extra workgroup barrier.
 // For d = 128 a wave covers both 32-row tiles of the block; for d = 64 two waves share a value tile,
 // one row tile each (and keep identical copies of the state slice).  Every wave computes the masked
-// score tiles it needs itself, so the scores never leave registers either.  One barrier per block.
+// score tiles it needs itself, so the scores never leave registers either.  One barrier per block
+// (the half-block kernel: two, the second for its output tile).
 //
 // MFMA 32x32x16 (v_mfma_f32_32x32x16_bf16) lane layouts (wave64, lane l, l32 = l % 32, hh = l / 32):
 //   A[m][k]: m = l32, k = 8 hh + j (j = 0..7)     B[k][n]: n = l32, k = 8 hh + j

@@ -130,8 +130,9 @@ hipError_t launch_state_copy(float* dst, const float* src, int64_t count, hipStr
 // comes is better left there; a model of several layers goes through all their states before it returns to the first one,
 // and what does not fit costs more than a stream.  Decode step, head_dim 128, through the caches (stores nt) against streaming,
 // us: states of 64, 128, 256 MiB, one state used again at once 22.5 23.4, 43 47, 82 91; three in turn 22.5 23.4, 44 47, 106 92;
-// twelve in turn 29.7 23.4, 55 47, 106 91.  Eight tokens a launch: 256 MiB 93 103, 114 104, 114 103.  The line: from where two
-// states never fit together, so that a state is found again only if nothing else runs in between.  Head_dim 256, whose
+// twelve in turn 29.7 23.4, 55 47, 106 91.  Eight tokens a launch: 256 MiB 93 103, 114 104, 114 103.  The line lies between 128
+// MiB, where the caches win with one and with three states in turn, and 256, where they win with one alone; many layers in turn
+// would stream from 64 MiB on, a few would lose 4 to 9 % there.  Head_dim 256, whose
 // workgroup has a compute unit to itself and loads and stores by turns, gains nothing (three of 256 MiB in turn 105, 106).
 bool stream_state(int64_t chains, int head_dim) {
   return head_dim != 256 && chains * head_dim * head_dim * (int64_t)sizeof(float) >= (int64_t)160 << 20;

@@ -7,7 +7,7 @@ namespace {
 using namespace bf16k;
 
 // Blocks of 32 positions, one wave per 32 value features (D / 32 waves per scan: 4 for d = 128, 2 for d = 64),
-// at most 256 registers and 80 KiB (d = 128) or 38 KiB (d = 64) of LDS, so that TWO (d = 128) or FOUR (d = 64)
+// at most 256 registers and 80 KiB (d = 128) or 40 KiB (d = 64) of LDS, so that TWO (d = 128) or FOUR (d = 64)
 // workgroups share a compute unit: two waves per SIMD.  One wave alone issues its
 // instructions one after the other (an MFMA holds the issue port for about half its run time, a
 // 16-byte-per-lane memory instruction for about 60 cycles), so a single wave per SIMD leaves the
@@ -72,8 +72,9 @@ void scan_bf16_half_kernel(ScanParams p) {
   // tensors of 16 MiB 0.92-0.94, 64 MiB 0.91-0.96, 128 MiB 0.92-0.97, 256 MiB in chunks 0.95-0.96, uncut 0.98 (a forward
   // pass alone, repeated on the same 1 GiB of tensors, 1.06-1.08; nt without sc1 1.01-1.02).
   // Whole rows against 64-byte pieces of them (both streaming): packed 65,536 positions, d 128, H 16 914 -> 877 us, d 64, H 32
-  // 940 -> 852; one chain batch of 65,536, d 128, from saved states 870 -> 858; batch 16, n 4096, d 64 342 -> 336; batch 4, n 2048,
-  // d 64 68.7 -> 70.1 (the second barrier of a block).
+  // 940 -> 852; batch 16, n 4096, d 64 342 -> 336; one chain batch of 65,536, d 128, from saved states 870 -> 858 (the whole launch
+  // sequence against ordinary stores, in turn on three boxes, 1.0 to 1.6 %); batch 4, n 2048, d 64 68.7 -> 70.1 (the second barrier
+  // of a block).
   constexpr int kStorePolicy = 18;
   constexpr int NDMA = NTL * Loader::DMA_PER_WAVE;   // direct loads per wave and block
   constexpr int NST = 32 * 4 / 64 + (NORM ? 1 : 0);   // stores per lane and block: 16-byte output stores, r

@@ -378,7 +378,8 @@ __device__ __forceinline__ int walk(const ScanParams& p, Lds<D, STATE_ONLY>& lds
     const int pos = keep ? blk * B + l32 : n;
     // Rows of 16 lanes exchange pieces so that an instruction stores whole 64-byte pieces of sixteen positions, which a
     // streaming store needs (16 bytes a lane in 32 rows: 1.25 times the time of the whole launch).  Batch 4, H 16, n 2048,
-    // d 128, forward + backward, against 16-byte pieces through the caches: 433 -> 425 us.
+    // d 128, forward + backward, against 16-byte pieces through the caches: 433 -> 425 us replayed from a graph; as a program's
+    // calls, the two in turn on three boxes, 0.5 to 0.9 %.
     auto store_rows = [&]() __attribute__((always_inline)) {
       const uint32_t row = (uint32_t)((keep ? blk * B : n) + (l32 & 15));
       const uint32_t off = (row * stride_n + (uint32_t)(32 * dvt + 8 * (l32 >> 4) + 4 * hh)) * 4u;

@@ -12,7 +12,8 @@
 // Work split: four waves, two row tiles of 32 x two key groups; a step is 64 positions of Y and Z, a tile of 32 per key
 // group, loaded straight into LDS (two buffers: the next step's tiles are on their way while one is used; one barrier a step).
 // The key groups' sums meet in LDS at the end, in the tiles' place, where the row is complete for the Norm epilogue.  Scores,
-// mask and operands as in the scan kernels: 16-bit operands, fp32 sums, the masked scores rounded to 16 bits once.
+// mask and operands as in the scan kernels: 16-bit operands, fp32 sums, the masked scores rounded to 16 bits once; what is
+// rounded carries the decay of one tile at most where the type's range asks for that (fp16 scores, all states).
 // MFMA and LDS layouts: la2_bf16_common.h.
 //
 // What bounds it: a workgroup's own instruction stream.  A step takes a lone workgroup about 0.65 us (d 128; 0.4 at d 64), of
@@ -22,10 +23,11 @@
 // launches 20-40 % slower), two waves (the reverse: 10 % either way), three and four buffers (no change: not the loads'
 // latency), all LDS reads ahead of the products (no change), the loads between the products (8 % slower: they come later),
 // the non-temporal hint on the loads (15 % slower: other workgroups read the same tiles).
-// Forward / backward of 16 chains, against the block recurrence (chunk-state pre-pass and scans), us from a replayed graph:
-// d 128, n 128: 7.7 -> 5.8, 17.7 -> 6.1; n 512: 19.4 -> 10.2, 46.5 -> 12.5; n 1024: 22.9 -> 15.9, 49.0 -> 24.0;
-// With the state handed out, 16 chains of 777 positions, d 128: 23.8 -> 14.8 (18.4 with one workgroup per chain's state).
-// d 64, n 128: 6.0 -> 4.5, 12.2 -> 4.6; n 512: 13.5 -> 7.2, 28.3 -> 8.2; n 1024: 14.5 -> 11.0, 26.5 -> 13.8.
+// Forward / backward of 16 chains, against the block recurrence (chunk-state pre-pass and scans), us from a replayed graph, bf16:
+// d 128, n 128: 8.1 -> 6.4, 18.5 -> 6.7; n 512: 20.0 -> 10.7, 48.3 -> 13.0; n 1024: 23.1 -> 16.8, 48.9 -> 25.9;
+// d 64, n 128: 6.5 -> 5.1, 12.9 -> 5.2; n 512: 14.5 -> 7.7, 30.0 -> 8.5; n 1024: 14.7 -> 11.3, 27.4 -> 13.7.
+// fp16 takes 8 to 15 % longer, d 64 up to 25 (the scores' scales, below).  With the state handed out, 16 chains of 777 positions,
+// d 128: 23.8 -> 14.8 (18.4 with one workgroup per chain's state).  A start state is read by every row block: 3 us more at d 128.
 #include "la2_bf16_common.h"
 
 namespace la2 {
