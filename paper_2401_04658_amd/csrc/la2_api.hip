@@ -646,7 +646,7 @@ size_t bwd_workspace_need(const la2_desc* d, bool has_d_kv_final) {
 //          64, 512     8.5   14.4   9.8   15.2     10.2  14.6    11.8  15.3      15.9  29.7   16.9  30.6     23.9  31.1
 //          128, 256    7.0   9.1    8.0   10.0     8.9   9.2     9.6   10.2      12.9  18.6   13.8  19.5     22.2  20.1
 //          512, 128    8.9   8.4    11.3  10.7     12.5  9.2     17.6  11.5      19.1  18.3   22.7  20.5     40.6  22.3
-// The lines below are where the ratio reaches 1, from 15 numbers of chains, 1 to 512, times 17 lengths, 33 to 3072, times the ten forms
+// The lines below are where the ratio reaches 1, from 15 numbers of chains, 1 to 512, times 17 lengths, 33 to 3072 (and 250 drawn shapes), times the ten forms
 // (forward with a start state or not, with the state out or not; backward with each of its states or not), times both types: of
 // the 4700 measured cells that they take four are slower than the recurrence, by 3 to 6 %.  (fp16 has more to do in the short
 // path: the scores' scales.)  A forward pass of one block of 32 is no faster.
@@ -672,14 +672,17 @@ bool short_forward(const la2_desc* d, bool in, bool out) {
   if (d->head_dim == 128) {
     if (n <= (f16 ? 64 : 32) || n > (f16 ? 1280 : 1536)) return false;
     if (in) {
-      if (n <= (out && !f16 ? 64 : 128) || n > (f16 ? 1024 : 1280)) return false;
+      if (n <= (!out ? 160 : f16 ? 128 : 96) || n > (f16 ? 1024 : 1280)) return false;
       if (8 * chains <= cus) return blocks <= (out && f16 ? 15 : 20);
       return !out && 4 * chains <= cus && blocks <= 11;
     }
     return 4 * chains <= cus ? blocks <= 20 : !out && 2 * chains <= cus && blocks <= 5;
   }
-  if (n <= (in && !out ? 64 : 32)) return false;
-  if (in || out) return n <= (in && out ? 640 : 1024) && 2 * chains <= cus && blocks <= (!in ? 20 : out ? 15 : 17.25);
+  if (n <= (in && !out ? 96 : 32)) return false;
+  if (in || out) {   // (a recurrence of up to 18 blocks that is not cut takes 17 to 28 us)
+    const int most = make_plan(d).nchunks == 1 ? 1152 : in && out ? 640 : 1024;
+    return n <= most && 2 * chains <= cus && blocks <= (!in ? 20 : out ? 15 : 17.25);
+  }
   if (2 * chains <= cus) return n <= (f16 ? 1280 : 1536) && blocks <= 20;
   return chains <= 2 * cus && n <= (f16 ? 64 : 128) && blocks <= 5;
 }

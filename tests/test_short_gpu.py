@@ -73,6 +73,7 @@ BORDERS = [(4, 1536), (4, 1537), (4, 3072), (4, 3073), (64, 768), (64, 769), (65
            (128, 512), (129, 64), (129, 65), (256, 128), (256, 129), (512, 64), (513, 64), (16, 32), (16, 33),
            # ... and of what states change: lengths, blocks of work with the states' share
            (4, 640), (4, 641), (4, 1024), (4, 1025), (4, 1280), (4, 1281), (4, 2048), (4, 2049), (4, 2560), (4, 2561),
+           (4, 96), (4, 97), (4, 160), (4, 161), (4, 700), (16, 1100), (16, 1152), (16, 1153),
            (32, 1024), (33, 640), (48, 512), (64, 384), (64, 640), (96, 128), (128, 128), (128, 200), (129, 33), (192, 128)]
 
 
