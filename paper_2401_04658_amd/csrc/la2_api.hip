@@ -313,10 +313,33 @@ Plan packed_call_plan(const la2_desc* d, int64_t total_positions, const void* wo
 // loads (both with streaming stores at head_dim 64 / 128), bf16, inputs changing from pass to pass: head_dim 64 / 128, 16 MiB
 // 0.97-1.01, 32 MiB 0.95-0.97, 64 MiB 0.94-0.97, 128 MiB 1.00-1.04, 256 MiB 1.03-1.07; head_dim 96, 18 and 72 MiB 0.91, 144
 // 0.97-0.99, 288 MiB 1.00; head_dim 256, 32 MiB 0.96, 128 MiB 0.99, 256 MiB 1.00-1.03.
-int keep_tiles(const la2_desc* d, const Plan& pl) {
-  const int64_t rows = (pl.total > 0 ? pl.total : (int64_t)d->batch * d->seqlen) * d->heads;
-  const int64_t most = (int64_t)(wide(d->head_dim) ? 160 : 96) << 20;
-  return rows * d->head_dim * elem_size(d->dtype) <= most;
+// prefill: a forward pass that hands out its state is followed by decoding, not by a backward pass that finds the tiles again.
+// Tiles kept -> not, in parts of the time without either policy (ordinary stores of 64-byte pieces, non-temporal loads), bf16, d
+// 128: 192, 256, 512 chains of 500 positions 1.05 -> 0.96, 1.12 -> 1.03, 1.07 -> 1.03, 256 of 777 and 1036 1.14 -> 1.08; d 256: 26 chains of 4096 and 8192 1.08 -> 1.04,
+// 1.05 -> 0.98; 160, 256, 512 of 500 1.07, 1.01, 1.06 -> 1.01, 0.99, 0.99; d 96, 512 of 500 1.09 -> 1.04.  Below 16 MiB it is even
+// (and a pass that is cut into chunks reads K and V twice: d 96, 26 chains of 2062 0.81 -> 0.92).
+int64_t tensor_bytes(const la2_desc* d, const Plan& pl) {
+  return (pl.total > 0 ? pl.total : (int64_t)d->batch * d->seqlen) * d->heads * d->head_dim * elem_size(d->dtype);
+}
+int keep_tiles(const la2_desc* d, const Plan& pl, bool prefill) {
+  return tensor_bytes(d, pl) <= (int64_t)(prefill ? 16 : wide(d->head_dim) ? 160 : 96) << 20;
+}
+
+// ScanParams::plain, forward passes.  Streaming stores (the default: see the kernels) leave the caches to the inputs, but they are
+// acknowledged later, and a wave that waits for its next tiles waits for its older stores as well.  Ordinary ones where that costs
+// more:
+// - a prefill in about one full round of workgroups on tensors that the caches hold several of (streaming against ordinary, both
+//   with non-temporal loads, in parts of the same time: d 128, 256 chains of 500, 777, 1036 1.03 0.98, 1.09 0.99, 1.08 1.00; 224 of 1036
+//   1.02 0.97; 192 of 1036 0.97 1.02; 288 1.00 0.96; 256 of 1500, 2048 0.99 0.99, 0.92 1.00; d 64, 512 of 500, 777, 1036, 2048
+//   1.03 0.99, 1.05 0.98, 1.07 0.99, 0.95 0.98; 384 1.00 0.99; 256 1.00 1.05);
+// - head_dim 96 / 256 with the Norm on packed batches of unequal lengths, which are not cut: at the end a few workgroups walk the
+//   longest sequences alone, and the Norm's block has two waits (63,827 positions, longest 15,699, H 8, d 96 710 -> 618 us, d 256
+//   1376 -> 1301; without the Norm the gain is nil to -10 %).
+int plain_stores(const la2_desc* d, const Plan& pl, const int32_t* cu, bool prefill, bool norm) {
+  const int64_t chains = (int64_t)d->batch * d->heads;
+  if (wide(d->head_dim)) return norm && cu != nullptr && pl.total > 0 && chains * d->seqlen > 2 * pl.total * d->heads;
+  return prefill && cu == nullptr && pl.nchunks == 1 && chains * d->head_dim >= (int64_t)112 * device_cu_count() &&
+         tensor_bytes(d, pl) <= (int64_t)72 << 20;
 }
 
 // Grid sizes of every launch a plan leads to, checked on the host before the first one: the scan kernels take
@@ -495,7 +518,7 @@ la2::ScanParams base_params(const la2_desc* d, const Plan& pl, const float* lamb
   p.even_chunks = pl.even;
   p.variant = g_scan_variant.load(std::memory_order_relaxed);
   p.self_prefix = self_prefix(d, pl, cu) ? 1 : 0;
-  p.keep = keep_tiles(d, pl);
+  p.keep = keep_tiles(d, pl, false);
   return p;
 }
 
@@ -554,6 +577,9 @@ la2_status run_scan(const la2_desc* d, const Plan& pl, bool reverse, const ScanA
   p.acc_states = a.acc_states;
   p.ragged_state = a.ragged_state ? 1 : 0;
   p.value_split = value_split(d, p);
+  p.keep = keep_tiles(d, pl, a.fin != nullptr);   // (of the launches here only a forward pass hands out a state)
+  p.plain = plain_stores(d, pl, a.cu, a.fin != nullptr, a.rstd != nullptr);
+  if (p.plain != 0 && !wide(d->head_dim)) p.keep = 0;
   hipError_t e = wide(d->head_dim) ? la2::launch_scan_wide(d->dtype, d->head_dim, reverse, false, p, s)
                 : is16(d->dtype)   ? la2::launch_scan_bf16(d->dtype, d->head_dim, reverse, p, s)
                                    : la2::launch_scan_f32(d->head_dim, reverse, p, s);

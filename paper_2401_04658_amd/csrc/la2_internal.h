@@ -97,6 +97,8 @@ struct ScanParams {
   // tensors two or three times; where those are small enough to be found in the 256 MiB memory-side cache (keep_tiles in
   // la2_api.hip) their loads carry no non-temporal hint.
   int32_t keep;
+  // 16-bit forward passes, non-zero: outputs are stored through the caches instead of past them (plain_stores in la2_api.hip)
+  int32_t plain;
 };
 // self_prefix: most terms a start state is formed from in the 16-bit half-block kernels, which keep them in registers (the
 // caller's start state and the local states of three chunks); the fp32 and the head_dim 96 kernels loop over them

@@ -44,11 +44,12 @@ constexpr int kBH = 32;
 // such a block reaches row r with lambda^(rem-1-r) and is carried on with lambda^rem.  A chain without positions
 // hands its start state (or zero) to fin.  All of it is off the per-block path of a chain's other blocks.
 //
-// KEEP: the tile loads without the non-temporal hint (ScanParams::keep).
-template <typename E, int D, bool KEEP, bool REV, bool TWIN, int NBUF, bool NORM = false, bool ACC = false, bool RS = false>
+// CACHE, bits: 1 the tile loads without the non-temporal hint (ScanParams::keep), 2 the outputs through the caches (plain).
+template <typename E, int D, int CACHE, bool REV, bool TWIN, int NBUF, bool NORM = false, bool ACC = false, bool RS = false>
 __global__ __launch_bounds__(((TWIN || ACC) ? 4 : 2) * D, ((TWIN || ACC) ? 1 : 2) * (128 / D))
 void scan_bf16_half_kernel(ScanParams p) {
   static_assert(D == 128 || D == 64, "head_dim");
+  constexpr bool KEEP = (CACHE & 1) != 0;
   static_assert(REV == TWIN, "forward: one scan; reverse: both scans of Algorithm 2's second loop");
   static_assert(!NORM || (!REV && !TWIN), "the Norm epilogue belongs to the forward pass");
   static_assert(!ACC || (!REV && !TWIN && !NORM), "the accumulating wave group rides on a plain forward scan");
@@ -75,7 +76,7 @@ void scan_bf16_half_kernel(ScanParams p) {
   // 940 -> 852; batch 16, n 4096, d 64 342 -> 336; one chain batch of 65,536, d 128, from saved states 870 -> 858 (the whole launch
   // sequence against ordinary stores, in turn on three boxes, 1.0 to 1.6 %); batch 4, n 2048, d 64 68.7 -> 70.1 (the second barrier
   // of a block).
-  constexpr int kStorePolicy = 18;
+  constexpr int kStorePolicy = (CACHE & 2) != 0 ? 0 : 18;
   constexpr int NDMA = NTL * Loader::DMA_PER_WAVE;   // direct loads per wave and block
   constexpr int NST = 32 * 4 / 64 + (NORM ? 1 : 0);   // stores per lane and block: 16-byte output stores, r
   constexpr int DMA_PER_SLOT = (NDMA + KS - 1) / KS;   // direct loads issued in each slot of phase 1
@@ -599,7 +600,7 @@ void scan_bf16_half_kernel(ScanParams p) {
 }  // namespace
 
 namespace {
-template <typename E, int D, bool KEEP>
+template <typename E, int D, int CACHE>
 hipError_t launch_half(bool reverse, bool twin, const ScanParams& p, hipStream_t s) {
   if (reverse != twin) return hipErrorInvalidValue;   // a reverse launch is the twin, a forward launch one scan
   const int64_t grid = p.wg_map != nullptr ? (int64_t)p.wg_pairs * p.heads : (int64_t)p.batch * p.heads * p.nchunks;
@@ -607,28 +608,38 @@ hipError_t launch_half(bool reverse, bool twin, const ScanParams& p, hipStream_t
   // compute unit to itself) measured no faster: such launches are bound by the memory system, not by the
   // bytes a workgroup keeps in flight.
   const dim3 g((unsigned)grid), plain(2 * D), twice(4 * D);   // threads: one wave per 32 value features, or two such groups
-  if (p.ragged_state != 0) {   // the host pairs this only with a reverse twin launch or a forward scan without ACC
-    if (p.acc_states != nullptr) return hipErrorInvalidValue;
-    if (reverse) hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, true, true, 3, false, false, true>), g, twice, 0, s, p);
-    else if (p.rstd == nullptr)
-      hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, false, false, true>), g, plain, 0, s, p);
-    else hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, true, false, true>), g, plain, 0, s, p);
-  } else if (reverse) {
-    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, true, true, 3>), g, twice, 0, s, p);
-  } else if (p.acc_states != nullptr) {
-    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, false, true>), g, twice, 0, s, p);
+  if constexpr ((CACHE & 2) == 0) {   // (forward scans alone have the others)
+    if (reverse) {
+      if (p.ragged_state != 0) hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, CACHE, true, true, 3, false, false, true>), g, twice, 0, s, p);
+      else                     hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, CACHE, true, true, 3>), g, twice, 0, s, p);
+      return hipGetLastError();
+    }
+    if (p.acc_states != nullptr) {
+      if (p.ragged_state != 0) return hipErrorInvalidValue;   // the host pairs these only with forward scans that do not accumulate
+      hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, CACHE, false, false, 3, false, true>), g, twice, 0, s, p);
+      return hipGetLastError();
+    }
+  }
+  if (reverse || p.acc_states != nullptr) return hipErrorInvalidValue;
+  if (p.ragged_state != 0) {
+    if (p.rstd == nullptr) hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, CACHE, false, false, 3, false, false, true>), g, plain, 0, s, p);
+    else                   hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, CACHE, false, false, 3, true, false, true>), g, plain, 0, s, p);
   } else if (p.rstd != nullptr) {
-    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3, true>), g, plain, 0, s, p);
+    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, CACHE, false, false, 3, true>), g, plain, 0, s, p);
   } else {
-    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, KEEP, false, false, 3>), g, plain, 0, s, p);
+    hipLaunchKernelGGL((scan_bf16_half_kernel<E, D, CACHE, false, false, 3>), g, plain, 0, s, p);
   }
   return hipGetLastError();
 }
+template <typename E, int D>
+hipError_t launch_half_of(bool reverse, bool twin, const ScanParams& p, hipStream_t s) {
+  // (the host asks for ordinary stores only on plain forward scans whose tiles are not kept)
+  if (p.plain != 0 && !reverse && p.acc_states == nullptr) return launch_half<E, D, 2>(reverse, twin, p, s);
+  return p.keep != 0 ? launch_half<E, D, 1>(reverse, twin, p, s) : launch_half<E, D, 0>(reverse, twin, p, s);
+}
 template <typename E>
 hipError_t launch_half_of(int head_dim, bool reverse, bool twin, const ScanParams& p, hipStream_t s) {
-  if (head_dim == 64)
-    return p.keep != 0 ? launch_half<E, 64, true>(reverse, twin, p, s) : launch_half<E, 64, false>(reverse, twin, p, s);
-  return p.keep != 0 ? launch_half<E, 128, true>(reverse, twin, p, s) : launch_half<E, 128, false>(reverse, twin, p, s);
+  return head_dim == 64 ? launch_half_of<E, 64>(reverse, twin, p, s) : launch_half_of<E, 128>(reverse, twin, p, s);
 }
 }  // namespace
 

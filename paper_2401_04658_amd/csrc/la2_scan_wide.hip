@@ -72,9 +72,11 @@ struct PlainAddr {
 // 777 177 -> 140, 88 chains of 1000 241 -> 213; 128 chains of 2048 502 -> 478 (only the forward and the dQ scan, the
 // reverse launch fills the units as it is).  What bounds it: vector instructions that every wave has whatever its
 // share (weights, addresses, waits): 3,900 cycles per block, half of them vector issue.
-// KEEP: the tile loads without the non-temporal hint (ScanParams::keep).
-template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT, bool KEEP>
+// CACHE, bits: 1 the tile loads without the non-temporal hint (ScanParams::keep), 2 the outputs through the caches (plain).
+template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT, int CACHE>
 __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
+  constexpr bool KEEP = (CACHE & 1) != 0;
+  constexpr int kStorePolicy = (CACHE & 2) != 0 ? 0 : 18;   // buffer instruction bits: 2 = nt, 16 = sc1
   static_assert(!SPLIT || (D == 256 && !STATE_ONLY && !NORM), "half the value features per workgroup: plain scans of head_dim 256");
   static_assert(!NORM || (!REV && !STATE_ONLY), "the Norm epilogue belongs to the forward scan");
   static_assert(!TWIN || (REV && !STATE_ONLY && !NORM), "the twin workgroup is the backward pass's reverse launch");
@@ -404,7 +406,7 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
     const uint32_t off =
         ((uint32_t)(blkv * B + (lr & 15)) * stride_n + (uint32_t)(32 * dvt + 16 * (lr >> 4) + 8 * lh)) * 2u;
 #pragma unroll
-    for (int g = 0; g < 2; g++) __builtin_amdgcn_raw_buffer_store_b128(pk[g].i, bw, off + 32u * g * stride_n, 0, 18);
+    for (int g = 0; g < 2; g++) __builtin_amdgcn_raw_buffer_store_b128(pk[g].i, bw, off + 32u * g * stride_n, 0, kStorePolicy);
   };
   // deferred tail of a block: intra-block part Z^T P^T from the shared score tile, then the output
   f32x16 acc_prev = zero16();
@@ -708,21 +710,21 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p) {
   }
 }
 
-template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool KEEP>
+template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, int CACHE>
 __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) void scan_wide_kernel(ScanParams p) {
-  scan_wide_body<E, D, REV, STATE_ONLY, NORM, TWIN, false, KEEP>(p);
+  scan_wide_body<E, D, REV, STATE_ONLY, NORM, TWIN, false, CACHE>(p);
 }
-template <typename E, int D, bool REV, bool KEEP>
+template <typename E, int D, bool REV, int CACHE>
 __global__ __launch_bounds__(2 * D, 2) void scan_wide_split_kernel(ScanParams p) {
-  scan_wide_body<E, D, REV, false, false, false, true, KEEP>(p);
+  scan_wide_body<E, D, REV, false, false, false, true, CACHE>(p);
 }
 
-template <typename E, int D, bool KEEP>
+template <typename E, int D, int CACHE>
 hipError_t launch_wide(bool reverse, bool state_only, const ScanParams& p, hipStream_t s) {
   const dim3 g((unsigned)((int64_t)p.batch * p.heads * p.nchunks * (state_only ? 1 : p.nscan))), b(2 * D);
   if constexpr (D == 96) {
     if (!state_only && reverse && p.nscan == 2 && p.y[1] == p.z[0] && p.z[1] == p.y[0]) {
-      hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, true, KEEP>),
+      hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, true, CACHE>),
                          dim3((unsigned)((int64_t)p.batch * p.heads * p.nchunks)), dim3(4 * D), 0, s, p);
       return hipGetLastError();
     }
@@ -730,25 +732,26 @@ hipError_t launch_wide(bool reverse, bool state_only, const ScanParams& p, hipSt
   if constexpr (D == 256) {
     if (!state_only && p.rstd == nullptr && p.value_split != 0) {
       const dim3 g2(2 * g.x);
-      if (reverse) hipLaunchKernelGGL((scan_wide_split_kernel<E, D, true, KEEP>), g2, b, 0, s, p);
-      else         hipLaunchKernelGGL((scan_wide_split_kernel<E, D, false, KEEP>), g2, b, 0, s, p);
+      if (reverse) hipLaunchKernelGGL((scan_wide_split_kernel<E, D, true, CACHE>), g2, b, 0, s, p);
+      else         hipLaunchKernelGGL((scan_wide_split_kernel<E, D, false, CACHE>), g2, b, 0, s, p);
       return hipGetLastError();
     }
   }
   if (!state_only && !reverse && p.rstd != nullptr) {
-    hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, true, false, KEEP>), g, b, 0, s, p);
+    if (p.plain != 0) hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, true, false, CACHE | 2>), g, b, 0, s, p);
+    else              hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, true, false, CACHE>), g, b, 0, s, p);
   } else if (state_only) {
-    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, true, false, false, KEEP>), g, b, 0, s, p);
-    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, true, false, false, KEEP>), g, b, 0, s, p);
+    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, true, false, false, CACHE>), g, b, 0, s, p);
+    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, true, false, false, CACHE>), g, b, 0, s, p);
   } else {
-    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, false, KEEP>), g, b, 0, s, p);
-    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, false, false, KEEP>), g, b, 0, s, p);
+    if (reverse) hipLaunchKernelGGL((scan_wide_kernel<E, D, true, false, false, false, CACHE>), g, b, 0, s, p);
+    else         hipLaunchKernelGGL((scan_wide_kernel<E, D, false, false, false, false, CACHE>), g, b, 0, s, p);
   }
   return hipGetLastError();
 }
 template <typename E, int D>
 hipError_t launch_wide_of(bool reverse, bool state_only, const ScanParams& p, hipStream_t s) {
-  return p.keep != 0 ? launch_wide<E, D, true>(reverse, state_only, p, s) : launch_wide<E, D, false>(reverse, state_only, p, s);
+  return p.keep != 0 ? launch_wide<E, D, 1>(reverse, state_only, p, s) : launch_wide<E, D, 0>(reverse, state_only, p, s);
 }
 
 }  // namespace

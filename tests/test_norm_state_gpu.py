@@ -221,3 +221,34 @@ def test_multi_token_decode_with_norm(dtype, d, T):
     assert_close(tag + " o", o, ro, dtype)
     assert_close(tag + " rstd", rstd, rr, dtype)
     assert_close(tag + " state", state, rs, dtype)
+
+
+@pytest.mark.parametrize("d,H,lengths", [(96, 3, [300, 20, 1, 40, 64, 0, 33]), (256, 2, [257, 20, 1, 40, 64, 0, 33]),
+                                         (96, 16, [3000] + [130] * 430), (256, 8, [1500] + [130] * 320)])
+def test_norm_over_packed_sequences_of_unequal_lengths_at_96_and_256(d, H, lengths):
+    """Such batches store through the caches, with their tiles kept (small) or not (above 160 MiB): rows of the longest, of a
+    middle and of the last sequence against the oracle, and the middle one bit for bit against a dense call on it."""
+    dtype = torch.bfloat16
+    total = sum(lengths)
+    assert len(lengths) * max(lengths) > 2 * total and (total * H * d * 2 > 160 << 20) == (len(lengths) > 100)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + total)
+    q, k, v = ((torch.randn((total, H, d), generator=gen, device=DEV) * d ** -0.5).to(dtype) for _ in range(3))
+    lam = torch.exp(-torch.pow(2.0, -8.0 * torch.arange(1, H + 1) / H)).to(DEV)
+    ends = np.concatenate([[0], np.cumsum(lengths)])
+    cu = torch.tensor(ends, dtype=torch.int32, device=DEV)
+    o, rstd = binding.la2_fwd_varlen_norm(q, k, v, lam, cu, max(lengths), EPS)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all() and torch.isfinite(rstd).all()
+    for s in (0, len(lengths) // 2, len(lengths) - 1):
+        lo, hi = int(ends[s]), int(ends[s + 1])
+        if s:
+            part = [x[lo:hi].permute(1, 0, 2)[None].contiguous() for x in (q, k, v)]
+            on, rn = binding.la2_fwd_norm(*part, lam, EPS)
+            torch.cuda.synchronize()
+            assert torch.equal(on[0].permute(1, 0, 2), o[lo:hi]) and torch.equal(rn[0], rstd[:, lo:hi])
+        for h in (0, H - 1):
+            x = [to64(t[lo:hi, h])[None, None] for t in (q, k, v)]
+            ro, rr = oracle.fwd_norm(*x, to64(lam[h:h + 1]), EPS)
+            assert_close("seq %d o" % s, o[lo:hi, h][None, None], ro, dtype)
+            assert_close("seq %d rstd" % s, rstd[h, lo:hi][None, None], rr, dtype)

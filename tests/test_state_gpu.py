@@ -386,3 +386,35 @@ def test_dq_launch_forms_the_reverse_chunk_states(dtype, d, n, chunk):
     for name, got, other, ref in (("dq", dq, uq, rdq), ("dk", dk, uk, rdk), ("dv", dv, uv, rdv), ("d_kv_init", g0, u0, rg0)):
         assert_close(tag + " " + name, got, ref, dtype)
         assert_close(tag + " unfused " + name, other, ref, dtype)
+
+
+@pytest.mark.parametrize("d,chains,n", [(128, 224, 128), (128, 224, 150), (128, 223, 150), (64, 448, 160), (64, 448, 129), (64, 447, 129),
+                                        (128, 256, 1152), (128, 256, 1153)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_prefill_of_a_full_round_stores_through_the_caches(dtype, d, chains, n):
+    """A forward pass that hands out its state, from as many chains as fill the units on, up to tensors of 72 MiB: four chains
+    against the oracle, with the Norm as well, and over whole blocks the bits of the pass without states, whose outputs go past
+    the caches.  (A ragged length with a state has an instantiation of its own, which forms its update weights as one exponential
+    each and not as a product of two: other roundings.)"""
+    H = next(h for h in (16, 7, 3, 1) if chains % h == 0)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + n + chains)
+    q, k, v = ((torch.randn((chains // H, H, n, d), generator=gen, device=DEV) * d ** -0.5).to(dtype) for _ in range(3))
+    lam = torch.exp(-torch.pow(2.0, -8.0 * torch.arange(1, H + 1) / H)).to(DEV)
+    assert binding.la2_workspace_bytes(q, binding.LA2_OP_FWD_STATE) == 0   # not cut
+    o, kvf = binding.la2_fwd_state(q, k, v, lam)
+    on, rstd, kvn = binding.la2_fwd_state_norm(q, k, v, lam, 1e-4)
+    plain = binding.la2_fwd(q, k, v, lam)
+    plain_n, plain_r = binding.la2_fwd_norm(q, k, v, lam, 1e-4)
+    torch.cuda.synchronize()
+    if n % 32 == 0:
+        assert torch.equal(o, plain) and torch.equal(on, plain_n) and torch.equal(rstd, plain_r)
+    assert torch.equal(kvf, kvn)
+    for b, h in ((0, 0), (chains // H - 1, H - 1), (chains // H // 2, H // 2), (0, H - 1)):
+        x = [to64(t[b:b + 1, h:h + 1]) for t in (q, k, v)]
+        ro, rkv = oracle.fwd_recurrent(*x, to64(lam[h:h + 1]), return_state=True)
+        assert_close("prefill o", o[b:b + 1, h:h + 1], ro, dtype)
+        assert_close("prefill state", kvf[b:b + 1, h:h + 1], rkv, dtype)
+        rn, rr, _ = oracle.fwd_norm_state(*x, to64(lam[h:h + 1]), 1e-4, None)
+        assert_close("prefill norm o", on[b:b + 1, h:h + 1], rn, dtype)
+        assert_close("prefill rstd", rstd[b:b + 1, h:h + 1], rr, dtype)
