@@ -553,17 +553,12 @@ la2_status run_prepass(const la2_desc* d, const Plan& pl, bool reverse, const vo
   return e == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
 }
 
-la2_status run_scan(const la2_desc* d, const Plan& pl, bool reverse, const ScanArgs& a, const float* lambda,
-                    void* workspace, hipStream_t s) {
-  const bool saved = a.saved_states != nullptr && pl.nchunks > 1;
-  if (!saved) {
-    la2_status st = run_prepass(d, pl, reverse, a.y, a.z, a.init, a.init_tr, lambda, workspace, s, a.cu, false, a.map);
-    if (st != LA2_OK) return st;
-  }
+// Launch parameters of one scan, whose chunk states are in the workspace or (saved_states) in the forward call's.
+la2::ScanParams scan_params(const la2_desc* d, const Plan& pl, const ScanArgs& a, const float* lambda, void* workspace) {
   la2::ScanParams p = base_params(d, pl, lambda, workspace, a.cu);
   p.wg_map = a.map;
   p.wg_pairs = pl.wg_pairs;
-  if (saved) {
+  if (a.saved_states != nullptr && pl.nchunks > 1) {
     p.states = const_cast<float*>(a.saved_states);   // read only
     p.state_transposed = a.saved_tr ? 1 : 0;
   }
@@ -580,19 +575,25 @@ la2_status run_scan(const la2_desc* d, const Plan& pl, bool reverse, const ScanA
   p.keep = keep_tiles(d, pl, a.fin != nullptr);   // (of the launches here only a forward pass hands out a state)
   p.plain = plain_stores(d, pl, a.cu, a.fin != nullptr, a.rstd != nullptr);
   if (p.plain != 0 && !wide(d->head_dim)) p.keep = 0;
+  return p;
+}
+
+la2_status run_scan(const la2_desc* d, const Plan& pl, bool reverse, const ScanArgs& a, const float* lambda,
+                    void* workspace, hipStream_t s) {
+  if (a.saved_states == nullptr || pl.nchunks <= 1) {
+    la2_status st = run_prepass(d, pl, reverse, a.y, a.z, a.init, a.init_tr, lambda, workspace, s, a.cu, false, a.map);
+    if (st != LA2_OK) return st;
+  }
+  const la2::ScanParams p = scan_params(d, pl, a, lambda, workspace);
   hipError_t e = wide(d->head_dim) ? la2::launch_scan_wide(d->dtype, d->head_dim, reverse, false, p, s)
                 : is16(d->dtype)   ? la2::launch_scan_bf16(d->dtype, d->head_dim, reverse, p, s)
                                    : la2::launch_scan_f32(d->head_dim, reverse, p, s);
   return e == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
 }
 
-// Two reverse scans whose states are transposes of each other (scan 1's y, z are scan 0's z, y): one
-// state pre-pass, one launch.
-// (local_ready: the workspace already holds the chunks' local states, left there by the dQ scan's launch)
-la2_status run_dual_reverse_scan(const la2_desc* d, const Plan& pl, const ScanArgs& a0, const ScanArgs& a1,
-                                 const float* lambda, void* workspace, hipStream_t s, bool local_ready = false) {
-  la2_status st = run_prepass(d, pl, true, a0.y, a0.z, a0.init, a0.init_tr, lambda, workspace, s, a0.cu, local_ready, a0.map);
-  if (st != LA2_OK) return st;
+// Launch parameters of two reverse scans whose states are transposes of each other (scan 1's y, z are scan 0's z, y).
+la2::ScanParams dual_reverse_params(const la2_desc* d, const Plan& pl, const ScanArgs& a0, const ScanArgs& a1,
+                                    const float* lambda, void* workspace) {
   la2::ScanParams p = base_params(d, pl, lambda, workspace, a0.cu);
   p.wg_map = a0.map;
   p.wg_pairs = pl.wg_pairs;
@@ -605,10 +606,79 @@ la2_status run_dual_reverse_scan(const la2_desc* d, const Plan& pl, const ScanAr
   p.x[0] = a0.x; p.y[0] = a0.y; p.z[0] = a0.z; p.w[0] = a0.w;
   p.x[1] = a1.x; p.y[1] = a1.y; p.z[1] = a1.z; p.w[1] = a1.w;
   p.value_split = value_split(d, p);
+  return p;
+}
+
+// ... with one state pre-pass, in one launch
+// (local_ready: the workspace already holds the chunks' local states, left there by the dQ scan's launch)
+la2_status run_dual_reverse_scan(const la2_desc* d, const Plan& pl, const ScanArgs& a0, const ScanArgs& a1,
+                                 const float* lambda, void* workspace, hipStream_t s, bool local_ready = false) {
+  la2_status st = run_prepass(d, pl, true, a0.y, a0.z, a0.init, a0.init_tr, lambda, workspace, s, a0.cu, local_ready, a0.map);
+  if (st != LA2_OK) return st;
+  const la2::ScanParams p = dual_reverse_params(d, pl, a0, a1, lambda, workspace);
   const hipError_t e = wide(d->head_dim) ? la2::launch_scan_wide(d->dtype, d->head_dim, true, false, p, s)
                        : is16(d->dtype) ? la2::launch_scan_bf16(d->dtype, d->head_dim, true, p, s)
                                         : la2::launch_scan_f32(d->head_dim, true, p, s);
   return e == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
+}
+
+// A backward pass whose three scans run in one launch, behind one launch for both families of chunk states (KV in `workspace`
+// or the forward call's, dKV in `rev_workspace`).  16-bit data, head_dim 64 / 128 (joint_plan).
+la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs& dq, const ScanArgs& dv, const ScanArgs& dk,
+                              const float* lambda, void* workspace, void* rev_workspace, hipStream_t s) {
+  const la2::ScanParams pq = scan_params(d, pl, dq, lambda, workspace);
+  const la2::ScanParams pr = dual_reverse_params(d, pl, dv, dk, lambda, rev_workspace);
+  if (pl.nchunks > 1) {
+    const bool saved = dq.saved_states != nullptr;
+    const hipError_t e = saved ? la2::launch_chunk_states_bf16(d->dtype, d->head_dim, true, pr, s)
+                               : la2::launch_chunk_state_pair_bf16(d->dtype, d->head_dim, pq, pr, s);
+    if (e != hipSuccess) return LA2_ERR_LAUNCH;
+    la2_status st = saved ? LA2_OK : run_prepass(d, pl, false, dq.y, dq.z, dq.init, dq.init_tr, lambda, workspace, s, dq.cu, true, dq.map);
+    if (st == LA2_OK) st = run_prepass(d, pl, true, dv.y, dv.z, dv.init, dv.init_tr, lambda, rev_workspace, s, dv.cu, true, dv.map);
+    if (st != LA2_OK) return st;
+  }
+  return la2::launch_bwd_scans_bf16(d->dtype, d->head_dim, pq, pr, s) == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
+}
+
+// The plan of a backward pass that takes that form (nchunks 0: it does not), by what it has otherwise: pl, and whether the forward
+// call left the KV states of pl's chunks.  A chain's dK / dV workgroup and its dQ workgroup are both short of work for a compute unit
+// on their own (head_dim 64: three waves' worth each of eight; 128: the dQ scan four of eight), so side by side they take little
+// longer than the longer one of them; and from 3 / 8 of the units on, both of every chain already draw what memory gives, so that
+// cutting the sequences only adds the pre-pass (4 of 14 tensor passes).  Forward + backward, bf16, against the dQ launch (cut: with
+// the chunk states on the side) and the dK / dV launch one after the other:
+// - uncut before as well: d 64, 96 to 128 chains 0.70 (n 1024), 160, 192, 256 of 300 to 2048 positions 0.79-0.83, 0.79-0.85,
+//   0.79-0.94, 512 0.91-0.96, 1024 0.96-1.01; above 96 MiB a tensor 224 and more 1.00-1.04 (272 of 4096 1.16), 160 and 192 0.95, 0.97.
+//   d 128, whose pairs want two units: 80 to 128 chains 0.74-0.77, 160 0.87-0.98, 192, 224, 256 up to 32 MiB 0.97-0.99, above
+//   0.99-1.04; a partial second or third round 272 to 320 0.85-0.87, 384 0.92-0.94, 416 0.98-1.00, 448 1.01-1.05, 640 0.93-0.96, 768 1.00.
+// - instead of a cut: n 1024, 2048, 4096, 8192, d 64, 96 chains 0.69, 0.84, 0.87, 0.89, 128 0.70, 0.84, 0.86, 0.92 (80: 0.89, 0.98,
+//   1.03, 1.08); d 128, 96 chains 0.83, 0.90, 0.92, 0.93, 128 0.88, 0.88, 0.94, 0.93 (64: 0.89, 1.04, 1.18, 1.24).  From saved
+//   states, which take a pre-pass out of the other form: d 64, 96 to 128 chains 0.94-1.00; d 128, 112 and 128 0.93-1.00 (96: 0.95-1.01).
+// - in pl's chunks (d 64; the pre-passes in one launch): 4 chains of 4096 0.83, 16 of 2048, 4096, 8192, 16384 0.83, 0.91, 0.94,
+//   0.99, 48 of 1024 to 16384 0.83, 0.90, 0.94, 0.97, 0.98, 64 of 1024, 2048, 4096, 8192 0.87, 0.93, 0.99, 1.03; saved, 64 of 1024,
+//   2048, 4096 0.93, 0.97, 1.03; packed batches up to 92 MiB 0.86-0.98.
+Plan joint_plan(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved_states) {
+  const Plan none{0, 0, 0};
+  if (!is16(d->dtype) || wide(d->head_dim) || g_scan_variant.load(std::memory_order_relaxed) != 0 ||
+      g_chunk_tokens_override.load(std::memory_order_relaxed) > 0)   // (the caller asks for a kernel, or plans)
+    return none;
+  const int64_t cus = device_cu_count(), chains = (int64_t)d->batch * d->heads, bytes = tensor_bytes(d, pl);
+  const int64_t MiB = (int64_t)1 << 20;
+  if (pl.nchunks == 1) {
+    if (d->head_dim == 64) return bytes <= 96 * MiB || (cu == nullptr && 4 * chains <= 3 * cus) ? pl : none;
+    if (cu != nullptr) return 2 * chains <= cus ? pl : none;
+    if (chains <= cus) return 8 * chains <= 5 * cus || bytes <= 32 * MiB ? pl : none;
+    return chains % cus > 0 && 2 * (chains % cus) <= cus && chains < 3 * cus ? pl : none;
+  }
+  const Plan uncut{1, (d->seqlen + 63) / 64 * 64, 0};
+  if (d->head_dim == 128) {
+    if (cu != nullptr) return none;
+    if (!saved_states && d->seqlen <= 1024 && 16 * chains >= 3 * cus) return uncut;
+    return 16 * chains >= (saved_states ? 7 : 6) * cus ? uncut : none;
+  }
+  if (cu != nullptr) return bytes <= 96 * MiB ? pl : none;
+  if (8 * chains >= 3 * cus) return uncut;
+  if (!saved_states && 16 * chains * pl.nchunks <= 15 * cus) return pl;
+  return bytes <= (saved_states ? 16 : 32) * MiB ? pl : none;
 }
 
 // The state entry points split a sequence whose length is not a multiple of state_granule() into whole
@@ -1083,8 +1153,18 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
   }
   float* handoff = split ? reinterpret_cast<float*>(static_cast<char*>(workspace) + sw.chunk_states) : nullptr;
   void* rev_workspace = workspace;
+  if (fuse && for_dq.saved_states == nullptr) rev_workspace = static_cast<char*>(workspace) + pl.workspace;
+  ScanArgs for_dv{k, q, d_o, dv}, for_dk{v, d_o, q, dk};
+  for_dv.init = d_kv_final;
+  for_dv.fin = d_kv_init;
+  for_dk.init = d_kv_final;
+  for_dk.init_tr = true;
+  for_dv.ragged_state = for_dk.ragged_state = d_kv_final != nullptr && ragged_end(desc);
+  // (the dQ scan reads kv_init while the other two write d_kv_init)
+  const Plan joint = joint_plan(desc, pl, nullptr, for_dq.saved_states != nullptr);
+  if (!split && joint.nchunks > 0 && !same_state(desc, d_kv_init, kv_init))
+    return run_joint_backward(desc, joint, for_dq, for_dv, for_dk, lambda, workspace, rev_workspace, s);
   if (fuse) {
-    if (for_dq.saved_states == nullptr) rev_workspace = static_cast<char*>(workspace) + pl.workspace;
     for_dq.acc_y = q;
     for_dq.acc_states = reinterpret_cast<float*>(rev_workspace);
   }
@@ -1094,7 +1174,6 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
   //   dV = [(Q K^T) * M]^T dO + decay(K) dKV        reverse scan of (K, Q, dO), state dKV = Q^T dO
   //   dK = [(dO V^T) * M]^T Q + decay(V) dKV^T      reverse scan of (V, dO, Q), state dKV^T
   // dKV starts from the gradient of the final state and ends as the gradient of the start state.
-  const float* rev_init = d_kv_final;
   if (split) {
     la2::RecurParams r = recur_params(desc, lambda, blocks.seqlen, desc->seqlen, true);
     r.x[0] = k; r.y[0] = q; r.z[0] = d_o; r.w[0] = dv;     // dv_t = k_t G_t, G = sum q^T do
@@ -1105,14 +1184,8 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
     if (la2::launch_recur(desc->head_dim, desc->dtype, desc->batch, 2, r, s) != hipSuccess)
       return LA2_ERR_LAUNCH;
     if (blocks.seqlen == 0) return LA2_OK;
-    rev_init = handoff;
+    for_dv.init = for_dk.init = handoff;
   }
-  ScanArgs for_dv{k, q, d_o, dv}, for_dk{v, d_o, q, dk};
-  for_dv.init = rev_init;
-  for_dv.fin = d_kv_init;
-  for_dk.init = rev_init;
-  for_dk.init_tr = true;
-  for_dv.ragged_state = for_dk.ragged_state = d_kv_final != nullptr && ragged_end(desc);
   return run_dual_reverse_scan(&blocks, pl_rev, for_dv, for_dk, lambda, rev_workspace, s, /*local_ready=*/fuse);
 }
 
@@ -1341,6 +1414,9 @@ la2_status bwd_varlen_impl(const la2_desc* desc, const int32_t* cu_seqlens, int6
   }
   workspace = static_cast<char*>(workspace) + pl.map_bytes;   // the states
   void* rev_workspace = fuse ? static_cast<char*>(workspace) + pl.workspace : workspace;
+  const Plan joint = joint_plan(desc, pl, cu_seqlens, false);
+  if (joint.nchunks > 0 && !same_state(desc, d_kv_init, kv_init))
+    return run_joint_backward(desc, joint, for_dq, for_dv, for_dk, lambda, workspace, rev_workspace, s);
   if (fuse) {
     for_dq.acc_y = q;
     for_dq.acc_states = reinterpret_cast<float*>(rev_workspace);

@@ -24,13 +24,12 @@ using namespace bf16k;
 // the key-feature tiles of half w / NT of the state slice, so that one wave's LDS and MFMA latencies hide behind
 // the other's instructions (a wave issues one instruction at a time).
 template <typename E, int D, bool REV, int NBUF>
-__global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(ScanParams p) {
+__device__ __forceinline__ void chunk_state(const ScanParams& p, const int wg, E (&sT)[NBUF][2][Cfg<D>::TILE]) {
   static_assert(NBUF >= 3 && NBUF <= 5, "the block loop below is unrolled for 3 to 5 buffers");
   using C = Cfg<D>;
   constexpr int NT = C::NT, TILE = C::TILE;
   constexpr int KT = NT / 2;   // key-feature tiles per wave
   using Loader = TileLoader<D, 2, kB, 2 * NT>;
-  __shared__ __attribute__((aligned(1024))) E sT[NBUF][2][TILE];   // [Y, Z]
   constexpr int NDMA = 2 * Loader::DMA_PER_WAVE;   // direct loads per wave and block
   constexpr int VM_YOUNGER = (NBUF - 2) * NDMA;    // loads younger than those of block it + 1 when it waits for them
   static_assert(VM_YOUNGER < 64, "vmcnt is a 6-bit counter");
@@ -40,7 +39,7 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
   const int dvt = w % NT, kt0 = (w / NT) * KT;
   int bi, hi, chunk, slot_stride, chunk_tokens;
   int64_t slot;
-  if (!place_workgroup(p, (int)blockIdx.x, bi, hi, chunk, slot, slot_stride, chunk_tokens)) return;
+  if (!place_workgroup(p, wg, bi, hi, chunk, slot, slot_stride, chunk_tokens)) return;
   int64_t base;
   int n;
   chain_extent(p, bi, hi, base, n);
@@ -124,6 +123,22 @@ __global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(Sca
   for (int t = 0; t < KT; t++)
 #pragma unroll
     for (int v = 0; v < 16; v++) gs[state_index<D>(dvt, l32, hh, kt0 + t, v, false)] = kv[t][v];
+}
+
+template <typename E, int D, bool REV, int NBUF>
+__global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_bf16_kernel(ScanParams p) {
+  __shared__ __attribute__((aligned(1024))) E sT[NBUF][2][Cfg<D>::TILE];   // [Y, Z]
+  chunk_state<E, D, REV, NBUF>(p, (int)blockIdx.x, sT);
+}
+
+// Both families of a backward pass's chunk states in one launch: the first half of the workgroups the forward ones, the second
+// half the reverse ones.
+template <typename E, int D, int NBUF>
+__global__ __launch_bounds__(128 * (D / 32), 1) void chunk_state_pair_bf16_kernel(ScanParams fwd, ScanParams rev) {
+  __shared__ __attribute__((aligned(1024))) E sT[NBUF][2][Cfg<D>::TILE];
+  const int units = (int)gridDim.x / 2, wg = (int)blockIdx.x;
+  if (wg < units) chunk_state<E, D, false, NBUF>(fwd, wg, sT);
+  else            chunk_state<E, D, true, NBUF>(rev, wg - units, sT);
 }
 
 // In place: states[chain][j] (local state of chunk j) -> start state of chunk j.
@@ -341,6 +356,17 @@ hipError_t launch_chunk_states_bf16(int dtype, int head_dim, bool reverse, const
   if (grid == 0 || p.n == 0) return hipSuccess;
   return dtype == kF16 ? launch_chunk_states<_Float16>(head_dim, reverse, p, s)
                        : launch_chunk_states<__bf16>(head_dim, reverse, p, s);
+}
+
+hipError_t launch_chunk_state_pair_bf16(int dtype, int head_dim, const ScanParams& fwd, const ScanParams& rev, hipStream_t s) {
+  const int64_t grid = 2 * (fwd.wg_map != nullptr ? (int64_t)fwd.wg_pairs * fwd.heads : (int64_t)fwd.batch * fwd.heads * fwd.nchunks);
+  if (head_dim != 64) return hipErrorInvalidValue;
+  if (grid == 0 || fwd.n == 0) return hipSuccess;
+  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;   // (the rule that leads here keeps it far below)
+  const dim3 g((unsigned)grid), b(256);
+  if (dtype == kF16) hipLaunchKernelGGL((chunk_state_pair_bf16_kernel<_Float16, 64, 4>), g, b, 0, s, fwd, rev);
+  else               hipLaunchKernelGGL((chunk_state_pair_bf16_kernel<__bf16, 64, 4>), g, b, 0, s, fwd, rev);
+  return hipGetLastError();
 }
 
 hipError_t launch_state_scan(int head_dim, bool reverse, const ScanParams& p, hipStream_t s) {

@@ -1,0 +1,61 @@
+"""Backward passes whose three scans run in one launch (16-bit data, head_dim 64 / 128), against the fp64 oracle and against the
+launches one after the other (scan variant 2)."""
+import pytest
+import torch
+
+import oracle
+from paper_2401_04658_amd import binding, workloads
+from parity import assert_close, rms_rel, to64
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(autouse=True)
+def _defaults():
+    binding.la2_set_chunk_tokens(0)
+    binding.la2_set_scan_variant(0)
+    yield
+    binding.la2_set_chunk_tokens(0)
+    binding.la2_set_scan_variant(0)
+
+
+# head_dim, batch, heads, length: in the plan's chunks with a scan over their states and without one, uncut instead of them, uncut as
+# before; up to half the units, about all of them, a partial second round
+@pytest.mark.parametrize("d,b,h,n", [(64, 1, 4, 2113), (64, 1, 16, 2048), (64, 3, 16, 1000), (64, 6, 16, 1100), (64, 8, 16, 1031),
+                                     (64, 10, 16, 200), (64, 16, 16, 257), (64, 18, 16, 130), (128, 5, 16, 416), (128, 3, 16, 1000),
+                                     (128, 6, 16, 1056), (128, 10, 16, 100), (128, 16, 16, 65), (128, 18, 16, 127)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_all_scans_in_one_launch(dtype, d, b, h, n):
+    """Batch rows are copies of one, so every row has the same bits; with states and without, the forward call's states and none,
+    and d_kv_init in kv_init's place (which the dQ scan has to have read by then)."""
+    t = workloads.Workload("joint", 1, h, n, d, dtype, seed=8300 + n + d, backward=True).tensors()
+    gen = torch.Generator(device="cpu")
+    gen.manual_seed(8300 + n)
+    init, dfin = (torch.randn((1, h, d, d), generator=gen) * 0.3 for _ in range(2))
+    lam = t["lam"].to(DEV)
+    q, k, v, do = (t[x].to(DEV).expand(b, -1, -1, -1).contiguous() for x in ("q", "k", "v", "d_o"))
+    q64, k64, v64, do64, lam64 = (to64(t[x]) for x in ("q", "k", "v", "d_o", "lam"))
+    for given in (False, True):
+        kv0, dkv = (x.to(DEV).expand(b, -1, -1, -1).contiguous() if given else None for x in (init, dfin))
+        i64, f64 = (to64(init), to64(dfin)) if given else (None, None)
+        refs = oracle.bwd_recurrent_state(q64, k64, v64, do64, lam64, kv_init=i64, d_kv_final=f64)
+        binding.la2_set_scan_variant(2)
+        apart = binding.la2_bwd_state(q, k, v, do, lam, kv_init=kv0, d_kv_final=dkv)
+        binding.la2_set_scan_variant(0)
+        ws = torch.empty(max(256, binding.la2_workspace_bytes(q, binding.LA2_OP_FWD_STATE)), dtype=torch.uint8, device=DEV)
+        binding.la2_fwd_state(q, k, v, lam, kv_init=kv0, want_final=False, workspace=ws)
+        runs = {"": binding.la2_bwd_state(q, k, v, do, lam, kv_init=kv0, d_kv_final=dkv),
+                "saved": binding.la2_bwd_state(q, k, v, do, lam, kv_init=kv0, d_kv_final=dkv, fwd_workspace=ws)}
+        if given:
+            place = kv0.clone()
+            runs["in place"] = binding.la2_bwd_state(q, k, v, do, lam, kv_init=place, d_kv_final=dkv, d_kv_init=place)
+        torch.cuda.synchronize()
+        for kind, outs in runs.items():
+            for name, x, ref, other in zip(("dq", "dk", "dv", "d_kv_init"), outs, refs, apart):
+                label = "%s d%d b%d h%d n%d states %s %s" % (name, d, b, h, n, given, kind)
+                assert torch.equal(x, x[:1].expand_as(x)), label
+                assert_close(label, x[:1], ref, dtype)
+                # no further from the truth than the launches apart (the same sums, or those of other chunks: up to their order)
+                assert rms_rel(to64(x[:1]), ref) <= 1.05 * rms_rel(to64(other[:1]), ref) + 1e-7, label
