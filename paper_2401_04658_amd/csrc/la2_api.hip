@@ -623,21 +623,22 @@ la2_status run_dual_reverse_scan(const la2_desc* d, const Plan& pl, const ScanAr
 }
 
 // A backward pass whose three scans run in one launch, behind one launch for both families of chunk states (KV in `workspace`
-// or the forward call's, dKV in `rev_workspace`).  16-bit data, head_dim 64 / 128 (joint_plan).
+// or the forward call's, dKV in `rev_workspace`).  16-bit data, head_dim 64, 96, 128 (joint_plan).
 la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs& dq, const ScanArgs& dv, const ScanArgs& dk,
                               const float* lambda, void* workspace, void* rev_workspace, hipStream_t s) {
   const la2::ScanParams pq = scan_params(d, pl, dq, lambda, workspace);
   const la2::ScanParams pr = dual_reverse_params(d, pl, dv, dk, lambda, rev_workspace);
   if (pl.nchunks > 1) {
     const bool saved = dq.saved_states != nullptr;
-    const hipError_t e = saved ? la2::launch_chunk_states_bf16(d->dtype, d->head_dim, true, pr, s)
-                               : la2::launch_chunk_state_pair_bf16(d->dtype, d->head_dim, pq, pr, s);
-    if (e != hipSuccess) return LA2_ERR_LAUNCH;
-    la2_status st = saved ? LA2_OK : run_prepass(d, pl, false, dq.y, dq.z, dq.init, dq.init_tr, lambda, workspace, s, dq.cu, true, dq.map);
-    if (st == LA2_OK) st = run_prepass(d, pl, true, dv.y, dv.z, dv.init, dv.init_tr, lambda, rev_workspace, s, dv.cu, true, dv.map);
+    const bool pair = !saved && d->head_dim == 64;   // (one launch for both; at head_dim 96 one fills the units)
+    if (pair && la2::launch_chunk_state_pair_bf16(d->dtype, d->head_dim, pq, pr, s) != hipSuccess) return LA2_ERR_LAUNCH;
+    la2_status st = saved ? LA2_OK : run_prepass(d, pl, false, dq.y, dq.z, dq.init, dq.init_tr, lambda, workspace, s, dq.cu, pair, dq.map);
+    if (st == LA2_OK) st = run_prepass(d, pl, true, dv.y, dv.z, dv.init, dv.init_tr, lambda, rev_workspace, s, dv.cu, pair, dv.map);
     if (st != LA2_OK) return st;
   }
-  return la2::launch_bwd_scans_bf16(d->dtype, d->head_dim, pq, pr, s) == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
+  const hipError_t e = wide(d->head_dim) ? la2::launch_bwd_scans_wide(d->dtype, d->head_dim, pq, pr, s)
+                                         : la2::launch_bwd_scans_bf16(d->dtype, d->head_dim, pq, pr, s);
+  return e == hipSuccess ? LA2_OK : LA2_ERR_LAUNCH;
 }
 
 // The plan of a backward pass that takes that form (nchunks 0: it does not), by what it has otherwise: pl, and whether the forward
@@ -656,20 +657,31 @@ la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs&
 // - in pl's chunks (d 64; the pre-passes in one launch): 4 chains of 4096 0.83, 16 of 2048, 4096, 8192, 16384 0.83, 0.91, 0.94,
 //   0.99, 48 of 1024 to 16384 0.83, 0.90, 0.94, 0.97, 0.98, 64 of 1024, 2048, 4096, 8192 0.87, 0.93, 0.99, 1.03; saved, 64 of 1024,
 //   2048, 4096 0.93, 0.97, 1.03; packed batches up to 92 MiB 0.86-0.98.
+// Head_dim 96 (two pairs share a unit; its pre-passes are launches that fill the device): uncut before as well, 4 to 128 chains of
+// 300 to 4096 positions 0.70-0.76, 160 0.73-0.84, 192 0.94-1.07, 256 0.98-1.04, 288 to 1024 0.76-1.02, packed 0.70-0.97; instead of a
+// cut, n 1024, 2048, 4096, 8192, 48 chains 0.86, 1.00, 1.11, 1.33, 64 0.86, 0.97, 1.08, 1.12, 80 0.81, 0.84, 0.92, 0.96, 112 0.75,
+// 0.75, 0.84, 0.82, saved 96 0.84, 0.84, 0.99, 0.95 (64: 0.99, 1.09, 1.21, 1.23).  In pl's chunks it would take a second set of states,
+// which the workspace has no room for; from saved states it does on up to half as many workgroups as units (0.83-0.87; more 0.96-1.14).
 Plan joint_plan(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved_states) {
   const Plan none{0, 0, 0};
-  if (!is16(d->dtype) || wide(d->head_dim) || g_scan_variant.load(std::memory_order_relaxed) != 0 ||
+  if (!is16(d->dtype) || d->head_dim == 256 || g_scan_variant.load(std::memory_order_relaxed) != 0 ||
       g_chunk_tokens_override.load(std::memory_order_relaxed) > 0)   // (the caller asks for a kernel, or plans)
     return none;
   const int64_t cus = device_cu_count(), chains = (int64_t)d->batch * d->heads, bytes = tensor_bytes(d, pl);
   const int64_t MiB = (int64_t)1 << 20;
   if (pl.nchunks == 1) {
+    if (d->head_dim == 96) return cu != nullptr || 8 * chains <= 5 * cus || chains > cus ? pl : none;
     if (d->head_dim == 64) return bytes <= 96 * MiB || (cu == nullptr && 4 * chains <= 3 * cus) ? pl : none;
     if (cu != nullptr) return 2 * chains <= cus ? pl : none;
     if (chains <= cus) return 8 * chains <= 5 * cus || bytes <= 32 * MiB ? pl : none;
     return chains % cus > 0 && 2 * (chains % cus) <= cus && chains < 3 * cus ? pl : none;
   }
   const Plan uncut{1, (d->seqlen + 63) / 64 * 64, 0};
+  if (d->head_dim == 96) {
+    if (cu != nullptr) return none;
+    if (saved_states) return 8 * chains >= 3 * cus ? uncut : 2 * chains * pl.nchunks <= cus ? pl : none;
+    return 16 * chains >= 5 * cus || (4 * chains >= cus && d->seqlen <= 2048) || (16 * chains >= 3 * cus && d->seqlen <= 1024) ? uncut : none;
+  }
   if (d->head_dim == 128) {
     if (cu != nullptr) return none;
     if (!saved_states && d->seqlen <= 1024 && 16 * chains >= 3 * cus) return uncut;
@@ -679,6 +691,16 @@ Plan joint_plan(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved
   if (8 * chains >= 3 * cus) return uncut;
   if (!saved_states && 16 * chains * pl.nchunks <= 15 * cus) return pl;
   return bytes <= (saved_states ? 16 : 32) * MiB ? pl : none;
+}
+
+// A batch a little above a whole number of chains per unit (rows_of_first_call) whose backward pass is better off as one launch of
+// all three scans than as two calls; forward + backward, one against two, n 2048, 3000, 4096: d 64, 272 chains 0.94, 1.03, 1.10
+// (above 96 MiB a tensor the launch does not pay), 304 0.95, 0.97, 1.02, 336 0.98, 0.97, 1.00; d 96, 272 0.87, 0.91, 0.97, 304 0.79, 0.84,
+// 0.90, 336 0.82, 0.88, 0.88; d 128, n 2048, 3000, 272 1.01, 1.03, 288 0.98, 0.98, 304 0.95, 0.95, 336 0.87, 0.88.
+bool joint_in_one_call(const la2_desc* d, const Plan& pl) {
+  const int64_t cus = device_cu_count(), chains = (int64_t)d->batch * d->heads;
+  return pl.nchunks == 1 && chains < 2 * cus && (d->head_dim != 128 || 8 * (chains % cus) >= cus) &&
+         joint_plan(d, pl, nullptr, false).nchunks == 1;
 }
 
 // The state entry points split a sequence whose length is not a multiple of state_granule() into whole
@@ -1194,7 +1216,7 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
 extern "C" {
 
 // One call, or two for a batch a little above a whole number of chains per compute unit (rows_of_first_call), each
-// part with its own states; the forward call's workspace holds the chunk states of its second part, which is the
+// part with its own states (or, all three scans in one launch, one after all: joint_in_one_call); the forward call's workspace holds the chunk states of its second part, which is the
 // part whose backward reads them.
 la2_status la2_bwd_saved(const la2_desc* desc, const void* q, const void* k, const void* v, const void* d_o,
                          const float* lambda, const float* kv_init, const float* d_kv_final, void* dq, void* dk,
@@ -1207,6 +1229,9 @@ la2_status la2_bwd_saved(const la2_desc* desc, const void* q, const void* k, con
                               fwd_workspace_bytes, fwd_wrote_kv_final, workspace, workspace_bytes, hip_stream, false);
   const RowParts p = row_parts(desc, rows);
   for (int pass = 0; pass < 2; ++pass) {   // 0: check both parts, 1: run them
+    if (pass == 1 && joint_in_one_call(desc, make_plan(desc)) && !same_state(desc, d_kv_init, kv_init))
+      return bwd_saved_one_call(desc, q, k, v, d_o, lambda, kv_init, d_kv_final, dq, dk, dv, d_kv_init, nullptr, 0, 0, workspace,
+                                workspace_bytes, hip_stream, false);
     // the first part never reads the forward call's workspace: should its plan cut (fewer chains than units when the
     // heads do not divide them), its chunk states were overwritten there by the second part's
     la2_status st = bwd_saved_one_call(&p.first, q, k, v, d_o, lambda, kv_init, d_kv_final, dq, dk, dv, d_kv_init,

@@ -218,6 +218,7 @@ hipError_t launch_scan_wide(int dtype, int head_dim, bool reverse, bool state_on
 // head_dim 64 / 128: the dQ scan (dq) and the dK / dV scans (rev, nscan 2) of a backward pass in one launch; head_dim 64: both
 // families of their chunks' local states (y[0], z[0] of each) in one
 hipError_t launch_bwd_scans_bf16(int dtype, int head_dim, const ScanParams& dq, const ScanParams& rev, hipStream_t s);
+hipError_t launch_bwd_scans_wide(int dtype, int head_dim, const ScanParams& dq, const ScanParams& rev, hipStream_t s);   // head_dim 96
 hipError_t launch_chunk_state_pair_bf16(int dtype, int head_dim, const ScanParams& fwd, const ScanParams& rev, hipStream_t s);
 // O(n^2 d) left-product evaluation of one scan, for comparison (bf16; uses x, y, z, w of scan 0):
 // w = [(x y^T) * M] z over all earlier blocks, or with `reverse` the transposed mask over all later blocks

@@ -1,4 +1,4 @@
-"""Backward passes whose three scans run in one launch (16-bit data, head_dim 64 / 128), against the fp64 oracle and against the
+"""Backward passes whose three scans run in one launch (16-bit data), against the fp64 oracle and against the
 launches one after the other (scan variant 2)."""
 import pytest
 import torch
@@ -22,10 +22,12 @@ def _defaults():
 
 
 # head_dim, batch, heads, length: in the plan's chunks with a scan over their states and without one, uncut instead of them, uncut as
-# before; up to half the units, about all of them, a partial second round
+# before; up to half the units, about all of them, a partial second round, and one that else runs as two calls
 @pytest.mark.parametrize("d,b,h,n", [(64, 1, 4, 2113), (64, 1, 16, 2048), (64, 3, 16, 1000), (64, 6, 16, 1100), (64, 8, 16, 1031),
                                      (64, 10, 16, 200), (64, 16, 16, 257), (64, 18, 16, 130), (128, 5, 16, 416), (128, 3, 16, 1000),
-                                     (128, 6, 16, 1056), (128, 10, 16, 100), (128, 16, 16, 65), (128, 18, 16, 127)])
+                                     (96, 3, 2, 300), (96, 3, 16, 1000), (96, 5, 16, 1100), (96, 17, 16, 97), (96, 1, 16, 2050),
+                                     (128, 6, 16, 1056), (128, 10, 16, 100), (128, 16, 16, 65), (128, 18, 16, 127),
+                                     (128, 19, 16, 2049), (96, 17, 16, 2053), (64, 19, 16, 2055)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 def test_all_scans_in_one_launch(dtype, d, b, h, n):
     """Batch rows are copies of one, so every row has the same bits; with states and without, the forward call's states and none,
@@ -55,7 +57,10 @@ def test_all_scans_in_one_launch(dtype, d, b, h, n):
         for kind, outs in runs.items():
             for name, x, ref, other in zip(("dq", "dk", "dv", "d_kv_init"), outs, refs, apart):
                 label = "%s d%d b%d h%d n%d states %s %s" % (name, d, b, h, n, given, kind)
-                assert torch.equal(x, x[:1].expand_as(x)), label
+                if kind == "in place":   # (one after the other again, where that is two calls with chunks of their own)
+                    assert_close(label, x[-1:], ref, dtype)
+                else:
+                    assert torch.equal(x, x[:1].expand_as(x)), label
                 assert_close(label, x[:1], ref, dtype)
                 # no further from the truth than the launches apart (the same sums, or those of other chunks: up to their order)
                 assert rms_rel(to64(x[:1]), ref) <= 1.05 * rms_rel(to64(other[:1]), ref) + 1e-7, label
