@@ -1,19 +1,23 @@
-"""Thin ctypes binding of libla2.so: argument marshalling only.
+"""Thin binding of libla2.so: argument marshalling only.  The calls of the path go through the native module _la2_native
+(csrc/la2_python.cpp: checks, output tensors, descriptors), queries and tuning knobs through ctypes.
 
 Every step of the path runs in the library's HIP kernels; there is no CPU or
 PyTorch fallback.  torch is used for device memory and streams.  If the shared
 library is missing the first call raises (build it with
 `python -m paper_2401_04658_amd.build` or `__graft_entry__.build()`).
 """
-import contextlib
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libla2.so")
+_NATIVE_PATH = os.path.join(_HERE, "_la2_native.so")
 _lib = None
+_native = None
 
 LA2_F32, LA2_BF16, LA2_F16 = 0, 1, 2
 LA2_OP_FWD, LA2_OP_BWD, LA2_OP_FWD_STATE, LA2_OP_BWD_STATE = 0, 1, 2, 3
@@ -112,6 +116,21 @@ def load():
     return lib
 
 
+def _module():
+    """The native module (no fallback: raises if it has not been built)."""
+    global _native
+    if _native is None:
+        if not os.path.exists(_NATIVE_PATH):
+            raise FileNotFoundError(
+                "%s not found: the native module has not been built (python -m paper_2401_04658_amd.build)" % _NATIVE_PATH)
+        loader = importlib.machinery.ExtensionFileLoader("_la2_native", _NATIVE_PATH)
+        spec = importlib.util.spec_from_file_location("_la2_native", _NATIVE_PATH, loader=loader)
+        module = importlib.util.module_from_spec(spec)
+        loader.exec_module(module)
+        _native = module
+    return _native
+
+
 def _check(code):
     if code != 0:
         raise LA2Error(code, load().la2_status_string(code).decode())
@@ -137,30 +156,38 @@ def make_desc(t):
     return la2_desc(b, h, n, d, _dtype_code(t), 0, t.stride(0), t.stride(1), t.stride(2))
 
 
-def _same_layout(ref, *others):
-    for o in others:
-        if o.shape != ref.shape or o.stride() != ref.stride() or o.dtype != ref.dtype or o.device != ref.device:
-            raise ValueError("la2: all sequence tensors must share shape, strides, dtype and device")
-
-
-# Host time of a call is the whole cost of a small decode step (kernel 3.3 us; batch 1, H 16, d 128: 11.0 us a call
-# with torch.cuda.device and torch.cuda.current_stream around it, 7.5 with these two): the stream handle and the
-# device number are taken from where those wrappers take them (a torch without these two: from the wrappers), and the
-# device is switched only if it has to be.
-_NO_SWITCH = contextlib.nullcontext()
+# The stream handle and the device number are taken from where torch.cuda.current_stream and torch.cuda.device take them (a
+# torch without these two: from the wrappers), and the device is switched only if it has to be (decode, batch 1: 11.0 us a call
+# with the wrappers, 7.5 without).
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 _current_stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None)
                    or (lambda device: torch.cuda.current_stream(device).cuda_stream))
 
 
-def _on(t):
-    """Context in which t's device is the current one."""
-    return _NO_SWITCH if t.get_device() == _current_device() else torch.cuda.device(t.device)
+def _run(entry, t, *args):
+    """entry(*args, stream) on the current stream of t's device, which is made the current device."""
+    device = t.get_device()
+    if device == _current_device():
+        code = entry(*args, _current_stream(device))
+    else:
+        with torch.cuda.device(device):
+            code = entry(*args, _current_stream(device))
+    if code:
+        _check(code)
 
 
-def _stream(t):
-    """Handle of the current stream of t's device."""
-    return _current_stream(t.get_device())
+def _on_gpu(t, name):
+    if not t.is_cuda:
+        raise ValueError("%s: tensors must live on the GPU" % name)
+
+
+def _outputs(lib, q, out):
+    """dq, dk, dv: the caller's or new ones."""
+    if out is None:
+        return lib.like(q), lib.like(q), lib.like(q)
+    dq, dk, dv = out
+    lib.same_layout(q, dq, dk, dv)
+    return dq, dk, dv
 
 
 def la2_workspace_bytes(t, op=LA2_OP_FWD):
@@ -189,107 +216,85 @@ def la2_set_scan_variant(variant):
     load().la2_set_scan_variant(int(variant))
 
 
-def _workspace(t, op, workspace):
-    if workspace is None:
-        need = la2_workspace_bytes(t, op)
-        if need == 0:
-            return None, 0, None
-        workspace = torch.empty(need, dtype=torch.uint8, device=t.device)
-    return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
-
-
 def la2_fwd(q, k, v, lam, out=None, workspace=None):
     """o = LA2(q, k, v; lam) on the GPU.  q, k, v: [b, H, n, d] bf16/fp32; lam: fp32 [H] (device)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd: tensors must live on the GPU")
-    _same_layout(q, k, v)
+    lib = _module()
+    _on_gpu(q, "la2_fwd")
+    lib.same_layout(q, k, v)
     if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD, workspace)
-    with _on(q):
-        _check(lib.la2_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
-                           out.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
+    ws = lib.workspace(q, LA2_OP_FWD) if workspace is None else workspace
+    _run(lib.la2_fwd, q, q, q, k, v, lam, out, ws, ws)
     return out
 
 
 def la2_fwd_noalloc(q, k, v, lam, out):
     """la2_fwd into `out` with the library's built-in scratch instead of a workspace; the call itself allocates
     nothing (so `out` is required)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd_noalloc: tensors must live on the GPU")
-    _same_layout(q, k, v, out)
-    desc = make_desc(q)
-    with _on(q):
-        _check(lib.la2_fwd_noalloc(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
-                                   out.data_ptr(), _stream(q)))
+    lib = _module()
+    _on_gpu(q, "la2_fwd_noalloc")
+    lib.same_layout(q, k, v, out)
+    _run(lib.la2_fwd_noalloc, q, q, q, k, v, lam, out)
     return out
 
 
 def la2_bwd(q, k, v, d_o, lam, out=None, workspace=None):
     """(dq, dk, dv) of sum(o * d_o) on the GPU."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_bwd: tensors must live on the GPU")
-    _same_layout(q, k, v, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
-    dq, dk, dv = out
-    _same_layout(q, dq, dk, dv)
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD, workspace)
-    with _on(q):
-        _check(lib.la2_bwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(),
-                           lam.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), ws_ptr, ws_bytes,
-                           _stream(q)))
+    lib = _module()
+    _on_gpu(q, "la2_bwd")
+    lib.same_layout(q, k, v, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
+    ws = lib.workspace(q, LA2_OP_BWD) if workspace is None else workspace
+    _run(lib.la2_bwd, q, q, q, k, v, d_o, lam, dq, dk, dv, ws, ws)
     return dq, dk, dv
+
+
+def _rstd(lib, rstd, q, shape, name, what):
+    """The caller's row scales, checked, or new ones."""
+    if rstd is None:
+        return lib.f32(q, *shape)
+    if rstd.dtype != torch.float32 or tuple(rstd.shape) != shape or not rstd.is_contiguous():
+        raise ValueError("%s: rstd must be a contiguous fp32 %s tensor" % (name, what))
+    return rstd
 
 
 def la2_fwd_norm(q, k, v, lam, eps=1e-6, out=None, rstd=None, workspace=None):
     """(o, rstd) = Norm(LA2(q, k, v; lam)): every output row scaled by rstd = 1 / sqrt(mean(row^2) + eps)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd_norm: tensors must live on the GPU")
-    _same_layout(q, k, v)
+    lib = _module()
+    _on_gpu(q, "la2_fwd_norm")
+    lib.same_layout(q, k, v)
     if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
-    if rstd is None:
-        rstd = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
-    if rstd.dtype != torch.float32 or tuple(rstd.shape) != tuple(q.shape[:3]) or not rstd.is_contiguous():
-        raise ValueError("la2_fwd_norm: rstd must be a contiguous fp32 [batch, heads, seqlen] tensor")
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD, workspace)
-    with _on(q):
-        _check(lib.la2_fwd_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
-                                float(eps), out.data_ptr(), rstd.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
+    rstd = _rstd(lib, rstd, q, tuple(q.shape[:3]), "la2_fwd_norm", "[batch, heads, seqlen]")
+    ws = lib.workspace(q, LA2_OP_FWD) if workspace is None else workspace
+    _run(lib.la2_fwd_norm, q, q, q, k, v, lam, eps, out, rstd, ws, ws)
     return out, rstd
+
+
+def _given_rstd(lib, rstd, q, shape, name, what):
+    if rstd is None:
+        raise ValueError("%s: rstd is the forward call's" % name)
+    return _rstd(lib, rstd, q, shape, name, what)
 
 
 def la2_bwd_norm(q, k, v, o, rstd, d_o, lam, out=None, d_u=None, workspace=None):
     """(dq, dk, dv) of sum(la2_fwd_norm(q, k, v)[0] * d_o); o, rstd are la2_fwd_norm's results.  d_u (same
     layout as d_o) receives the gradient with respect to the un-normalised output."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_bwd_norm: tensors must live on the GPU")
-    _same_layout(q, k, v, o, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
+    lib = _module()
+    _on_gpu(q, "la2_bwd_norm")
+    lib.same_layout(q, k, v, o, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
     if d_u is None:
-        d_u = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    dq, dk, dv = out
-    _same_layout(q, dq, dk, dv, d_u)
-    if rstd.dtype != torch.float32 or tuple(rstd.shape) != tuple(q.shape[:3]) or not rstd.is_contiguous():
-        raise ValueError("la2_bwd_norm: rstd must be a contiguous fp32 [batch, heads, seqlen] tensor")
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD, workspace)
-    with _on(q):
-        _check(lib.la2_bwd_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                rstd.data_ptr(), d_o.data_ptr(), lam.data_ptr(), d_u.data_ptr(), dq.data_ptr(),
-                                dk.data_ptr(), dv.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
+        d_u = lib.like(q)
+    else:
+        lib.same_layout(q, d_u)
+    _given_rstd(lib, rstd, q, tuple(q.shape[:3]), "la2_bwd_norm", "[batch, heads, seqlen]")
+    ws = lib.workspace(q, LA2_OP_BWD) if workspace is None else workspace
+    _run(lib.la2_bwd_norm, q, q, q, k, v, o, rstd, d_o, lam, d_u, dq, dk, dv, ws, ws)
     return dq, dk, dv
 
 
@@ -306,212 +311,135 @@ def _varlen_desc(q, cu_seqlens, max_seqlen):
 def _varlen_workspace(q, desc, op, workspace):
     need = int(load().la2_varlen_workspace_bytes(ctypes.byref(desc), q.shape[0], op))
     if need == 0:
-        return None, 0, None
+        return None
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        return torch.empty(need, dtype=torch.uint8, device=q.device)
     if workspace.numel() * workspace.element_size() < need:
         raise ValueError("la2: workspace too small (%d < %d bytes)" % (workspace.numel() * workspace.element_size(), need))
-    return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
+    return workspace
 
 
 def la2_fwd_varlen(q, k, v, lam, cu_seqlens, max_seqlen, out=None, workspace=None):
     """o for packed sequences of different lengths: q, k, v [total_positions, heads, head_dim]; sequence b is
     positions cu_seqlens[b] .. cu_seqlens[b + 1] - 1; max_seqlen bounds the lengths."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd_varlen: tensors must live on the GPU")
-    _same_layout(q, k, v)
+    lib = _module()
+    _on_gpu(q, "la2_fwd_varlen")
+    lib.same_layout(q, k, v)
     if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
-    ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
-    with _on(q):
-        _check(lib.la2_fwd_varlen(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                  lam.data_ptr(), out.data_ptr(), ws_ptr, ws_bytes, _stream(q)))
+    ws = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
+    _run(lib.la2_fwd_varlen, q, desc, cu_seqlens, q.shape[0], q, k, v, lam, out, ws, ws)
     return out
 
 
 def la2_bwd_varlen(q, k, v, d_o, lam, cu_seqlens, max_seqlen, out=None, workspace=None):
     """(dq, dk, dv) for packed sequences of different lengths (see la2_fwd_varlen)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_bwd_varlen: tensors must live on the GPU")
-    _same_layout(q, k, v, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
-    dq, dk, dv = out
-    _same_layout(q, dq, dk, dv)
+    lib = _module()
+    _on_gpu(q, "la2_bwd_varlen")
+    lib.same_layout(q, k, v, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
-    ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
-    with _on(q):
-        _check(lib.la2_bwd_varlen(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                  d_o.data_ptr(), lam.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), ws_ptr,
-                                  ws_bytes, _stream(q)))
+    ws = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
+    _run(lib.la2_bwd_varlen, q, desc, cu_seqlens, q.shape[0], q, k, v, d_o, lam, dq, dk, dv, ws, ws)
     return dq, dk, dv
-
-
-def _packed_state(t, q, cu_seqlens, name):
-    """A dense fp32 [sequences, H, d, d] state tensor (or None) -> pointer argument."""
-    if t is None:
-        return None
-    nseq, h, d = cu_seqlens.numel() - 1, q.shape[1], q.shape[2]
-    if t.dtype != torch.float32 or tuple(t.shape) != (nseq, h, d, d) or not t.is_contiguous() or t.device != q.device:
-        raise ValueError("%s must be dense fp32 [sequences, H, d, d] on the tensors' device" % name)
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
 
 
 def la2_fwd_varlen_state(q, k, v, lam, cu_seqlens, max_seqlen, kv_init=None, want_final=True, out=None, kv_final=None,
                          workspace=None):
     """Packed sequences as segments: o and every sequence's state after its last position, each started from its
     kv_init (fp32 [sequences, H, d, d], None = zero).  Returns (o, kv_final or None)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd_varlen_state: tensors must live on the GPU")
-    _same_layout(q, k, v)
+    lib = _module()
+    _on_gpu(q, "la2_fwd_varlen_state")
+    lib.same_layout(q, k, v)
     if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
-    if want_final and kv_final is None:
-        kv_final = torch.empty((cu_seqlens.numel() - 1, q.shape[1], q.shape[2], q.shape[2]), dtype=torch.float32,
-                               device=q.device)
-    ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
-    with _on(q):
-        _check(lib.la2_fwd_varlen_state(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
-                                        v.data_ptr(), lam.data_ptr(), _packed_state(kv_init, q, cu_seqlens, "kv_init"),
-                                        out.data_ptr(),
-                                        _packed_state(kv_final, q, cu_seqlens, "kv_final") if want_final else None,
-                                        ws_ptr, ws_bytes, _stream(q)))
-    return out, (kv_final if want_final else None)
+    nseq = desc.batch
+    if not want_final:
+        kv_final = None
+    elif kv_final is None:
+        kv_final = lib.f32(q, nseq, q.shape[1], q.shape[2], q.shape[2])
+    ws = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
+    _run(lib.la2_fwd_varlen_state, q, desc, cu_seqlens, q.shape[0], q, k, v, lam, lib.state(kv_init, q, "kv_init", nseq), out,
+         lib.state(kv_final, q, "kv_final", nseq), ws, ws)
+    return out, kv_final
 
 
 def la2_bwd_varlen_state(q, k, v, d_o, lam, cu_seqlens, max_seqlen, kv_init=None, d_kv_final=None, want_d_kv_init=True,
                          out=None, d_kv_init=None, workspace=None):
     """Backward of la2_fwd_varlen_state.  Returns (dq, dk, dv, d_kv_init or None)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_bwd_varlen_state: tensors must live on the GPU")
-    _same_layout(q, k, v, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
-    dq, dk, dv = out
-    _same_layout(q, dq, dk, dv)
+    lib = _module()
+    _on_gpu(q, "la2_bwd_varlen_state")
+    lib.same_layout(q, k, v, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
-    if want_d_kv_init and d_kv_init is None:
-        d_kv_init = torch.empty((cu_seqlens.numel() - 1, q.shape[1], q.shape[2], q.shape[2]), dtype=torch.float32,
-                                device=q.device)
-    ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
-    with _on(q):
-        _check(lib.la2_bwd_varlen_state(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
-                                        v.data_ptr(), d_o.data_ptr(), lam.data_ptr(),
-                                        _packed_state(kv_init, q, cu_seqlens, "kv_init"),
-                                        _packed_state(d_kv_final, q, cu_seqlens, "d_kv_final"), dq.data_ptr(),
-                                        dk.data_ptr(), dv.data_ptr(),
-                                        _packed_state(d_kv_init, q, cu_seqlens, "d_kv_init") if want_d_kv_init else None,
-                                        ws_ptr, ws_bytes, _stream(q)))
-    return dq, dk, dv, (d_kv_init if want_d_kv_init else None)
+    nseq = desc.batch
+    if not want_d_kv_init:
+        d_kv_init = None
+    elif d_kv_init is None:
+        d_kv_init = lib.f32(q, nseq, q.shape[1], q.shape[2], q.shape[2])
+    ws = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
+    _run(lib.la2_bwd_varlen_state, q, desc, cu_seqlens, q.shape[0], q, k, v, d_o, lam, lib.state(kv_init, q, "kv_init", nseq),
+         lib.state(d_kv_final, q, "d_kv_final", nseq), dq, dk, dv, lib.state(d_kv_init, q, "d_kv_init", nseq), ws, ws)
+    return dq, dk, dv, d_kv_init
 
 
 def la2_fwd_varlen_norm(q, k, v, lam, cu_seqlens, max_seqlen, eps=1e-6, out=None, rstd=None, workspace=None):
     """(o, rstd) of the normalised operator over packed sequences; rstd is fp32 [heads, total_positions]."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd_varlen_norm: tensors must live on the GPU")
-    _same_layout(q, k, v)
+    lib = _module()
+    _on_gpu(q, "la2_fwd_varlen_norm")
+    lib.same_layout(q, k, v)
     if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
-    if rstd is None:
-        rstd = torch.empty((q.shape[1], q.shape[0]), dtype=torch.float32, device=q.device)
-    if rstd.dtype != torch.float32 or tuple(rstd.shape) != (q.shape[1], q.shape[0]) or not rstd.is_contiguous():
-        raise ValueError("la2_fwd_varlen_norm: rstd must be a contiguous fp32 [heads, total_positions] tensor")
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
+    rstd = _rstd(lib, rstd, q, (q.shape[1], q.shape[0]), "la2_fwd_varlen_norm", "[heads, total_positions]")
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
-    ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
-    with _on(q):
-        _check(lib.la2_fwd_varlen_norm(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
-                                       v.data_ptr(), lam.data_ptr(), float(eps), out.data_ptr(), rstd.data_ptr(), ws_ptr,
-                                       ws_bytes, _stream(q)))
+    ws = _varlen_workspace(q, desc, LA2_OP_FWD, workspace)
+    _run(lib.la2_fwd_varlen_norm, q, desc, cu_seqlens, q.shape[0], q, k, v, lam, eps, out, rstd, ws, ws)
     return out, rstd
 
 
 def la2_bwd_varlen_norm(q, k, v, o, rstd, d_o, lam, cu_seqlens, max_seqlen, out=None, d_u=None, workspace=None):
     """(dq, dk, dv) of the normalised operator over packed sequences (o, rstd from la2_fwd_varlen_norm)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_bwd_varlen_norm: tensors must live on the GPU")
-    _same_layout(q, k, v, o, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
+    lib = _module()
+    _on_gpu(q, "la2_bwd_varlen_norm")
+    lib.same_layout(q, k, v, o, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
     if d_u is None:
-        d_u = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    dq, dk, dv = out
-    _same_layout(q, dq, dk, dv, d_u)
-    if rstd.dtype != torch.float32 or tuple(rstd.shape) != (q.shape[1], q.shape[0]) or not rstd.is_contiguous():
-        raise ValueError("la2_bwd_varlen_norm: rstd must be a contiguous fp32 [heads, total_positions] tensor")
+        d_u = lib.like(q)
+    else:
+        lib.same_layout(q, d_u)
+    _given_rstd(lib, rstd, q, (q.shape[1], q.shape[0]), "la2_bwd_varlen_norm", "[heads, total_positions]")
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
-    ws_ptr, ws_bytes, _keep = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
-    with _on(q):
-        _check(lib.la2_bwd_varlen_norm(ctypes.byref(desc), cu_seqlens.data_ptr(), q.shape[0], q.data_ptr(), k.data_ptr(),
-                                       v.data_ptr(), o.data_ptr(), rstd.data_ptr(), d_o.data_ptr(), lam.data_ptr(),
-                                       d_u.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), ws_ptr, ws_bytes,
-                                       _stream(q)))
+    ws = _varlen_workspace(q, desc, LA2_OP_BWD, workspace)
+    _run(lib.la2_bwd_varlen_norm, q, desc, cu_seqlens, q.shape[0], q, k, v, o, rstd, d_o, lam, d_u, dq, dk, dv, ws, ws)
     return dq, dk, dv
-
-
-def la2_decode_multi_norm(q, k, v, lam, kv_state, eps=1e-6, out=None, rstd=None):
-    """ntokens consecutive steps of the normalised operator in one launch; returns (o, rstd [b, H, T])."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_decode_multi_norm: tensors must live on the GPU")
-    b, h, t, d = q.shape
-    for x in (q, k, v):
-        if x.shape != q.shape or x.dtype != q.dtype or not x.is_contiguous():
-            raise ValueError("la2_decode_multi_norm: q, k, v must be dense [b, H, T, d] of one dtype")
-    if kv_state.dtype != torch.float32 or tuple(kv_state.shape) != (b, h, d, d) or not kv_state.is_contiguous():
-        raise ValueError("la2_decode_multi_norm: kv_state must be dense fp32 [b, H, d, d]")
-    if out is None:
-        out = torch.empty_like(q)
-    if rstd is None:
-        rstd = torch.empty((b, h, t), dtype=torch.float32, device=q.device)
-    with _on(q):
-        _check(lib.la2_decode_multi_norm(b, h, d, t, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                         lam.data_ptr(), kv_state.data_ptr(), float(eps), out.data_ptr(), rstd.data_ptr(),
-                                         _stream(q)))
-    return out, rstd
-
-
-def _state(t, q, name):
-    """A dense fp32 [b, H, d, d] state tensor (or None) -> pointer argument."""
-    if t is None:
-        return None
-    b, h, _, d = q.shape
-    if t.dtype != torch.float32 or tuple(t.shape) != (b, h, d, d) or not t.is_contiguous() or t.device != q.device:
-        raise ValueError("%s must be dense fp32 [b, H, d, d] on the tensors' device" % name)
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
 
 
 def la2_fwd_state(q, k, v, lam, kv_init=None, want_final=True, out=None, kv_final=None, workspace=None):
     """One segment of a sequence: o and the state after its last position, started from kv_init
     (fp32 [b, H, d, d], None = zero).  Returns (o, kv_final or None)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd_state: tensors must live on the GPU")
-    _same_layout(q, k, v)
+    lib = _module()
+    _on_gpu(q, "la2_fwd_state")
+    lib.same_layout(q, k, v)
     if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
     b, h, _, d = q.shape
-    if want_final and kv_final is None:
-        kv_final = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD_STATE, workspace)
-    with _on(q):
-        _check(lib.la2_fwd_state(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
-                                 _state(kv_init, q, "kv_init"), out.data_ptr(),
-                                 _state(kv_final, q, "kv_final") if want_final else None,
-                                 ws_ptr, ws_bytes, _stream(q)))
-    return out, (kv_final if want_final else None)
+    if not want_final:
+        kv_final = None
+    elif kv_final is None:
+        kv_final = lib.f32(q, b, h, d, d)
+    ws = lib.workspace(q, LA2_OP_FWD_STATE) if workspace is None else workspace
+    _run(lib.la2_fwd_state, q, q, q, k, v, lam, lib.state(kv_init, q, "kv_init"), out, lib.state(kv_final, q, "kv_final"), ws, ws)
+    return out, kv_final
 
 
 def la2_bwd_state(q, k, v, d_o, lam, kv_init=None, d_kv_final=None, want_d_kv_init=True, out=None,
@@ -519,173 +447,132 @@ def la2_bwd_state(q, k, v, d_o, lam, kv_init=None, d_kv_final=None, want_d_kv_in
     """Backward of one segment.  Returns (dq, dk, dv, d_kv_init or None).  fwd_workspace: the workspace
     tensor the forward call used (contents untouched since), to reuse its chunk states; fwd_wrote_kv_final:
     whether that call handed out kv_final."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_bwd_state: tensors must live on the GPU")
-    _same_layout(q, k, v, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
-    dq, dk, dv = out
-    _same_layout(q, dq, dk, dv)
+    lib = _module()
+    _on_gpu(q, "la2_bwd_state")
+    lib.same_layout(q, k, v, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
     b, h, _, d = q.shape
-    if want_d_kv_init and d_kv_init is None:
-        d_kv_init = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD_STATE, workspace)
-    with _on(q):
-        fwd_ws = ctypes.c_void_p(fwd_workspace.data_ptr()) if fwd_workspace is not None else None
-        _check(lib.la2_bwd_saved(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(),
-                                 lam.data_ptr(), _state(kv_init, q, "kv_init"),
-                                 _state(d_kv_final, q, "d_kv_final"), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
-                                 _state(d_kv_init, q, "d_kv_init") if want_d_kv_init else None,
-                                 fwd_ws, fwd_workspace.numel() * fwd_workspace.element_size() if fwd_workspace is not None else 0,
-                                 1 if fwd_wrote_kv_final else 0, ws_ptr, ws_bytes, _stream(q)))
-    return dq, dk, dv, (d_kv_init if want_d_kv_init else None)
+    if not want_d_kv_init:
+        d_kv_init = None
+    elif d_kv_init is None:
+        d_kv_init = lib.f32(q, b, h, d, d)
+    ws = lib.workspace(q, LA2_OP_BWD_STATE) if workspace is None else workspace
+    _run(lib.la2_bwd_saved, q, q, q, k, v, d_o, lam, lib.state(kv_init, q, "kv_init"), lib.state(d_kv_final, q, "d_kv_final"),
+         dq, dk, dv, lib.state(d_kv_init, q, "d_kv_init"), fwd_workspace, fwd_workspace, 1 if fwd_wrote_kv_final else 0, ws, ws)
+    return dq, dk, dv, d_kv_init
+
+
+def la2_fwd_state_norm(q, k, v, lam, eps=1e-6, kv_init=None, want_final=True, out=None, rstd=None, kv_final=None,
+                       workspace=None):
+    """la2_fwd_norm on one segment of a sequence, started from kv_init.  Returns (o, rstd, kv_final or None)."""
+    lib = _module()
+    _on_gpu(q, "la2_fwd_state_norm")
+    lib.same_layout(q, k, v)
+    if out is None:
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
+    b, h, n, d = q.shape
+    rstd = _rstd(lib, rstd, q, (b, h, n), "la2_fwd_state_norm", "[batch, heads, seqlen]")
+    if not want_final:
+        kv_final = None
+    elif kv_final is None:
+        kv_final = lib.f32(q, b, h, d, d)
+    ws = lib.workspace(q, LA2_OP_FWD_STATE) if workspace is None else workspace
+    _run(lib.la2_fwd_state_norm, q, q, q, k, v, lam, lib.state(kv_init, q, "kv_init"), eps, out, rstd,
+         lib.state(kv_final, q, "kv_final"), ws, ws)
+    return out, rstd, kv_final
+
+
+def la2_bwd_state_norm(q, k, v, o, rstd, d_o, lam, kv_init=None, d_kv_final=None, want_d_kv_init=True, out=None,
+                       d_u=None, d_kv_init=None, workspace=None):
+    """Backward of la2_fwd_state_norm.  Returns (dq, dk, dv, d_kv_init or None)."""
+    lib = _module()
+    _on_gpu(q, "la2_bwd_state_norm")
+    lib.same_layout(q, k, v, o, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
+    if d_u is None:
+        d_u = lib.like(q)
+    else:
+        lib.same_layout(q, d_u)
+    b, h, n, d = q.shape
+    _given_rstd(lib, rstd, q, (b, h, n), "la2_bwd_state_norm", "[batch, heads, seqlen]")
+    if not want_d_kv_init:
+        d_kv_init = None
+    elif d_kv_init is None:
+        d_kv_init = lib.f32(q, b, h, d, d)
+    ws = lib.workspace(q, LA2_OP_BWD_STATE) if workspace is None else workspace
+    _run(lib.la2_bwd_state_norm, q, q, q, k, v, o, rstd, d_o, lam, lib.state(kv_init, q, "kv_init"),
+         lib.state(d_kv_final, q, "d_kv_final"), d_u, dq, dk, dv, lib.state(d_kv_init, q, "d_kv_init"), ws, ws)
+    return dq, dk, dv, d_kv_init
 
 
 def la2_decode_step(q, k, v, lam, kv_state, out=None):
     """One recurrent step; kv_state (fp32 [b, H, d, d]) is updated in place, returns o [b, H, d]."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_decode_step: tensors must live on the GPU")
-    b, h, d = q.shape
-    for t in (q, k, v):
-        if t.shape != q.shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError("la2_decode_step: q, k, v must be dense [b, H, d] of one dtype")
-    if kv_state.dtype != torch.float32 or tuple(kv_state.shape) != (b, h, d, d) or not kv_state.is_contiguous():
-        raise ValueError("la2_decode_step: kv_state must be dense fp32 [b, H, d, d]")
+    lib = _module()
+    _on_gpu(q, "la2_decode_step")
+    b, h, d, dtype = lib.decode_shape("la2_decode_step", 3, q, k, v, kv_state)
     if out is None:
-        out = torch.empty_like(q)
-    with _on(q):
-        _check(lib.la2_decode_step(b, h, d, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                   lam.data_ptr(), kv_state.data_ptr(), out.data_ptr(), _stream(q)))
+        out = lib.like(q)
+    _run(lib.la2_decode_step, q, b, h, d, dtype, q, k, v, lam, kv_state, out)
     return out
 
 
 def la2_decode_multi(q, k, v, lam, kv_state, out=None):
     """ntokens consecutive recurrent steps in one launch.  q, k, v: dense [b, H, T, d]; kv_state (fp32
     [b, H, d, d]) is updated in place; returns o [b, H, T, d]."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_decode_multi: tensors must live on the GPU")
-    b, h, t, d = q.shape
-    for x in (q, k, v):
-        if x.shape != q.shape or x.dtype != q.dtype or not x.is_contiguous():
-            raise ValueError("la2_decode_multi: q, k, v must be dense [b, H, T, d] of one dtype")
-    if kv_state.dtype != torch.float32 or tuple(kv_state.shape) != (b, h, d, d) or not kv_state.is_contiguous():
-        raise ValueError("la2_decode_multi: kv_state must be dense fp32 [b, H, d, d]")
+    lib = _module()
+    _on_gpu(q, "la2_decode_multi")
+    b, h, t, d, dtype = lib.decode_shape("la2_decode_multi", 4, q, k, v, kv_state)
     if out is None:
-        out = torch.empty_like(q)
-    with _on(q):
-        _check(lib.la2_decode_multi(b, h, d, t, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                    lam.data_ptr(), kv_state.data_ptr(), out.data_ptr(), _stream(q)))
+        out = lib.like(q)
+    _run(lib.la2_decode_multi, q, b, h, d, t, dtype, q, k, v, lam, kv_state, out)
     return out
-
-
-def la2_left_product_fwd(q, k, v, lam, out=None):
-    """The forward pass as the O(n^2 d) masked left product (comparison kernel, bf16)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_left_product_fwd: tensors must live on the GPU")
-    _same_layout(q, k, v)
-    if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
-    desc = make_desc(q)
-    with _on(q):
-        _check(lib.la2_left_product_fwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
-                                        out.data_ptr(), _stream(q)))
-    return out
-
-
-def la2_left_product_bwd(q, k, v, d_o, lam, out=None):
-    """(dq, dk, dv) as O(n^2 d) masked products (comparison kernel, bf16)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_left_product_bwd: tensors must live on the GPU")
-    _same_layout(q, k, v, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
-    dq, dk, dv = out
-    _same_layout(q, dq, dk, dv)
-    desc = make_desc(q)
-    with _on(q):
-        _check(lib.la2_left_product_bwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), d_o.data_ptr(),
-                                        lam.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), _stream(q)))
-    return dq, dk, dv
-
-
-def la2_fwd_state_norm(q, k, v, lam, eps=1e-6, kv_init=None, want_final=True, out=None, rstd=None, kv_final=None,
-                       workspace=None):
-    """la2_fwd_norm on one segment of a sequence, started from kv_init.  Returns (o, rstd, kv_final or None)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_fwd_state_norm: tensors must live on the GPU")
-    _same_layout(q, k, v)
-    if out is None:
-        out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, out)
-    b, h, n, d = q.shape
-    if rstd is None:
-        rstd = torch.empty((b, h, n), dtype=torch.float32, device=q.device)
-    if rstd.dtype != torch.float32 or tuple(rstd.shape) != (b, h, n) or not rstd.is_contiguous():
-        raise ValueError("la2_fwd_state_norm: rstd must be a contiguous fp32 [batch, heads, seqlen] tensor")
-    if want_final and kv_final is None:
-        kv_final = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_FWD_STATE, workspace)
-    with _on(q):
-        _check(lib.la2_fwd_state_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), lam.data_ptr(),
-                                      _state(kv_init, q, "kv_init"), float(eps), out.data_ptr(), rstd.data_ptr(),
-                                      _state(kv_final, q, "kv_final") if want_final else None,
-                                      ws_ptr, ws_bytes, _stream(q)))
-    return out, rstd, (kv_final if want_final else None)
-
-
-def la2_bwd_state_norm(q, k, v, o, rstd, d_o, lam, kv_init=None, d_kv_final=None, want_d_kv_init=True, out=None,
-                       d_u=None, d_kv_init=None, workspace=None):
-    """Backward of la2_fwd_state_norm.  Returns (dq, dk, dv, d_kv_init or None)."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_bwd_state_norm: tensors must live on the GPU")
-    _same_layout(q, k, v, o, d_o)
-    if out is None:
-        out = tuple(torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device) for _ in range(3))
-    if d_u is None:
-        d_u = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
-    _same_layout(q, d_u, *out)
-    b, h, n, d = q.shape
-    if rstd.dtype != torch.float32 or tuple(rstd.shape) != (b, h, n) or not rstd.is_contiguous():
-        raise ValueError("la2_bwd_state_norm: rstd must be a contiguous fp32 [batch, heads, seqlen] tensor")
-    if want_d_kv_init and d_kv_init is None:
-        d_kv_init = torch.empty((b, h, d, d), dtype=torch.float32, device=q.device)
-    desc = make_desc(q)
-    ws_ptr, ws_bytes, _keep = _workspace(q, LA2_OP_BWD_STATE, workspace)
-    with _on(q):
-        _check(lib.la2_bwd_state_norm(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                      rstd.data_ptr(), d_o.data_ptr(), lam.data_ptr(), _state(kv_init, q, "kv_init"),
-                                      _state(d_kv_final, q, "d_kv_final"), d_u.data_ptr(), out[0].data_ptr(),
-                                      out[1].data_ptr(), out[2].data_ptr(),
-                                      _state(d_kv_init, q, "d_kv_init") if want_d_kv_init else None,
-                                      ws_ptr, ws_bytes, _stream(q)))
-    return out[0], out[1], out[2], (d_kv_init if want_d_kv_init else None)
 
 
 def la2_decode_step_norm(q, k, v, lam, kv_state, eps=1e-6, out=None):
     """One recurrent step of the normalised operator; kv_state (fp32 [b, H, d, d]) is updated in place, returns
     the normalised o [b, H, d]."""
-    lib = load()
-    if not q.is_cuda:
-        raise ValueError("la2_decode_step_norm: tensors must live on the GPU")
-    b, h, d = q.shape
-    for t in (q, k, v):
-        if t.shape != q.shape or t.dtype != q.dtype or not t.is_contiguous():
-            raise ValueError("la2_decode_step_norm: q, k, v must be dense [b, H, d] of one dtype")
-    if kv_state.dtype != torch.float32 or tuple(kv_state.shape) != (b, h, d, d) or not kv_state.is_contiguous():
-        raise ValueError("la2_decode_step_norm: kv_state must be dense fp32 [b, H, d, d]")
+    lib = _module()
+    _on_gpu(q, "la2_decode_step_norm")
+    b, h, d, dtype = lib.decode_shape("la2_decode_step_norm", 3, q, k, v, kv_state)
     if out is None:
-        out = torch.empty_like(q)
-    with _on(q):
-        _check(lib.la2_decode_step_norm(b, h, d, _dtype_code(q), q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                        lam.data_ptr(), kv_state.data_ptr(), float(eps), out.data_ptr(), _stream(q)))
+        out = lib.like(q)
+    _run(lib.la2_decode_step_norm, q, b, h, d, dtype, q, k, v, lam, kv_state, eps, out)
     return out
+
+
+def la2_decode_multi_norm(q, k, v, lam, kv_state, eps=1e-6, out=None, rstd=None):
+    """ntokens consecutive steps of the normalised operator in one launch; returns (o, rstd [b, H, T])."""
+    lib = _module()
+    _on_gpu(q, "la2_decode_multi_norm")
+    b, h, t, d, dtype = lib.decode_shape("la2_decode_multi_norm", 4, q, k, v, kv_state)
+    if out is None:
+        out = lib.like(q)
+    if rstd is None:
+        rstd = lib.f32(q, b, h, t)
+    _run(lib.la2_decode_multi_norm, q, b, h, d, t, dtype, q, k, v, lam, kv_state, eps, out, rstd)
+    return out, rstd
+
+
+def la2_left_product_fwd(q, k, v, lam, out=None):
+    """The forward pass as the O(n^2 d) masked left product (comparison kernel, bf16)."""
+    lib = _module()
+    _on_gpu(q, "la2_left_product_fwd")
+    lib.same_layout(q, k, v)
+    if out is None:
+        out = lib.like(q)
+    else:
+        lib.same_layout(q, out)
+    _run(lib.la2_left_product_fwd, q, q, q, k, v, lam, out)
+    return out
+
+
+def la2_left_product_bwd(q, k, v, d_o, lam, out=None):
+    """(dq, dk, dv) as O(n^2 d) masked products (comparison kernel, bf16)."""
+    lib = _module()
+    _on_gpu(q, "la2_left_product_bwd")
+    lib.same_layout(q, k, v, d_o)
+    dq, dk, dv = _outputs(lib, q, out)
+    _run(lib.la2_left_product_bwd, q, q, q, k, v, d_o, lam, dq, dk, dv)
+    return dq, dk, dv

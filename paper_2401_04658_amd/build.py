@@ -1,10 +1,11 @@
 """Builds libla2.so (the C-ABI library) and libla2_bench.so (the benchmark's measurement kernels) for gfx950 with
-hipcc, in-tree."""
+hipcc, and _la2_native.so (the binding's native module) with the host compiler, in-tree."""
 import json
 import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
@@ -14,6 +15,8 @@ SOURCES = ["la2_api.hip", "la2_scan_bf16.hip", "la2_scan_bf16_half.hip", "la2_bw
            "la2_short_bf16.hip"]
 BENCH_LIB = os.path.join(_HERE, "libla2_bench.so")
 BENCH_SOURCES = ["bench_probe.hip"]
+NATIVE = os.path.join(_HERE, "_la2_native.so")
+NATIVE_SOURCE = "la2_python.cpp"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
@@ -53,8 +56,22 @@ def _take_resource_remarks(out, resources):
     return "\n".join(rest)
 
 
+def _native_commands(obj):
+    """Compile and link commands of the native module.  torch's libraries are in the process when it is imported (found by their
+    names), libla2.so lies beside it."""
+    import torch
+    home = os.path.dirname(os.path.abspath(torch.__file__))
+    cxx = os.environ.get("CXX", "g++")
+    compile_ = [cxx, "-O2", "-std=c++17", "-fPIC", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+                "-isystem", os.path.join(home, "include"), "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
+                "-isystem", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
+    link = [cxx, "-shared", "-fPIC", obj, "-L" + _HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",
+            "-L" + os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    return compile_, link
+
+
 def build(verbose=False):
-    """Compiles every HIP source and links libla2.so and libla2_bench.so.  Always rebuilds."""
+    """Compiles every source and links libla2.so, libla2_bench.so and _la2_native.so.  Always rebuilds."""
     objs = []
     procs = []
     bdir = os.path.join(_HERE, "_build")
@@ -66,13 +83,16 @@ def build(verbose=False):
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    native_obj = os.path.join(bdir, NATIVE_SOURCE.replace(".cpp", ".o"))
+    native_compile, native_link = _native_commands(native_obj)
+    procs.append((NATIVE_SOURCE, subprocess.Popen(native_compile, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     resources = {}
     for src, pr in procs:
         out, _ = pr.communicate()
         out = _take_resource_remarks(out, resources)
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if pr.returncode != 0:
-            raise RuntimeError("hipcc failed on %s:\n%s" % (src, out))
+            raise RuntimeError("compiler failed on %s:\n%s" % (src, out))
         if verbose and out.strip():
             print(out)
     with open(os.path.join(bdir, "kernel_resources.json"), "w") as f:
@@ -81,6 +101,9 @@ def build(verbose=False):
         tmp = lib + ".tmp%d" % os.getpid()
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + part)
         os.replace(tmp, lib)
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    subprocess.check_call(native_link + ["-o", tmp])
+    os.replace(tmp, NATIVE)
     return LIB
 
 
