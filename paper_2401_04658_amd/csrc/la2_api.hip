@@ -325,6 +325,14 @@ int keep_tiles(const la2_desc* d, const Plan& pl, bool prefill) {
   return tensor_bytes(d, pl) <= (int64_t)(prefill ? 16 : wide(d->head_dim) ? 160 : 96) << 20;
 }
 
+// ... of a forward pass at head_dim 64 that is not cut and hands out no state: up to 192 MiB a tensor.  The launch itself takes 2 to 5 %
+// longer than with non-temporal loads (256 chains of 4096 94.7 -> 98.6 us), the backward pass behind it, whose first launch starts at the
+// sequences' ends, finds what it read last.  Forward + backward, 256 chains of 3500, 4096, 6000 0.92, 0.95, 0.95 (8192, 256 MiB,
+// 0.97), 512 of 2048 0.94, 1024 of 1024 0.91; head_dim 128, 192 and 256 chains, 96 to 256 MiB, 0.97-1.02: not there.
+int keep_forward(const la2_desc* d, const Plan& pl, const int32_t* cu) {
+  return is16(d->dtype) && d->head_dim == 64 && cu == nullptr && pl.nchunks == 1 && tensor_bytes(d, pl) <= (int64_t)192 << 20;
+}
+
 // ScanParams::plain, forward passes.  Streaming stores (the default: see the kernels) leave the caches to the inputs, but they are
 // acknowledged later, and a wave that waits for its next tiles waits for its older stores as well.  Ordinary ones where that costs
 // more:
@@ -477,6 +485,7 @@ struct ScanArgs {
   const int4* map = nullptr;
   // states at sequence ends that are not block boundaries (ScanParams::ragged_state; 16-bit half-block kernels)
   bool ragged_state = false;
+  bool outputs = false;   // the scan that forms O
 };
 
 // A problem cut into a few chunks (16-bit half-block and fp32 kernels up to four, head_dim 96 as below; dense or packed
@@ -573,6 +582,7 @@ la2::ScanParams scan_params(const la2_desc* d, const Plan& pl, const ScanArgs& a
   p.ragged_state = a.ragged_state ? 1 : 0;
   p.value_split = value_split(d, p);
   p.keep = keep_tiles(d, pl, a.fin != nullptr);   // (of the launches here only a forward pass hands out a state)
+  if (a.outputs && a.fin == nullptr && a.rstd == nullptr && keep_forward(d, pl, a.cu)) p.keep = 1;
   p.plain = plain_stores(d, pl, a.cu, a.fin != nullptr, a.rstd != nullptr);
   if (p.plain != 0 && !wide(d->head_dim)) p.keep = 0;
   return p;
@@ -1003,6 +1013,7 @@ la2_status fwd_state_one_call(const la2_desc* desc, const void* q, const void* k
     return run_short_fwd(desc, q, k, v, lambda, kv_init, o, kv_final, rstd, eps, desc->seqlen, nullptr, s);
   if (blocks.seqlen > 0) {
     ScanArgs a{q, k, v, o};
+    a.outputs = true;
     a.init = kv_init;
     a.fin = kv_final;
     a.ragged_state = kv_final != nullptr && ragged_end(desc);
@@ -1190,6 +1201,14 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
   if (fuse) {
     for_dq.acc_y = q;
     for_dq.acc_states = reinterpret_cast<float*>(rev_workspace);
+  }
+  // Sequences that are not cut: the second loop first.  It starts where the forward pass and the pass over the rows ended and ends where
+  // the dQ scan starts, so that each launch finds in the caches what the one before read last.  Forward + backward against the
+  // dQ scan first: d 64 0.99-1.00, d 96, 192 and 256 chains 0.93-0.97 (192 MiB a tensor 1.00), d 128 0.97-0.99 (96 MiB and more 0.99-1.00),
+  // d 256 0.98-1.00 (192 chains of 700 1.01).
+  if (is16(desc->dtype) && pl.nchunks == 1 && !same_state(desc, d_kv_init, kv_init)) {
+    st = run_dual_reverse_scan(desc, pl, for_dv, for_dk, lambda, rev_workspace, s);
+    return st == LA2_OK ? run_scan(desc, pl, false, for_dq, lambda, workspace, s) : st;
   }
   st = run_scan(desc, pl, false, for_dq, lambda, workspace, s);
   if (st != LA2_OK) return st;
