@@ -49,6 +49,39 @@ constexpr int kBH = 32;
 //
 // CACHE, bits: 1 the tile loads without the non-temporal hint (ScanParams::keep), 2 the outputs through the caches (plain).
 //
+// Transposing reads take the columns of their tile in the order pi: bits 2 and 3 of the index exchanged (lane s of a group of sixteen
+// passes the address of the 8-byte piece whose two index bits are exchanged; an instruction's set of addresses, hence its bank
+// behaviour, is the same).  Element v of state tile t in a lane is then key feature 32 t + 16 (v / 8) + 8 hh + v % 8 and value feature
+// 32 dvt + pi(l32): the eight elements that a lane converts for a k-step are those a row fragment of X holds, without the exchange
+// between the lane halves that the natural order needs (sixteen lane swaps per wave and block at head_dim 128), and a lane's sixteen
+// outputs are two 16-byte pieces of a row.  States in memory keep their layout.  Forward / backward with all chains on one chain's
+// tensors (no memory time), 256 chains of 4096, d 128 162 -> 148, 430 -> 410 us, d 64 95 -> 87, 208 -> 195; forward + backward as they
+// are, batch 8, n 3001, d 64, Norm 0.973, 128 chains of 2048, d 64 0.974, 16 of 2048 0.971, 256 of 4096 and one batch of 65,536, d 128 0.99.
+template <int D>
+struct PiAddr : LaneAddr<D> {
+  int tp0, tp1;   // as LaneAddr's tr0, tr1
+  __device__ __forceinline__ PiAddr(int l) : LaneAddr<D>(l) {
+    const int hh = l >> 5, s16 = l & 15, g2 = (l >> 4) & 1;
+    const int trc = 2 * g2 + (s16 & 1), trh = 4 * ((s16 & 3) >> 1);
+    const int r0 = 4 * hh + (s16 >> 2), r1 = r0 + 8;
+    tp0 = r0 * D + 8 * (trc ^ swz<D>(r0)) + trh;
+    tp1 = r1 * D + 8 * (trc ^ swz<D>(r1)) + trh;
+  }
+  template <typename E>
+  __device__ __forceinline__ ex8<E> read_cols(const E* tile, int c0, int t) const {
+    union { struct { s16x4 lo, hi; } s; ex8<E> v; } u;
+    u.s.lo = lds_read_tr(tile + c0 * D + (tp0 ^ (32 * t)));
+    u.s.hi = lds_read_tr(tile + c0 * D + (tp1 ^ (32 * t)));
+    return u.v;
+  }
+};
+template <int D>
+__device__ __forceinline__ int state_index_pi(int dvt, int l32, int hh, int t, int v, bool transposed) {
+  const int dk = 32 * t + 16 * (v >> 3) + 8 * hh + (v & 7);
+  const int dv = 32 * dvt + ((l32 & 19) | ((l32 & 4) << 1) | ((l32 & 8) >> 1));
+  return transposed ? dv * D + dk : dk * D + dv;
+}
+
 // half_scan is the body of one workgroup; a kernel gives it a workgroup number and the LDS.  (The kernels call it from a lambda:
 // inlined from there the compiler sees the kernel's arguments as such and loads them where they are used; called directly it
 // loads them all in front and spills scalar registers.)
@@ -140,7 +173,7 @@ __device__ __forceinline__ void half_scan(const ScanParams& p, const int wg, Hal
       for (int t = 0; t < NT; t++)
 #pragma unroll
         for (int v = 0; v < 16; v++)
-          gf0[state_index<D>(dvt, l32, hh, t, v, trf)] = gi0 != nullptr ? gi0[state_index<D>(dvt, l32, hh, t, v, tri)] : 0.f;
+          gf0[state_index_pi<D>(dvt, l32, hh, t, v, trf)] = gi0 != nullptr ? gi0[state_index_pi<D>(dvt, l32, hh, t, v, tri)] : 0.f;
     }
   }
   if (blk_lo >= blk_hi) return;
@@ -171,7 +204,7 @@ __device__ __forceinline__ void half_scan(const ScanParams& p, const int wg, Hal
   }
   // this wave's X, Y, Z among the tiles of a block
   constexpr int xi = TWIN ? WH : 0, yi = TWIN ? 2 + WH : 1, zi = TWIN ? 3 - WH : 2;
-  const LaneAddr<D> la(l);
+  const PiAddr<D> la(l);
 
   // The first NBUF - 1 blocks' tiles are on their way before anything else is fetched or computed: the start state (a
   // microsecond or two of latency of its own), the decay weights.  (Waits the compiler places for its own loads cover
@@ -240,7 +273,7 @@ __device__ __forceinline__ void half_scan(const ScanParams& p, const int wg, Hal
 #pragma unroll
         for (int t = 0; t < NT; t++)
 #pragma unroll
-          for (int v = 0; v < 16; v++) gs[state_index<D>(dvt, l32, hh, t, v, false)] = acc[t][v];
+          for (int v = 0; v < 16; v++) gs[state_index_pi<D>(dvt, l32, hh, t, v, false)] = acc[t][v];
       }
       return;
     }
@@ -295,13 +328,13 @@ __device__ __forceinline__ void half_scan(const ScanParams& p, const int wg, Hal
 #pragma unroll
         for (int t = 0; t < NT; t++)
 #pragma unroll
-          for (int v = 0; v < 16; v++) x[16 * t + v] = gs[state_index<D>(dvt, l32, hh, t, v, false)];
+          for (int v = 0; v < 16; v++) x[16 * t + v] = gs[state_index_pi<D>(dvt, l32, hh, t, v, false)];
       } else {
 #pragma unroll
         for (int t = 0; t < NT; t++)
 #pragma unroll
           for (int v = 0; v < 16; v += 4) {
-            const f32x4 r = *reinterpret_cast<const f32x4*>(gs + state_index<D>(dvt, l32, hh, t, v, true));
+            const f32x4 r = *reinterpret_cast<const f32x4*>(gs + state_index_pi<D>(dvt, l32, hh, t, v, true));
             x[16 * t + v] = r[0]; x[16 * t + v + 1] = r[1]; x[16 * t + v + 2] = r[2]; x[16 * t + v + 3] = r[3];
           }
       }
@@ -391,7 +424,7 @@ __device__ __forceinline__ void half_scan(const ScanParams& p, const int wg, Hal
     ex8<E> f;
 #pragma unroll
     for (int j = 0; j < 8; j++) f[j] = (E)kv[ks >> 1][8 * (ks & 1) + j];
-    return to_perm_order(f);
+    return f;
   };
   ex8<E> sa_first = state_operand(0);
   E* const stage = sW[TWIN ? WH : 0];
@@ -567,12 +600,12 @@ __device__ __forceinline__ void half_scan(const ScanParams& p, const int wg, Hal
     // d 64 192 -> 194 us, n 4096, d 128 501 -> 505; packed 40,000 positions, d 128 681 -> 675.)
     E* const st = NORM ? const_cast<E*>(tX) + dvt * (TILE / SW) : stage;
 #pragma unroll
-    for (int g = 0; g < 4; g++) {
-      ex4<E> pk;
+    for (int g = 0; g < 2; g++) {
+      ex8<E> pk;
 #pragma unroll
-      for (int e = 0; e < 4; e++) pk[e] = (E)inter[4 * g + e];
-      const int at = NORM ? l32 * LW + 8 * (g ^ ((l32 >> 2) & 3)) : l32 * D + 8 * ((4 * dvt + g) ^ swz<D>(l32));
-      *reinterpret_cast<ex4<E>*>(st + at + 4 * hh) = pk;
+      for (int e = 0; e < 8; e++) pk[e] = (E)inter[8 * g + e];
+      const int piece = 2 * g + hh;   // of the wave's 32 features
+      *reinterpret_cast<ex8<E>*>(st + (NORM ? l32 * LW + 8 * (piece ^ ((l32 >> 2) & 3)) : l32 * D + 8 * ((4 * dvt + piece) ^ swz<D>(l32)))) = pk;
     }
     if (!NORM) lds_barrier();   // second barrier (the tile is written again behind the next block's first one)
 #pragma unroll
@@ -602,7 +635,7 @@ __device__ __forceinline__ void half_scan(const ScanParams& p, const int wg, Hal
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) gf[state_index<D>(dvt, l32, hh, t, v, trf)] = kv[t][v];
+      for (int v = 0; v < 16; v++) gf[state_index_pi<D>(dvt, l32, hh, t, v, trf)] = kv[t][v];
   }
 #undef LA2_SLOT_END
   };
