@@ -714,6 +714,15 @@ bool joint_in_one_call(const la2_desc* d, const Plan& pl) {
          joint_plan(d, pl, nullptr, false).nchunks == 1;
 }
 
+// fp32 in chunks: both families of chunk states come from one launch where there is room for both.  The workspace holds one; the KV
+// states wait in dV, which only the last launch writes, behind the dQ scan that reads them: dense tensors (no memory between the rows
+// that is somebody else's) of at least that many floats.
+bool f32_states_in_output(const la2_desc* d, const Plan& pl, bool split, bool saved_states) {
+  return d->dtype == LA2_F32 && !wide(d->head_dim) && pl.nchunks > 1 && !split && !saved_states && d->stride_n == d->head_dim &&
+         d->stride_h == (int64_t)d->seqlen * d->head_dim && (d->batch == 1 || d->stride_b == d->heads * d->stride_h) &&
+         (int64_t)pl.nchunks * d->head_dim <= d->seqlen;
+}
+
 // The state entry points split a sequence whose length is not a multiple of state_granule() into whole
 // blocks (block kernels) and a tail (token recurrence) when the state beyond the tail is asked for.
 // Their workspace: chunk states of whichever of the two plans needs more, then (backward only) one
@@ -1210,6 +1219,17 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
     st = run_dual_reverse_scan(desc, pl, for_dv, for_dk, lambda, rev_workspace, s);
     return st == LA2_OK ? run_scan(desc, pl, false, for_dq, lambda, workspace, s) : st;
   }
+  bool local_ready = fuse;
+  if (f32_states_in_output(desc, pl, split, for_dq.saved_states != nullptr)) {
+    ScanArgs dq_states = for_dq;
+    const la2::ScanParams pq = scan_params(desc, pl, dq_states, lambda, dv);
+    const la2::ScanParams pr = dual_reverse_params(desc, pl, for_dv, for_dk, lambda, workspace);
+    if (la2::launch_chunk_state_pair_f32(desc->head_dim, pq, pr, s) != hipSuccess) return LA2_ERR_LAUNCH;
+    st = run_prepass(desc, pl, false, v, k, for_dq.init, for_dq.init_tr, lambda, dv, s, nullptr, true);
+    if (st != LA2_OK) return st;
+    for_dq.saved_states = static_cast<const float*>(dv);
+    local_ready = true;
+  }
   st = run_scan(desc, pl, false, for_dq, lambda, workspace, s);
   if (st != LA2_OK) return st;
   // Algorithm 2, second loop (descending, running dKV):
@@ -1228,7 +1248,7 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
     if (blocks.seqlen == 0) return LA2_OK;
     for_dv.init = for_dk.init = handoff;
   }
-  return run_dual_reverse_scan(&blocks, pl_rev, for_dv, for_dk, lambda, rev_workspace, s, /*local_ready=*/fuse);
+  return run_dual_reverse_scan(&blocks, pl_rev, for_dv, for_dk, lambda, rev_workspace, s, local_ready);
 }
 
 }  // namespace

@@ -226,6 +226,7 @@ hipError_t launch_left_product_bf16(int head_dim, bool reverse, const ScanParams
 // fp32 path
 hipError_t launch_scan_f32(int head_dim, bool reverse, const ScanParams& p, hipStream_t s);
 hipError_t launch_chunk_states_f32(int head_dim, bool reverse, const ScanParams& p, hipStream_t s);
+hipError_t launch_chunk_state_pair_f32(int head_dim, const ScanParams& fwd, const ScanParams& rev, hipStream_t s);   // both directions'
 // packed batch in chunks: fills map[0 .. p.wg_pairs) and long_list[0 .. p.nlong) from p.cu_seqlens (one small workgroup)
 hipError_t launch_varlen_map(const ScanParams& p, int4* map, int32_t* long_list, int64_t nslots, hipStream_t s);
 // turns the per-chunk local states in p.states into chunk start states (any dtype: states are fp32);

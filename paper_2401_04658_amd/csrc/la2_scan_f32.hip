@@ -645,14 +645,12 @@ __device__ __forceinline__ int walk(const ScanParams& p, Lds<D, STATE_ONLY>& lds
 // Scan kernel (STATE_ONLY = false) and chunk-state pre-pass (STATE_ONLY = true: the local state of the chunk is written to
 // p.states).  D / 32 waves.
 template <int D, bool REV, bool STATE_ONLY>
-__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) void scan_f32_kernel(ScanParams p) {
+__device__ __forceinline__ void scan_f32(const ScanParams& p, int wg, const int grid, Lds<D, STATE_ONLY>& lds) {
   constexpr int NT = D / 32;
-  __shared__ Lds<D, STATE_ONLY> lds;
   Place at;
   at.which = 0;
-  int wg = (int)blockIdx.x;
   if (!STATE_ONLY && p.nscan == 2) {   // two scans that read the same tiles: eight workgroups apart, on one XCD
-    if (((gridDim.x >> 1) & 7) == 0) {
+    if (((grid >> 1) & 7) == 0) {
       at.which = (wg >> 3) & 1;
       wg = ((wg >> 4) << 3) | (wg & 7);
     } else {
@@ -696,6 +694,25 @@ __global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) v
   }
 }
 
+template <int D, bool REV, bool STATE_ONLY>
+__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) void scan_f32_kernel(ScanParams p) {
+  __shared__ Lds<D, STATE_ONLY> lds;
+  // (from a lambda: called directly the compiler loads all arguments in front and spills scalar registers)
+  [&]() __attribute__((always_inline)) { scan_f32<D, REV, STATE_ONLY>(p, (int)blockIdx.x, (int)gridDim.x, lds); }();
+}
+
+// Both families of a backward pass's chunk states in one launch: the first half of the workgroups the forward ones, the second half
+// the reverse ones.  Each alone has at most one workgroup of four waves per compute unit at head_dim 128, bound by its issue, which a
+// second one fills.  Forward + backward with one launch against two, the states the same bits: d 128, 48 chains of 1500 287 -> 274 us,
+// 64 of 1024, 2048 246 -> 234, 431 -> 415, 128 of 1024 418 -> 388; d 64, 4 chains of 1000 78 -> 71, 64 of 2048 211 -> 206, 96 even.
+template <int D>
+__global__ __launch_bounds__(2 * D) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_state_pair_f32_kernel(ScanParams fwd, ScanParams rev) {
+  __shared__ Lds<D, true> lds;
+  const int units = (int)gridDim.x / 2, wg = (int)blockIdx.x;
+  if (wg < units) scan_f32<D, false, true>(fwd, wg, units, lds);
+  else            scan_f32<D, true, true>(rev, wg - units, units, lds);
+}
+
 template <bool STATE_ONLY>
 hipError_t launch(int head_dim, bool reverse, const ScanParams& p, hipStream_t s) {
   const int64_t grid = (int64_t)p.batch * p.heads * p.nchunks * (STATE_ONLY ? 1 : p.nscan);
@@ -717,6 +734,16 @@ int block_size_f32(int) { return kBF; }
 
 hipError_t launch_scan_f32(int head_dim, bool reverse, const ScanParams& p, hipStream_t s) {
   return launch<false>(head_dim, reverse, p, s);
+}
+
+hipError_t launch_chunk_state_pair_f32(int head_dim, const ScanParams& fwd, const ScanParams& rev, hipStream_t s) {
+  const int64_t grid = 2 * (int64_t)fwd.batch * fwd.heads * fwd.nchunks;
+  if (grid == 0 || fwd.n == 0) return hipSuccess;
+  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;   // (the host has checked that two scans' workgroups fit a grid)
+  const dim3 g((unsigned)grid), b(2 * head_dim);
+  if (head_dim == 128) hipLaunchKernelGGL((chunk_state_pair_f32_kernel<128>), g, b, 0, s, fwd, rev);
+  else                 hipLaunchKernelGGL((chunk_state_pair_f32_kernel<64>), g, b, 0, s, fwd, rev);
+  return hipGetLastError();
 }
 
 hipError_t launch_chunk_states_f32(int head_dim, bool reverse, const ScanParams& p, hipStream_t s) {

@@ -64,3 +64,27 @@ def test_all_scans_in_one_launch(dtype, d, b, h, n):
                 assert_close(label, x[:1], ref, dtype)
                 # no further from the truth than the launches apart (the same sums, or those of other chunks: up to their order)
                 assert rms_rel(to64(x[:1]), ref) <= 1.05 * rms_rel(to64(other[:1]), ref) + 1e-7, label
+
+
+@pytest.mark.parametrize("d,h,n", [(64, 4, 1000), (64, 16, 2050), (128, 16, 1500), (128, 8, 3001)])
+def test_fp32_chunk_states_in_one_launch(d, h, n):
+    """fp32 in chunks: on dense tensors the KV states wait in dV's place; with rows further apart nothing between them is touched."""
+    t = workloads.Workload("pair", 2, h, n, d, torch.float32, seed=8600 + n + d, backward=True).tensors()
+    assert binding.la2_chunk_plan(t["q"])[0] > 1
+    g = {x: y.to(DEV) for x, y in t.items()}
+    dense = binding.la2_bwd(g["q"], g["k"], g["v"], g["d_o"], g["lam"])
+
+    def apart(x):   # rows 16 floats further apart, 7.0 between them
+        store = torch.full(x.shape[:3] + (d + 16,), 7.0, device=DEV)
+        store[..., :d] = x
+        return store[..., :d], store
+
+    q, k, v, do = (apart(g[x])[0] for x in ("q", "k", "v", "d_o"))
+    outs, stores = zip(*(apart(torch.zeros_like(g["q"])) for _ in range(3)))
+    binding.la2_bwd(q, k, v, do, g["lam"], out=outs)
+    torch.cuda.synchronize()
+    refs = oracle.bwd_recurrent_state(*(to64(t[x][:1]) for x in ("q", "k", "v", "d_o")), to64(t["lam"]))
+    for name, x, y, store, ref in zip(("dq", "dk", "dv"), dense, outs, stores, refs):
+        assert torch.equal(x, y), name
+        assert bool((store[..., d:] == 7.0).all()), name
+        assert_close("%s d%d h%d n%d" % (name, d, h, n), x[:1], ref, torch.float32)
