@@ -107,6 +107,9 @@ size_t la2_workspace_bytes(const la2_desc* desc, int32_t op);
  * chains there are and the more states a call carries) run as one launch that forms every output row from all the
  * positions it depends on, without chunks and in time quadratic in seqlen, where that was measured to be faster.
  * What a call asks for stays the same: the workspace of the plan is required as always and left as it is.
+ * A backward pass of 16-bit data at head_dim 64, 96 or 128 whose three scans run in one launch may leave sequences whole that the
+ * forward pass cuts (from 3/8 of a chain per compute unit on, on fewer chains up to about 1000 positions); the workspace is then
+ * required and left as it is as well, and a forward call's is not read.
  * And a batch with a few more chains than a whole number (one to four) per compute unit,
  * which as one launch gives some units a workgroup more than the others and takes up to twice as long as whole
  * rounds.  Every entry point that takes a dense
@@ -114,7 +117,8 @@ size_t la2_workspace_bytes(const la2_desc* desc, int32_t op);
  * stream: the first floor(rounds * units / heads) batch rows by the plan of that many rows (one chunk), the
  * remaining rows, with their rows of the states and of rstd, by the plan of a descriptor with that many rows
  * (several chunks); la2_workspace_bytes() answers for both, and what either part would refuse is refused before the
- * first launch.  A forward call's workspace then holds the chunk states of its second part, which is what
+ * first launch.  (A backward pass that is faster as one launch of all its scans is checked the same and runs as one call.)  A
+ * forward call's workspace then holds the chunk states of its second part, which is what
  * la2_bwd_saved reads.  Which shapes: seqlen >= 2048 (fp32: 1024), no la2_set_chunk_tokens(), and a partial round
  * of at most 1/8 to 3/8 of the unit count, by dtype and head_dim, as measured.  Results are those of the same block
  * loop either way, up to the rounding of the chunk states.
