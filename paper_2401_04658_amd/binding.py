@@ -220,6 +220,7 @@ def la2_fwd(q, k, v, lam, out=None, workspace=None):
     """o = LA2(q, k, v; lam) on the GPU.  q, k, v: [b, H, n, d] bf16/fp32; lam: fp32 [H] (device)."""
     lib = _module()
     _on_gpu(q, "la2_fwd")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -235,6 +236,7 @@ def la2_fwd_noalloc(q, k, v, lam, out):
     nothing (so `out` is required)."""
     lib = _module()
     _on_gpu(q, "la2_fwd_noalloc")
+    lib.given(lam)
     lib.same_layout(q, k, v, out)
     _run(lib.la2_fwd_noalloc, q, q, q, k, v, lam, out)
     return out
@@ -244,6 +246,7 @@ def la2_bwd(q, k, v, d_o, lam, out=None, workspace=None):
     """(dq, dk, dv) of sum(o * d_o) on the GPU."""
     lib = _module()
     _on_gpu(q, "la2_bwd")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     ws = lib.workspace(q, LA2_OP_BWD) if workspace is None else workspace
@@ -264,6 +267,7 @@ def la2_fwd_norm(q, k, v, lam, eps=1e-6, out=None, rstd=None, workspace=None):
     """(o, rstd) = Norm(LA2(q, k, v; lam)): every output row scaled by rstd = 1 / sqrt(mean(row^2) + eps)."""
     lib = _module()
     _on_gpu(q, "la2_fwd_norm")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -286,6 +290,7 @@ def la2_bwd_norm(q, k, v, o, rstd, d_o, lam, out=None, d_u=None, workspace=None)
     layout as d_o) receives the gradient with respect to the un-normalised output."""
     lib = _module()
     _on_gpu(q, "la2_bwd_norm")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v, o, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     if d_u is None:
@@ -324,6 +329,7 @@ def la2_fwd_varlen(q, k, v, lam, cu_seqlens, max_seqlen, out=None, workspace=Non
     positions cu_seqlens[b] .. cu_seqlens[b + 1] - 1; max_seqlen bounds the lengths."""
     lib = _module()
     _on_gpu(q, "la2_fwd_varlen")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -339,6 +345,7 @@ def la2_bwd_varlen(q, k, v, d_o, lam, cu_seqlens, max_seqlen, out=None, workspac
     """(dq, dk, dv) for packed sequences of different lengths (see la2_fwd_varlen)."""
     lib = _module()
     _on_gpu(q, "la2_bwd_varlen")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
@@ -353,6 +360,7 @@ def la2_fwd_varlen_state(q, k, v, lam, cu_seqlens, max_seqlen, kv_init=None, wan
     kv_init (fp32 [sequences, H, d, d], None = zero).  Returns (o, kv_final or None)."""
     lib = _module()
     _on_gpu(q, "la2_fwd_varlen_state")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -375,6 +383,7 @@ def la2_bwd_varlen_state(q, k, v, d_o, lam, cu_seqlens, max_seqlen, kv_init=None
     """Backward of la2_fwd_varlen_state.  Returns (dq, dk, dv, d_kv_init or None)."""
     lib = _module()
     _on_gpu(q, "la2_bwd_varlen_state")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     desc = _varlen_desc(q, cu_seqlens, max_seqlen)
@@ -393,6 +402,7 @@ def la2_fwd_varlen_norm(q, k, v, lam, cu_seqlens, max_seqlen, eps=1e-6, out=None
     """(o, rstd) of the normalised operator over packed sequences; rstd is fp32 [heads, total_positions]."""
     lib = _module()
     _on_gpu(q, "la2_fwd_varlen_norm")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -409,6 +419,7 @@ def la2_bwd_varlen_norm(q, k, v, o, rstd, d_o, lam, cu_seqlens, max_seqlen, out=
     """(dq, dk, dv) of the normalised operator over packed sequences (o, rstd from la2_fwd_varlen_norm)."""
     lib = _module()
     _on_gpu(q, "la2_bwd_varlen_norm")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v, o, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     if d_u is None:
@@ -427,6 +438,7 @@ def la2_fwd_state(q, k, v, lam, kv_init=None, want_final=True, out=None, kv_fina
     (fp32 [b, H, d, d], None = zero).  Returns (o, kv_final or None)."""
     lib = _module()
     _on_gpu(q, "la2_fwd_state")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -449,6 +461,7 @@ def la2_bwd_state(q, k, v, d_o, lam, kv_init=None, d_kv_final=None, want_d_kv_in
     whether that call handed out kv_final."""
     lib = _module()
     _on_gpu(q, "la2_bwd_state")
+    lib.given(lam, workspace, fwd_workspace)
     lib.same_layout(q, k, v, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     b, h, _, d = q.shape
@@ -467,6 +480,7 @@ def la2_fwd_state_norm(q, k, v, lam, eps=1e-6, kv_init=None, want_final=True, ou
     """la2_fwd_norm on one segment of a sequence, started from kv_init.  Returns (o, rstd, kv_final or None)."""
     lib = _module()
     _on_gpu(q, "la2_fwd_state_norm")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -489,6 +503,7 @@ def la2_bwd_state_norm(q, k, v, o, rstd, d_o, lam, kv_init=None, d_kv_final=None
     """Backward of la2_fwd_state_norm.  Returns (dq, dk, dv, d_kv_init or None)."""
     lib = _module()
     _on_gpu(q, "la2_bwd_state_norm")
+    lib.given(lam, workspace)
     lib.same_layout(q, k, v, o, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     if d_u is None:
@@ -511,7 +526,7 @@ def la2_decode_step(q, k, v, lam, kv_state, out=None):
     """One recurrent step; kv_state (fp32 [b, H, d, d]) is updated in place, returns o [b, H, d]."""
     lib = _module()
     _on_gpu(q, "la2_decode_step")
-    b, h, d, dtype = lib.decode_shape("la2_decode_step", 3, q, k, v, kv_state)
+    b, h, d, dtype = lib.decode_shape("la2_decode_step", 3, q, k, v, kv_state, lam, out)
     if out is None:
         out = lib.like(q)
     _run(lib.la2_decode_step, q, b, h, d, dtype, q, k, v, lam, kv_state, out)
@@ -523,7 +538,7 @@ def la2_decode_multi(q, k, v, lam, kv_state, out=None):
     [b, H, d, d]) is updated in place; returns o [b, H, T, d]."""
     lib = _module()
     _on_gpu(q, "la2_decode_multi")
-    b, h, t, d, dtype = lib.decode_shape("la2_decode_multi", 4, q, k, v, kv_state)
+    b, h, t, d, dtype = lib.decode_shape("la2_decode_multi", 4, q, k, v, kv_state, lam, out)
     if out is None:
         out = lib.like(q)
     _run(lib.la2_decode_multi, q, b, h, d, t, dtype, q, k, v, lam, kv_state, out)
@@ -535,7 +550,7 @@ def la2_decode_step_norm(q, k, v, lam, kv_state, eps=1e-6, out=None):
     the normalised o [b, H, d]."""
     lib = _module()
     _on_gpu(q, "la2_decode_step_norm")
-    b, h, d, dtype = lib.decode_shape("la2_decode_step_norm", 3, q, k, v, kv_state)
+    b, h, d, dtype = lib.decode_shape("la2_decode_step_norm", 3, q, k, v, kv_state, lam, out)
     if out is None:
         out = lib.like(q)
     _run(lib.la2_decode_step_norm, q, b, h, d, dtype, q, k, v, lam, kv_state, eps, out)
@@ -546,7 +561,7 @@ def la2_decode_multi_norm(q, k, v, lam, kv_state, eps=1e-6, out=None, rstd=None)
     """ntokens consecutive steps of the normalised operator in one launch; returns (o, rstd [b, H, T])."""
     lib = _module()
     _on_gpu(q, "la2_decode_multi_norm")
-    b, h, t, d, dtype = lib.decode_shape("la2_decode_multi_norm", 4, q, k, v, kv_state)
+    b, h, t, d, dtype = lib.decode_shape("la2_decode_multi_norm", 4, q, k, v, kv_state, lam, out, rstd)
     if out is None:
         out = lib.like(q)
     if rstd is None:
@@ -559,6 +574,7 @@ def la2_left_product_fwd(q, k, v, lam, out=None):
     """The forward pass as the O(n^2 d) masked left product (comparison kernel, bf16)."""
     lib = _module()
     _on_gpu(q, "la2_left_product_fwd")
+    lib.given(lam)
     lib.same_layout(q, k, v)
     if out is None:
         out = lib.like(q)
@@ -572,6 +588,7 @@ def la2_left_product_bwd(q, k, v, d_o, lam, out=None):
     """(dq, dk, dv) as O(n^2 d) masked products (comparison kernel, bf16)."""
     lib = _module()
     _on_gpu(q, "la2_left_product_bwd")
+    lib.given(lam)
     lib.same_layout(q, k, v, d_o)
     dq, dk, dv = _outputs(lib, q, out)
     _run(lib.la2_left_product_bwd, q, q, q, k, v, d_o, lam, dq, dk, dv)

@@ -191,6 +191,22 @@ PyObject* same_layout(PyObject*, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
+// The Python functions hand these arguments on as they are, and an entry point also takes a number for a pointer: the caller's own
+// number is refused here, before it can become an address on the device.
+void tensor_or_none(PyObject* o) {
+  if (o != Py_None) tensor(o);
+}
+
+// given(lam, ...): TypeError unless lam is a tensor and every other one a tensor or None
+PyObject* given(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  return guarded([&]() -> PyObject* {
+    if (n < 1) raise(PyExc_TypeError, "la2: no decay");
+    tensor(args[0]);
+    for (Py_ssize_t i = 1; i < n; i++) tensor_or_none(args[i]);
+    Py_RETURN_NONE;
+  });
+}
+
 // like(t): an uninitialised tensor of t's shape, strides, dtype and device
 PyObject* like(PyObject*, PyObject* arg) {
   return guarded([&] {
@@ -241,11 +257,13 @@ PyObject* state(PyObject*, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
-// decode_shape(name, dims, q, k, v, kv): checks a decoding call's tensors (dims 3: [b, H, d], 4: [b, H, T, d]); q's extents and
-// the dtype's code
+// decode_shape(name, dims, q, k, v, kv[, lam, ...]): checks a decoding call's tensors (dims 3: [b, H, d], 4: [b, H, T, d]; lam and what
+// follows as given() does); q's extents and the dtype's code
 PyObject* decode_shape(PyObject*, PyObject* const* args, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
-    if (n != 6) raise(PyExc_TypeError, "la2: name, dims, q, k, v, kv");
+    if (n < 6) raise(PyExc_TypeError, "la2: name, dims, q, k, v, kv");
+    if (n > 6) tensor(args[6]);
+    for (Py_ssize_t i = 7; i < n; i++) tensor_or_none(args[i]);
     const int64_t dims = Integer<int64_t>(args[1]).get();
     const at::Tensor& q = tensor(args[2]);
     if (q.dim() != dims) {
@@ -280,7 +298,7 @@ PyMethodDef methods[] = {
     ENTRY(la2_fwd_varlen_state), ENTRY(la2_bwd_varlen_state), ENTRY(la2_fwd_varlen_norm), ENTRY(la2_bwd_varlen_norm),
     ENTRY(la2_decode_step), ENTRY(la2_decode_step_norm), ENTRY(la2_decode_multi), ENTRY(la2_decode_multi_norm),
     ENTRY(la2_left_product_fwd), ENTRY(la2_left_product_bwd),
-    FAST("same_layout", same_layout), FAST("f32", f32), FAST("workspace", workspace), FAST("state", state),
+    FAST("same_layout", same_layout), FAST("given", given), FAST("f32", f32), FAST("workspace", workspace), FAST("state", state),
     FAST("decode_shape", decode_shape),
     {"like", like, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};

@@ -110,3 +110,65 @@ def test_calls_from_several_threads():
     [t.start() for t in threads]
     [t.join() for t in threads]
     assert not bad
+
+
+PUBLIC = {   # name: (sequence tensors in front of lam or kv_state, arguments that the caller may give as a tensor or leave out)
+    "la2_fwd": ("q k v lam", ("workspace",)), "la2_fwd_noalloc": ("q k v lam out", ()), "la2_bwd": ("q k v o lam", ("workspace",)),
+    "la2_fwd_norm": ("q k v lam", ("workspace",)), "la2_bwd_norm": ("q k v o rstd o lam", ("workspace",)),
+    "la2_fwd_state": ("q k v lam", ("workspace",)), "la2_bwd_state": ("q k v o lam", ("workspace", "fwd_workspace")),
+    "la2_fwd_state_norm": ("q k v lam", ("workspace",)), "la2_bwd_state_norm": ("q k v o rstd o lam", ("workspace",)),
+    "la2_decode_step": ("dq dq dq lam kv", ("out",)), "la2_decode_step_norm": ("dq dq dq lam kv", ("out",)),
+    "la2_decode_multi": ("q q q lam kv", ("out",)), "la2_decode_multi_norm": ("q q q lam kv", ("out", "rstd")),
+    "la2_left_product_fwd": ("q k v lam", ()), "la2_left_product_bwd": ("q k v o lam", ()),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PUBLIC))
+def test_a_number_never_becomes_an_address(name, monkeypatch):
+    """Every pointer that a caller of the Python functions hands over has to be a tensor: a number (or a truth value) is refused before
+    the call."""
+    reached = []
+    monkeypatch.setattr(binding, "_on_gpu", lambda t, what: None)
+    monkeypatch.setattr(binding, "_run", lambda entry, t, *args: reached.append(args))
+    have = {x: q4(2, 3) for x in ("q", "k", "v", "o", "out")}
+    have.update(lam=torch.ones(3), rstd=torch.ones(2, 3, 5), dq=torch.zeros(2, 3, 64), kv=torch.zeros(2, 3, 64, 64))
+    front, optional = PUBLIC[name]
+    args = [have[x] for x in front.split()]
+    fn = getattr(binding, name)
+    fn(*args)
+    assert len(reached) == 1
+    for x in optional:   # a tensor is taken
+        fn(*args, **{x: torch.empty(64, dtype=torch.uint8)})
+    assert len(reached) == 1 + len(optional)
+    del reached[:]
+    at = front.split().index("lam")
+    for bad in (4096, True, 1.0, "x"):
+        with pytest.raises(TypeError):
+            fn(*args[:at], bad, *args[at + 1:])
+        for x in optional:
+            with pytest.raises(TypeError):
+                fn(*args, **{x: bad})
+    with pytest.raises(TypeError):
+        fn(*args[:at], None, *args[at + 1:])
+    assert not reached
+
+
+def test_a_packed_call_takes_no_number_either(monkeypatch):
+    reached = []
+    monkeypatch.setattr(binding, "_on_gpu", lambda t, what: None)
+    monkeypatch.setattr(binding, "_run", lambda entry, t, *args: reached.append(args))
+    monkeypatch.setattr(binding, "_varlen_desc", lambda q, cu, longest: binding.la2_desc(2, 3, 30, 64, binding.LA2_BF16, 0, 0, 64, 192))
+    x, cu, rstd = torch.zeros(50, 3, 64, dtype=torch.bfloat16), torch.tensor([0, 20, 50], dtype=torch.int32), torch.ones(3, 50)
+    for name, front in (("la2_fwd_varlen", (x,) * 3), ("la2_bwd_varlen", (x,) * 4), ("la2_fwd_varlen_state", (x,) * 3),
+                        ("la2_bwd_varlen_state", (x,) * 4), ("la2_fwd_varlen_norm", (x,) * 3),
+                        ("la2_bwd_varlen_norm", (x, x, x, x, rstd, x))):
+        fn = getattr(binding, name)
+        fn(*front, torch.ones(3), cu, 30)
+        assert len(reached) == 1, name
+        del reached[:]
+        for bad in (4096, True, None):
+            with pytest.raises(TypeError):
+                fn(*front, bad, cu, 30)
+        with pytest.raises(TypeError):
+            fn(*front, torch.ones(3), cu, 30, workspace=4096)
+        assert not reached, name
