@@ -133,8 +133,11 @@ struct Arg<size_t> {
 template <>
 struct Arg<float> {
   float value;
-  explicit Arg(PyObject* o) : value((float)PyFloat_AsDouble(o)) {
-    if (PyErr_Occurred()) throw Raised{};
+  explicit Arg(PyObject* o) {   // what float(o) takes
+    PyObject* const f = PyNumber_Float(o);
+    if (f == nullptr) throw Raised{};
+    value = (float)PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
   }
   float get() const { return value; }
 };

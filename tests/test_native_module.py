@@ -172,3 +172,13 @@ def test_a_packed_call_takes_no_number_either(monkeypatch):
         with pytest.raises(TypeError):
             fn(*front, torch.ones(3), cu, 30, workspace=4096)
         assert not reached, name
+
+
+def test_eps_is_what_float_takes():
+    q = q4(n=64)
+    for eps in (1e-6, 0, "1e-6", torch.tensor(1e-6)):
+        assert lib.la2_fwd_norm(q, None, q, q, q, eps, q, q, None, 0, 0) == 1   # LA2_ERR_NULL: eps was taken
+    assert lib.la2_fwd_norm(q, q, q, q, q, -1, q, q, None, 0, 0) == 7            # LA2_ERR_VALUE
+    for eps, error in ((None, TypeError), ("x", ValueError), ([], TypeError)):
+        with pytest.raises(error):
+            lib.la2_fwd_norm(q, None, q, q, q, eps, q, q, None, 0, 0)
