@@ -673,7 +673,7 @@ la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs&
 // cut, n 1024, 2048, 4096, 8192, 48 chains 0.86, 1.00, 1.11, 1.33, 64 0.86, 0.97, 1.08, 1.12, 80 0.81, 0.84, 0.92, 0.96, 112 0.75,
 // 0.75, 0.84, 0.82, saved 96 0.84, 0.84, 0.99, 0.95 (64: 0.99, 1.09, 1.21, 1.23).  In pl's chunks it would take a second set of states,
 // which the workspace has no room for; from saved states it does on up to half as many workgroups as units (0.83-0.87; more 0.96-1.14).
-Plan joint_plan(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved_states) {
+Plan joint_rule(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved_states) {
   const Plan none{0, 0, 0};
   if (!is16(d->dtype) || d->head_dim == 256 || g_scan_variant.load(std::memory_order_relaxed) != 0 ||
       g_chunk_tokens_override.load(std::memory_order_relaxed) > 0)   // (the caller asks for a kernel, or plans)
@@ -704,6 +704,14 @@ Plan joint_plan(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved
   return bytes <= (saved_states ? 16 : 32) * MiB ? pl : none;
 }
 
+// ... unless the launch would be too large: it has twice the workgroups of the widest one otherwise, of 4 d threads each, and a grid
+// has at most 2^32 - 1 work-items (head_dim 96: 5.6 million chains; memory holds more of a few positions, or packed ones of none).
+Plan joint_plan(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved_states) {
+  const Plan j = joint_rule(d, pl, cu, saved_states);
+  const int64_t units = j.wg_pairs > 0 ? (int64_t)j.wg_pairs * d->heads : (int64_t)d->batch * d->heads * j.nchunks;
+  return 2 * units * 4 * d->head_dim <= 0xFFFFFFFFll ? j : Plan{0, 0, 0};
+}
+
 // A batch a little above a whole number of chains per unit (rows_of_first_call) whose backward pass is better off as one launch of
 // all three scans than as two calls; forward + backward, one against two, n 2048, 3000, 4096: d 64, 272 chains 0.94, 1.03, 1.10
 // (above 96 MiB a tensor the launch does not pay), 304 0.95, 0.97, 1.02, 336 0.98, 0.97, 1.00; d 96, 272 0.87, 0.91, 0.97, 304 0.79, 0.84,
@@ -720,7 +728,8 @@ bool joint_in_one_call(const la2_desc* d, const Plan& pl) {
 bool f32_states_in_output(const la2_desc* d, const Plan& pl, bool split, bool saved_states) {
   return d->dtype == LA2_F32 && !wide(d->head_dim) && pl.nchunks > 1 && !split && !saved_states && d->stride_n == d->head_dim &&
          d->stride_h == (int64_t)d->seqlen * d->head_dim && (d->batch == 1 || d->stride_b == d->heads * d->stride_h) &&
-         (int64_t)pl.nchunks * d->head_dim <= d->seqlen;
+         (int64_t)pl.nchunks * d->head_dim <= d->seqlen &&
+         2 * (int64_t)d->batch * d->heads * pl.nchunks * 2 * d->head_dim <= 0xFFFFFFFFll;   // work-items of that launch
 }
 
 // The state entry points split a sequence whose length is not a multiple of state_granule() into whole

@@ -362,7 +362,7 @@ hipError_t launch_chunk_state_pair_bf16(int dtype, int head_dim, const ScanParam
   const int64_t grid = 2 * (fwd.wg_map != nullptr ? (int64_t)fwd.wg_pairs * fwd.heads : (int64_t)fwd.batch * fwd.heads * fwd.nchunks);
   if (head_dim != 64) return hipErrorInvalidValue;
   if (grid == 0 || fwd.n == 0) return hipSuccess;
-  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;   // (the rule that leads here keeps it far below)
+  if (grid * 256 > 0xFFFFFFFFll) return hipErrorInvalidValue;   // work-items (joint_plan in la2_api.hip sends no such call here)
   const dim3 g((unsigned)grid), b(256);
   if (dtype == kF16) hipLaunchKernelGGL((chunk_state_pair_bf16_kernel<_Float16, 64, 4>), g, b, 0, s, fwd, rev);
   else               hipLaunchKernelGGL((chunk_state_pair_bf16_kernel<__bf16, 64, 4>), g, b, 0, s, fwd, rev);

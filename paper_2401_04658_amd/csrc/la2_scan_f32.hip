@@ -739,7 +739,7 @@ hipError_t launch_scan_f32(int head_dim, bool reverse, const ScanParams& p, hipS
 hipError_t launch_chunk_state_pair_f32(int head_dim, const ScanParams& fwd, const ScanParams& rev, hipStream_t s) {
   const int64_t grid = 2 * (int64_t)fwd.batch * fwd.heads * fwd.nchunks;
   if (grid == 0 || fwd.n == 0) return hipSuccess;
-  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;   // (the host has checked that two scans' workgroups fit a grid)
+  if (grid * 2 * head_dim > 0xFFFFFFFFll) return hipErrorInvalidValue;   // work-items (la2_api.hip sends no such call here)
   const dim3 g((unsigned)grid), b(2 * head_dim);
   if (head_dim == 128) hipLaunchKernelGGL((chunk_state_pair_f32_kernel<128>), g, b, 0, s, fwd, rev);
   else                 hipLaunchKernelGGL((chunk_state_pair_f32_kernel<64>), g, b, 0, s, fwd, rev);

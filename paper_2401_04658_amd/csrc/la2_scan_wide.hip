@@ -808,7 +808,7 @@ hipError_t launch_bwd_scans_wide(int dtype, int head_dim, const ScanParams& dq, 
     return hipErrorInvalidValue;
   const int64_t grid = 2 * (int64_t)dq.batch * dq.heads * dq.nchunks;
   if (grid == 0 || dq.n == 0) return hipSuccess;
-  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;   // (the rule that leads here keeps it far below)
+  if (grid * 4 * head_dim > 0xFFFFFFFFll) return hipErrorInvalidValue;   // work-items (joint_plan in la2_api.hip sends no such call here)
   return dtype == kF16 ? launch_bwd_of<_Float16>(dq, rev, s) : launch_bwd_of<__bf16>(dq, rev, s);
 }
 

@@ -1,0 +1,31 @@
+"""Which kernels the calls take (CPU: launchers that only write down what they are asked for)."""
+import pytest
+
+import routes
+from paper_2401_04658_amd import binding
+
+DTYPES = [binding.LA2_BF16, binding.LA2_F16]
+
+
+def work_items(x):
+    """Work-items of the launch of all three scans: two workgroups of 4 d threads per chain (or pair) and chunk."""
+    units = x["pairs"] * x["heads"] if x["pairs"] else x["batch"] * x["heads"] * x["nchunks"]
+    return 2 * units * 4 * x["d"]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("d", [64, 96, 128])
+def test_one_launch_stays_below_the_largest_grid(d, dtype):
+    """A grid has at most 2^32 - 1 work-items; the launch of all three scans has twice the workgroups of the widest launch otherwise.
+    Batches up to the largest that is accepted (2^24 chains), dense and packed, the packed ones almost all of empty sequences."""
+    taken = 0
+    for chains in (384, 1 << 12, 1 << 20, 5 << 20, 5600000, (1 << 23) - 16, 1 << 23, 11000000, 1 << 24):
+        for n in (1, 8, 64, 200):
+            x = routes.one_launch(routes.backward(routes.desc(chains // 16, 16, n, d, dtype)))
+            taken += x is not None
+            assert x is None or work_items(x) < 1 << 32, (chains, n)
+            for total in (0, 1000, chains // 16 * n):
+                x = routes.one_launch(routes.backward(routes.desc(chains // 16, 16, n, d, dtype, packed=True), total=total))
+                taken += x is not None
+                assert x is None or work_items(x) < 1 << 32, (chains, n, total)
+    assert taken > 0 or d == 128
