@@ -73,30 +73,24 @@ struct PlainAddr {
 // reverse launch fills the units as it is).  What bounds it: vector instructions that every wave has whatever its
 // share (weights, addresses, waits): 3,900 cycles per block, half of them vector issue.
 // CACHE, bits: 1 the tile loads without the non-temporal hint (ScanParams::keep), 2 the outputs through the caches (plain).
-// The body takes its workgroup's number among `grid` and the LDS from the kernel: the tile buffers, and at head_dim 96 the decay mask.
-template <typename E, int NBUF, int NTL, int TILE>
-struct WideTiles {
-  __attribute__((aligned(1024))) E tiles[NBUF][NTL][TILE];
-};
-template <bool MASK>
-struct WideMask {   // [element group][lane]
-  f32x4 mask[4][64];
-  __device__ __forceinline__ f32x4 (*decay_mask())[64] { return mask; }
-};
-template <>
-struct WideMask<false> {
-  __device__ __forceinline__ f32x4 (*decay_mask())[64] { return nullptr; }
-};
-// tiles of a block: [X,] Y, Z; twin: X0, X1, Y0 = Z1, Z0 = Y1; split: X, Y (Z: the workgroup's half only, sZ), and three buffers: a
+// The body takes its workgroup's number among `grid` from the kernel, and, where two bodies share a kernel, the tile buffers and the
+// decay mask of head_dim 96 ([element group][lane]); else (JOINT false) they are its own.  (Given to all of them as one object, the Norm
+// kernels of head_dim 96 spilled up to twice as much: 8 chains of 4332, forward + backward 88.5 -> 90.5 us, 64 of 3189 220 -> 226.)
+// Tiles of a block: [X,] Y, Z; twin: X0, X1, Y0 = Z1, Z0 = Y1; split: X, Y (Z: the workgroup's half only, sZ), and three buffers: a
 // wave has half the work per block to hide a load behind
-template <typename E, int D, bool STATE_ONLY, bool TWIN, bool SPLIT>
-struct WideLds : WideTiles<E, SPLIT ? 3 : 2, TWIN ? 4 : STATE_ONLY || SPLIT ? 2 : 3, 32 * D>, WideMask<!STATE_ONLY && D != 256> {
-  static constexpr int NBUF = SPLIT ? 3 : 2, NTL = TWIN ? 4 : STATE_ONLY || SPLIT ? 2 : 3;
+template <int D, bool STATE_ONLY, bool TWIN, bool SPLIT>
+struct WideShape {
+  static constexpr int NBUF = SPLIT ? 3 : 2, NTL = TWIN ? 4 : STATE_ONLY || SPLIT ? 2 : 3, MASK = (STATE_ONLY || D == 256) ? 1 : 4;
 };
+template <typename E, int D, bool STATE_ONLY, bool TWIN, bool SPLIT>
+using WideTiles = E[WideShape<D, STATE_ONLY, TWIN, SPLIT>::NBUF][WideShape<D, STATE_ONLY, TWIN, SPLIT>::NTL][32 * D];
+template <int N>
+using WideMask = f32x4[N][64];
 
-template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT, int CACHE>
-__device__ __forceinline__ void scan_wide_body(const ScanParams& p, const int number, const int grid,
-                                               WideLds<E, D, STATE_ONLY, TWIN, SPLIT>& lds) {
+template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, bool SPLIT, int CACHE, bool JOINT = false>
+__device__ __forceinline__ void scan_wide_body(const ScanParams& p, const int number, const unsigned grid,
+                                               WideTiles<E, D, STATE_ONLY, TWIN, SPLIT>* tiles = nullptr,
+                                               WideMask<WideShape<D, STATE_ONLY, TWIN, SPLIT>::MASK>* mask = nullptr) {
   constexpr bool KEEP = (CACHE & 1) != 0;
   constexpr int kStorePolicy = (CACHE & 2) != 0 ? 0 : 18;   // buffer instruction bits: 2 = nt, 16 = sc1
   static_assert(!SPLIT || (D == 256 && !STATE_ONLY && !NORM), "half the value features per workgroup: plain scans of head_dim 256");
@@ -107,8 +101,8 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p, const int nu
   constexpr int NT = C::NT, TILE = C::TILE;
   constexpr int KT = SPLIT ? NT / 2 : NT;           // key-feature tiles of a wave's state slice
   constexpr int KS = SPLIT ? C::KS / 2 : C::KS;     // k-steps of a wave's inter-block product
-  using Lds = WideLds<E, D, STATE_ONLY, TWIN, SPLIT>;
-  constexpr int NTL = Lds::NTL, NBUF = Lds::NBUF;
+  using Shape = WideShape<D, STATE_ONLY, TWIN, SPLIT>;
+  constexpr int NTL = Shape::NTL, NBUF = Shape::NBUF;
   constexpr bool SHP = D == 256 && !STATE_ONLY;   // shared score tile (see sP below)
   // The tile loads of a block: every wave its share.  With the shared score tile, waves 4 .. 7 load (one
   // instruction per slot of the inter-block product, so that eight waves do not queue 48 of them at the tile
@@ -116,7 +110,10 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p, const int nu
   constexpr int NLW = SHP ? 4 : (TWIN ? 2 : 1) * NT;
   using Loader = TileLoader<D, NTL, B, NLW>;
   constexpr int NDMA = NTL * Loader::DMA_PER_WAVE + (SPLIT ? 2 : 0);
-  auto& sT = lds.tiles;
+  using Tiles = WideTiles<E, D, STATE_ONLY, TWIN, SPLIT>;
+  using Mask = WideMask<Shape::MASK>;
+  __shared__ __attribute__((aligned(1024))) Tiles sOwnT;
+  Tiles& sT = JOINT ? *tiles : sOwnT;
   constexpr int ZT = B * D / 2;
   __shared__ __attribute__((aligned(1024))) E sZ[SPLIT ? NBUF : 1][SPLIT ? ZT : 8];   // tile layout of head_dim 128
   float* const sRed = NormExchange<NORM ? B * (D / 32) : 0>::get();   // [position][wave]
@@ -133,7 +130,8 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p, const int nu
   constexpr bool DEFER = SHP && !NORM;
   __shared__ __attribute__((aligned(16))) E sP[DEFER ? 2 : 1][SHP ? 32 * PROW : 8];
   __shared__ f32x4 sAcc[SPLIT ? 2 : 1][SPLIT ? 4 : 1][SPLIT ? 4 : 1][64];   // [block parity][wave][element group][lane]
-  f32x4 (*const sDg)[64] = lds.decay_mask();
+  __shared__ Mask sOwnDg;
+  Mask& sDg = JOINT ? *mask : sOwnDg;   // decay mask
 
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l32 = l & 31, hh = l >> 5;
   int dvt = SPLIT ? w & 3 : w % NT;
@@ -146,7 +144,7 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p, const int nu
   // time, so that the second read of a shared tile can hit that XCD's L2 (workgroup numbers go round the eight XCDs);
   // when the count of pairs is no multiple of eight they are neighbours instead.
   int which = group, wg = number;
-  const int scans = SPLIT ? grid >> 1 : grid;   // workgroups, or pairs of them
+  const int scans = SPLIT ? (int)(grid >> 1) : (int)grid;   // workgroups, or pairs of them
   int vh = 0;
   if constexpr (SPLIT) {
     if ((scans & 7) == 0) {   // the pair eight workgroup numbers apart, as below
@@ -733,13 +731,11 @@ __device__ __forceinline__ void scan_wide_body(const ScanParams& p, const int nu
 
 template <typename E, int D, bool REV, bool STATE_ONLY, bool NORM, bool TWIN, int CACHE>
 __global__ __launch_bounds__((TWIN ? 4 : 2) * D, TWIN ? 2 : (D == 96 ? 3 : 2)) void scan_wide_kernel(ScanParams p) {
-  __shared__ WideLds<E, D, STATE_ONLY, TWIN, false> lds;
-  scan_wide_body<E, D, REV, STATE_ONLY, NORM, TWIN, false, CACHE>(p, (int)blockIdx.x, (int)gridDim.x, lds);
+  scan_wide_body<E, D, REV, STATE_ONLY, NORM, TWIN, false, CACHE>(p, (int)blockIdx.x, gridDim.x);
 }
 template <typename E, int D, bool REV, int CACHE>
 __global__ __launch_bounds__(2 * D, 2) void scan_wide_split_kernel(ScanParams p) {
-  __shared__ WideLds<E, D, false, false, true> lds;
-  scan_wide_body<E, D, REV, false, false, false, true, CACHE>(p, (int)blockIdx.x, (int)gridDim.x, lds);
+  scan_wide_body<E, D, REV, false, false, false, true, CACHE>(p, (int)blockIdx.x, gridDim.x);
 }
 
 // Head_dim 96: all three scans of a backward pass in one launch, as bwd_scans_half_kernel does for head_dim 64 / 128: the first half
@@ -748,14 +744,15 @@ __global__ __launch_bounds__(2 * D, 2) void scan_wide_split_kernel(ScanParams p)
 template <typename E, int D, int CACHE>
 __global__ __launch_bounds__(4 * D, 3) void bwd_scans_wide_kernel(ScanParams dq, ScanParams rev) {
   __shared__ union {
-    WideLds<E, D, false, true, false> twin;
-    WideLds<E, D, false, false, false> one;
-  } lds;
+    __attribute__((aligned(1024))) WideTiles<E, D, false, true, false> twin;
+    __attribute__((aligned(1024))) WideTiles<E, D, false, false, false> one;
+  } tiles;
+  __shared__ WideMask<4> mask;
   const int units = (int)gridDim.x / 2, wg = (int)blockIdx.x;
   if (wg < units)
-    scan_wide_body<E, D, true, false, false, true, false, CACHE>(rev, wg, units, lds.twin);
+    scan_wide_body<E, D, true, false, false, true, false, CACHE, true>(rev, wg, (unsigned)units, &tiles.twin, &mask);
   else if (threadIdx.x < 2 * D)
-    scan_wide_body<E, D, false, false, false, false, false, CACHE>(dq, wg - units, units, lds.one);
+    scan_wide_body<E, D, false, false, false, false, false, CACHE, true>(dq, wg - units, (unsigned)units, &tiles.one, &mask);
 }
 
 template <typename E, int D, int CACHE>
