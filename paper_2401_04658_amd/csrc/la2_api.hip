@@ -313,6 +313,8 @@ Plan packed_call_plan(const la2_desc* d, int64_t total_positions, const void* wo
 // loads (both with streaming stores at head_dim 64 / 128), bf16, inputs changing from pass to pass: head_dim 64 / 128, 16 MiB
 // 0.97-1.01, 32 MiB 0.95-0.97, 64 MiB 0.94-0.97, 128 MiB 1.00-1.04, 256 MiB 1.03-1.07; head_dim 96, 18 and 72 MiB 0.91, 144
 // 0.97-0.99, 288 MiB 1.00; head_dim 256, 32 MiB 0.96, 128 MiB 0.99, 256 MiB 1.00-1.03.
+// A forward pass alone loses 2 to 5 % where its tiles are kept above 96 MiB (head_dim 64, 256 to 2048 chains, 103 to 181 MiB), for
+// 5 to 9 % of it and a backward pass right behind it together; no call knows what comes next, so the line is one for all.
 // prefill: a forward pass that hands out its state is followed by decoding, not by a backward pass that finds the tiles again.
 // Tiles kept -> not, in parts of the time without either policy (ordinary stores of 64-byte pieces, non-temporal loads), bf16, d
 // 128: 192, 256, 512 chains of 500 positions 1.05 -> 0.96, 1.12 -> 1.03, 1.07 -> 1.03, 256 of 777 and 1036 1.14 -> 1.08; d 256: 26 chains of 4096 and 8192 1.08 -> 1.04,
@@ -323,14 +325,6 @@ int64_t tensor_bytes(const la2_desc* d, const Plan& pl) {
 }
 int keep_tiles(const la2_desc* d, const Plan& pl, bool prefill) {
   return tensor_bytes(d, pl) <= (int64_t)(prefill ? 16 : wide(d->head_dim) ? 160 : 96) << 20;
-}
-
-// ... of a forward pass at head_dim 64 that is not cut and hands out no state: up to 192 MiB a tensor.  The launch itself takes 2 to 5 %
-// longer than with non-temporal loads (256 chains of 4096 94.7 -> 98.6 us), the backward pass behind it, whose first launch starts at the
-// sequences' ends, finds what it read last.  Forward + backward, 256 chains of 3500, 4096, 6000 0.92, 0.95, 0.95 (8192, 256 MiB,
-// 0.97), 512 of 2048 0.94, 1024 of 1024 0.91; head_dim 128, 192 and 256 chains, 96 to 256 MiB, 0.97-1.02: not there.
-int keep_forward(const la2_desc* d, const Plan& pl, const int32_t* cu) {
-  return is16(d->dtype) && d->head_dim == 64 && cu == nullptr && pl.nchunks == 1 && tensor_bytes(d, pl) <= (int64_t)192 << 20;
 }
 
 // ScanParams::plain, forward passes.  Streaming stores (the default: see the kernels) leave the caches to the inputs, but they are
@@ -485,7 +479,6 @@ struct ScanArgs {
   const int4* map = nullptr;
   // states at sequence ends that are not block boundaries (ScanParams::ragged_state; 16-bit half-block kernels)
   bool ragged_state = false;
-  bool outputs = false;   // the scan that forms O
 };
 
 // A problem cut into a few chunks (16-bit half-block and fp32 kernels up to four, head_dim 96 as below; dense or packed
@@ -582,7 +575,6 @@ la2::ScanParams scan_params(const la2_desc* d, const Plan& pl, const ScanArgs& a
   p.ragged_state = a.ragged_state ? 1 : 0;
   p.value_split = value_split(d, p);
   p.keep = keep_tiles(d, pl, a.fin != nullptr);   // (of the launches here only a forward pass hands out a state)
-  if (a.outputs && a.fin == nullptr && a.rstd == nullptr && keep_forward(d, pl, a.cu)) p.keep = 1;
   p.plain = plain_stores(d, pl, a.cu, a.fin != nullptr, a.rstd != nullptr);
   if (p.plain != 0 && !wide(d->head_dim)) p.keep = 0;
   return p;
@@ -1031,7 +1023,6 @@ la2_status fwd_state_one_call(const la2_desc* desc, const void* q, const void* k
     return run_short_fwd(desc, q, k, v, lambda, kv_init, o, kv_final, rstd, eps, desc->seqlen, nullptr, s);
   if (blocks.seqlen > 0) {
     ScanArgs a{q, k, v, o};
-    a.outputs = true;
     a.init = kv_init;
     a.fin = kv_final;
     a.ragged_state = kv_final != nullptr && ragged_end(desc);
