@@ -40,3 +40,17 @@ def test_a_forward_pass_keeps_its_tiles_only_where_it_gains_itself(dtype):
     for d, b, n in ((64, 16, 3000), (64, 16, 100), (128, 16, 1500)):
         for x in routes.forward(routes.desc(b, 16, n, d, dtype)):
             assert x["launcher"] == "short" or x["keep"] == 1, (d, b, n)
+
+
+@pytest.mark.parametrize("d,b,h,n", [(96, 16, 16, 900), (96, 7, 32, 855), (128, 16, 16, 900), (256, 8, 16, 189), (64, 16, 16, 8192)])
+def test_the_order_of_a_backward_pass_that_is_not_cut(d, b, h, n):
+    """dK and dV first where no state is given or wanted, the dQ scan first with any state (measured: la2_api.hip)."""
+    A = routes.ADDRESS
+    x = routes.desc(b, h, n, d)
+    reverse = [y["rev"] for y in routes.backward(x)]
+    assert reverse == [1, 0]
+    for states in (dict(init=A["kv_init"]), dict(d_final=A["d_kv_final"]), dict(d_init=A["d_kv_init"]),
+                   dict(init=A["kv_init"], d_final=A["d_kv_final"], d_init=A["d_kv_init"]), dict(init=A["kv_init"], d_init=A["kv_init"])):
+        launches = routes.backward(x, **states)
+        assert [y["rev"] for y in launches] == [0, 1], states
+        assert launches[0]["w"] == "0x%x" % A["dq"] and launches[0]["nscan"] == 1 and launches[1]["nscan"] == 2
