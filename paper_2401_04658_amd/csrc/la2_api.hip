@@ -650,7 +650,12 @@ la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs&
 // cutting the sequences only adds the pre-pass (4 of 14 tensor passes).  Forward + backward, bf16, against the dQ launch (cut: with
 // the chunk states on the side) and the dK / dV launch one after the other:
 // - uncut before as well: d 64, 96 to 128 chains 0.70 (n 1024), 160, 192, 256 of 300 to 2048 positions 0.79-0.83, 0.79-0.85,
-//   0.79-0.94, 512 0.91-0.96, 1024 0.96-1.01; above 96 MiB a tensor 224 and more 1.00-1.04 (272 of 4096 1.16), 160 and 192 0.95, 0.97.
+//   0.79-0.94, 512 0.91-0.96; above 96 MiB a tensor 224 and more 1.00-1.04 (272 of 4096 1.16), 160 and 192 0.95, 0.97.
+//   Many chains (the backward pass alone, n 32, 64, 128, 224, 300): 768 0.98, 1.00, 1.01, 0.92, 0.95, 896 1.01, 1.00, 0.98, 0.94, 0.93,
+//   1024 1.10, 1.08, 1.04, 1.00, 0.97, 1152 0.99, 0.97, 0.94, 0.91, 0.91, 1280 1.05, 1.03, 0.99, 0.94, 0.95, 1664 1.05, 0.98, 0.96, 0.95, 0.96,
+//   1792 1.09, 1.01, 1.00, 0.97, 0.97, 2304 1.13, 1.05, 1.02, 0.97, 1.00, 3072 1.12, 1.06, 1.00, 1.02; 8192 of 32 1.20: a pair of workgroups
+//   takes LDS and registers for the longer of the two, and with few blocks a chain it is the workgroups' starts that count.
+//   Packed the same by the average length (1164 chains of 253 0.89, 2520 of 307 0.98, 3780 of 47 1.09, 11,520 of 34 1.23).
 //   d 128, whose pairs want two units: 80 to 128 chains 0.74-0.77, 160 0.87-0.98, 192, 224, 256 up to 32 MiB 0.97-0.99, above
 //   0.99-1.04; a partial second or third round 272 to 320 0.85-0.87, 384 0.92-0.94, 416 0.98-1.00, 448 1.01-1.05, 640 0.93-0.96, 768 1.00.
 // - instead of a cut: n 1024, 2048, 4096, 8192, d 64, 96 chains 0.69, 0.84, 0.87, 0.89, 128 0.70, 0.84, 0.86, 0.92 (80: 0.89, 0.98,
@@ -661,7 +666,10 @@ la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs&
 //   0.99, 48 of 1024 to 16384 0.83, 0.90, 0.94, 0.97, 0.98, 64 of 1024, 2048, 4096, 8192 0.87, 0.93, 0.99, 1.03; saved, 64 of 1024,
 //   2048, 4096 0.93, 0.97, 1.03; packed batches up to 92 MiB 0.86-0.98.
 // Head_dim 96 (two pairs share a unit; its pre-passes are launches that fill the device): uncut before as well, 4 to 128 chains of
-// 300 to 4096 positions 0.70-0.76, 160 0.73-0.84, 192 0.94-1.07, 256 0.98-1.04, 288 to 1024 0.76-1.02, packed 0.70-0.97; instead of a
+// 300 to 4096 positions 0.70-0.76, 160 0.73-0.84, 192 0.94-1.07, 256 0.98-1.04, 288 to 640 0.76-0.97, packed 0.70-0.97; many chains (the
+// backward pass alone, n 32, 64, 128, 224): 704 1.02, 1.02, 1.01, 0.97, 768 1.03, 0.98, 0.95, 0.98, 1024 0.98, 0.94, 0.96, 0.96, 1152 0.97, 0.97, 0.94,
+// 0.94, 1280 1.05, 1.02, 0.98, 0.99, 1792 1.07, 1.02, 1.01, 1.00, 2560 1.08, 1.03, 1.01, 0.96, 4096 1.11, 1.05, 0.99, 16,384 of 32 1.16; packed, average
+// in brackets, 1344 (39) 0.97, 1792 (34) 1.01, 2432 (81) 0.97, 4976 (76) 1.02, 7512 (34) 1.12; instead of a
 // cut, n 1024, 2048, 4096, 8192, 48 chains 0.86, 1.00, 1.11, 1.33, 64 0.86, 0.97, 1.08, 1.12, 80 0.81, 0.84, 0.92, 0.96, 112 0.75,
 // 0.75, 0.84, 0.82, saved 96 0.84, 0.84, 0.99, 0.95 (64: 0.99, 1.09, 1.21, 1.23).  In pl's chunks it would take a second set of states,
 // which the workspace has no room for; from saved states it does on up to half as many workgroups as units (0.83-0.87; more 0.96-1.14).
@@ -673,8 +681,16 @@ Plan joint_rule(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved
   const int64_t cus = device_cu_count(), chains = (int64_t)d->batch * d->heads, bytes = tensor_bytes(d, pl);
   const int64_t MiB = (int64_t)1 << 20;
   if (pl.nchunks == 1) {
-    if (d->head_dim == 96) return cu != nullptr || 8 * chains <= 5 * cus || chains > cus ? pl : none;
-    if (d->head_dim == 64) return bytes <= 96 * MiB || (cu == nullptr && 4 * chains <= 3 * cus) ? pl : none;
+    const int64_t n = pl.total > 0 ? pl.total / d->batch : d->seqlen;   // positions of a chain, packed: on average
+    if (d->head_dim == 96) {
+      if (cu != nullptr) return chains <= 6 * cus || n >= 96 ? pl : none;
+      if (2 * chains <= 5 * cus) return 8 * chains <= 5 * cus || chains > cus ? pl : none;
+      return n >= (2 * chains <= 9 * cus ? 64 : 128) ? pl : none;
+    }
+    if (d->head_dim == 64) {
+      const bool many_pay = chains <= 3 * cus ? true : 2 * chains <= 7 * cus ? n > 32 : chains <= 4 * cus ? n >= 192 : chains <= 7 * cus && n >= 64;
+      return (bytes <= 96 * MiB && many_pay) || (cu == nullptr && 4 * chains <= 3 * cus) ? pl : none;
+    }
     if (cu != nullptr) return 2 * chains <= cus ? pl : none;
     if (chains <= cus) return 8 * chains <= 5 * cus || bytes <= 32 * MiB ? pl : none;
     return chains % cus > 0 && 2 * (chains % cus) <= cus && chains < 3 * cus ? pl : none;

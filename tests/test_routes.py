@@ -54,3 +54,28 @@ def test_the_order_of_a_backward_pass_that_is_not_cut(d, b, h, n):
         launches = routes.backward(x, **states)
         assert [y["rev"] for y in launches] == [0, 1], states
         assert launches[0]["w"] == "0x%x" % A["dq"] and launches[0]["nscan"] == 1 and launches[1]["nscan"] == 2
+
+
+# chains, positions, one launch; either side of every line for many chains
+LINES = {64: [(768, 32, True), (784, 32, False), (784, 33, True), (896, 64, True), (912, 64, False), (912, 191, False), (912, 192, True),
+              (1024, 128, False), (1024, 300, True), (1040, 63, False), (1040, 64, True), (1792, 64, True), (1808, 300, False), (2048, 32, False),
+              (8192, 64, False), (16384, 32, False), (272, 32, True), (512, 400, True)],
+         96: [(272, 8, True), (640, 8, True), (656, 63, False), (656, 64, True), (1152, 64, True), (1168, 127, False), (1168, 128, True),
+              (4096, 64, False), (4096, 128, True), (16384, 32, False), (16384, 128, True), (160, 8, True), (176, 8, False), (256, 300, False)]}
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("d,chains,n,one", [(d, *x) for d in LINES for x in LINES[d]])
+def test_one_launch_of_many_short_chains(d, chains, n, one, dtype):
+    launchers = [x["launcher"] for x in routes.backward(routes.desc(chains // 16, 16, n, d, dtype))]
+    if launchers != ["short"]:   # (up to two chains per unit the short path comes first)
+        assert any(x in ("bwd_scans_bf16", "bwd_scans_wide") for x in launchers) == one, launchers
+
+
+@pytest.mark.parametrize("d,sequences,average,longest,one", [(64, 48, 100, 160, True), (64, 230, 47, 90, False), (64, 64, 80, 120, False), (64, 70, 80, 120, True),
+                                                             (64, 110, 80, 120, True), (64, 128, 80, 120, False), (64, 700, 51, 90, False), (96, 96, 30, 60, True),
+                                                             (96, 98, 95, 180, False), (96, 98, 96, 180, True), (96, 700, 46, 90, False)])
+def test_one_launch_of_many_packed_sequences(d, sequences, average, longest, one):
+    """As for dense batches, by the average length."""
+    x = routes.desc(sequences, 16, longest, d, packed=True)
+    assert (routes.one_launch(routes.backward(x, total=sequences * average)) is not None) == one
