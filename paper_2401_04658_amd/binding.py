@@ -10,6 +10,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sys
 
 import torch
 
@@ -123,10 +124,19 @@ def _module():
         if not os.path.exists(_NATIVE_PATH):
             raise FileNotFoundError(
                 "%s not found: the native module has not been built (python -m paper_2401_04658_amd.build)" % _NATIVE_PATH)
-        loader = importlib.machinery.ExtensionFileLoader("_la2_native", _NATIVE_PATH)
-        spec = importlib.util.spec_from_file_location("_la2_native", _NATIVE_PATH, loader=loader)
-        module = importlib.util.module_from_spec(spec)
-        loader.exec_module(module)
+        here = sys.version_info[:2] + (str(torch.__version__),)
+        try:
+            loader = importlib.machinery.ExtensionFileLoader("_la2_native", _NATIVE_PATH)
+            spec = importlib.util.spec_from_file_location("_la2_native", _NATIVE_PATH, loader=loader)
+            module = importlib.util.module_from_spec(spec)
+            loader.exec_module(module)
+        except ImportError as e:   # (a torch without a function that it calls, among others)
+            raise ImportError("%s does not load with Python %d.%d and torch %s; build it with them (python -m paper_2401_04658_amd.build): %s"
+                              % ((_NATIVE_PATH,) + here + (e,))) from e
+        built = getattr(module, "built_for", None)
+        if built != here:
+            raise ImportError("%s was built for %s, not for Python %d.%d and torch %s; build it again (python -m paper_2401_04658_amd.build)"
+                              % ((_NATIVE_PATH, "Python %d.%d and torch %s" % built if built else "another torch") + here))
         _native = module
     return _native
 

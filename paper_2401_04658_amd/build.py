@@ -63,6 +63,7 @@ def _native_commands(obj):
     home = os.path.dirname(os.path.abspath(torch.__file__))
     cxx = os.environ.get("CXX", "g++")
     compile_ = [cxx, "-O2", "-std=c++17", "-fPIC", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+                '-DLA2_TORCH_VERSION="%s"' % torch.__version__,
                 "-isystem", os.path.join(home, "include"), "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
                 "-isystem", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
     link = [cxx, "-shared", "-fPIC", obj, "-L" + _HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",

@@ -312,4 +312,16 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_la2_native", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__la2_native() { return PyModule_Create(&module); }
+// built_for: the Python and the torch whose headers this was compiled with; the binding refuses any other (a tensor's layout in memory
+// is what the checks above read)
+PyMODINIT_FUNC PyInit__la2_native() {
+  PyObject* const m = PyModule_Create(&module);
+  if (m == nullptr) return nullptr;
+  PyObject* const built = Py_BuildValue("(iis)", PY_MAJOR_VERSION, PY_MINOR_VERSION, LA2_TORCH_VERSION);
+  if (built == nullptr || PyModule_AddObject(m, "built_for", built) != 0) {
+    Py_XDECREF(built);
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -182,3 +182,20 @@ def test_eps_is_what_float_takes():
     for eps, error in ((None, TypeError), ("x", ValueError), ([], TypeError)):
         with pytest.raises(error):
             lib.la2_fwd_norm(q, None, q, q, q, eps, q, q, None, 0, 0)
+
+
+def test_the_module_is_refused_by_a_torch_that_it_was_not_built_for(monkeypatch, tmp_path):
+    monkeypatch.setattr(binding, "_native", None)
+    assert binding._module().built_for[2] == torch.__version__
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.setattr(torch, "__version__", "1.0.0")
+    with pytest.raises(ImportError, match="built for .* not for .* torch 1.0.0; build it again"):
+        binding._module()
+    assert binding._native is None
+    monkeypatch.undo()
+    monkeypatch.setattr(binding, "_native", None)
+    broken = tmp_path / "_la2_native.so"
+    broken.write_bytes(b"not a library")
+    monkeypatch.setattr(binding, "_NATIVE_PATH", str(broken))
+    with pytest.raises(ImportError, match="does not load with .* build it with them"):
+        binding._module()
