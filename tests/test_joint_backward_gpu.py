@@ -1,5 +1,6 @@
 """Backward passes whose three scans run in one launch (16-bit data), against the fp64 oracle and against the
 launches one after the other (scan variant 2)."""
+import numpy as np
 import pytest
 import torch
 
@@ -25,7 +26,7 @@ def _defaults():
 # before; up to half the units, about all of them, a partial second round, and one that else runs as two calls
 @pytest.mark.parametrize("d,b,h,n", [(64, 1, 4, 2113), (64, 1, 16, 2048), (64, 3, 16, 1000), (64, 6, 16, 1100), (64, 8, 16, 1031),
                                      (64, 10, 16, 200), (64, 16, 16, 257), (64, 18, 16, 130), (128, 5, 16, 416), (128, 3, 16, 1000),
-                                     (96, 3, 2, 300), (96, 3, 16, 1000), (96, 5, 16, 1100), (96, 17, 16, 97), (96, 1, 16, 2050),
+                                     (96, 3, 2, 300), (96, 3, 16, 1000), (96, 5, 16, 1100), (96, 17, 16, 97), (96, 1, 16, 2050), (96, 1, 4, 2050),
                                      (128, 6, 16, 1056), (128, 10, 16, 100), (128, 16, 16, 65), (128, 18, 16, 127),
                                      (128, 19, 16, 2049), (96, 17, 16, 2053), (64, 19, 16, 2055)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
@@ -64,6 +65,61 @@ def test_all_scans_in_one_launch(dtype, d, b, h, n):
                 assert_close(label, x[:1], ref, dtype)
                 # no further from the truth than the launches apart (the same sums, or those of other chunks: up to their order)
                 assert rms_rel(to64(x[:1]), ref) <= 1.05 * rms_rel(to64(other[:1]), ref) + 1e-7, label
+
+
+# packed: in the plan's chunks through the pair map (a scan over the chunk states, none), uncut, few chains of head_dim 128, head_dim 96
+# (no states there); sequences of no position, of one, off the block boundaries
+PACKED = [(64, 2, [2500, 700, 33, 0, 1, 400]), (64, 16, [1, 33, 700, 0, 257, 64, 900, 31, 500, 450, 300, 222]), (64, 16, [1100, 1000, 1050, 0, 1200, 1]),
+          (128, 16, [416, 33, 0, 257, 400]), (96, 4, [300, 33, 1, 257, 0, 400, 31]), (96, 16, [97] * 40 + [96, 1, 130])]
+
+
+@pytest.mark.parametrize("d,h,lengths", PACKED)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_all_scans_of_a_packed_batch_in_one_launch(dtype, d, h, lengths):
+    """With states and without (head_dim 96: without), and with d_kv_init in kv_init's place, against the launches apart and the oracle."""
+    total, nseq = sum(lengths), len(lengths)
+    t = workloads.Workload("joint", 1, h, total, d, dtype, seed=8700 + total + d, backward=True).tensors()
+    gen = torch.Generator(device="cpu")
+    gen.manual_seed(8700 + total)
+    init, dfin = (torch.randn((nseq, h, d, d), generator=gen) * 0.3 for _ in range(2))
+    q, k, v, do = (t[x][0].permute(1, 0, 2).contiguous().to(DEV) for x in ("q", "k", "v", "d_o"))
+    lam, ends = t["lam"].to(DEV), [0]
+    for n in lengths:
+        ends.append(ends[-1] + n)
+    cu, longest = torch.tensor(ends, dtype=torch.int32, device=DEV), max(lengths)
+    for given in (False, True) if d != 96 else (False,):
+        kv0, dkv = (init.to(DEV), dfin.to(DEV)) if given else (None, None)
+        call = dict(kv_init=kv0, d_kv_final=dkv, want_d_kv_init=given)
+        binding.la2_set_scan_variant(2)
+        apart = binding.la2_bwd_varlen_state(q, k, v, do, lam, cu, longest, **call)
+        binding.la2_set_scan_variant(0)
+        runs = {"": binding.la2_bwd_varlen_state(q, k, v, do, lam, cu, longest, **call)}
+        if given:
+            place = kv0.clone()
+            runs["in place"] = binding.la2_bwd_varlen_state(q, k, v, do, lam, cu, longest, kv_init=place, d_kv_final=dkv, d_kv_init=place)
+        torch.cuda.synchronize()
+        refs = [[], [], []]
+        for i, n in enumerate(lengths):
+            if n == 0:
+                continue
+            seq = {x: to64(t[x][:, :, ends[i]:ends[i + 1]].contiguous()) for x in ("q", "k", "v", "d_o")}
+            grads = oracle.bwd_recurrent_state(seq["q"], seq["k"], seq["v"], seq["d_o"], to64(t["lam"]),
+                                               kv_init=to64(init[i:i + 1]) if given else None, d_kv_final=to64(dfin[i:i + 1]) if given else None)
+            for ref, x in zip(refs, grads):
+                ref.append(x[0].transpose(1, 0, 2))
+            for kind, outs in runs.items():
+                if given:
+                    assert_close("d_kv_init seq %d %s" % (i, kind), outs[3][i:i + 1], grads[3], dtype)
+        for kind, outs in runs.items():
+            for name, x, ref, other in zip(("dq", "dk", "dv"), outs, refs, apart):
+                label = "%s d%d h%d %s states %s %s" % (name, d, h, lengths[:8], given, kind)
+                ref = np.concatenate(ref)
+                assert_close(label, x, ref, dtype)
+                # no further from the truth than the launches apart
+                assert rms_rel(to64(x), ref) <= 1.05 * rms_rel(to64(other), ref) + 1e-7, label
+            if given:   # a sequence of no positions passes its state's gradient on
+                for i, n in enumerate(lengths):
+                    assert n > 0 or torch.equal(outs[3][i].cpu(), dfin[i])
 
 
 @pytest.mark.parametrize("d,h,n", [(64, 4, 1000), (64, 16, 2050), (128, 16, 1500), (128, 8, 3001)])

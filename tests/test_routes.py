@@ -91,3 +91,38 @@ def test_nothing_between_the_short_path_and_the_one_launch(dtype):
             for states in (dict(), dict(init=A["kv_init"], d_final=A["d_kv_final"], d_init=A["d_kv_init"])):
                 launches = [x["launcher"] for x in routes.backward(routes.desc(chains // h, h, n, 128, dtype), **states)]
                 assert launches == ["short"] or "bwd_scans_bf16" in launches, (chains, n, launches)
+
+
+# what test_joint_backward_gpu.py runs: chunks of the one launch (None: another path) without states, with all of them, and both again from
+# the forward call's workspace
+JOINT = {(64, 1, 4, 2113): (None, 9, None, 9), (64, 1, 16, 2048): (8, 8, 8, 8), (64, 3, 16, 1000): (4, 4, 4, 4), (64, 6, 16, 1100): (1, 1, 1, 1),
+         (64, 8, 16, 1031): (1, 1, 1, 1), (64, 10, 16, 200): (1, 1, 1, 1), (64, 16, 16, 257): (1, 1, 1, 1), (64, 18, 16, 130): (1, 1, 1, 1),
+         (128, 5, 16, 416): (1, 1, 1, 1), (128, 3, 16, 1000): (1, 1, None, None), (96, 3, 2, 300): (1, 1, 1, 1), (96, 3, 16, 1000): (1, 1, None, None),
+         (96, 5, 16, 1100): (1, 1, None, None), (96, 17, 16, 97): (1, 1, 1, 1), (96, 1, 16, 2050): (None,) * 4, (96, 1, 4, 2050): (None, None, 9, 9),
+         (128, 6, 16, 1056): (1, 1, None, None), (128, 10, 16, 100): (1, 1, 1, 1), (128, 16, 16, 65): (1, 1, 1, 1), (128, 18, 16, 127): (1, 1, 1, 1),
+         (128, 19, 16, 2049): (1, 1, 1, 1), (96, 17, 16, 2053): (1, 1, 1, 1), (64, 19, 16, 2055): (1, 1, 1, 1)}
+# (chunks, pairs of the map: 0 none) of its packed batches
+PACKED = [(10, 20), (4, 25), (1, 0), (1, 0), (1, 0), (1, 0)]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_the_gpu_test_of_the_one_launch_reaches_it(dtype):
+    import test_joint_backward_gpu as gpu
+    A = routes.ADDRESS
+    states = dict(init=A["kv_init"], d_final=A["d_kv_final"], d_init=A["d_kv_init"])
+    shapes = [m.args[1] for m in gpu.test_all_scans_in_one_launch.pytestmark if m.args and m.args[0] == "d,b,h,n"][0]
+    assert set(shapes) == set(JOINT)
+    for (d, b, h, n), want in JOINT.items():
+        x = routes.desc(b, h, n, d, dtype)
+        got = [routes.one_launch(routes.backward(x, saved=saved, **st)) for saved in (False, True) for st in ({}, states)]
+        assert tuple(y and y["nchunks"] for y in got) == want, (d, b, h, n)
+        # d_kv_init in kv_init's place: the dQ scan has read it by then, in a launch of its own
+        in_place = routes.backward(x, init=A["kv_init"], d_final=A["d_kv_final"], d_init=A["kv_init"])
+        assert routes.one_launch(in_place) is None
+    for (d, h, lengths), want in zip(gpu.PACKED, PACKED):
+        x = routes.desc(len(lengths), h, max(lengths), d, dtype, packed=True)
+        for st in ({}, states) if d != 96 else ({},):
+            y = routes.one_launch(routes.backward(x, total=sum(lengths), **st))
+            assert (y["nchunks"], y["pairs"]) == want, (d, h, lengths)
+        if d != 96:
+            assert routes.one_launch(routes.backward(x, total=sum(lengths), init=A["kv_init"], d_final=A["d_kv_final"], d_init=A["kv_init"])) is None
