@@ -660,8 +660,7 @@ la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs&
 //   0.99-1.04; a partial second or third round 272 to 320 0.85-0.87, 384 0.92-0.94, 416 0.98-1.00, 448 1.01-1.05, 640 0.93-0.96, 768 1.00.
 // - instead of a cut: n 1024, 2048, 4096, 8192, d 64, 96 chains 0.69, 0.84, 0.87, 0.89, 128 0.70, 0.84, 0.86, 0.92 (80: 0.89, 0.98,
 //   1.03, 1.08); d 128, 96 chains 0.83, 0.90, 0.92, 0.93, 128 0.88, 0.88, 0.94, 0.93 (64: 0.90, 1.04, 1.18, 1.24; n 768, 900, 1152, 48 chains 0.99, 0.95, 0.94,
-//   64 0.89, 0.87, 0.91, 80 0.87, 0.89, 0.91; what the short path leaves below that, the backward pass alone: n 600, 700 66 to 78 chains
-//   0.67-0.70, 0.74-0.78, fp16, 64 of 700 0.78; forward + backward with all states, n 600, 700 48 to 78 chains 0.76-0.81, 0.80-0.86).  From saved
+//   64 0.89, 0.87, 0.91, 80 0.87, 0.89, 0.91; n 640, 700 80 chains 0.82, 0.84, fewer take the short path).  From saved
 //   states, which take a pre-pass out of the other form: d 64, 96 to 128 chains 0.94-1.00; d 128, 112 and 128 0.93-1.00 (96: 0.95-1.01).
 // - in pl's chunks (d 64; the pre-passes in one launch): 4 chains of 4096 0.83, 16 of 2048, 4096, 8192, 16384 0.83, 0.91, 0.94,
 //   0.99, 48 of 1024 to 16384 0.83, 0.90, 0.94, 0.97, 0.98, 64 of 1024, 2048, 4096, 8192 0.87, 0.93, 0.99, 1.03; saved, 64 of 1024,
@@ -704,7 +703,7 @@ Plan joint_rule(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved
   }
   if (d->head_dim == 128) {
     if (cu != nullptr) return none;
-    if (!saved_states && d->seqlen <= 1152 && 16 * chains >= 3 * cus) return uncut;   // (what the short path does not take)
+    if (!saved_states && d->seqlen <= 1152 && 16 * chains >= (d->seqlen > 704 ? 3 : 5) * cus) return uncut;
     return 16 * chains >= (saved_states ? 7 : 6) * cus ? uncut : none;
   }
   if (cu != nullptr) return bytes <= 96 * MiB ? pl : none;

@@ -81,18 +81,6 @@ def test_one_launch_of_many_packed_sequences(d, sequences, average, longest, one
     assert (routes.one_launch(routes.backward(x, total=sequences * average)) is not None) == one
 
 
-@pytest.mark.parametrize("dtype", DTYPES)
-def test_nothing_between_the_short_path_and_the_one_launch(dtype):
-    """head_dim 128, from 3/16 of a chain per unit on, up to 1152 positions: what the short path does not take, with states or without,
-    goes to the one launch, wherever the short path's own line lies."""
-    A = routes.ADDRESS
-    for chains, h in ((48, 16), (56, 8), (64, 16), (66, 6), (72, 8), (78, 6), (80, 16)):
-        for n in range(260, 1152, 60):
-            for states in (dict(), dict(init=A["kv_init"], d_final=A["d_kv_final"], d_init=A["d_kv_init"])):
-                launches = [x["launcher"] for x in routes.backward(routes.desc(chains // h, h, n, 128, dtype), **states)]
-                assert launches == ["short"] or "bwd_scans_bf16" in launches, (chains, n, launches)
-
-
 # what test_joint_backward_gpu.py runs: chunks of the one launch (None: another path) without states, with all of them, and both again from
 # the forward call's workspace
 JOINT = {(64, 1, 4, 2113): (None, 9, None, 9), (64, 1, 16, 2048): (8, 8, 8, 8), (64, 3, 16, 1000): (4, 4, 4, 4), (64, 6, 16, 1100): (1, 1, 1, 1),
