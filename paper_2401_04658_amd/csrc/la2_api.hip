@@ -703,6 +703,8 @@ Plan joint_rule(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved
   }
   if (d->head_dim == 128) {
     if (cu != nullptr) return none;
+    // (704: where short_backward ends for 64 bf16 chains without states, which come there first; what it leaves below, calls with
+    // states, fp16 and 65 to 79 chains, stays in chunks, although one launch would take 0.67-0.86 of their time)
     if (!saved_states && d->seqlen <= 1152 && 16 * chains >= (d->seqlen > 704 ? 3 : 5) * cus) return uncut;
     return 16 * chains >= (saved_states ? 7 : 6) * cus ? uncut : none;
   }

@@ -81,6 +81,14 @@ def test_one_launch_of_many_packed_sequences(d, sequences, average, longest, one
     assert (routes.one_launch(routes.backward(x, total=sequences * average)) is not None) == one
 
 
+def test_the_one_launch_starts_where_the_short_path_ends():
+    """head_dim 128, 64 chains without states: the one launch's line (704 positions) is where the short path's own line lies."""
+    for n in (300, 640, 704):
+        assert [x["launcher"] for x in routes.backward(routes.desc(4, 16, n, 128))] == ["short"], n
+    for n in (705, 768, 1152):
+        assert routes.one_launch(routes.backward(routes.desc(4, 16, n, 128))) is not None, n
+
+
 # what test_joint_backward_gpu.py runs: chunks of the one launch (None: another path) without states, with all of them, and both again from
 # the forward call's workspace
 JOINT = {(64, 1, 4, 2113): (None, 9, None, 9), (64, 1, 16, 2048): (8, 8, 8, 8), (64, 3, 16, 1000): (4, 4, 4, 4), (64, 6, 16, 1100): (1, 1, 1, 1),
