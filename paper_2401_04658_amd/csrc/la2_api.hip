@@ -1235,9 +1235,10 @@ la2_status bwd_saved_one_call(const la2_desc* desc, const void* q, const void* k
   // chains of 700 1.01).  With states the dQ scan first: the other order takes, d 96, 256 chains of 900, 2500 1.09, 1.04, 224 of 2500 1.02,
   // d 128, 256 of 900 1.05, d 256, 112 of 200 1.04, 192 of 500 1.02 (d 96, 192 of 500, 900 0.97, d 256, 112 of 900 0.96).  With more chains too,
   // whose launches start with other chains than the one before ended with: d 64, 3072 of 160, 224 1.03, 1.04, 4096 of 160 1.03, 8192 of 64 1.03,
-  // d 128, 2048 of 160 1.04, d 256, 512 of 500 1.03, 2048 of 64 1.02 (d 64, 16,384 of 64 0.97; most others 0.99-1.01).
-  if (is16(desc->dtype) && pl.nchunks == 1 && chains <= device_cu_count() && kv_init == nullptr && d_kv_final == nullptr &&
-      d_kv_init == nullptr) {
+  // d 128, 2048 of 160 1.04, d 256, 512 of 500 1.03, 2048 of 64 1.02 (d 64, 16,384 of 64 0.97; most others 0.99-1.01).  Nor up to 16 MiB a
+  // tensor, all of which the caches hold in either order (d 96 with the Norm, 176 to 256 chains of 157 1.02-1.03, of 300 1.01-1.02; plain 0.99-1.00).
+  if (is16(desc->dtype) && pl.nchunks == 1 && chains <= device_cu_count() && tensor_bytes(desc, pl) > (int64_t)16 << 20 &&
+      kv_init == nullptr && d_kv_final == nullptr && d_kv_init == nullptr) {
     st = run_dual_reverse_scan(desc, pl, for_dv, for_dk, lambda, rev_workspace, s);
     return st == LA2_OK ? run_scan(desc, pl, false, for_dq, lambda, workspace, s) : st;
   }

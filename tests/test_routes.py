@@ -42,9 +42,10 @@ def test_a_forward_pass_keeps_its_tiles_only_where_it_gains_itself(dtype):
             assert x["launcher"] == "short" or x["keep"] == 1, (d, b, n)
 
 
-@pytest.mark.parametrize("d,b,h,n", [(96, 16, 16, 900), (96, 7, 32, 855), (128, 16, 16, 900), (256, 8, 16, 189), (64, 16, 16, 8192)])
+@pytest.mark.parametrize("d,b,h,n", [(96, 16, 16, 900), (96, 7, 32, 855), (128, 16, 16, 900), (256, 8, 16, 289), (64, 16, 16, 8192)])
 def test_the_order_of_a_backward_pass_that_is_not_cut(d, b, h, n):
-    """dK and dV first on at most one chain per unit where no state is given or wanted, else the dQ scan first (measured: la2_api.hip)."""
+    """dK and dV first on at most one chain per unit and above 16 MiB a tensor where no state is given or wanted, else the dQ scan first
+    (measured: la2_api.hip)."""
     A = routes.ADDRESS
     x = routes.desc(b, h, n, d)
     reverse = [y["rev"] for y in routes.backward(x)]
@@ -54,6 +55,8 @@ def test_the_order_of_a_backward_pass_that_is_not_cut(d, b, h, n):
         launches = routes.backward(x, **states)
         assert [y["rev"] for y in launches] == [0, 1], states
         assert launches[0]["w"] == "0x%x" % A["dq"] and launches[0]["nscan"] == 1 and launches[1]["nscan"] == 2
+    few = routes.backward(routes.desc(b, h, (16 << 20) // (2 * b * h * d), d))   # (at head_dim 64 one launch)
+    assert routes.one_launch(few) is not None or [y["rev"] for y in few] == [0, 1]
     more = routes.backward(routes.desc(4096 // h, h, 160, d))   # (at head_dim 96 one launch)
     assert routes.one_launch(more) is not None or [y["rev"] for y in more] == [0, 1]
 
