@@ -107,9 +107,10 @@ size_t la2_workspace_bytes(const la2_desc* desc, int32_t op);
  * chains there are and the more states a call carries) run as one launch that forms every output row from all the
  * positions it depends on, without chunks and in time quadratic in seqlen, where that was measured to be faster.
  * What a call asks for stays the same: the workspace of the plan is required as always and left as it is.
- * A backward pass of 16-bit data at head_dim 64, 96 or 128 whose three scans run in one launch may leave sequences whole that the
- * forward pass cuts (from 3/8 of a chain per compute unit on, on fewer chains up to about 1000 positions); the workspace is then
- * required and left as it is as well, and a forward call's is not read.
+ * A backward pass of 16-bit data at head_dim 64, 96 or 128 whose three scans run in one launch (where that was measured to be
+ * faster, by head_dim, number of chains, length and whether a forward call's states are given; no la2_set_chunk_tokens(),
+ * la2_set_scan_variant() 0) may leave sequences whole that the forward pass cuts; the workspace is then required and left as it
+ * is as well, and a forward call's is not read.
  * And a batch with a few more chains than a whole number (one to four) per compute unit,
  * which as one launch gives some units a workgroup more than the others and takes up to twice as long as whole
  * rounds.  Every entry point that takes a dense
@@ -428,7 +429,8 @@ int32_t la2_block_size(const la2_desc* desc);
 void la2_set_chunk_tokens(int32_t tokens);
 
 /*
- * Test / tuning knob: which 16-bit scan kernel la2_fwd / la2_bwd launch at head_dim 64 and 128.
+ * Test / tuning knob: which 16-bit scan kernel la2_fwd / la2_bwd launch at head_dim 64 and 128, and whether the scans of a
+ * backward pass may run in one launch at head_dim 64, 96 and 128.
  *   0  automatic (currently the half-block kernel: blocks of 32 positions, up to two workgroups per
  *      compute unit; it measured faster than the full-block kernel at every launch size; short sequences on few
  *      chains run as one launch of masked products instead, see la2_chunk_plan)
@@ -436,7 +438,9 @@ void la2_set_chunk_tokens(int32_t tokens);
  *   2  the half-block kernel
  * Other values are taken as 0.  Both kernels implement Algorithm 1's block recurrence (the block
  * size is the algorithm's free parameter B); results differ by rounding only, from the one launch's too.
- * Process-global, as la2_set_chunk_tokens.  Ignored for fp32 and for head_dim 96 / 256.  Calls that carry states or
+ * Process-global, as la2_set_chunk_tokens.  Ignored for fp32 and for head_dim 256.  With 1 or 2 a backward pass runs its scans in
+ * launches of their own and in the chunks of la2_chunk_plan(), where with 0 it may run them all in one launch and leave the
+ * sequences whole; at head_dim 96 that is all the knob does.  Calls that carry states or
  * the Norm epilogue run the half-block kernel with 1 as with 2 (only it has those).  With 1 the backward pass of a sequence-chunked problem forms
  * the chunk states of its second loop in a pass of its own instead of inside the first loop's launch.
  */

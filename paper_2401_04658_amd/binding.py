@@ -43,7 +43,8 @@ def lib_path():
 
 
 def load():
-    """Loads libla2.so (no fallback: raises if it has not been built)."""
+    """Loads libla2.so (no fallback: raises if it has not been built).  The argument types are those of the whole C ABI, for programs
+    and tests that call it through ctypes; the functions below go through the native module but for queries and knobs."""
     global _lib
     if _lib is not None:
         return _lib

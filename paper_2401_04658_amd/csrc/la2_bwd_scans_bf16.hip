@@ -7,7 +7,7 @@ using namespace bf16k;
 
 // The first half of the workgroups are the twin's (dK, dV of a chain and chunk), the second half run the dQ scan on the first half of
 // their waves; the others end at once (a barrier counts the waves that are left).  The two kinds need nothing from each other, and
-// each alone is short of work for the unit it runs on: at head_dim 64 (57 KiB of LDS, four waves) both of a chain share a unit, at
+// each alone is short of work for the unit it runs on: at head_dim 64 (56 KiB of LDS, four waves) both of a chain share a unit, at
 // 128, where a twin takes all of a unit's registers, a chain takes two units.  The long ones start first.  Two workgroups with the same
 // place in their halves read the same tiles from opposite ends of the chain, on the same XCD when the halves are multiples of eight.
 // Bound by memory from about half a round of workgroups on (d 64, 128 chains of 2048: 59 us for ten tensor passes of 32 MiB, 5.7 TB/s),
