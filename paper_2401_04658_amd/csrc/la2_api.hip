@@ -735,12 +735,12 @@ bool joint_in_one_call(const la2_desc* d, const Plan& pl) {
 // fp32 in chunks: both families of chunk states come from one launch where there is room for both.  The workspace holds one; the KV
 // states wait in dV, which only the last launch writes, behind the dQ scan that reads them: dense tensors (no memory between the rows
 // that is somebody else's) of at least that many floats.  The backward pass against two launches: head_dim 128, 1 to 16 chains 0.94-1.00, 24 to
-// 64 0.92-0.99, 96 and 128 0.88; 64, up to 10 MiB a tensor 0.86-0.93, to 30 MiB 0.91-1.00, to 48 0.98-1.01, 59 MiB 1.00-1.03, 70 MiB 1.02-1.03
-// (a unit's workgroups of either family fill it there): up to 48 MiB.
+// 64 0.92-0.99, 96 and 128 0.88; 64, up to 10 MiB a tensor 0.86-0.93, to 24 MiB 0.91-1.00, 24 to 48 0.98-1.01 (3 chains of 39,661, 29 MiB,
+// 1.03, with the forward pass 1.04), 59 MiB 1.00-1.03, 70 MiB 1.02-1.03 (a unit's workgroups of either family fill it there): up to 24 MiB.
 bool f32_states_in_output(const la2_desc* d, const Plan& pl, bool split, bool saved_states) {
   return d->dtype == LA2_F32 && !wide(d->head_dim) && pl.nchunks > 1 && !split && !saved_states && d->stride_n == d->head_dim &&
          d->stride_h == (int64_t)d->seqlen * d->head_dim && (d->batch == 1 || d->stride_b == d->heads * d->stride_h) &&
-         (int64_t)pl.nchunks * d->head_dim <= d->seqlen && (d->head_dim == 128 || tensor_bytes(d, pl) <= (int64_t)48 << 20) &&
+         (int64_t)pl.nchunks * d->head_dim <= d->seqlen && (d->head_dim == 128 || tensor_bytes(d, pl) <= (int64_t)24 << 20) &&
          2 * (int64_t)d->batch * d->heads * pl.nchunks * 2 * d->head_dim <= 0xFFFFFFFFll;   // work-items of that launch
 }
 
