@@ -656,19 +656,22 @@ la2_status run_joint_backward(const la2_desc* d, const Plan& pl, const ScanArgs&
 //   1792 1.09, 1.01, 1.00, 0.97, 0.97, 2304 1.13, 1.05, 1.02, 0.97, 1.00, 3072 1.12, 1.06, 1.00, 1.02; 8192 of 32 1.20: a pair of workgroups
 //   takes LDS and registers for the longer of the two, and with few blocks a chain it is the workgroups' starts that count.
 //   Packed the same by the average length (1164 chains of 253 0.89, 2520 of 307 0.98, 3780 of 47 1.09, 11,520 of 34 1.23).
-//   d 128, whose pairs want two units: 80 to 128 chains 0.74-0.77, 160 0.87-0.98, 192, 224, 256 up to 32 MiB 0.97-0.99, above
-//   0.99-1.04; a partial second or third round 272 to 320 0.85-0.87, 384 0.92-0.94, 416 0.98-1.00, 448 1.01-1.05, 640 0.93-0.96, 768 1.00.
+//   d 128, whose pairs want two units: 80 to 128 chains 0.74-0.77, 132 to 160 0.78-0.94, above 96 MiB a tensor 1.02-1.05 (112, 128 there
+//   0.93-0.94), 168, 180 0.98-1.02, 192 to 256 of 200 to 500 positions, up to 32 MiB, 0.97-1.01, of 90 and 134 0.98-1.04 (the launch's code, 88 KiB,
+//   is fetched again behind every forward pass: 2 us), above 0.99-1.04; a partial second or third round 272 to 336 0.71-0.90, 384 0.83-0.95,
+//   416 0.98-1.00, 448 1.01-1.05, 640 0.95-1.00, of 40 and 64 1.01, 1.02, 768 1.00.
 // - instead of a cut: n 1024, 2048, 4096, 8192, d 64, 96 chains 0.69, 0.84, 0.87, 0.89, 128 0.70, 0.84, 0.86, 0.92 (80: 0.89, 0.98,
 //   1.03, 1.08); d 128, 96 chains 0.83, 0.90, 0.92, 0.93, 128 0.88, 0.88, 0.94, 0.93 (64: 0.90, 1.04, 1.18, 1.24; n 768, 900, 1152, 48 chains 0.99, 0.95, 0.94,
 //   64 0.89, 0.87, 0.91, 80 0.87, 0.89, 0.91; n 640, 700 80 chains 0.82, 0.84, fewer take the short path).  From saved
 //   states, which take a pre-pass out of the other form: d 64, 96 to 128 chains 0.94-1.00; d 128, 112 and 128 0.93-1.00 (96: 0.95-1.01).
-// - in pl's chunks (d 64; the pre-passes in one launch): 4 chains of 4096 0.83, 16 of 2048, 4096, 8192, 16384 0.83, 0.91, 0.94,
-//   0.99, 48 of 1024 to 16384 0.83, 0.90, 0.94, 0.97, 0.98, 64 of 1024, 2048, 4096, 8192 0.87, 0.93, 0.99, 1.03; saved, 64 of 1024,
-//   2048, 4096 0.93, 0.97, 1.03; packed batches up to 92 MiB 0.86-0.98.
+// - in pl's chunks (d 64; the pre-passes in one launch), by the bytes of a tensor: 1 to 60 chains up to 8 MiB 0.83-0.95, 8 to 22 MiB 0.95-1.00 (60 chains
+//   of 3000 0.97, 16 of 8001 0.98), 24 to 32 MiB 1.00-1.02 (the backward pass alone 1.02-1.06), 40 to 250 MiB 1.00-1.04 (60 of 31,455 1.04, 24 of
+//   16,000 1.04, 32 of 16,000 1.01); 64 of 1024, 2048, 4096, 8192 0.87, 0.93, 0.99, 1.03; saved, 64 of 1024, 2048, 4096 0.93, 0.97, 1.03, 2 to 36
+//   chains at 10 to 12 MiB 1.01-1.02; packed batches up to 92 MiB 0.86-1.00.
 // Head_dim 96 (two pairs share a unit; its pre-passes are launches that fill the device): uncut before as well, 4 to 128 chains of
-// 300 to 4096 positions 0.70-0.76, 160 0.73-0.84, 192 0.94-1.07, 256 0.98-1.04, 288 to 640 0.76-0.97, packed 0.70-0.97; many chains (the
-// backward pass alone, n 32, 64, 128, 224): 704 1.02, 1.02, 1.01, 0.97, 768 1.03, 0.98, 0.95, 0.98, 1024 0.98, 0.94, 0.96, 0.96, 1152 0.97, 0.97, 0.94,
-// 0.94, 1280 1.05, 1.02, 0.98, 0.99, 1792 1.07, 1.02, 1.01, 1.00, 2560 1.08, 1.03, 1.01, 0.96, 4096 1.11, 1.05, 0.99, 16,384 of 32 1.16; packed, average
+// 300 to 4096 positions 0.70-0.76, 160 0.73-0.84, 192 0.94-1.07, 256 0.98-1.04, 288 to 640 0.76-0.97, packed 0.70-0.97; many chains (n 33, 64,
+// 100, 130, 180, 300): 768 1.00, 1.02, 1.02, 1.02, 1.00, 0.98, 1024 1.00, 1.02, 0.98, 1.01, 0.96, 0.98, 1152 1.00, 0.97, 0.96, 0.95, 0.94, 0.97 (the
+// backward pass alone, n 32, 64, 128, 224): 1280 1.05, 1.02, 0.98, 0.99, 1792 1.07, 1.02, 1.01, 1.00, 2560 1.08, 1.03, 1.01, 0.96, 4096 1.11, 1.05, 0.99, 16,384 of 32 1.16; packed, average
 // in brackets, 1344 (39) 0.97, 1792 (34) 1.01, 2432 (81) 0.97, 4976 (76) 1.02, 7512 (34) 1.12; instead of a
 // cut, n 1024, 2048, 4096, 8192, 48 chains 0.86, 1.00, 1.11, 1.33, 64 0.86, 0.97, 1.08, 1.12, 80 0.81, 0.84, 0.92, 0.96, 112 0.75,
 // 0.75, 0.84, 0.82, saved 96 0.84, 0.84, 0.99, 0.95 (64: 0.99, 1.09, 1.21, 1.23).  In pl's chunks it would take a second set of states,
@@ -685,15 +688,16 @@ Plan joint_rule(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved
     if (d->head_dim == 96) {
       if (cu != nullptr) return chains <= 6 * cus || n >= 96 ? pl : none;
       if (2 * chains <= 5 * cus) return 8 * chains <= 5 * cus || chains > cus ? pl : none;
-      return n >= (2 * chains <= 9 * cus ? 64 : 128) ? pl : none;
+      return n >= (chains <= 4 * cus ? 160 : 2 * chains <= 9 * cus ? 64 : 128) ? pl : none;
     }
     if (d->head_dim == 64) {
       const bool many_pay = chains <= 3 * cus ? true : 2 * chains <= 7 * cus ? n > 32 : chains <= 4 * cus ? n >= 192 : chains <= 7 * cus && n >= 64;
       return (bytes <= 96 * MiB && many_pay) || (cu == nullptr && 4 * chains <= 3 * cus) ? pl : none;
     }
     if (cu != nullptr) return 2 * chains <= cus ? pl : none;
-    if (chains <= cus) return 8 * chains <= 5 * cus || bytes <= 32 * MiB ? pl : none;
-    return chains % cus > 0 && 2 * (chains % cus) <= cus && chains < 3 * cus ? pl : none;
+    if (8 * chains <= 5 * cus) return 2 * chains <= cus || bytes <= 96 * MiB ? pl : none;
+    if (chains <= cus) return 4 * chains >= 3 * cus && n >= 200 && bytes <= 32 * MiB ? pl : none;
+    return chains % cus > 0 && 2 * (chains % cus) <= cus && (chains < 2 * cus || (chains < 3 * cus && n > 64)) ? pl : none;
   }
   const Plan uncut{1, (d->seqlen + 63) / 64 * 64, 0};
   if (d->head_dim == 96) {
@@ -710,8 +714,7 @@ Plan joint_rule(const la2_desc* d, const Plan& pl, const int32_t* cu, bool saved
   }
   if (cu != nullptr) return bytes <= 96 * MiB ? pl : none;
   if (8 * chains >= 3 * cus) return uncut;
-  if (!saved_states && 16 * chains * pl.nchunks <= 15 * cus) return pl;
-  return bytes <= (saved_states ? 16 : 32) * MiB ? pl : none;
+  return bytes <= (!saved_states ? 22 : 16 * chains >= 3 * cus ? 16 : 8) * MiB ? pl : none;
 }
 
 // ... unless the launch would be too large: it has twice the workgroups of the widest one otherwise, of 4 d threads each, and a grid

@@ -27,7 +27,7 @@ def _defaults():
 @pytest.mark.parametrize("d,b,h,n", [(64, 1, 4, 2113), (64, 1, 16, 2048), (64, 3, 16, 1000), (64, 6, 16, 1100), (64, 8, 16, 1031),
                                      (64, 10, 16, 200), (64, 16, 16, 257), (64, 18, 16, 130), (128, 5, 16, 416), (128, 3, 16, 1000),
                                      (96, 3, 2, 300), (96, 3, 16, 1000), (96, 5, 16, 1100), (96, 17, 16, 97), (96, 1, 16, 2050), (96, 1, 4, 2050),
-                                     (128, 6, 16, 1056), (128, 10, 16, 100), (128, 16, 16, 65), (128, 18, 16, 127),
+                                     (128, 6, 16, 1056), (128, 10, 16, 100), (128, 16, 16, 65), (128, 13, 16, 225), (128, 18, 16, 127),
                                      (128, 19, 16, 2049), (96, 17, 16, 2053), (64, 19, 16, 2055)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 def test_all_scans_in_one_launch(dtype, d, b, h, n):

@@ -65,8 +65,10 @@ def test_the_order_of_a_backward_pass_that_is_not_cut(d, b, h, n):
 LINES = {64: [(768, 32, True), (784, 32, False), (784, 33, True), (896, 64, True), (912, 64, False), (912, 191, False), (912, 192, True),
               (1024, 128, False), (1024, 300, True), (1040, 63, False), (1040, 64, True), (1792, 64, True), (1808, 300, False), (2048, 32, False),
               (8192, 64, False), (16384, 32, False), (272, 32, True), (512, 400, True)],
-         96: [(272, 8, True), (640, 8, True), (656, 63, False), (656, 64, True), (1152, 64, True), (1168, 127, False), (1168, 128, True),
-              (4096, 64, False), (4096, 128, True), (16384, 32, False), (16384, 128, True), (160, 8, True), (176, 8, False), (256, 300, False)]}
+         96: [(272, 8, True), (640, 8, True), (656, 159, False), (656, 160, True), (1024, 64, False), (1040, 64, True), (1152, 64, True), (1168, 127, False), (1168, 128, True),
+              (4096, 64, False), (4096, 128, True), (16384, 32, False), (16384, 128, True), (160, 8, True), (176, 8, False), (256, 300, False)],
+         128: [(160, 2300, True), (160, 2500, False), (128, 5000, True), (176, 300, False), (192, 300, True), (192, 199, False), (256, 134, False),
+               (272, 33, True), (336, 90, True), (640, 64, False), (640, 65, True), (448, 300, False), (768, 300, False)]}
 
 
 @pytest.mark.parametrize("dtype", DTYPES)
@@ -100,7 +102,7 @@ JOINT = {(64, 1, 4, 2113): (None, 9, None, 9), (64, 1, 16, 2048): (8, 8, 8, 8), 
          (64, 8, 16, 1031): (1, 1, 1, 1), (64, 10, 16, 200): (1, 1, 1, 1), (64, 16, 16, 257): (1, 1, 1, 1), (64, 18, 16, 130): (1, 1, 1, 1),
          (128, 5, 16, 416): (1, 1, 1, 1), (128, 3, 16, 1000): (1, 1, None, None), (96, 3, 2, 300): (1, 1, 1, 1), (96, 3, 16, 1000): (1, 1, None, None),
          (96, 5, 16, 1100): (1, 1, None, None), (96, 17, 16, 97): (1, 1, 1, 1), (96, 1, 16, 2050): (None,) * 4, (96, 1, 4, 2050): (None, None, 9, 9),
-         (128, 6, 16, 1056): (1, 1, None, None), (128, 10, 16, 100): (1, 1, 1, 1), (128, 16, 16, 65): (1, 1, 1, 1), (128, 18, 16, 127): (1, 1, 1, 1),
+         (128, 6, 16, 1056): (1, 1, None, None), (128, 10, 16, 100): (1, 1, 1, 1), (128, 16, 16, 65): (None,) * 4, (128, 13, 16, 225): (1, 1, 1, 1), (128, 18, 16, 127): (1, 1, 1, 1),
          (128, 19, 16, 2049): (1, 1, 1, 1), (96, 17, 16, 2053): (1, 1, 1, 1), (64, 19, 16, 2055): (1, 1, 1, 1)}
 # (chunks, pairs of the map: 0 none) of its packed batches
 PACKED = [(10, 20), (4, 25), (1, 0), (1, 0), (1, 0), (1, 0)]
@@ -141,3 +143,14 @@ def test_fp32_chunk_states_in_one_launch(d, b, h, n, pair):
     if pair:
         first, second = [y for y in routes.backward(x) if y["launcher"] in ("chunk_state_pair_f32", "+rev")]
         assert first["states"] == "0x%x" % routes.ADDRESS["dv"] and second["states"] == "0x%x" % routes.ADDRESS["ws"]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_one_launch_in_chunks_at_head_dim_64(dtype):
+    """By the bytes of a tensor: up to 22 MiB, from saved states 16 (48 chains and more) or 8."""
+    for b, h, n, fresh, saved in ((3, 20, 2900, True, False), (3, 20, 3100, False, False), (1, 16, 8001, True, False), (2, 12, 8161, False, False),
+                                  (3, 20, 31455, False, False), (2, 2, 53997, False, False), (4, 16, 2048, True, True), (3, 16, 1300, True, True),
+                                  (1, 12, 5000, True, True), (1, 12, 6000, True, False)):
+        x = routes.desc(b, h, n, 64, dtype)
+        assert (routes.one_launch(routes.backward(x)) is not None) == fresh, (b, h, n)
+        assert (routes.one_launch(routes.backward(x, saved=True)) is not None) == saved, (b, h, n)
